@@ -1420,23 +1420,34 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
 
 
 // k-means scratch: centroid norms, the float64 re-check bound, the re-check
-// and tiny-coordinate counters, per-workgroup float64 sums and counts.
+// and tiny-coordinate counters, per-workgroup float64 sums and counts. The
+// generic path's packed centroids are read before the first partial is
+// written and share the partials' memory.
 struct KmCarve {
   uint64_t o_cn, o_cmax, o_nr, o_ps, o_pc, bytes;
 };
-KmCarve km_carve(uint32_t k, uint32_t d, uint32_t G) {
+KmCarve km_carve(uint32_t k, uint32_t d, uint32_t G, bool generic) {
   KmCarve r;
   Carve c;
-  r.o_cn = c.take(4ull * k);
-  r.o_cmax = c.take(8);
+  const uint64_t nkb = (k + 31) / 32, packed = generic ? nkb * ((d + 7) / 8) * 1024 : 0;
+  r.o_cn = c.take(4ull * nkb * 32);
+  r.o_cmax = c.take(8 * nkb);
   r.o_nr = c.take(16);
-  r.o_ps = c.take(8ull * G * k * d);
+  r.o_ps = c.take(std::max<uint64_t>(8ull * G * k * d, packed));
   r.o_pc = c.take(4ull * G * k);
   r.bytes = c.off;
   return r;
 }
-uint32_t km_grid(uint64_t N, int n_cu, bool mfma) {
-  return mfma ? (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)n_cu * 3, (N + 127) / 128)) : 1u;
+// Workgroups (partials) of the matrix-core path at d = 32, k = 64.
+uint32_t km_grid(uint64_t N, int n_cu) {
+  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)n_cu * 3, (N + 127) / 128));
+}
+// Scratch of a step. The matrix-core path's includes the generic path's,
+// which redoes a step on coordinates outside its exact split (with as many
+// partials as its own scratch holds).
+uint64_t km_bytes(uint64_t N, uint32_t k, uint32_t d, int n_cu, bool mfma) {
+  const uint64_t g = km_carve(k, d, km_upd_plan(N, k, d, n_cu).G, true).bytes;
+  return mfma ? km_carve(k, d, km_grid(N, n_cu), false).bytes : g;
 }
 
 mr_status run_kmeans(mr_job* job, const void* d_input, uint64_t bytes, mr_output* out) {
@@ -1464,37 +1475,51 @@ mr_status run_kmeans(mr_job* job, const void* d_input, uint64_t bytes, mr_output
   L.k = k;
   L.d = d;
   L.mfma = d == 32 && k == 64 && (uintptr_t)d_input % 16 == 0;
-  L.G = km_grid(N, job->n_cu, L.mfma);
-  const KmCarve kc = km_carve(k, d, L.G);
-  const uint64_t o_cn = kc.o_cn, o_cmax = kc.o_cmax, o_nr = kc.o_nr, o_ps = kc.o_ps, o_pc = kc.o_pc;
-  mr_status st = ensure_ws(job, kc.bytes);
+  L.G = km_grid(N, job->n_cu);
+  L.upd = km_upd_plan(N, k, d, (uint32_t)job->n_cu);
+  uint64_t want = km_bytes(N, k, d, job->n_cu, L.mfma);
+  if (job->cws) {
+    // a smaller caller workspace takes fewer partials (the update is then slower, the result the same)
+    const uint64_t off = align_up(job->cws_off, 256), room = job->cws_bytes > off ? job->cws_bytes - off : 0;
+    while (!L.mfma && want > room && L.upd.G > 1) {
+      L.upd.G /= 2;
+      want = km_carve(k, d, L.upd.G, true).bytes;
+    }
+  }
+  mr_status st = ensure_ws(job, want);
   if (st != MR_OK) return st;
+  while (L.upd.G > 1 && km_carve(k, d, L.upd.G, true).bytes > want) L.upd.G /= 2;  // (a redone matrix-core step)
   job->table_clean_bytes = 0;  // this scratch overwrites the word table region
   job->graph_valid = false;
   uint8_t* ws = job->ws;
-  L.cn = reinterpret_cast<float*>(ws + o_cn);
-  L.cmax = reinterpret_cast<double*>(ws + o_cmax);
-  L.n_recheck = reinterpret_cast<unsigned long long*>(ws + o_nr);
-  L.tiny = L.n_recheck + 1;
-  L.part_sum = reinterpret_cast<double*>(ws + o_ps);
-  L.part_cnt = reinterpret_cast<uint32_t*>(ws + o_pc);
+  auto place = [&](const KmCarve& kc) {
+    L.cn = reinterpret_cast<float*>(ws + kc.o_cn);
+    L.cmax = reinterpret_cast<double*>(ws + kc.o_cmax);
+    L.n_recheck = reinterpret_cast<unsigned long long*>(ws + kc.o_nr);
+    L.tiny = L.n_recheck + 1;
+    L.part_sum = reinterpret_cast<double*>(ws + kc.o_ps);
+    L.cp = reinterpret_cast<float*>(ws + kc.o_ps);
+    L.part_cnt = reinterpret_cast<uint32_t*>(ws + kc.o_pc);
+  };
+  place(L.mfma ? km_carve(k, d, L.G, false) : km_carve(k, d, L.upd.G, true));
   L.assign = out->assign;
   L.sums = out->sums;
   L.counts = out->counts;
   L.cent = out->centroids;
-  unsigned long long flags[2] = {0, 0};  // rechecks, tiny
+  unsigned long long flags[2] = {0, 0};  // rechecks, tiny (matrix-core path)
   for (int pass = 0; pass < 2; ++pass) {
-    MR_HIP(hipMemsetAsync(L.n_recheck, 0, 16, job->stream));
+    if (L.mfma) MR_HIP(hipMemsetAsync(L.n_recheck, 0, 16, job->stream));
     MR_HIP(hipEventRecord(job->ev0, job->stream));
     MR_HIP(km_enqueue(L, job->stream, job->cfg.timing ? job->ev2 : nullptr, job->cfg.timing ? job->ev3 : nullptr));
     MR_HIP(hipEventRecord(job->ev1, job->stream));
-    MR_HIP(hipMemcpyAsync(flags, L.n_recheck, 16, hipMemcpyDeviceToHost, job->stream));
+    if (L.mfma) MR_HIP(hipMemcpyAsync(flags, L.n_recheck, 16, hipMemcpyDeviceToHost, job->stream));
     MR_HIP(hipStreamSynchronize(job->stream));
     // coordinates too small for the matrix-core path's exact split: the
-    // generic kernel redoes the step (it writes every output again)
+    // generic path redoes the step (it writes every output again)
     if (!L.mfma || !flags[1]) break;
     L.mfma = false;
-    L.G = 1;
+    flags[0] = 0;
+    place(km_carve(k, d, L.upd.G, true));
   }
   const unsigned long long nr = flags[0];
   float ms = 0.f;
@@ -1672,7 +1697,8 @@ extern "C" mr_status mr_workspace_bytes(const mr_job_config* cfg, mr_map_kind ki
       if (!cfg->km_k || !cfg->km_d) return fail(MR_ERR_INVALID_ARG, "k-means needs km_k and km_d");
       const uint64_t N = n / (4ull * cfg->km_d);
       r.add(4ull * cfg->km_k * cfg->km_d);
-      r.add(km_carve(cfg->km_k, cfg->km_d, km_grid(N, n_cu, cfg->km_d == 32 && cfg->km_k == 64)).bytes);
+      // (an input whose alignment the matrix-core path does not take runs the generic path, which needs less)
+      r.add(km_bytes(N, cfg->km_k, cfg->km_d, n_cu, cfg->km_d == 32 && cfg->km_k == 64));
       break;
     }
     case MR_MAP_BLOOM: {

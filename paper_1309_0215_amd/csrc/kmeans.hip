@@ -22,6 +22,12 @@
 // contraction did. The float32 sums stay in the accumulators for at most 16
 // groups of 32 points per wave and are then added into float64 LDS sums; the
 // per-workgroup float64 partials are added in a fixed order at the end.
+//
+// Any other d and k (and points not 16-byte aligned): float32 matrix-core scores
+// with the same float64 re-check (k_km_assign), then the sums in a second kernel
+// (k_km_update).
+#include <algorithm>
+
 #include "common.h"
 #include "launch.h"
 
@@ -80,17 +86,6 @@ __global__ __launch_bounds__(256) void k_km_prep(const float* __restrict__ C, ui
     for (int i = 0; i < 256; ++i) b = m[i] > b ? m[i] : b;
     *cmax = sqrt(b);
   }
-}
-
-// float64 direct-form squared distance (the definition of the step).
-MR_DEV double dist64(const float* __restrict__ x, const float* __restrict__ c, uint32_t d) {
-  double s = 0.0;
-#pragma unroll 1
-  for (uint32_t t = 0; t < d; ++t) {
-    const double q = (double)x[t] - (double)c[t];
-    s += q * q;
-  }
-  return s;
 }
 
 // Assignment + local sums for d = 32, k = 64.
@@ -383,31 +378,349 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(3, 3
   if (threadIdx.x < K) part_cnt[(uint64_t)blockIdx.x * K + threadIdx.x] = scnt[threadIdx.x];
 }
 
-// Any d, k: float64 direct-form assignment (exact decisions) and float64 sums.
-__global__ __launch_bounds__(256) void k_km_generic(const float* __restrict__ X, uint64_t N, const float* __restrict__ C,
-                                                    uint32_t k, uint32_t d, int32_t* __restrict__ assign,
-                                                    double* __restrict__ part_sum, uint32_t* __restrict__ part_cnt) {
-  // part_sum/part_cnt hold a single partial here, accumulated with atomics
-  for (uint64_t p = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; p < N; p += (uint64_t)gridDim.x * blockDim.x) {
-    const float* xp = X + p * d;
-    double bd = INFINITY;
-    uint32_t bj = 0;
-    for (uint32_t j = 0; j < k; ++j) {
-      const double dj = dist64(xp, C + (uint64_t)j * d, d);
-      if (dj < bd) {
-        bd = dj;
-        bj = j;
+// ----------------------------------------------------------------------------
+// any d, k: assignment on the float32 matrix cores, update in LDS
+// ----------------------------------------------------------------------------
+// Quotient of a small index by a fixed divisor: exact for i * y < 2^32.
+struct SmallDiv {
+  uint32_t y, m;
+  MR_DEV explicit SmallDiv(uint32_t y_) : y(y_), m(0xFFFFFFFFu / y_ + 1u) {}
+  MR_DEV uint32_t div(uint32_t i) const { return y == 1 ? i : __umulhi(i, m); }
+};
+
+// Centroids in the order the score contraction reads them: block kb holds
+// centroids 32 kb .. 32 kb + 31, and its 8-dim chunk q is one 1 KiB row, lane
+// (col, h) holding dims 8q + 4h .. 8q + 4h + 3 of centroid 32 kb + col (zero
+// past d or k). cn: squared norms (+inf past k, so a padded row never wins);
+// cmax[kb]: the block's largest |c| (float64). One workgroup of 256 per block.
+__global__ __launch_bounds__(256) void k_km_pack(const float* __restrict__ C, uint32_t k, uint32_t d, uint32_t dq,
+                                                 float* __restrict__ Cp, float* __restrict__ cn, double* __restrict__ cmax) {
+  __shared__ double m[32];
+  const uint32_t kb = blockIdx.x, lane = lane_id(), wv = threadIdx.x / kWave;
+  for (uint32_t i = threadIdx.x; i < dq * kWave * 4; i += blockDim.x) {
+    const uint32_t q = i / (kWave * 4), l = i / 4 % kWave, e = i % 4;
+    const uint32_t j = kb * 32 + l % 32, t = 8 * q + 4 * (l / 32) + e;
+    Cp[(uint64_t)kb * dq * kWave * 4 + i] = j < k && t < d ? C[(uint64_t)j * d + t] : 0.f;
+  }
+  for (uint32_t r = wv; r < 32; r += 256 / kWave) {
+    const uint32_t j = kb * 32 + r;
+    double s = 0.0;
+    if (j < k)
+      for (uint32_t t = lane; t < d; t += kWave) {
+        const double v = C[(uint64_t)j * d + t];
+        s += v * v;
       }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (lane == 0) {
+      cn[j] = j < k ? (float)s : INFINITY;
+      m[r] = s;
     }
-    assign[p] = (int32_t)bj;
-    atomicAdd(&part_cnt[bj], 1u);
-    for (uint32_t t = 0; t < d; ++t) atomicAdd(&part_sum[(uint64_t)bj * d + t], (double)xp[t]);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double b = 0.0;
+    for (int r = 0; r < 32; ++r) b = m[r] > b ? m[r] : b;
+    cmax[kb] = sqrt(b);
   }
 }
 
-__global__ void k_km_zero(double* __restrict__ a, uint64_t na, uint32_t* __restrict__ b, uint64_t nb) {
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < na; i += (uint64_t)gridDim.x * blockDim.x) a[i] = 0.0;
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < nb; i += (uint64_t)gridDim.x * blockDim.x) b[i] = 0u;
+// float64 direct-form squared distance (the definition of the step), summed in
+// index order, of the row x (zero past d) to packed centroid j.
+MR_DEV double dist64(const float* x, const float* __restrict__ Cp, uint32_t dq, uint32_t j) {
+  double s = 0.0;
+  const float* c = Cp + ((uint64_t)(j / 32) * dq * kWave + j % 32) * 4;
+#pragma unroll 2
+  for (uint32_t q = 0; q < 2 * dq; ++q, c += kWave / 2 * 4) {
+    const f32x4 cv = *gp(reinterpret_cast<const f32x4*>(c));
+    const f32x4 xv = *reinterpret_cast<const f32x4*>(x + 4 * q);
+    double e;
+    e = (double)xv.x - (double)cv.x; s = fma(e, e, s);
+    e = (double)xv.y - (double)cv.y; s = fma(e, e, s);
+    e = (double)xv.z - (double)cv.z; s = fma(e, e, s);
+    e = (double)xv.w - (double)cv.w; s = fma(e, e, s);
+  }
+  return s;
+}
+
+// Nearest centroid of every point for any d <= 256 and k <= 1024. A wave
+// takes 32 points: it stages their rows in its own LDS slab (whole rows, read
+// coalesced; the row stride is an odd number of 16-byte units, so the 16-byte
+// operand reads of 32 rows spread over the banks) and takes their scores
+// |c|^2 - 2 <x, c> against KB blocks of 32 centroids at a time with
+// v_mfma_f32_32x32x2_f32, the packed centroids coming 1 KiB per load from the
+// cache. Each lane keeps the best and second best score of its rows; a point
+// whose gap is within the rounding bound is decided again by the whole wave
+// from the float64 direct form over all k, so the decisions are those of
+// dist64 for every point. Its floor is the matrix cores' float32 rate (32 x 32 x 2
+// multiply-adds per 64 cycles and SIMD: 52 us at 500,003 x 64, k = 100, padded
+// to 128); it takes 136 us there, two waves per SIMD hiding the row loads and
+// the comparisons (five vector instructions per score). One thread per point
+// with float64 distances and global atomics for the sums took 48.8 ms.
+constexpr uint32_t kKmSlabMax = 16 * 1024;  // LDS bytes of a wave's slab with which four waves share a workgroup
+
+MR_DEV uint32_t km_slab_stride(uint32_t dq) { return 8 * dq + 4; }
+
+template <int KB>
+__global__ __launch_bounds__(256) void k_km_assign(const float* __restrict__ X, uint64_t N,
+                                                   const float* __restrict__ Cp, const float* __restrict__ cn,
+                                                   const double* __restrict__ cmax_g, uint32_t k, uint32_t d, uint32_t dq,
+                                                   uint32_t nkb, int32_t* __restrict__ assign) {
+  extern __shared__ float slabs[];
+  const uint32_t lane = lane_id(), h = lane >> 5, col = lane & 31u;
+  const uint32_t wv = threadIdx.x / kWave, ld = km_slab_stride(dq), D8 = 8 * dq;
+  float* const xs = slabs + wv * 32 * ld;
+  double cmax64 = 0.0;
+  for (uint32_t b = 0; b < nkb; ++b) cmax64 = cmax_g[b] > cmax64 ? cmax_g[b] : cmax64;
+  const uint64_t step = (uint64_t)gridDim.x * (blockDim.x / kWave) * 32;
+  // (waves are independent: no workgroup barriers below)
+  for (uint64_t p0 = ((uint64_t)blockIdx.x * (blockDim.x / kWave) + wv) * 32; p0 < N; p0 += step) {
+    const uint32_t np = N - p0 < 32 ? (uint32_t)(N - p0) : 32u;
+    const float* const Xp = X + p0 * d;
+    constexpr int kBatch = 8;  // loads in flight per lane
+    if (d % 4 == 0 && ((uintptr_t)X & 15u) == 0) {
+      const SmallDiv by(D8 / 4);
+      const uint32_t total = 32 * D8 / 4;
+      for (uint32_t i0 = 0; i0 < total; i0 += kBatch * kWave) {
+        f32x4 v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          const uint32_t i = i0 + u * kWave + lane, r = by.div(i), c = 4 * (i - r * by.y);
+          v[u] = f32x4{};
+          if (r < np && c < d) v[u] = *gp(reinterpret_cast<const f32x4*>(Xp + r * d + c));
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          const uint32_t i = i0 + u * kWave + lane, r = by.div(i), c = 4 * (i - r * by.y);
+          if (i < total) *reinterpret_cast<f32x4*>(xs + r * ld + c) = v[u];
+        }
+      }
+    } else {
+      const SmallDiv by(D8);
+      const uint32_t total = 32 * D8;
+      for (uint32_t i0 = 0; i0 < total; i0 += kBatch * kWave) {
+        float v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          const uint32_t i = i0 + u * kWave + lane, r = by.div(i), c = i - r * by.y;
+          v[u] = r < np && c < d ? *gp(Xp + r * d + c) : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          const uint32_t i = i0 + u * kWave + lane, r = by.div(i), c = i - r * by.y;
+          if (i < total) xs[r * ld + c] = v[u];
+        }
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+
+    float b1 = INFINITY, b2 = INFINITY, nx = 0.f;
+    uint32_t i1 = 0;
+    const float* const xrow = xs + col * ld + 4 * h;
+    for (uint32_t g0 = 0; g0 < nkb; g0 += KB) {
+      f32x16 acc[KB];
+#pragma unroll
+      for (int b = 0; b < KB; ++b) acc[b] = f32x16{};
+      const float* const cp = Cp + (uint64_t)g0 * dq * (kWave * 4) + lane * 4;
+      auto load_c = [&](uint32_t q, f32x4 (&c)[KB]) {
+#pragma unroll
+        for (int b = 0; b < KB; ++b)  // (blocks past the last read the first of the group; their scores are not looked at)
+          c[b] = *gp(reinterpret_cast<const f32x4*>(cp + ((uint64_t)(g0 + b < nkb ? b : 0) * dq + q) * (kWave * 4)));
+      };
+      f32x4 cnext[KB];
+      load_c(0, cnext);
+      for (uint32_t q = 0; q < dq; ++q) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(xrow + 8 * q);
+        f32x4 c[KB];
+#pragma unroll
+        for (int b = 0; b < KB; ++b) c[b] = cnext[b];
+        load_c(q + 1 < dq ? q + 1 : q, cnext);  // the next chunk's centroids are in flight during this one
+        if (g0 == 0) nx = fmaf(x.w, x.w, fmaf(x.z, x.z, fmaf(x.y, x.y, fmaf(x.x, x.x, nx))));
+#pragma unroll
+        for (int b = 0; b < KB; ++b) {
+          acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(c[b].x, x.x, acc[b], 0, 0, 0);
+          acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(c[b].y, x.y, acc[b], 0, 0, 0);
+          acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(c[b].z, x.z, acc[b], 0, 0, 0);
+          acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(c[b].w, x.w, acc[b], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int b = 0; b < KB; ++b) {
+        if (g0 + b >= nkb) break;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {  // rows in increasing index order: strict < keeps the lowest index
+          const uint32_t idx = (g0 + b) * 32 + 8 * (r / 4) + 4 * h + (r % 4);
+          const float v = *gp(cn + idx) - 2.f * acc[b][r];
+          const bool better = v < b1;
+          b2 = better ? b1 : (v < b2 ? v : b2);
+          i1 = better ? idx : i1;
+          b1 = better ? v : b1;
+        }
+      }
+    }
+    // combine with the partner lane (the other half of every block's rows)
+    const float o1 = __shfl_xor(b1, 32), o2 = __shfl_xor(b2, 32);
+    const uint32_t oi = (uint32_t)__shfl_xor((int)i1, 32);
+    const bool other = o1 < b1 || (o1 == b1 && oi < i1);
+    const float best = other ? o1 : b1;
+    const float second = other ? (b1 < o2 ? b1 : o2) : (b2 < o1 ? b2 : o1);
+    uint32_t bi = other ? oi : i1;
+    // Rounding bound of a gap between two scores, four times (|c|^2 and the
+    // product's factor 2, two scores) the bounds of the norm, the accumulation
+    // of 8 dq products and the subtraction, and a quarter more for the
+    // roundings of the bound itself. The floors keep the bound valid where squares or products fall below the
+    // normal range; where they could pass the float32 range, every decision is
+    // made again.
+    constexpr float u = 5.9604645e-08f;  // 2^-24
+    constexpr float kFloor = 3.4694470e-18f, kAbs = 7.8886091e-31f, kHuge = 1.3292280e+36f;  // 2^-58, 2^-100, 2^120
+    nx += __shfl_xor(nx, 32);
+    nx = sqrtf(nx) + kFloor;
+    const float cmax = (float)cmax64 + kFloor;
+    const float ops = (float)(2 * D8 + 8) * u, gam = ops / (1.f - ops);
+    const float eps = 5.f * u * cmax * cmax + 5.f * (gam + u) * cmax * nx + kAbs;
+    const bool sure = second - best > eps && nx * cmax < kHuge && cmax * cmax < kHuge;
+    uint64_t again = __ballot(!sure && col < np) & 0xFFFFFFFFull;
+    while (again) {
+      const int r = __builtin_ctzll(again);
+      again &= again - 1;
+      double bd = INFINITY;
+      uint32_t bj = ~0u;
+      for (uint32_t j = lane; j < k; j += kWave) {
+        const double dj = dist64(xs + r * ld, Cp, dq, j);
+        if (dj < bd) {
+          bd = dj;
+          bj = j;
+        }
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const double od = __shfl_xor(bd, o);
+        const uint32_t oj = (uint32_t)__shfl_xor((int)bj, o);
+        if (od < bd || (od == bd && oj < bj)) {
+          bd = od;
+          bj = oj;
+        }
+      }
+      if (col == (uint32_t)r) bi = bj == ~0u ? 0u : bj;  // no distance below infinity: index 0
+    }
+    if (h == 0 && col < np) assign[p0 + col] = (int32_t)bi;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
+
+// Per-cluster float64 sums and counts of the assigned points. A workgroup
+// takes a range of points and a slice of `ds` dims (all of them where k x d
+// float64 sums fit its LDS). It orders a tile of points by cluster (counting
+// sort in LDS); a wave - or each of its groups of lanes, where a row takes at
+// most half a wave - takes an equal part of that order and adds its rows, one
+// dim per lane, in a float64 register that goes to the LDS sums when the
+// cluster changes, so a run of one cluster costs one LDS atomic per dim
+// instead of one per point (float64 LDS atomics take about a cycle per lane: 61 us with one per point and
+// dim, 27 us this way, at 500,003 x 64, k = 100). The workgroup's sums are one partial of k_km_final.
+constexpr uint32_t kKmUpdThreads = 1024;
+constexpr uint32_t kKmUpdTile = 4096;        // points per tile
+constexpr uint32_t kKmUpdLds = 124 * 1024;   // LDS bytes of the sums and counts
+
+__global__ __launch_bounds__(kKmUpdThreads) void k_km_update(const float* __restrict__ X, uint64_t N, uint32_t k, uint32_t d,
+                                                             uint32_t ds, uint32_t G, const int32_t* __restrict__ assign,
+                                                             double* __restrict__ part_sum, uint32_t* __restrict__ part_cnt) {
+  extern __shared__ double s64[];
+  __shared__ uint32_t order[kKmUpdTile];  // (cluster << 16) | point of the tile
+  __shared__ uint32_t next[kKmUpdThreads];
+  __shared__ uint32_t wsum[kKmUpdThreads / kWave];
+  const uint32_t g = blockIdx.x % G, t0 = blockIdx.x / G * ds;
+  const uint32_t w = d - t0 < ds ? d - t0 : ds;  // dims of this slice
+  uint32_t* const cnt = reinterpret_cast<uint32_t*>(s64 + (uint64_t)k * w);
+  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+  for (uint32_t i = threadIdx.x; i < k * w; i += blockDim.x) s64[i] = 0.0;
+  for (uint32_t i = threadIdx.x; i < k; i += blockDim.x) cnt[i] = 0;
+  // lanes of one point: the power of two that covers the slice, at most a wave
+  uint32_t lpp = 1;
+  while (lpp < w && lpp < kWave) lpp *= 2;
+  const uint32_t side = kWave / lpp, sub = lane / lpp, t = lane % lpp;
+  const uint64_t lo = N * g / G, hi = N * (g + 1) / G;
+  for (uint64_t base = lo; base < hi; base += kKmUpdTile) {
+    const uint32_t m = hi - base < kKmUpdTile ? (uint32_t)(hi - base) : kKmUpdTile;
+    // 1. the tile's points ordered by cluster
+    constexpr uint32_t kPer = kKmUpdTile / kKmUpdThreads;
+    uint32_t a[kPer];
+    next[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u) {
+      const uint32_t i = u * kKmUpdThreads + threadIdx.x;
+      a[u] = i < m ? (uint32_t)assign[base + i] : ~0u;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u)
+      if (a[u] != ~0u) atomicAdd(&next[a[u]], 1u);
+    __syncthreads();
+    const uint32_t c = next[threadIdx.x];  // (at most 1024 clusters: one per thread)
+    const uint32_t incl = wave_incl_scan(c);
+    if (lane == kWave - 1) wsum[wv] = incl;
+    __syncthreads();
+    uint32_t run = incl - c;
+    for (uint32_t q = 0; q < wv; ++q) run += wsum[q];
+    next[threadIdx.x] = run;
+    if (threadIdx.x < k) cnt[threadIdx.x] += c;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u)
+      if (a[u] != ~0u) order[atomicAdd(&next[a[u]], 1u)] = a[u] << 16 | (u * kKmUpdThreads + threadIdx.x);
+    __syncthreads();
+    // 2. each group of lpp lanes takes an equal part of the order
+    const uint32_t grp = wv * side + sub, groups = (kKmUpdThreads / kWave) * side;
+    const uint32_t b0 = m * grp / groups, b1 = m * (grp + 1) / groups;
+    const float* const Xb = X + base * d + t0;
+    constexpr uint32_t kBatch = 16;  // rows in flight per lane
+    for (uint32_t tc = t; tc < w; tc += kWave) {
+      double s = 0.0;
+      uint32_t cur = ~0u;
+      for (uint32_t i0 = b0; i0 < b1; i0 += kBatch) {
+        uint32_t e[kBatch];
+        float v[kBatch];
+#pragma unroll
+        for (uint32_t u = 0; u < kBatch; ++u) e[u] = order[i0 + u < b1 ? i0 + u : b1 - 1];
+#pragma unroll
+        for (uint32_t u = 0; u < kBatch; ++u) v[u] = *gp(Xb + (e[u] & 0xFFFFu) * d + tc);
+#pragma unroll
+        for (uint32_t u = 0; u < kBatch; ++u) {
+          const uint32_t j = e[u] >> 16;
+          if (i0 + u >= b1) v[u] = 0.f;  // (repeats the last point's cluster)
+          if (j != cur) {
+            if (cur != ~0u) atomicAdd(&s64[cur * w + tc], s);
+            cur = j;
+            s = 0.0;
+          }
+          s += (double)v[u];
+        }
+      }
+      if (cur != ~0u) atomicAdd(&s64[cur * w + tc], s);
+    }
+    __syncthreads();
+  }
+  for (uint32_t i = threadIdx.x; i < k * w; i += blockDim.x)
+    part_sum[((uint64_t)g * k + i / w) * d + t0 + i % w] = s64[i];
+  if (t0 == 0)
+    for (uint32_t i = threadIdx.x; i < k; i += blockDim.x) part_cnt[(uint64_t)g * k + i] = cnt[i];
+}
+
+// Dims per slice and partials of the update: slices as wide as the LDS sums
+// allow; enough partials for one workgroup per CU, each with at least 256
+// points and, over all, at most 2^21 float64 sums to write and add.
+KmUpdPlan km_upd_plan(uint64_t N, uint32_t k, uint32_t d, uint32_t n_cu) {
+  KmUpdPlan u{};
+  u.ds = std::min<uint32_t>(d, (kKmUpdLds - 4 * k) / (8 * k));
+  u.slices = (d + u.ds - 1) / u.ds;
+  uint64_t g = std::max<uint32_t>(1, n_cu / u.slices);
+  g = std::min<uint64_t>(g, (N + 255) / 256);
+  g = std::min<uint64_t>(g, (1ull << 21) / ((uint64_t)k * d));
+  u.G = (uint32_t)std::max<uint64_t>(1, g);
+  return u;
 }
 
 // Sum the G partials in a fixed order (deterministic), write float32 sums,
@@ -468,22 +781,48 @@ __global__ __launch_bounds__(kFinalWaves * kWave) void k_km_final(const double* 
   }
 }
 
+static hipError_t km_enqueue_generic(const KmLaunch& L, hipStream_t s) {
+  const uint32_t dq = (L.d + 7) / 8, nkb = (L.k + 31) / 32;
+  if (L.N) {
+    const uint32_t slab = 32 * (8 * dq + 4) * sizeof(float);
+    const uint32_t waves = slab <= kKmSlabMax ? 4 : 1;
+    const uint64_t grid = std::min<uint64_t>((L.N + 32 * waves - 1) / (32 * waves), 1u << 16);
+#define MR_KM_ASSIGN(KB)                                                                                          \
+  hipLaunchKernelGGL(k_km_assign<KB>, dim3((uint32_t)grid), dim3(waves * kWave), waves * slab, s, L.X, L.N,      \
+                     L.cp, L.cn, L.cmax, L.k, L.d, dq, nkb, L.assign)
+    if (nkb == 1) MR_KM_ASSIGN(1);
+    else if (nkb == 2) MR_KM_ASSIGN(2);
+    else MR_KM_ASSIGN(4);
+#undef MR_KM_ASSIGN
+  }
+  const KmUpdPlan u = L.upd;
+  const uint32_t lds = 8u * L.k * u.ds + 4u * L.k;
+  if (lds > 32 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_km_update),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kKmUpdLds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_km_update, dim3(u.G * u.slices), dim3(kKmUpdThreads), lds, s, L.X, L.N, L.k, L.d, u.ds, u.G,
+                     L.assign, L.part_sum, L.part_cnt);
+  return hipGetLastError();
+}
+
 hipError_t km_enqueue(const KmLaunch& L, hipStream_t s, hipEvent_t map0, hipEvent_t map1) {
-  hipLaunchKernelGGL(k_km_prep, dim3(1), dim3(256), 0, s, L.C, L.k, L.d, L.cn, L.cmax, L.tiny);
+  if (L.mfma) hipLaunchKernelGGL(k_km_prep, dim3(1), dim3(256), 0, s, L.C, L.k, L.d, L.cn, L.cmax, L.tiny);
+  else
+    hipLaunchKernelGGL(k_km_pack, dim3((L.k + 31) / 32), dim3(256), 0, s, L.C, L.k, L.d, (L.d + 7) / 8, L.cp, L.cn, L.cmax);
   if (map0) (void)hipEventRecord(map0, s);
   if (L.mfma) {
     hipLaunchKernelGGL(k_km_mfma, dim3(L.G), dim3(kKmThreads), 0, s, L.X, L.N, L.C, L.cn, L.cmax, L.assign, L.part_sum,
                        L.part_cnt, L.n_recheck, L.tiny);
   } else {
-    hipLaunchKernelGGL(k_km_zero, dim3(256), dim3(256), 0, s, L.part_sum, (uint64_t)L.k * L.d, L.part_cnt, (uint64_t)L.k);
-    const uint64_t b = (L.N + 255) / 256;
-    hipLaunchKernelGGL(k_km_generic, dim3((uint32_t)(b ? (b < 4096 ? b : 4096) : 1)), dim3(256), 0, s, L.X, L.N, L.C, L.k,
-                       L.d, L.assign, L.part_sum, L.part_cnt);
+    const hipError_t e = km_enqueue_generic(L, s);
+    if (e != hipSuccess) return e;
   }
   if (map1) (void)hipEventRecord(map1, s);
   const uint64_t kd = (uint64_t)L.k * L.d;
   hipLaunchKernelGGL(k_km_final, dim3((uint32_t)((kd + kWave - 1) / kWave)), dim3(kFinalWaves * kWave), 0, s, L.part_sum, L.part_cnt,
-                     L.mfma ? L.G : 1u, L.k, L.d, L.C, L.sums, L.counts, L.cent);
+                     L.mfma ? L.G : L.upd.G, L.k, L.d, L.C, L.sums, L.counts, L.cent);
   return hipGetLastError();
 }
 

@@ -167,17 +167,25 @@ hipError_t int_enqueue_sort(const IntLaunch& L, hipStream_t s);
 uint32_t int_lds_array_bytes(uint64_t R, uint32_t op);
 
 // One k-means step.
+// Update of the generic path: dims per LDS slice, slices, and partials (ranges of points).
+struct KmUpdPlan {
+  uint32_t ds, slices, G;
+};
+KmUpdPlan km_upd_plan(uint64_t N, uint32_t k, uint32_t d, uint32_t n_cu);
+
 struct KmLaunch {
   const float* X;       // points [N][d]
   uint64_t N;
   const float* C;       // centroids [k][d]
   uint32_t k, d;
-  float* cn;            // scratch [k]
-  double* cmax;         // scratch [1]
-  uint32_t G;           // workgroups of the assignment kernel
+  float* cn;            // scratch [k rounded up to 32]
+  double* cmax;         // scratch [k / 32, rounded up]
+  float* cp;            // generic path: centroids packed for the score contraction (shares the partials' memory)
+  KmUpdPlan upd;        // generic path
+  uint32_t G;           // workgroups of the assignment kernel (matrix-core path at d = 32, k = 64)
   bool mfma;            // d == 32, k == 64 and X 16-byte aligned
   int32_t* assign;      // [N]
-  double* part_sum;     // [G][k][d]
+  double* part_sum;     // [G][k][d] (generic path: upd.G partials)
   uint32_t* part_cnt;   // [G][k]
   unsigned long long* n_recheck;
   unsigned long long* tiny;  // set when a coordinate is nonzero and below 2^-100 (the step is then redone generically)

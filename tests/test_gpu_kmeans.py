@@ -138,6 +138,27 @@ def test_generic_path_any_shape(torch):
     _check_update(X, Cn, a, s, c, cent)
 
 
+# the generic path's edges: one block of 32 centroids and one past it, four
+# blocks and one past them; dims around the 8-dim chunk, the widest rows that
+# share a workgroup (120) and one past them, the widest of all; cluster
+# counts whose sums fill one LDS slice, and several (1024 x 17, 1024 x 256)
+@pytest.mark.parametrize("n,d,k,shift", [
+    (1, 1, 1, 0), (33, 1, 2, 0), (31, 7, 32, 0), (97, 8, 33, 0), (1500, 9, 3, 1000), (700, 12, 64, 0),
+    (513, 16, 65, 0), (1025, 33, 128, 0), (260, 64, 129, 1000), (200, 120, 40, 0), (200, 121, 40, 0),
+    (4100, 17, 1024, 0), (3000, 255, 5, 0), (2100, 256, 1024, 0)])
+def test_generic_path_edges(torch, n, d, k, shift):
+    """Random points and centroids drawn apart; `shift` adds a common offset,
+    which puts every score gap within the float32 rounding bound."""
+    rng = np.random.default_rng(n + d + k)
+    X = (rng.standard_normal((n, d)) + shift).astype(np.float32)
+    Cn = (rng.standard_normal((k, d)) + shift).astype(np.float32)
+    for offset in (0, 1):
+        a, s, c, cent, st = _run(torch, X, Cn, offset=offset)
+        assert st["strategy_used"] == 0
+        _check_assign(X, Cn, a)
+        _check_update(X, Cn, a, s, c, cent)
+
+
 def test_unaligned_points_use_generic_path(torch):
     X, Cn = gen.kmeans(4, n=2000, d=32, k=64)
     a, s, c, cent, st = _run(torch, X, Cn, offset=1)
