@@ -113,7 +113,10 @@ typedef enum {
   MR_STRAT_LEARNED = 1,
   MR_STRAT_LDS_ARRAY = 2,    /* per-workgroup LDS array, partials merged without atomics */
   MR_STRAT_GLOBAL_ARRAY = 3, /* one global array updated with atomics */
-  MR_STRAT_HASH = 4,         /* LDS hash cache per workgroup in front of a global open-addressing table */
+  MR_STRAT_HASH = 4,         /* LDS hash cache per workgroup in front of a global open-addressing table; with
+                                too many keys for the caches (or too few elements to fill them) the pairs are
+                                ordered and reduced in runs instead, unless the job sets table_slots or
+                                debug_hash */
   MR_STRAT_SORT = 5          /* radix sort of all pairs, then a segmented reduce */
 } mr_strategy;
 
@@ -156,7 +159,7 @@ typedef struct {
 typedef struct {
   uint32_t strategy_used;  /* mr_strategy actually run */
   uint32_t retries;        /* hash-table regrowths */
-  uint64_t table_slots;    /* final global hash table slots */
+  uint64_t table_slots;    /* final global hash table slots (0: no table was used) */
   uint64_t n_items;        /* number of map elements (words, keys, pixels, points) */
   float gpu_ms;            /* device time of the job's kernels (HIP events) */
   float map_ms;            /* device time of the map (dominant) kernel alone; needs cfg.timing */

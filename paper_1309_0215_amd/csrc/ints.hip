@@ -14,7 +14,7 @@
 //   HASH         a per-workgroup LDS hash cache (the bounded local container of
 //                Section III-D) in front of a global open-addressing table;
 //                keys fit the CAS word, so claim and compare are one step.
-//   SORT         LSD radix sort of the pairs, then a segmented reduce.
+//   SORT         LSD radix sort of the pairs, then a segmented reduce (sort.hip).
 // Every container ends in a compaction to distinct keys in ascending order.
 #include "common.h"
 #include "launch.h"
@@ -534,6 +534,7 @@ struct IntTable {
   uint64_t cap;               // power of two
   uint32_t* claimed;          // slots claimed, in claim order
   unsigned long long* n_claimed;
+  uint64_t max_probes;        // slots an insert looks at before the table counts as full
   uint32_t* side_cnt;         // key 0xFFFFFFFF: count and value
   void* side_val;
   uint32_t* flags;
@@ -556,7 +557,7 @@ MR_DEV void g_int_insert(const IntTable& T, uint32_t k, uint32_t c, unsigned lon
   }
   const uint64_t mask = T.cap - 1;
   uint64_t i = (debug_hash ? 0ull : hash_u32(k)) & mask;
-  for (uint64_t p = 0; p <= mask; ++p) {
+  for (uint64_t p = 0; p < T.max_probes; ++p) {
     uint32_t cur = __hip_atomic_load(&T.keys[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (cur == kEmptyKey) {
       cur = atomicCAS(&T.keys[i], kEmptyKey, k);
@@ -618,6 +619,99 @@ __global__ __launch_bounds__(kIntThreads) void k_int_hash(IntIn in, IntTable T, 
   for (uint32_t s = threadIdx.x; s < S; s += blockDim.x) {
     if (lk[s] != kEmptyKey && lc[s])
       g_int_insert<OP>(T, lk[s], lc[s], OP == 1 ? ls[s] : 0ull, OP >= 2 ? lm[s] : 0u, debug_hash);
+  }
+}
+
+// Distinct keys among kSampleSize elements spread evenly over the input
+// (counted in an LDS hash set by one workgroup): tells inputs of few keys,
+// which the LDS caches combine, from the others before any pass over them.
+constexpr uint32_t kSampleSize = 8192;
+
+__global__ __launch_bounds__(1024) void k_int_sample(IntIn in, uint32_t* __restrict__ distinct) {
+  constexpr uint32_t S = 2 * kSampleSize;
+  __shared__ uint32_t set[S];
+  __shared__ uint32_t n;
+  for (uint32_t i = threadIdx.x; i < S; i += blockDim.x) set[i] = kEmptyKey;
+  if (threadIdx.x == 0) n = 0;
+  constexpr uint32_t kPer = kSampleSize / 1024;
+  uint32_t k[kPer];
+#pragma unroll
+  for (uint32_t u = 0; u < kPer; ++u) {
+    const uint64_t q = u * 1024 + threadIdx.x;
+    k[u] = in.p[(q * in.n / kSampleSize) * (in.kv ? 2 : 1)];
+  }
+  __syncthreads();
+  uint32_t mine = 0;
+#pragma unroll
+  for (uint32_t u = 0; u < kPer; ++u) {
+    if (k[u] == kEmptyKey) continue;
+    uint32_t s = (uint32_t)hash_u32(k[u]) & (S - 1);
+    for (;;) {  // (the set has twice the slots: a free one is met)
+      const uint32_t cur = atomicCAS(&set[s], kEmptyKey, k[u]);
+      if (cur == kEmptyKey) ++mine;
+      if (cur == kEmptyKey || cur == k[u]) break;
+      s = (s + 1) & (S - 1);
+    }
+  }
+  if (mine) atomicAdd(&n, mine);
+  __syncthreads();
+  if (threadIdx.x == 0) *distinct = n;
+}
+
+// Output of a table of few keys by one workgroup: the claimed slots' keys are
+// sorted in LDS (bitonic, with their claim index), the pairs written in order
+// and the slots cleared, the side slot appended. Does nothing when there are
+// more than kSmallOut keys or the table was full. One launch instead of the
+// gather, the radix passes and the split (16 launches, about 80 us).
+constexpr uint32_t kSmallOut = 4096;
+
+template <int OP>
+__global__ __launch_bounds__(1024) void k_int_small_out(IntTable T, uint32_t* __restrict__ out_keys, void* __restrict__ out_vals,
+                                                        uint64_t cap, unsigned long long* __restrict__ n_out) {
+  __shared__ unsigned long long e[kSmallOut];
+  const unsigned long long nc = *T.n_claimed;
+  if (nc > kSmallOut || (*T.flags & kFlagTableFull)) return;
+  const uint32_t n = (uint32_t)nc;
+  uint32_t m = 1;
+  while (m < n) m *= 2;
+  for (uint32_t q = threadIdx.x; q < m; q += blockDim.x)
+    e[q] = q < n ? (unsigned long long)T.keys[T.claimed[q]] << 32 | q : ~0ull;  // (claim indices are below 2^32 - 1)
+  __syncthreads();
+  for (uint32_t size = 2; size <= m; size *= 2) {
+    for (uint32_t step = size / 2; step; step /= 2) {
+      for (uint32_t q = threadIdx.x; q < m / 2; q += blockDim.x) {
+        const uint32_t a = 2 * q - (q & (step - 1)), b = a + step;
+        const unsigned long long x = e[a], y = e[b];
+        if ((x > y) == ((a & size) == 0)) {
+          e[a] = y;
+          e[b] = x;
+        }
+      }
+      __syncthreads();
+    }
+  }
+  for (uint32_t r = threadIdx.x; r < n; r += blockDim.x) {
+    const uint32_t i = T.claimed[(uint32_t)e[r]];
+    if (r < cap) {
+      out_keys[r] = (uint32_t)(e[r] >> 32);
+      if (OP == 0) reinterpret_cast<uint32_t*>(out_vals)[r] = T.cnt[i];
+      else if (OP == 1) reinterpret_cast<unsigned long long*>(out_vals)[r] = reinterpret_cast<unsigned long long*>(T.val)[i];
+      else reinterpret_cast<uint32_t*>(out_vals)[r] = dec_minmax(OP, reinterpret_cast<uint32_t*>(T.val)[i]);
+    }
+    T.keys[i] = kEmptyKey;
+    T.cnt[i] = 0;
+    if (OP == 1) reinterpret_cast<unsigned long long*>(T.val)[i] = 0;
+    if (OP >= 2) reinterpret_cast<uint32_t*>(T.val)[i] = 0;
+  }
+  if (threadIdx.x == 0) {
+    const bool side = *T.side_cnt != 0;  // key 0xFFFFFFFF, after all others
+    if (side && n < cap) {
+      out_keys[n] = kEmptyKey;
+      if (OP == 0) reinterpret_cast<uint32_t*>(out_vals)[n] = *T.side_cnt;
+      else if (OP == 1) reinterpret_cast<unsigned long long*>(out_vals)[n] = *reinterpret_cast<unsigned long long*>(T.side_val);
+      else reinterpret_cast<uint32_t*>(out_vals)[n] = dec_minmax(OP, *reinterpret_cast<uint32_t*>(T.side_val));
+    }
+    *n_out = n + (side ? 1u : 0u);
   }
 }
 
@@ -795,119 +889,6 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const unsigned long long*
       key_out[dst] = k[e];
       val_out[dst] = v[e];
     }
-  }
-}
-
-// ----------------------------------------------------------------------------
-// sort strategy: build records, reduce runs
-// ----------------------------------------------------------------------------
-
-// Records for the sort: COUNT/SUM sort by key with the value alongside; MIN/MAX
-// sort by (key << 32 | value), so each run starts with its minimum and ends
-// with its maximum.
-__global__ void k_sort_records(IntIn in, int op, uint64_t R, uint32_t* flags, unsigned long long* __restrict__ rk,
-                               unsigned long long* __restrict__ rv) {
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < in.n; i += (uint64_t)gridDim.x * blockDim.x) {
-    uint32_t k, v;
-    load_elem(in, i, k, v);
-    if (R && k >= R) atomicOr(flags, kFlagBadInput);
-    rk[i] = op >= 2 ? (((unsigned long long)k << 32) | v) : (unsigned long long)k;
-    rv[i] = v;
-  }
-}
-
-// head[i] = 1 where a run of equal keys starts (key = bits 32.. for MIN/MAX).
-__global__ void k_run_heads(const unsigned long long* __restrict__ rk, uint64_t n, int op, uint32_t* __restrict__ head) {
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t a = op >= 2 ? (rk[i] >> 32) : rk[i];
-    const uint64_t b = i ? (op >= 2 ? (rk[i - 1] >> 32) : rk[i - 1]) : ~0ull;
-    head[i] = (i == 0 || a != b) ? 1u : 0u;
-  }
-}
-
-// Inclusive 64-bit prefix sums of the values (for SUM runs), in place: per-block
-// partial sums are computed first, then added. Simple two-pass version.
-constexpr uint32_t kPsTile = 4096;
-
-__global__ __launch_bounds__(256) void k_ps64_blocks(const unsigned long long* __restrict__ a, uint64_t n,
-                                                     unsigned long long* __restrict__ sums) {
-  __shared__ unsigned long long s[256 / kWave];
-  const uint64_t base = (uint64_t)blockIdx.x * kPsTile;
-  unsigned long long c = 0;
-  for (uint32_t q = threadIdx.x; q < kPsTile; q += blockDim.x)
-    if (base + q < n) c += a[base + q];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-  if (lane_id() == 0) s[threadIdx.x / kWave] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long t = 0;
-    for (int w = 0; w < 256 / kWave; ++w) t += s[w];
-    sums[blockIdx.x] = t;
-  }
-}
-
-__global__ void k_ps64_scan_sums(unsigned long long* sums, uint32_t nb) {
-  if (threadIdx.x || blockIdx.x) return;
-  unsigned long long c = 0;
-  for (uint32_t b = 0; b < nb; ++b) {
-    const unsigned long long x = sums[b];
-    sums[b] = c;
-    c += x;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_ps64_apply(unsigned long long* __restrict__ a, uint64_t n,
-                                                    const unsigned long long* __restrict__ sums) {
-  __shared__ unsigned long long ws[256 / kWave];
-  const uint64_t base = (uint64_t)blockIdx.x * kPsTile;
-  unsigned long long carry = sums[blockIdx.x];
-  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
-  for (uint32_t q0 = 0; q0 < kPsTile; q0 += blockDim.x) {
-    const uint64_t i = base + q0 + threadIdx.x;
-    const unsigned long long x = i < n ? a[i] : 0ull;
-    unsigned long long inc = x;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const unsigned long long t = __shfl_up(inc, o);
-      if (lane >= (uint32_t)o) inc += t;
-    }
-    if (lane == kWave - 1) ws[wv] = inc;
-    __syncthreads();
-    unsigned long long pre = carry, tot = 0;
-    for (uint32_t w = 0; w < blockDim.x / kWave; ++w) {
-      if (w < wv) pre += ws[w];
-      tot += ws[w];
-    }
-    if (i < n) a[i] = pre + inc;  // inclusive
-    carry += tot;
-    __syncthreads();
-  }
-}
-
-// Start position of every run: hpos[pos[i]] = i for each head i, and
-// hpos[n_runs] = n.
-__global__ void k_run_starts(const uint32_t* __restrict__ head, const uint32_t* __restrict__ pos, uint64_t n,
-                             const unsigned long long* __restrict__ n_runs, uint32_t* __restrict__ hpos) {
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    if (head[i]) hpos[pos[i]] = (uint32_t)i;
-  if (blockIdx.x == 0 && threadIdx.x == 0) hpos[*n_runs] = (uint32_t)n;
-}
-
-// One output per run [hpos[r], hpos[r + 1]). COUNT: the run length; SUM: the
-// difference of inclusive prefix sums; MIN / MAX: the first / last value
-// (records were sorted by key then value).
-__global__ void k_run_write(const unsigned long long* __restrict__ rk, const unsigned long long* __restrict__ ps,
-                            const uint32_t* __restrict__ hpos, const unsigned long long* __restrict__ n_runs, int op,
-                            uint32_t* __restrict__ out_keys, void* __restrict__ out_vals, uint64_t cap) {
-  const uint64_t R = *n_runs;
-  for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < R && r < cap; r += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t b = hpos[r], e = hpos[r + 1];
-    out_keys[r] = (uint32_t)(op >= 2 ? (rk[b] >> 32) : rk[b]);
-    if (op == 0) reinterpret_cast<uint32_t*>(out_vals)[r] = (uint32_t)(e - b);
-    else if (op == 1) reinterpret_cast<unsigned long long*>(out_vals)[r] = ps[e - 1] - (b ? ps[b - 1] : 0ull);
-    else if (op == 2) reinterpret_cast<uint32_t*>(out_vals)[r] = (uint32_t)rk[b];
-    else reinterpret_cast<uint32_t*>(out_vals)[r] = (uint32_t)rk[e - 1];
   }
 }
 
@@ -1089,7 +1070,7 @@ hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, bool blk_counte
 
 hipError_t int_enqueue_hash_map(const IntLaunch& L, hipStream_t s) {
   const IntIn in{L.in, L.n, L.kv};
-  IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.side_cnt, L.side_val, L.flags};
+  IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.max_probes, L.side_cnt, L.side_val, L.flags};
 #define HASH_CASE(OP) \
   case OP: hipLaunchKernelGGL((k_int_hash<OP, 12>), dim3(L.G), dim3(kIntThreads), 0, s, in, T, L.G, L.debug_hash, L.R); break;
   switch (L.op) {
@@ -1099,6 +1080,24 @@ hipError_t int_enqueue_hash_map(const IntLaunch& L, hipStream_t s) {
     HASH_CASE(3)
   }
 #undef HASH_CASE
+  return hipGetLastError();
+}
+
+hipError_t int_enqueue_sample(const IntLaunch& L, uint32_t* distinct, hipStream_t s) {
+  hipLaunchKernelGGL(k_int_sample, dim3(1), dim3(1024), 0, s, IntIn{L.in, L.n, L.kv}, distinct);
+  return hipGetLastError();
+}
+
+uint32_t int_small_out_max() { return kSmallOut; }
+
+hipError_t int_enqueue_small_out(const IntLaunch& L, hipStream_t s) {
+  IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.max_probes, L.side_cnt, L.side_val, L.flags};
+  switch (L.op) {
+    case 0: hipLaunchKernelGGL(k_int_small_out<0>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out); break;
+    case 1: hipLaunchKernelGGL(k_int_small_out<1>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out); break;
+    case 2: hipLaunchKernelGGL(k_int_small_out<2>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out); break;
+    case 3: hipLaunchKernelGGL(k_int_small_out<3>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out); break;
+  }
   return hipGetLastError();
 }
 
@@ -1130,7 +1129,7 @@ hipError_t radix_sort64(unsigned long long* k0, unsigned long long* v0, unsigned
 }
 
 hipError_t int_enqueue_hash_out(const IntLaunch& L, uint64_t n_claimed_host, hipStream_t s) {
-  IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.side_cnt, L.side_val, L.flags};
+  IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.max_probes, L.side_cnt, L.side_val, L.flags};
   const uint64_t n = n_claimed_host;
   const uint32_t g = blocks_for(n, 256, 4096);
   switch (L.op) {
@@ -1157,40 +1156,6 @@ hipError_t int_enqueue_hash_sort_out(const IntLaunch& L, uint64_t n, hipStream_t
   hipLaunchKernelGGL(k_split_out, dim3(g), dim3(256), 0, s, rk, rv, n, L.op, L.out_keys, L.out_vals, L.cap);
   hipLaunchKernelGGL(k_side_append, dim3(1), dim3(64), 0, s, L.side_cnt, L.side_val, L.op, L.n_claimed, L.n_out,
                      L.out_keys, L.out_vals, L.cap);
-  return hipGetLastError();
-}
-
-hipError_t int_enqueue_sort(const IntLaunch& L, hipStream_t s) {
-  const IntIn in{L.in, L.n, L.kv};
-  const uint64_t n = L.n;
-  const uint32_t g = blocks_for(n, 256, 8192);
-  hipLaunchKernelGGL(k_sort_records, dim3(g), dim3(256), 0, s, in, (int)L.op, L.R, L.flags, L.rk0, L.rv0);
-  bool in1 = false;
-  hipError_t e = radix_sort64(L.rk0, L.rv0, L.rk1, L.rv1, n, L.op >= 2 ? 64 : 32, L.hist, L.scan_sums, &in1, s);
-  if (e != hipSuccess) return e;
-  unsigned long long* rk = in1 ? L.rk1 : L.rk0;
-  unsigned long long* rv = in1 ? L.rv1 : L.rv0;
-  // heads and their exclusive scan (run index of each head)
-  hipLaunchKernelGGL(k_run_heads, dim3(g), dim3(256), 0, s, rk, n, (int)L.op, L.head);
-  if (n) {
-    const hipError_t e2 = hipMemcpyAsync(L.pos, L.head, 4 * n, hipMemcpyDeviceToDevice, s);
-    if (e2 != hipSuccess) return e2;
-  }
-  const uint32_t sb = (uint32_t)((n + kScanTile - 1) / kScanTile);
-  if (n) {
-    hipLaunchKernelGGL(k_scan_blocks, dim3(sb), dim3(256), 0, s, L.pos, n, L.scan_sums);
-    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, L.scan_sums, sb, L.n_out);
-    hipLaunchKernelGGL(k_scan_apply, dim3(sb), dim3(256), 0, s, L.pos, n, L.scan_sums);
-  }
-  if (L.op == 1 && n) {
-    const uint32_t pb = (uint32_t)((n + kPsTile - 1) / kPsTile);
-    hipLaunchKernelGGL(k_ps64_blocks, dim3(pb), dim3(256), 0, s, rv, n, L.ps_sums);
-    hipLaunchKernelGGL(k_ps64_scan_sums, dim3(1), dim3(64), 0, s, L.ps_sums, pb);
-    hipLaunchKernelGGL(k_ps64_apply, dim3(pb), dim3(256), 0, s, rv, n, L.ps_sums);
-  }
-  hipLaunchKernelGGL(k_run_starts, dim3(g), dim3(256), 0, s, L.head, L.pos, n, L.n_out, L.hpos);
-  hipLaunchKernelGGL(k_run_write, dim3(g), dim3(256), 0, s, rk, rv, L.hpos, L.n_out, (int)L.op, L.out_keys, L.out_vals,
-                     L.cap);
   return hipGetLastError();
 }
 

@@ -109,6 +109,7 @@ struct IntLaunch {
   uint64_t t_cap;
   uint32_t* claimed;
   unsigned long long* n_claimed;
+  uint64_t max_probes;  // slots an insert looks at before the table counts as full
   uint32_t* side_cnt;
   void* side_val;
   // sort scratch
@@ -116,16 +117,42 @@ struct IntLaunch {
   unsigned long long *rk0, *rv0, *rk1, *rv1;
   uint32_t* hist;
   uint32_t* scan_sums;
-  uint32_t* head;
-  uint32_t* pos;
-  uint32_t* hpos;
-  unsigned long long* ps_sums;
   // outputs
   uint32_t* out_keys;
   void* out_vals;
   uint64_t cap;
   unsigned long long* n_out;  // device: number of distinct keys
 };
+
+// Radix sort of all elements and the reduce of the runs (sort.hip).
+constexpr uint32_t kRadixTile = 8192;  // elements per tile
+constexpr uint32_t kRunsChunk = 1024;  // sorted elements per wave of the reduce
+struct RadixPlan {
+  uint32_t n_tiles;
+  uint64_t hist_words;  // digit counts of all tiles
+  uint64_t n_chunks;    // chunks of the reduce
+};
+RadixPlan radix_plan(uint64_t n);
+struct SortLaunch {
+  const uint32_t* in;
+  uint64_t n;              // elements, below 2^32
+  uint32_t kv, op;         // as in IntLaunch
+  uint64_t R;              // declared key range (0 = none)
+  uint32_t bits;           // key bits that can differ
+  uint32_t* flags;
+  unsigned long long* diff;  // zero at the start: gathers the differing key bits
+  void *buf0, *buf1;       // [n] each: uint32 keys for COUNT, (key, value) pairs otherwise
+  uint32_t* hist;          // [hist_words]
+  uint32_t* tot;           // [256]
+  uint32_t* heads;         // [n_chunks] run heads per chunk
+  uint32_t* scan_sums;     // scan_sums_count(n_chunks)
+  unsigned long long* lead;  // [n_chunks]
+  uint32_t* out_keys;
+  void* out_vals;
+  uint64_t cap;
+  unsigned long long* n_out;
+};
+hipError_t int_enqueue_sort(const SortLaunch& L, hipStream_t s);
 
 hipError_t int_enqueue_lds_array(const IntLaunch& L, hipStream_t s);
 // device-wide exclusive scan of uint32 counts (sums: scan_sums_count(n) entries)
@@ -161,9 +188,11 @@ hipError_t int_enqueue_global_array_tiles(const IntLaunch& L, const PartPlan& pp
 hipError_t int_enqueue_global_array(const IntLaunch& L, hipStream_t s);
 hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, bool blk_counted, hipStream_t s);
 hipError_t int_enqueue_hash_map(const IntLaunch& L, hipStream_t s);
+hipError_t int_enqueue_sample(const IntLaunch& L, uint32_t* distinct, hipStream_t s);
+uint32_t int_small_out_max();  // keys int_enqueue_small_out handles
+hipError_t int_enqueue_small_out(const IntLaunch& L, hipStream_t s);
 hipError_t int_enqueue_hash_out(const IntLaunch& L, uint64_t n_claimed_host, hipStream_t s);
 hipError_t int_enqueue_hash_sort_out(const IntLaunch& L, uint64_t n, hipStream_t s);
-hipError_t int_enqueue_sort(const IntLaunch& L, hipStream_t s);
 uint32_t int_lds_array_bytes(uint64_t R, uint32_t op);
 
 // One k-means step.

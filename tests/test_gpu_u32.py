@@ -171,3 +171,49 @@ def test_sort_at_the_one_workgroup_scan_limit(torch, n):
     res = _run(torch, _job(STRATS["sort"]), keys, vals, "sum", 1 << 20)
     assert res.stats["strategy_used"] == STRATS["sort"]
     _check(res, keys, vals, "sum")
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1024, 1025, 8191, 8192, 8193, 16_385, 131_073])
+@pytest.mark.parametrize("strat", ["hash", "sort"])
+def test_sorted_runs_at_tile_and_chunk_edges(torch, strat, n):
+    """The radix sort takes tiles of 8192 elements and the reduce chunks of
+    1024 in rows of 64: sizes at those edges, with runs of one key (longer
+    than chunks and tiles), of every element its own key, and keys that differ
+    in their top byte, their middle bytes or one bit only (passes skipped)."""
+    rng = np.random.default_rng(n)
+    i = np.arange(n, dtype=np.uint64)
+    inputs = [np.full(n, 0xFFFFFFFF), i * 2654435761 % 2**32, (i % 3) << 24, (i % 700) << 8, (i // 1500) & 1,
+              rng.integers(0, 50, n) ** 4 % 2**32]
+    vals = rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+    for x in inputs:
+        keys = np.asarray(x).astype(np.uint32)
+        for op in OPS:
+            _check(_run(torch, _job(STRATS[strat]), keys, None if op == "count" else vals, op, 0), keys,
+                   None if op == "count" else vals, op)
+
+
+def test_sort_of_keys_4_bytes_past_a_16_byte_boundary(torch):
+    keys, _ = gen.u32_keys(41, 20_001, 5000, 0.5)
+    kt = torch.from_numpy(keys.view(np.int32)).to("cuda:0")[1:]
+    assert kt.data_ptr() % 16 == 4
+    for strat in ("hash", "sort"):
+        _check(_job(STRATS[strat]).u32(kt), keys[1:], None, "count")
+
+
+# rare keys beside one frequent key, so that a sample of 8192 elements holds
+# few distinct keys: as many claimed slots as one workgroup orders (4096) and
+# one more, and more keys than the small table holds (2^18 slots)
+@pytest.mark.parametrize("n,rare", [((1 << 20) - 1, 4095), (1 << 20, 4095), (1 << 20, 4096), (6_000_000, 300_000)])
+def test_hash_of_few_frequent_keys(torch, n, rare):
+    rng = np.random.default_rng(rare)
+    keys = np.full(n, 77, np.uint32)
+    at = rng.permutation(n)[:rare]
+    keys[at] = 1000 + np.arange(rare, dtype=np.uint32) * 13
+    keys[at[0]] = 0xFFFFFFFF  # kept beside the table
+    vals = rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+    for op in OPS if rare < 10_000 else ["sum"]:
+        r = _run(torch, _job(STRATS["hash"]), keys, None if op == "count" else vals, op, 0)
+        assert r.stats["strategy_used"] == STRATS["hash"]
+        _check(r, keys, None if op == "count" else vals, op)
+    # the table is clean for the next job
+    _check(_run(torch, _job(STRATS["hash"]), keys[: 1 << 20], vals[: 1 << 20], "max", 0), keys[: 1 << 20], vals[: 1 << 20], "max")
