@@ -935,11 +935,10 @@ mr_status run_links(mr_job* job, mr_reduce_op op, const void* d_input, uint64_t 
   const uint64_t F = rec ? std::max<uint64_t>(n_rec, 1) : 1;
   const uint32_t kb = bits_for(nk * F + 1);
   const int sort_bits = (int)std::max<uint32_t>(8, (kb + 7) / 8 * 8);
-  const uint64_t hw = links_hist_words(n);
   Carve c2 = c;
-  const uint64_t o_k0 = c2.take(8 * n), o_v0 = c2.take(8 * n), o_k1 = c2.take(8 * n), o_v1 = c2.take(8 * n);
-  const uint64_t o_hist = c2.take(4 * std::max<uint64_t>(hw, 1));
-  const uint64_t o_sums = c2.take(4 * std::max(scan_sums_count(hw), scan_sums_count(n)));
+  const uint64_t o_k0 = c2.take(8 * n), o_k1 = c2.take(8 * n), o_k2 = c2.take(8 * n), o_diff = c2.take(8);
+  const uint64_t o_hist = c2.take(4 * radix_plan(n).hist_words), o_dig = c2.take(4 * 256);
+  const uint64_t o_sums = c2.take(4 * scan_sums_count(n));
   const uint64_t o_head = c2.take(4 * std::max<uint64_t>(n, 1)), o_tot = c2.take(8), o_val = c2.take(8), o_fl = c2.take(8);
   const uint64_t o_first = c2.take(4 * (nk + 1));
   if (c2.off > job->link_dev_bytes) {
@@ -966,9 +965,10 @@ mr_status run_links(mr_job* job, mr_reduce_op op, const void* d_input, uint64_t 
   P.file_mod = F;
   P.sort_bits = sort_bits;
   P.k0 = reinterpret_cast<unsigned long long*>(d + o_k0);
-  P.v0 = reinterpret_cast<unsigned long long*>(d + o_v0);
   P.k1 = reinterpret_cast<unsigned long long*>(d + o_k1);
-  P.v1 = reinterpret_cast<unsigned long long*>(d + o_v1);
+  P.k2 = reinterpret_cast<unsigned long long*>(d + o_k2);
+  P.diff = reinterpret_cast<unsigned long long*>(d + o_diff);
+  P.tot = reinterpret_cast<uint32_t*>(d + o_dig);
   P.hist = reinterpret_cast<uint32_t*>(d + o_hist);
   P.scan_sums = reinterpret_cast<uint32_t*>(d + o_sums);
   P.head = reinterpret_cast<uint32_t*>(d + o_head);
@@ -977,11 +977,10 @@ mr_status run_links(mr_job* job, mr_reduce_op op, const void* d_input, uint64_t 
   P.flags = reinterpret_cast<uint32_t*>(d + o_fl);
   P.first = reinterpret_cast<uint32_t*>(d + o_first);
   MR_HIP(hipEventRecord(job->ev0, job->stream));
-  bool in1 = false;
-  MR_HIP(links_enqueue_rank_sort(P, &in1, job->stream));
+  MR_HIP(links_enqueue_rank_sort(P, job->stream));
   // the lists are written at once (entries past the capacity are skipped);
   // their size and the error flag are checked after the one synchronisation
-  MR_HIP(links_enqueue_write(P, in1, out->list_ids, out->cap_list_ids, out->list_offsets,
+  MR_HIP(links_enqueue_write(P, out->list_ids, out->cap_list_ids, out->list_offsets,
                              static_cast<uint32_t*>(out->values), job->stream));
   unsigned long long tv[2] = {0, 0};
   uint32_t flags = 0;
@@ -1177,20 +1176,18 @@ DenseCarve dense_carve(mr_strategy strat, uint64_t n, uint64_t R, uint32_t op, u
   d.bytes = c.off;
   return d;
 }
-struct HashCarve {  // output records and radix sort of nc claimed keys
-  uint64_t o_rk32, o_rk0, o_rv0, o_rk1, o_rv1, o_hist, o_ss, bytes;
+struct HashCarve {  // output pairs, values and radix sort of nc claimed keys
+  uint64_t o_pairs, o_vals, o_b0, o_b1, o_hist, o_tot, bytes;
 };
 HashCarve hash_carve(uint64_t nc) {
   HashCarve h;
   Carve c;
-  const uint64_t hn = 256 * std::max<uint64_t>((nc + 2047) / 2048, 1);
-  h.o_rk32 = c.take(4 * (nc + 1));
-  h.o_rk0 = c.take(8 * (nc + 1));
-  h.o_rv0 = c.take(8 * (nc + 1));
-  h.o_rk1 = c.take(8 * (nc + 1));
-  h.o_rv1 = c.take(8 * (nc + 1));
-  h.o_hist = c.take(4 * hn);
-  h.o_ss = c.take(4 * (hn / 4096 + 2));
+  h.o_pairs = c.take(8 * (nc + 1));
+  h.o_vals = c.take(8 * (nc + 1));
+  h.o_b0 = c.take(8 * (nc + 1));
+  h.o_b1 = c.take(8 * (nc + 1));
+  h.o_hist = c.take(4 * radix_plan(nc).hist_words);
+  h.o_tot = c.take(4 * 256);
   h.bytes = c.off;
   return h;
 }
@@ -1206,9 +1203,9 @@ SortCarve sort_carve(uint64_t n, uint32_t op) {
   s.o_b1 = c.take(e * n);
   s.o_hist = c.take(4 * p.hist_words);
   s.o_tot = c.take(4 * 256);
-  s.o_heads = c.take(4 * p.n_chunks);
-  s.o_ss = c.take(4 * scan_sums_count(p.n_chunks));
-  s.o_lead = c.take(8 * p.n_chunks);
+  s.o_heads = c.take(4 * p.chunk_cap);
+  s.o_ss = c.take(4 * scan_sums_count(p.chunk_cap));
+  s.o_lead = c.take(8 * p.chunk_cap);
   s.bytes = c.off;
   return s;
 }
@@ -1405,18 +1402,11 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
       }
       // records and sort scratch for nc keys
       const HashCarve hc = hash_carve(nc);
-      const uint64_t o_rk32 = hc.o_rk32, o_rk0 = hc.o_rk0, o_rv0 = hc.o_rv0, o_rk1 = hc.o_rk1, o_rv1 = hc.o_rv1,
-                     o_hist = hc.o_hist, o_ss = hc.o_ss;
       st = scratch(hc.bytes);
       if (st != MR_OK) return st;
       uint8_t* sc = static_cast<uint8_t*>(job->int_scratch);
-      L.rk32 = reinterpret_cast<uint32_t*>(sc + o_rk32);
-      L.rk0 = reinterpret_cast<unsigned long long*>(sc + o_rk0);
-      L.rv0 = reinterpret_cast<unsigned long long*>(sc + o_rv0);
-      L.rk1 = reinterpret_cast<unsigned long long*>(sc + o_rk1);
-      L.rv1 = reinterpret_cast<unsigned long long*>(sc + o_rv1);
-      L.hist = reinterpret_cast<uint32_t*>(sc + o_hist);
-      L.scan_sums = reinterpret_cast<uint32_t*>(sc + o_ss);
+      L.pairs = sc + hc.o_pairs;
+      L.vals = reinterpret_cast<unsigned long long*>(sc + hc.o_vals);
       MR_HIP(int_enqueue_hash_out(L, nc, job->stream));  // gathers and clears the claimed slots
       if (!own_table && (hs.flags & kFlagTableFull)) {
         MR_HIP(hipMemsetAsync(sm, 0, sizeof(IntSmall), job->stream));
@@ -1430,7 +1420,21 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
         MR_HIP(hipMemsetAsync(sm, 0, sizeof(IntSmall), job->stream));
         continue;
       }
-      MR_HIP(int_enqueue_hash_sort_out(L, nc, job->stream));
+      SortLaunch S{};
+      S.in = reinterpret_cast<const uint32_t*>(L.pairs);
+      S.n = nc;
+      S.op = o;
+      S.flags = L.flags;
+      S.diff = &sm->diff;
+      S.buf0 = sc + hc.o_b0;
+      S.buf1 = sc + hc.o_b1;
+      S.hist = reinterpret_cast<uint32_t*>(sc + hc.o_hist);
+      S.tot = reinterpret_cast<uint32_t*>(sc + hc.o_tot);
+      S.out_keys = L.out_keys;
+      S.out_vals = L.out_vals;
+      S.cap = L.cap;
+      MR_HIP(pairs_enqueue_out(S, L.vals, job->stream));
+      MR_HIP(int_enqueue_side_append(L, job->stream));
       break;
     }
   }
@@ -1821,13 +1825,13 @@ extern "C" mr_status mr_workspace_bytes(const mr_job_config* cfg, mr_map_kind ki
       const uint64_t grid_cap = std::max<uint64_t>(1, (uint64_t)n_cu * eff_grid_pct(&tmp, n) / 100);
       r.add(plan_words(items, true, false, grid_cap).c.off);
       // the file-list pass: at most one pair and one URL per marker
-      const uint64_t hw = links_hist_words(cap);
       c.take(8 * cap);
       c.take(8 * cap);
       c.take(8 * cap);
-      c.take(8 * cap);
-      c.take(4 * std::max<uint64_t>(hw, 1));
-      c.take(4 * std::max(scan_sums_count(hw), scan_sums_count(cap)));
+      c.take(8);
+      c.take(4 * radix_plan(cap).hist_words);
+      c.take(4 * 256);
+      c.take(4 * scan_sums_count(cap));
       c.take(4 * cap);
       c.take(8);
       c.take(8);

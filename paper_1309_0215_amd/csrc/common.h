@@ -151,4 +151,14 @@ MR_DEV unsigned long long wave_claim(unsigned long long* counter) {
   return base + mbcnt(active);
 }
 
+// ---------------------------------------------------------------------------
+// radix sort (sort.hip)
+// ---------------------------------------------------------------------------
+// Passes that move data before digit `shift / 8`: the first, and each later one with a differing bit.
+MR_DEV uint32_t rs_moves_before(uint64_t diff, uint32_t shift) {
+  uint32_t c = 0;
+  for (uint32_t s = 0; s < shift; s += 8) c += (s == 0 || ((diff >> s) & 0xFFu)) ? 1u : 0u;
+  return c;
+}
+
 }  // namespace mr

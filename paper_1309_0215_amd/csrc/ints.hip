@@ -715,13 +715,13 @@ __global__ __launch_bounds__(1024) void k_int_small_out(IntTable T, uint32_t* __
   }
 }
 
-// Claimed slots -> (key, value) records; slots are cleared for reuse.
+// Claimed slots -> (key, claim index) pairs and values; slots are cleared for reuse.
 template <int OP>
-__global__ __launch_bounds__(256) void k_int_gather(IntTable T, uint32_t* __restrict__ rk, unsigned long long* __restrict__ rv) {
+__global__ __launch_bounds__(256) void k_int_gather(IntTable T, uint2* __restrict__ rk, unsigned long long* __restrict__ rv) {
   const uint64_t n = *T.n_claimed;
   for (uint64_t q = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; q < n; q += (uint64_t)gridDim.x * blockDim.x) {
     const uint32_t i = T.claimed[q];
-    rk[q] = T.keys[i];
+    rk[q] = make_uint2(T.keys[i], (uint32_t)q);
     unsigned long long v;
     if (OP == 0) v = T.cnt[i];
     else if (OP == 1) v = reinterpret_cast<unsigned long long*>(T.val)[i];
@@ -735,23 +735,8 @@ __global__ __launch_bounds__(256) void k_int_gather(IntTable T, uint32_t* __rest
 }
 
 // ----------------------------------------------------------------------------
-// LSD radix sort of (u64 key, u64 value) records, 8-bit digits, stable
+// scans
 // ----------------------------------------------------------------------------
-constexpr uint32_t kSortTile = 2048;  // elements per block (256 threads x 8)
-
-__global__ __launch_bounds__(256) void k_radix_hist(const unsigned long long* __restrict__ key, uint64_t n, int shift,
-                                                    uint32_t n_tiles, uint32_t* __restrict__ hist /* [256][n_tiles] */) {
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
-  for (uint32_t q = threadIdx.x; q < kSortTile; q += blockDim.x) {
-    const uint64_t i = base + q;
-    if (i < n) atomicAdd(&h[(key[i] >> shift) & 0xFFu], 1u);
-  }
-  __syncthreads();
-  hist[(uint64_t)threadIdx.x * n_tiles + blockIdx.x] = h[threadIdx.x];
-}
 
 // Device-wide exclusive scan of a (in place): per-block sums, scan of sums, add back.
 constexpr uint32_t kScanTile = 4096;
@@ -793,112 +778,6 @@ __global__ __launch_bounds__(256) void k_scan_apply(uint32_t* __restrict__ a, ui
     if (i < n) a[i] = pre + inc - x;
     carry += tot;
     __syncthreads();
-  }
-}
-
-// Stable scatter: each tile sorts itself by the digit in LDS with eight
-// one-bit splits, then writes each element to its digit's global offset.
-__global__ __launch_bounds__(256) void k_radix_scatter(const unsigned long long* __restrict__ key_in,
-                                                       const unsigned long long* __restrict__ val_in, uint64_t n, int shift,
-                                                       uint32_t n_tiles, const uint32_t* __restrict__ hist,
-                                                       unsigned long long* __restrict__ key_out,
-                                                       unsigned long long* __restrict__ val_out) {
-  __shared__ unsigned long long sk[kSortTile];
-  __shared__ unsigned long long sv[kSortTile];
-  __shared__ uint32_t dstart[256];
-  __shared__ uint32_t dcount[256];
-  __shared__ uint32_t ws[256 / kWave];
-  const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
-  const uint32_t m = (uint32_t)((n - base) < kSortTile ? (n - base) : kSortTile);
-  constexpr uint32_t E = kSortTile / 256;
-  // each thread owns E consecutive elements
-  unsigned long long k[E], v[E];
-#pragma unroll
-  for (uint32_t e = 0; e < E; ++e) {
-    const uint32_t li = threadIdx.x * E + e;
-    if (li < m) {
-      k[e] = key_in[base + li];
-      v[e] = val_in[base + li];
-    } else {
-      k[e] = ~0ull;  // padding sorts last and is never written
-      v[e] = 0;
-    }
-  }
-  dcount[threadIdx.x] = 0;
-  __syncthreads();
-  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
-  for (int bit = 0; bit < 8; ++bit) {
-    uint32_t ones = 0;
-#pragma unroll
-    for (uint32_t e = 0; e < E; ++e) ones += (uint32_t)((k[e] >> (shift + bit)) & 1ull);
-    const uint32_t zeros = E - ones;
-    // block exclusive scan of zeros (DPP lane shifts within the wave)
-    const uint32_t inc = wave_incl_scan(zeros);
-    if (lane == kWave - 1) ws[wv] = inc;
-    __syncthreads();
-    uint32_t pre = 0, tot = 0;
-    for (uint32_t w = 0; w < 256 / kWave; ++w) {
-      if (w < wv) pre += ws[w];
-      tot += ws[w];
-    }
-    uint32_t zpos = pre + inc - zeros;               // zeros before this thread
-    uint32_t opos = tot + threadIdx.x * E - zpos;     // ones before this thread, after all zeros
-#pragma unroll
-    for (uint32_t e = 0; e < E; ++e) {
-      const bool one = (k[e] >> (shift + bit)) & 1ull;
-      const uint32_t dst = one ? opos++ : zpos++;
-      sk[dst] = k[e];
-      sv[dst] = v[e];
-    }
-    __syncthreads();
-#pragma unroll
-    for (uint32_t e = 0; e < E; ++e) {
-      k[e] = sk[threadIdx.x * E + e];
-      v[e] = sv[threadIdx.x * E + e];
-    }
-    __syncthreads();
-  }
-  // per-digit start within the tile, from the locally sorted order
-#pragma unroll
-  for (uint32_t e = 0; e < E; ++e) {
-    const uint32_t li = threadIdx.x * E + e;
-    if (li < m) atomicAdd(&dcount[(k[e] >> shift) & 0xFFu], 1u);
-  }
-  __syncthreads();
-  {
-    const uint32_t x = dcount[threadIdx.x];
-    uint32_t inc = x;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const uint32_t t = __shfl_up(inc, o);
-      if (lane >= (uint32_t)o) inc += t;
-    }
-    if (lane == kWave - 1) ws[wv] = inc;
-    __syncthreads();
-    uint32_t pre = 0;
-    for (uint32_t w = 0; w < wv; ++w) pre += ws[w];
-    dstart[threadIdx.x] = pre + inc - x;
-  }
-  __syncthreads();
-#pragma unroll
-  for (uint32_t e = 0; e < E; ++e) {
-    const uint32_t li = threadIdx.x * E + e;
-    if (li < m) {
-      const uint32_t d = (uint32_t)((k[e] >> shift) & 0xFFu);
-      const uint64_t dst = (uint64_t)hist[(uint64_t)d * n_tiles + blockIdx.x] + (li - dstart[d]);
-      key_out[dst] = k[e];
-      val_out[dst] = v[e];
-    }
-  }
-}
-
-// Split sorted 64-bit records back into u32 keys and values (hash strategy output).
-__global__ void k_split_out(const unsigned long long* __restrict__ rk, const unsigned long long* __restrict__ rv, uint64_t n,
-                            int op, uint32_t* __restrict__ out_keys, void* __restrict__ out_vals, uint64_t cap) {
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n && i < cap; i += (uint64_t)gridDim.x * blockDim.x) {
-    out_keys[i] = (uint32_t)rk[i];
-    if (op == 1) reinterpret_cast<unsigned long long*>(out_vals)[i] = rv[i];
-    else reinterpret_cast<uint32_t*>(out_vals)[i] = (uint32_t)rv[i];
   }
 }
 
@@ -1101,60 +980,21 @@ hipError_t int_enqueue_small_out(const IntLaunch& L, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Radix sort of n records (64-bit keys and values) over the given key bits.
-hipError_t radix_sort64(unsigned long long* k0, unsigned long long* v0, unsigned long long* k1, unsigned long long* v1,
-                        uint64_t n, int bits, uint32_t* hist, uint32_t* scan_sums, bool* result_in_1, hipStream_t s) {
-  const uint32_t n_tiles = (uint32_t)((n + kSortTile - 1) / kSortTile);
-  const uint64_t hn = 256ull * n_tiles;
-  const uint32_t sb = (uint32_t)((hn + kScanTile - 1) / kScanTile);
-  bool in1 = false;
-  for (int sh = 0; sh < bits; sh += 8) {
-    unsigned long long *ki = in1 ? k1 : k0, *vi = in1 ? v1 : v0, *ko = in1 ? k0 : k1, *vo = in1 ? v0 : v1;
-    if (n) {
-      hipLaunchKernelGGL(k_radix_hist, dim3(n_tiles), dim3(256), 0, s, ki, n, sh, n_tiles, hist);
-      if (hn <= kScanOneMax) {
-        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneWaves * kWave), 0, s, hist, (uint32_t)hn,
-                           (unsigned long long*)nullptr);
-      } else {
-        hipLaunchKernelGGL(k_scan_blocks, dim3(sb), dim3(256), 0, s, hist, hn, scan_sums);
-        hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, scan_sums, sb, (unsigned long long*)nullptr);
-        hipLaunchKernelGGL(k_scan_apply, dim3(sb), dim3(256), 0, s, hist, hn, scan_sums);
-      }
-      hipLaunchKernelGGL(k_radix_scatter, dim3(n_tiles), dim3(256), 0, s, ki, vi, n, sh, n_tiles, hist, ko, vo);
-    }
-    in1 = !in1;
-  }
-  *result_in_1 = in1;
-  return hipGetLastError();
-}
-
 hipError_t int_enqueue_hash_out(const IntLaunch& L, uint64_t n_claimed_host, hipStream_t s) {
   IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.max_probes, L.side_cnt, L.side_val, L.flags};
   const uint64_t n = n_claimed_host;
   const uint32_t g = blocks_for(n, 256, 4096);
   switch (L.op) {
-    case 0: hipLaunchKernelGGL(k_int_gather<0>, dim3(g), dim3(256), 0, s, T, L.rk32, L.rv0); break;
-    case 1: hipLaunchKernelGGL(k_int_gather<1>, dim3(g), dim3(256), 0, s, T, L.rk32, L.rv0); break;
-    case 2: hipLaunchKernelGGL(k_int_gather<2>, dim3(g), dim3(256), 0, s, T, L.rk32, L.rv0); break;
-    case 3: hipLaunchKernelGGL(k_int_gather<3>, dim3(g), dim3(256), 0, s, T, L.rk32, L.rv0); break;
+    case 0: hipLaunchKernelGGL(k_int_gather<0>, dim3(g), dim3(256), 0, s, T, static_cast<uint2*>(L.pairs), L.vals); break;
+    case 1: hipLaunchKernelGGL(k_int_gather<1>, dim3(g), dim3(256), 0, s, T, static_cast<uint2*>(L.pairs), L.vals); break;
+    case 2: hipLaunchKernelGGL(k_int_gather<2>, dim3(g), dim3(256), 0, s, T, static_cast<uint2*>(L.pairs), L.vals); break;
+    case 3: hipLaunchKernelGGL(k_int_gather<3>, dim3(g), dim3(256), 0, s, T, static_cast<uint2*>(L.pairs), L.vals); break;
   }
   return hipGetLastError();
 }
 
-__global__ void k_widen_keys(const uint32_t* __restrict__ a, unsigned long long* __restrict__ b, uint64_t n) {
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) b[i] = a[i];
-}
-
-hipError_t int_enqueue_hash_sort_out(const IntLaunch& L, uint64_t n, hipStream_t s) {
-  const uint32_t g = blocks_for(n, 256, 4096);
-  hipLaunchKernelGGL(k_widen_keys, dim3(g), dim3(256), 0, s, L.rk32, L.rk0, n);
-  bool in1 = false;
-  hipError_t e = radix_sort64(L.rk0, L.rv0, L.rk1, L.rv1, n, 32, L.hist, L.scan_sums, &in1, s);
-  if (e != hipSuccess) return e;
-  const unsigned long long* rk = in1 ? L.rk1 : L.rk0;
-  const unsigned long long* rv = in1 ? L.rv1 : L.rv0;
-  hipLaunchKernelGGL(k_split_out, dim3(g), dim3(256), 0, s, rk, rv, n, L.op, L.out_keys, L.out_vals, L.cap);
-  hipLaunchKernelGGL(k_side_append, dim3(1), dim3(64), 0, s, L.side_cnt, L.side_val, L.op, L.n_claimed, L.n_out,
+hipError_t int_enqueue_side_append(const IntLaunch& L, hipStream_t s) {
+  hipLaunchKernelGGL(k_side_append, dim3(1), dim3(64), 0, s, L.side_cnt, L.side_val, (int)L.op, L.n_claimed, L.n_out,
                      L.out_keys, L.out_vals, L.cap);
   return hipGetLastError();
 }

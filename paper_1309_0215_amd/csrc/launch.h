@@ -51,8 +51,10 @@ struct LinksPost {
   uint64_t n_keys;              // distinct URLs
   uint64_t file_mod;            // sort key = rank * file_mod + record (file_mod: the record count, at least 1)
   int sort_bits;                // key bits, a multiple of 8, with 2^sort_bits > n_keys * file_mod
-  unsigned long long *k0, *v0, *k1, *v1;  // [n] each: sort keys, unused values, and their second buffers
+  unsigned long long *k0, *k1, *k2;  // [n] each: sort keys and the sort's two buffers
+  unsigned long long* diff;     // device: differing key bits
   uint32_t* hist;               // radix histogram
+  uint32_t* tot;                // [256]
   uint32_t* scan_sums;
   uint32_t* head;               // [n]
   unsigned long long* total;    // device: distinct (URL, file) pairs
@@ -60,12 +62,9 @@ struct LinksPost {
   uint32_t* flags;              // device: internal errors
   uint32_t* first;              // [n_keys + 1] first sorted pair of each rank
 };
-hipError_t links_enqueue_rank_sort(const LinksPost& P, bool* sorted_in_1, hipStream_t s);
-hipError_t links_enqueue_write(const LinksPost& P, bool sorted_in_1, uint32_t* ids, uint64_t cap_ids, uint64_t* list_off,
+hipError_t links_enqueue_rank_sort(const LinksPost& P, hipStream_t s);
+hipError_t links_enqueue_write(const LinksPost& P, uint32_t* ids, uint64_t cap_ids, uint64_t* list_off,
                                uint32_t* counts, hipStream_t s);
-uint64_t links_hist_words(uint64_t n);
-hipError_t radix_sort64(unsigned long long* k0, unsigned long long* v0, unsigned long long* k1, unsigned long long* v1,
-                        uint64_t n, int bits, uint32_t* hist, uint32_t* scan_sums, bool* result_in_1, hipStream_t s);
 
 // Allocation-free histogram: partial rows in a static device array of
 // kRgbStaticRows rows (3 MiB per GPU). rgb_static_init looks up its address
@@ -112,11 +111,9 @@ struct IntLaunch {
   uint64_t max_probes;  // slots an insert looks at before the table counts as full
   uint32_t* side_cnt;
   void* side_val;
-  // sort scratch
-  uint32_t* rk32;
-  unsigned long long *rk0, *rv0, *rk1, *rv1;
-  uint32_t* hist;
-  uint32_t* scan_sums;
+  // hash output: (key, index) pairs and values of the claimed slots
+  void* pairs;
+  unsigned long long* vals;
   // outputs
   uint32_t* out_keys;
   void* out_vals;
@@ -125,12 +122,12 @@ struct IntLaunch {
 };
 
 // Radix sort of all elements and the reduce of the runs (sort.hip).
-constexpr uint32_t kRadixTile = 8192;  // elements per tile
-constexpr uint32_t kRunsChunk = 1024;  // sorted elements per wave of the reduce
 struct RadixPlan {
   uint32_t n_tiles;
-  uint64_t hist_words;  // digit counts of all tiles
   uint64_t n_chunks;    // chunks of the reduce
+  // scratch sizes, not below those of any smaller n
+  uint64_t hist_words;  // digit counts of all tiles
+  uint64_t chunk_cap;   // entries per chunk array
 };
 RadixPlan radix_plan(uint64_t n);
 struct SortLaunch {
@@ -144,15 +141,31 @@ struct SortLaunch {
   void *buf0, *buf1;       // [n] each: uint32 keys for COUNT, (key, value) pairs otherwise
   uint32_t* hist;          // [hist_words]
   uint32_t* tot;           // [256]
-  uint32_t* heads;         // [n_chunks] run heads per chunk
-  uint32_t* scan_sums;     // scan_sums_count(n_chunks)
-  unsigned long long* lead;  // [n_chunks]
+  uint32_t* heads;         // [chunk_cap] run heads per chunk
+  uint32_t* scan_sums;     // scan_sums_count(chunk_cap)
+  unsigned long long* lead;  // [chunk_cap]
   uint32_t* out_keys;
   void* out_vals;
   uint64_t cap;
   unsigned long long* n_out;
 };
 hipError_t int_enqueue_sort(const SortLaunch& L, hipStream_t s);
+// in: n pairs (key, index into vals); writes keys ascending and their values
+// (uses in, n, op, flags, diff, buf0, buf1, hist, tot and the outputs).
+hipError_t pairs_enqueue_out(const SortLaunch& L, const unsigned long long* vals, hipStream_t s);
+// Sort of uint64 keys by their low `bits` bits. The result is in buf0 when
+// rs_moves_before(*diff, keys64_sorted_bits(bits)) is odd, else in buf1.
+struct Keys64Sort {
+  const unsigned long long* in;
+  uint64_t n;
+  uint32_t bits;
+  unsigned long long* diff;  // device, zero at the start
+  unsigned long long *buf0, *buf1;
+  uint32_t* hist;            // [radix_plan(n).hist_words]
+  uint32_t* tot;             // [256]
+};
+hipError_t keys64_enqueue_sort(const Keys64Sort& L, hipStream_t s);
+uint32_t keys64_sorted_bits(uint32_t bits);
 
 hipError_t int_enqueue_lds_array(const IntLaunch& L, hipStream_t s);
 // device-wide exclusive scan of uint32 counts (sums: scan_sums_count(n) entries)
@@ -192,7 +205,7 @@ hipError_t int_enqueue_sample(const IntLaunch& L, uint32_t* distinct, hipStream_
 uint32_t int_small_out_max();  // keys int_enqueue_small_out handles
 hipError_t int_enqueue_small_out(const IntLaunch& L, hipStream_t s);
 hipError_t int_enqueue_hash_out(const IntLaunch& L, uint64_t n_claimed_host, hipStream_t s);
-hipError_t int_enqueue_hash_sort_out(const IntLaunch& L, uint64_t n, hipStream_t s);
+hipError_t int_enqueue_side_append(const IntLaunch& L, hipStream_t s);
 uint32_t int_lds_array_bytes(uint64_t R, uint32_t op);
 
 // One k-means step.

@@ -16,10 +16,11 @@
 namespace mr {
 
 constexpr uint32_t kLinksThreads = 256;
-constexpr uint32_t kLinksRadixTile = 2048;  // elements per tile of the radix sort in ints.hip
 
-__global__ void k_links_init(unsigned long long* total, unsigned long long* n_valid, uint32_t* flags) {
+__global__ void k_links_init(unsigned long long* total, unsigned long long* n_valid, unsigned long long* diff,
+                             uint32_t* flags) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *diff = 0ull;
     *total = 0ull;
     *n_valid = 0ull;
     *flags = 0u;
@@ -40,15 +41,23 @@ __global__ __launch_bounds__(kLinksThreads) void k_links_rank(LinksPost P) {
       else atomicOr(P.flags, kFlagInternal);  // every URL of the table has an output rank
     }
     P.k0[i] = key;
-    P.v0[i] = 0ull;  // the sort carries values; these are not used
   }
+}
+
+// Where the sorted keys are (sort.hip).
+struct LinksSorted {
+  const unsigned long long *a, *b, *diff;
+  uint32_t bits;
+};
+MR_DEV const unsigned long long* links_sorted(const LinksSorted& S) {
+  return rs_moves_before(*S.diff, S.bits) % 2 ? S.a : S.b;
 }
 
 // head[i] = 1 for the first of each run of equal valid keys; the last valid
 // key writes the number of links (valid keys come first).
-__global__ __launch_bounds__(kLinksThreads) void k_links_heads(const unsigned long long* __restrict__ k, uint64_t n,
-                                                               uint32_t* __restrict__ head,
+__global__ __launch_bounds__(kLinksThreads) void k_links_heads(LinksSorted S, uint64_t n, uint32_t* __restrict__ head,
                                                                unsigned long long* __restrict__ n_valid) {
+  const unsigned long long* const k = links_sorted(S);
   for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
     const unsigned long long x = k[i];
     head[i] = (x != ~0ull && (i == 0 || x != k[i - 1])) ? 1u : 0u;
@@ -61,12 +70,13 @@ __global__ __launch_bounds__(kLinksThreads) void k_links_heads(const unsigned lo
 // reports the capacity error after the launch); the first head of a rank writes the rank's list
 // offset and its first index among the sorted pairs. list_off[n_keys] = the
 // number of list entries, first[n_keys] = the number of links.
-__global__ __launch_bounds__(kLinksThreads) void k_links_write(const unsigned long long* __restrict__ k, uint64_t n,
+__global__ __launch_bounds__(kLinksThreads) void k_links_write(LinksSorted S, uint64_t n,
                                                                const uint32_t* __restrict__ pos, uint64_t file_mod,
                                                                const unsigned long long* __restrict__ total,
                                                                const unsigned long long* __restrict__ n_valid,
                                                                uint64_t n_keys, uint32_t* __restrict__ ids, uint64_t cap_ids,
                                                                uint64_t* __restrict__ list_off, uint32_t* __restrict__ first) {
+  const unsigned long long* const k = links_sorted(S);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     list_off[n_keys] = *total;
     first[n_keys] = (uint32_t)*n_valid;
@@ -92,29 +102,26 @@ __global__ __launch_bounds__(kLinksThreads) void k_links_counts(const uint32_t* 
     counts[r] = first[r + 1] - first[r];
 }
 
-uint64_t links_hist_words(uint64_t n) { return 256ull * ((n + kLinksRadixTile - 1) / kLinksRadixTile); }
-
 static uint32_t links_grid(uint64_t n) {
   const uint64_t g = (n + kLinksThreads - 1) / kLinksThreads;
   return (uint32_t)(g < 1 ? 1 : (g > 8192 ? 8192 : g));
 }
 
-hipError_t links_enqueue_rank_sort(const LinksPost& P, bool* sorted_in_1, hipStream_t s) {
-  *sorted_in_1 = false;
-  hipLaunchKernelGGL(k_links_init, dim3(1), dim3(64), 0, s, P.total, P.n_valid, P.flags);
+static LinksSorted links_where(const LinksPost& P) { return {P.k1, P.k2, P.diff, keys64_sorted_bits((uint32_t)P.sort_bits)}; }
+
+hipError_t links_enqueue_rank_sort(const LinksPost& P, hipStream_t s) {
+  hipLaunchKernelGGL(k_links_init, dim3(1), dim3(64), 0, s, P.total, P.n_valid, P.diff, P.flags);
   if (!P.n) return hipGetLastError();
   hipLaunchKernelGGL(k_links_rank, dim3(links_grid(P.n)), dim3(kLinksThreads), 0, s, P);
-  hipError_t e = radix_sort64(P.k0, P.v0, P.k1, P.v1, P.n, P.sort_bits, P.hist, P.scan_sums, sorted_in_1, s);
+  const hipError_t e = keys64_enqueue_sort({P.k0, P.n, (uint32_t)P.sort_bits, P.diff, P.k1, P.k2, P.hist, P.tot}, s);
   if (e != hipSuccess) return e;
-  const unsigned long long* k = *sorted_in_1 ? P.k1 : P.k0;
-  hipLaunchKernelGGL(k_links_heads, dim3(links_grid(P.n)), dim3(kLinksThreads), 0, s, k, P.n, P.head, P.n_valid);
+  hipLaunchKernelGGL(k_links_heads, dim3(links_grid(P.n)), dim3(kLinksThreads), 0, s, links_where(P), P.n, P.head, P.n_valid);
   return scan_exclusive_u32(P.head, P.n, P.scan_sums, P.total, s);
 }
 
-hipError_t links_enqueue_write(const LinksPost& P, bool sorted_in_1, uint32_t* ids, uint64_t cap_ids, uint64_t* list_off,
+hipError_t links_enqueue_write(const LinksPost& P, uint32_t* ids, uint64_t cap_ids, uint64_t* list_off,
                                uint32_t* counts, hipStream_t s) {
-  const unsigned long long* k = sorted_in_1 ? P.k1 : P.k0;
-  hipLaunchKernelGGL(k_links_write, dim3(links_grid(P.n)), dim3(kLinksThreads), 0, s, k, P.n, P.head, P.file_mod,
+  hipLaunchKernelGGL(k_links_write, dim3(links_grid(P.n)), dim3(kLinksThreads), 0, s, links_where(P), P.n, P.head, P.file_mod,
                      P.total, P.n_valid, P.n_keys, ids, cap_ids, list_off, P.first);
   if (P.n_keys)
     hipLaunchKernelGGL(k_links_counts, dim3(links_grid(P.n_keys)), dim3(kLinksThreads), 0, s, P.first, P.n_keys, counts);

@@ -13,6 +13,8 @@
 // later pass over a digit in which no bit differs would copy its input as it
 // stands; its kernels return at once, and every kernel derives from the same
 // word where the data is.
+#include <algorithm>
+
 #include "common.h"
 #include "launch.h"
 
@@ -20,10 +22,13 @@ namespace mr {
 
 constexpr uint32_t kRsThreads = 512;
 constexpr uint32_t kRsWaves = kRsThreads / kWave;
-constexpr uint32_t kRsPer = 16;                       // elements per thread
-constexpr uint32_t kRsTile = kRsThreads * kRsPer;     // elements per tile
 constexpr uint32_t kRsDigits = 256;
-static_assert(kRsTile == kRadixTile, "the tile the scratch is planned for");
+// Elements per thread (PER below): 16, so that a digit's run of a tile is 32
+// elements on average, or 4 for inputs of up to kRsSmall elements, which leave
+// CUs idle with tiles of 8192 and wait on one tile's chain of 16 rows (10,000
+// pairs: 8.8 us per scatter with 16, 4.2 us with 4).
+constexpr uint32_t kRsPerLarge = 16, kRsPerSmall = 4;
+constexpr uint64_t kRsSmall = 1ull << 20;
 
 MR_DEV uint64_t rs_key(uint32_t e) { return e; }
 MR_DEV uint64_t rs_key(uint2 e) { return e.x; }
@@ -32,12 +37,6 @@ MR_DEV uint32_t rs_digit(uint32_t e, uint32_t shift) { return (e >> shift) & 0xF
 MR_DEV uint32_t rs_digit(uint2 e, uint32_t shift) { return (e.x >> shift) & 0xFFu; }
 MR_DEV uint32_t rs_digit(unsigned long long e, uint32_t shift) { return (uint32_t)(e >> shift) & 0xFFu; }
 
-// Passes that move data before digit `shift / 8`: the first, and each later one with a differing bit.
-MR_DEV uint32_t rs_moves_before(uint64_t diff, uint32_t shift) {
-  uint32_t c = 0;
-  for (uint32_t s = 0; s < shift; s += 8) c += (s == 0 || ((diff >> s) & 0xFFu)) ? 1u : 0u;
-  return c;
-}
 MR_DEV bool rs_skip(uint64_t diff, uint32_t shift) { return shift && !((diff >> shift) & 0xFFu); }
 
 // Where the data of a pass is: the input, or one of the two buffers.
@@ -88,10 +87,11 @@ MR_DEV void rs_store<uint2>(uint2* p, uint64_t i, uint2 x) {
 // (the top digits of small keys, skewed keys) serialise eight lanes, not 64.
 // The first pass (FIRST) checks the declared range and gathers the differing
 // key bits.
-template <typename E, bool FIRST>
+template <typename E, bool FIRST, uint32_t PER>
 __global__ __launch_bounds__(kRsThreads) void k_rsort_hist(RsData<E> D, uint32_t shift, uint32_t n_tiles,
                                                            uint32_t* __restrict__ hist, uint64_t R,
                                                            uint32_t* __restrict__ flags) {
+  constexpr uint32_t kTile = kRsThreads * PER;
   constexpr uint32_t kCopies = 8, kLd = kRsDigits + 4;  // (copies start 4 banks apart)
   __shared__ uint32_t h[kCopies * kLd];
   __shared__ unsigned long long wdiff[kRsWaves];
@@ -101,13 +101,13 @@ __global__ __launch_bounds__(kRsThreads) void k_rsort_hist(RsData<E> D, uint32_t
     if (rs_skip(diff, shift)) return;
   }
   for (uint32_t i = threadIdx.x; i < kCopies * kLd; i += kRsThreads) h[i] = 0;
-  const uint64_t base = (uint64_t)blockIdx.x * kRsTile;
-  const uint32_t m = D.n - base < kRsTile ? (uint32_t)(D.n - base) : kRsTile;
+  const uint64_t base = (uint64_t)blockIdx.x * kTile;
+  const uint32_t m = D.n - base < kTile ? (uint32_t)(D.n - base) : kTile;
   const E* src = nullptr;
   if (!FIRST) src = rs_moves_before(diff, shift) % 2 ? D.a : D.b;
-  E e[kRsPer];
+  E e[PER];
 #pragma unroll
-  for (uint32_t u = 0; u < kRsPer; ++u) {
+  for (uint32_t u = 0; u < PER; ++u) {
     const uint32_t i = u * kRsThreads + threadIdx.x;
     e[u] = E{};
     if (i < m) e[u] = FIRST ? rs_in<E>(D, base + i) : rs_load<E>(src, base + i);
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rsort_hist(RsData<E> D, uint32_t
   bool bad = false;
   const uint64_t k0 = FIRST ? rs_key(rs_in<E>(D, 0)) : 0;
 #pragma unroll
-  for (uint32_t u = 0; u < kRsPer; ++u) {
+  for (uint32_t u = 0; u < PER; ++u) {
     if (u * kRsThreads + threadIdx.x >= m) break;
     atomicAdd(&mine[rs_digit(e[u], shift)], 1u);
     if (FIRST) {
@@ -202,16 +202,17 @@ MR_DEV uint64_t rs_match(uint32_t d) {
   return (uint64_t)hi << 32 | lo;
 }
 
-// Stable scatter of one tile. Wave w holds the tile's elements [1024 w,
-// 1024 (w + 1)) as 16 rows of 64; row by row, a lane's rank among the wave's
+// Stable scatter of one tile. Wave w holds the w-th eighth of the tile's
+// elements as PER rows of 64; row by row, a lane's rank among the wave's
 // elements of its digit is the wave's count so far plus the matching lanes
 // below it. The tile's order is (digit, wave, row, lane); it is written to
 // LDS and from there to the digits' global places.
-template <typename E, bool FIRST>
+template <typename E, bool FIRST, uint32_t PER>
 __global__ __launch_bounds__(kRsThreads) void k_rsort_scatter(RsData<E> D, uint32_t shift, uint32_t n_tiles,
                                                               const uint32_t* __restrict__ hist,
                                                               const uint32_t* __restrict__ tot) {
-  __shared__ E st[kRsTile];
+  constexpr uint32_t kTile = kRsThreads * PER;
+  __shared__ E st[kTile];
   __shared__ uint32_t wh[kRsWaves][kRsDigits];  // the wave's digit counts, then its first place per digit
   __shared__ uint32_t delta[kRsDigits];         // global place of LDS place i of digit d: delta[d] + i
   __shared__ uint32_t sa[kRsDigits / kWave], sb[kRsDigits / kWave];
@@ -220,16 +221,16 @@ __global__ __launch_bounds__(kRsThreads) void k_rsort_scatter(RsData<E> D, uint3
     diff = *D.diff;
     if (rs_skip(diff, shift)) return;
   }
-  const uint64_t base = (uint64_t)blockIdx.x * kRsTile;
-  const uint32_t m = D.n - base < kRsTile ? (uint32_t)(D.n - base) : kRsTile;
+  const uint64_t base = (uint64_t)blockIdx.x * kTile;
+  const uint32_t m = D.n - base < kTile ? (uint32_t)(D.n - base) : kTile;
   const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
   const bool odd = FIRST ? false : rs_moves_before(diff, shift) % 2;
   const E* const src = odd ? D.a : D.b;
   E* const dst = FIRST || !odd ? D.a : D.b;
-  E e[kRsPer];
+  E e[PER];
 #pragma unroll
-  for (uint32_t u = 0; u < kRsPer; ++u) {
-    const uint32_t i = wv * (kWave * kRsPer) + u * kWave + lane;
+  for (uint32_t u = 0; u < PER; ++u) {
+    const uint32_t i = wv * (kWave * PER) + u * kWave + lane;
     e[u] = E{};
     if (i < m) e[u] = FIRST ? rs_in<E>(D, base + i) : rs_load<E>(src, base + i);
   }
@@ -241,12 +242,12 @@ __global__ __launch_bounds__(kRsThreads) void k_rsort_scatter(RsData<E> D, uint3
     dtot = tot[threadIdx.x];
   }
   __syncthreads();
-  uint32_t rank[kRsPer];
+  uint32_t rank[PER];
 #pragma unroll
-  for (uint32_t u = 0; u < kRsPer; ++u) {
+  for (uint32_t u = 0; u < PER; ++u) {
     // elements past the end sit behind all others of the tile; they count in
     // the last digit, after every real element, and are not written
-    const bool act = wv * (kWave * kRsPer) + u * kWave + lane < m;
+    const bool act = wv * (kWave * PER) + u * kWave + lane < m;
     const uint32_t d = act ? rs_digit(e[u], shift) : kRsDigits - 1;
     const uint64_t same = rs_match(d);
     const uint32_t below = mbcnt(same);
@@ -285,14 +286,14 @@ __global__ __launch_bounds__(kRsThreads) void k_rsort_scatter(RsData<E> D, uint3
   }
   __syncthreads();
 #pragma unroll
-  for (uint32_t u = 0; u < kRsPer; ++u) {
-    const bool act = wv * (kWave * kRsPer) + u * kWave + lane < m;
+  for (uint32_t u = 0; u < PER; ++u) {
+    const bool act = wv * (kWave * PER) + u * kWave + lane < m;
     const uint32_t d = act ? rs_digit(e[u], shift) : kRsDigits - 1;
     st[wh[wv][d] + rank[u]] = e[u];
   }
   __syncthreads();
 #pragma unroll
-  for (uint32_t u = 0; u < kRsPer; ++u) {
+  for (uint32_t u = 0; u < PER; ++u) {
     const uint32_t i = u * kRsThreads + threadIdx.x;
     if (i < m) {
       const E x = st[i];
@@ -304,37 +305,35 @@ __global__ __launch_bounds__(kRsThreads) void k_rsort_scatter(RsData<E> D, uint3
 // ----------------------------------------------------------------------------
 // reduce of sorted runs
 // ----------------------------------------------------------------------------
-// A wave takes a chunk of 1024 sorted elements as 16 rows of 64. The first
+// A wave takes a chunk of PER rows of 64 sorted elements. The first
 // kernel counts the chunk's run heads; after the scan, the second writes the
 // key of every head and the value of every run that starts in the chunk, as
 // far as the chunk sees it, and leaves the value of the elements before the
 // first head (a run from an earlier chunk) in lead[chunk]; the third adds
 // those to their runs.
-constexpr uint32_t kRunRows = 16;
-constexpr uint32_t kRunChunk = kWave * kRunRows;
+// Small inputs take chunks of 4 rows, for the reason given at kRsPerSmall.
 constexpr uint32_t kRunThreads = 256;
-static_assert(kRunChunk == kRunsChunk, "the chunk the scratch is planned for");
 
 template <typename E>
 MR_DEV const E* rs_sorted(const RsData<E>& D, uint32_t bits) {
   return rs_moves_before(*D.diff, bits) % 2 ? D.a : D.b;
 }
 
-template <typename E>
+template <typename E, uint32_t PER>
 __global__ __launch_bounds__(kRunThreads) void k_runs_count(RsData<E> D, uint32_t bits, uint32_t* __restrict__ heads) {
   const E* const s = rs_sorted(D, bits);
   const uint32_t lane = lane_id();
-  const uint64_t c = (uint64_t)blockIdx.x * (kRunThreads / kWave) + threadIdx.x / kWave, base = c * kRunChunk;
+  const uint64_t c = (uint64_t)blockIdx.x * (kRunThreads / kWave) + threadIdx.x / kWave, base = c * (kWave * PER);
   if (base >= D.n) return;
-  uint32_t k[kRunRows];
+  uint32_t k[PER];
 #pragma unroll
-  for (uint32_t u = 0; u < kRunRows; ++u) {
+  for (uint32_t u = 0; u < PER; ++u) {
     const uint64_t i = base + u * kWave + lane;
     k[u] = i < D.n ? (uint32_t)rs_key(rs_load<E>(s, i)) : 0u;
   }
   uint32_t last = base ? (uint32_t)rs_key(rs_load<E>(s, base - 1)) : 0u, n = 0;
 #pragma unroll
-  for (uint32_t u = 0; u < kRunRows; ++u) {
+  for (uint32_t u = 0; u < PER; ++u) {
     const uint64_t i = base + u * kWave + lane;
     const uint32_t prev = from_prev_lane(k[u], last);
     n += popc64(__ballot(i < D.n && (i == 0 || k[u] != prev)));
@@ -383,17 +382,17 @@ MR_DEV unsigned long long run_row_value(uint32_t v, uint32_t lane, uint32_t star
 MR_DEV uint32_t rs_val(uint32_t) { return 1u; }
 MR_DEV uint32_t rs_val(uint2 e) { return e.y; }
 
-template <typename E, int OP>
+template <typename E, int OP, uint32_t PER>
 __global__ __launch_bounds__(kRunThreads) void k_runs_write(RsData<E> D, uint32_t bits, const uint32_t* __restrict__ heads,
                                                             uint32_t* __restrict__ out_keys, void* __restrict__ out_vals,
                                                             uint64_t cap, unsigned long long* __restrict__ lead) {
   const E* const s = rs_sorted(D, bits);
   const uint32_t lane = lane_id();
-  const uint64_t c = (uint64_t)blockIdx.x * (kRunThreads / kWave) + threadIdx.x / kWave, base = c * kRunChunk;
+  const uint64_t c = (uint64_t)blockIdx.x * (kRunThreads / kWave) + threadIdx.x / kWave, base = c * (kWave * PER);
   if (base >= D.n) return;
-  E e[kRunRows];
+  E e[PER];
 #pragma unroll
-  for (uint32_t u = 0; u < kRunRows; ++u) {
+  for (uint32_t u = 0; u < PER; ++u) {
     const uint64_t i = base + u * kWave + lane;
     e[u] = E{};
     if (i < D.n) e[u] = rs_load<E>(s, i);
@@ -405,7 +404,7 @@ __global__ __launch_bounds__(kRunThreads) void k_runs_write(RsData<E> D, uint32_
   bool has_open = false, inside = false, led = false;
   unsigned long long lead_v = 0;
 #pragma unroll
-  for (uint32_t u = 0; u < kRunRows; ++u) {
+  for (uint32_t u = 0; u < PER; ++u) {
     const uint64_t r0 = base + u * kWave;
     if (r0 >= D.n) break;
     const uint32_t m = D.n - r0 < kWave ? (uint32_t)(D.n - r0) : kWave;  // elements of the row
@@ -489,51 +488,73 @@ __global__ __launch_bounds__(256) void k_runs_lead(uint64_t n_chunks, const uint
 // host launchers
 // ----------------------------------------------------------------------------
 
+static uint32_t rs_per(uint64_t n) { return n <= kRsSmall ? kRsPerSmall : kRsPerLarge; }
+
 RadixPlan radix_plan(uint64_t n) {
   RadixPlan p{};
-  p.n_tiles = (uint32_t)((n + kRsTile - 1) / kRsTile);
-  p.hist_words = (uint64_t)kRsDigits * p.n_tiles;
-  p.n_chunks = (n + kRunChunk - 1) / kRunChunk;
+  const uint64_t tile = (uint64_t)kRsThreads * rs_per(n), chunk = (uint64_t)kWave * rs_per(n);
+  p.n_tiles = (uint32_t)((n + tile - 1) / tile);
+  p.n_chunks = (n + chunk - 1) / chunk;
+  // (scratch that covers every smaller input too)
+  const bool large = n > kRsSmall;
+  p.hist_words = (uint64_t)kRsDigits * std::max<uint64_t>(p.n_tiles, large ? kRsSmall / (kRsThreads * kRsPerSmall) : 0);
+  p.chunk_cap = std::max<uint64_t>(p.n_chunks, large ? kRsSmall / (kWave * kRsPerSmall) : 0);
   return p;
 }
 
-template <typename E>
-static hipError_t rs_sort(const RsData<E>& D, uint32_t bits, uint32_t* hist, uint32_t* tot, uint64_t R, uint32_t* flags,
-                          hipStream_t s) {
+template <typename E, uint32_t PER>
+static void rs_sort_per(const RsData<E>& D, uint32_t bits, uint32_t* hist, uint32_t* tot, uint64_t R, uint32_t* flags,
+                        hipStream_t s) {
   const uint32_t n_tiles = radix_plan(D.n).n_tiles;
   for (uint32_t sh = 0; sh < bits; sh += 8) {
     if (sh == 0) {
-      hipLaunchKernelGGL((k_rsort_hist<E, true>), dim3(n_tiles), dim3(kRsThreads), 0, s, D, sh, n_tiles, hist, R, flags);
+      hipLaunchKernelGGL((k_rsort_hist<E, true, PER>), dim3(n_tiles), dim3(kRsThreads), 0, s, D, sh, n_tiles, hist, R, flags);
     } else {
-      hipLaunchKernelGGL((k_rsort_hist<E, false>), dim3(n_tiles), dim3(kRsThreads), 0, s, D, sh, n_tiles, hist, R, flags);
+      hipLaunchKernelGGL((k_rsort_hist<E, false, PER>), dim3(n_tiles), dim3(kRsThreads), 0, s, D, sh, n_tiles, hist, R, flags);
     }
     hipLaunchKernelGGL(k_rsort_scan, dim3(kRsDigits), dim3(kRsScanThreads), 0, s, hist, n_tiles, sh, D.diff, tot);
     if (sh == 0) {
-      hipLaunchKernelGGL((k_rsort_scatter<E, true>), dim3(n_tiles), dim3(kRsThreads), 0, s, D, sh, n_tiles, hist, tot);
+      hipLaunchKernelGGL((k_rsort_scatter<E, true, PER>), dim3(n_tiles), dim3(kRsThreads), 0, s, D, sh, n_tiles, hist, tot);
     } else {
-      hipLaunchKernelGGL((k_rsort_scatter<E, false>), dim3(n_tiles), dim3(kRsThreads), 0, s, D, sh, n_tiles, hist, tot);
+      hipLaunchKernelGGL((k_rsort_scatter<E, false, PER>), dim3(n_tiles), dim3(kRsThreads), 0, s, D, sh, n_tiles, hist, tot);
     }
   }
+}
+
+// Sorts by the low `bits` key bits (rounded up to whole digits, at least one).
+template <typename E>
+static hipError_t rs_sort(const RsData<E>& D, uint32_t bits, uint32_t* hist, uint32_t* tot, uint64_t R, uint32_t* flags,
+                          hipStream_t s) {
+  if (rs_per(D.n) == kRsPerSmall) rs_sort_per<E, kRsPerSmall>(D, bits, hist, tot, R, flags, s);
+  else rs_sort_per<E, kRsPerLarge>(D, bits, hist, tot, R, flags, s);
   return hipGetLastError();
 }
 
-template <typename E, int OP>
-static hipError_t rs_reduce(const RsData<E>& D, uint32_t bits, const SortLaunch& L, hipStream_t s) {
+template <typename E, int OP, uint32_t PER>
+static hipError_t rs_reduce_per(const RsData<E>& D, uint32_t bits, const SortLaunch& L, hipStream_t s) {
   const uint64_t n_chunks = radix_plan(D.n).n_chunks;
   const uint32_t g = (uint32_t)((n_chunks + kRunThreads / kWave - 1) / (kRunThreads / kWave));
-  hipLaunchKernelGGL((k_runs_count<E>), dim3(g), dim3(kRunThreads), 0, s, D, bits, L.heads);
+  hipLaunchKernelGGL((k_runs_count<E, PER>), dim3(g), dim3(kRunThreads), 0, s, D, bits, L.heads);
   const hipError_t e = scan_exclusive_u32(L.heads, n_chunks, L.scan_sums, L.n_out, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_runs_write<E, OP>), dim3(g), dim3(kRunThreads), 0, s, D, bits, L.heads, L.out_keys, L.out_vals, L.cap,
-                     L.lead);
+  hipLaunchKernelGGL((k_runs_write<E, OP, PER>), dim3(g), dim3(kRunThreads), 0, s, D, bits, L.heads, L.out_keys, L.out_vals,
+                     L.cap, L.lead);
   hipLaunchKernelGGL(k_runs_lead<OP>, dim3((uint32_t)((n_chunks + 255) / 256)), dim3(256), 0, s, n_chunks, L.heads, L.lead,
                      L.out_vals, L.cap);
   return hipGetLastError();
 }
 
+template <typename E, int OP>
+static hipError_t rs_reduce(const RsData<E>& D, uint32_t bits, const SortLaunch& L, hipStream_t s) {
+  return rs_per(D.n) == kRsPerSmall ? rs_reduce_per<E, OP, kRsPerSmall>(D, bits, L, s)
+                                    : rs_reduce_per<E, OP, kRsPerLarge>(D, bits, L, s);
+}
+
+static uint32_t whole_digits(uint32_t bits) { return bits < 8 ? 8 : (bits + 7) / 8 * 8; }
+
 hipError_t int_enqueue_sort(const SortLaunch& L, hipStream_t s) {
   if (!L.n) return hipSuccess;
-  const uint32_t bits = L.bits < 8 ? 8 : (L.bits + 7) / 8 * 8;
+  const uint32_t bits = whole_digits(L.bits);
   if (L.op == 0) {  // the keys alone
     const RsData<uint32_t> D{L.in, L.kv ? 2u : 1u, L.n, static_cast<uint32_t*>(L.buf0), static_cast<uint32_t*>(L.buf1), L.diff};
     const hipError_t e = rs_sort(D, bits, L.hist, L.tot, L.R, L.flags, s);
@@ -548,5 +569,38 @@ hipError_t int_enqueue_sort(const SortLaunch& L, hipStream_t s) {
     default: return rs_reduce<uint2, 3>(D, bits, L, s);
   }
 }
+
+// Hash-table output: pairs (key, index of its value) sorted by key, then keys and values written in order.
+__global__ __launch_bounds__(256) void k_pairs_out(RsData<uint2> D, uint32_t bits, const unsigned long long* __restrict__ vals,
+                                                   int op, uint32_t* __restrict__ out_keys, void* __restrict__ out_vals,
+                                                   uint64_t cap) {
+  const uint2* const s = rs_sorted(D, bits);
+  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < D.n && i < cap; i += (uint64_t)gridDim.x * blockDim.x) {
+    const uint2 e = rs_load<uint2>(s, i);
+    out_keys[i] = e.x;
+    const unsigned long long v = vals[e.y];
+    if (op == 1) reinterpret_cast<unsigned long long*>(out_vals)[i] = v;
+    else reinterpret_cast<uint32_t*>(out_vals)[i] = (uint32_t)v;
+  }
+}
+
+hipError_t pairs_enqueue_out(const SortLaunch& L, const unsigned long long* vals, hipStream_t s) {
+  if (!L.n) return hipSuccess;
+  const RsData<uint2> D{L.in, 1u, L.n, static_cast<uint2*>(L.buf0), static_cast<uint2*>(L.buf1), L.diff};
+  const hipError_t e = rs_sort(D, 32, L.hist, L.tot, 0, L.flags, s);
+  if (e != hipSuccess) return e;
+  const uint64_t g = (L.n + 255) / 256;
+  hipLaunchKernelGGL(k_pairs_out, dim3((uint32_t)(g < 4096 ? g : 4096)), dim3(256), 0, s, D, 32u, vals, (int)L.op, L.out_keys,
+                     L.out_vals, L.cap);
+  return hipGetLastError();
+}
+
+hipError_t keys64_enqueue_sort(const Keys64Sort& L, hipStream_t s) {
+  if (!L.n) return hipSuccess;
+  const RsData<unsigned long long> D{L.in, 1u, L.n, L.buf0, L.buf1, L.diff};
+  return rs_sort(D, whole_digits(L.bits), L.hist, L.tot, 0, nullptr, s);
+}
+
+uint32_t keys64_sorted_bits(uint32_t bits) { return whole_digits(bits); }
 
 }  // namespace mr
