@@ -1113,6 +1113,14 @@ mr_status int_ensure(mr_job* job, int id, void** p, uint64_t* have, uint64_t byt
   return MR_OK;
 }
 
+// Whether a scratch region of `bytes` bytes fits the caller's workspace (library memory grows as needed).
+bool scratch_fits(const mr_job* job, uint64_t bytes) {
+  if (!job->cws) return true;
+  for (const mr_job::Region& r : job->cws_cur)
+    if (r.id == kRegScratch && r.bytes >= bytes) return true;
+  return align_up(job->cws_off, 256) + bytes <= job->cws_bytes;
+}
+
 // The LDS budget of the rule's per-workgroup arrays: the tuned one, at most the default.
 uint64_t eff_lds_array_bytes(const mr_job* job, mr_map_kind kind, uint64_t bytes) {
   const mr_tune_entry* t = tune_for(job, kind, bytes);
@@ -1153,11 +1161,13 @@ mr_status u32_finish(mr_job* job, mr_output* out, const IntSmall& hs) {
 
 // Scratch layouts of the integer-key containers (offsets in the scratch region).
 struct DenseCarve {  // LDS or global array over n elements and range R, G workgroups
-  uint64_t o_blk = 0, o_cp = 0, o_vp = 0, o_ph = 0, o_pk = 0, bytes = 0;
-  bool parts = false;  // a large COUNT array filled by key-range partitions
-  PartPlan pp;
+  uint64_t o_blk = 0, o_cp = 0, o_vp = 0, o_ph = 0, o_pk = 0, o_pv = 0, o_tot = 0, bytes = 0;
+  bool vparts = false;  // a global array filled by key-range partitions
+  VpPlan vp;
 };
-DenseCarve dense_carve(mr_strategy strat, uint64_t n, uint64_t R, uint32_t op, uint32_t G) {
+// with_vparts: whether the partitions may be used (without them a global
+// array is filled by atomics, which needs no scratch per element).
+DenseCarve dense_carve(mr_strategy strat, uint64_t n, uint64_t R, uint32_t op, uint32_t G, uint32_t n_cu, bool with_vparts) {
   DenseCarve d;
   Carve c;
   const uint64_t nb = (R + 2047) / 2048;
@@ -1166,12 +1176,15 @@ DenseCarve dense_carve(mr_strategy strat, uint64_t n, uint64_t R, uint32_t op, u
     d.o_cp = c.take(4ull * G * R);
     d.o_vp = c.take((op == MR_REDUCE_SUM ? 8ull : 4ull) * G * R);
   }
-  // a large array counted by key-range partitions instead of atomics
-  d.pp = part_plan(n, R);
-  d.parts = strat == MR_STRAT_GLOBAL_ARRAY && op == MR_REDUCE_COUNT && d.pp.usable;
-  if (d.parts) {
-    d.o_ph = c.take(4 * d.pp.runs);
-    d.o_pk = c.take(2 * d.pp.part_elems);
+  if (strat == MR_STRAT_GLOBAL_ARRAY && with_vparts) {
+    d.vp = vp_plan(n, R, op, n_cu);
+    d.vparts = d.vp.usable;
+    if (d.vparts) {
+      d.o_ph = c.take(4 * d.vp.runs);
+      d.o_pk = c.take(2 * d.vp.elems);
+      d.o_pv = c.take(op == MR_REDUCE_COUNT ? 0 : 4 * d.vp.elems);
+      d.o_tot = c.take(4ull * d.vp.slices * d.vp.P);
+    }
   }
   d.bytes = c.off;
   return d;
@@ -1327,9 +1340,8 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
     if (dense_fresh) job->int_dense_R = key_range;
     L.dcnt = static_cast<uint32_t*>(job->int_dense);
     L.dval = static_cast<uint8_t*>(job->int_dense) + ((4 * job->int_dense_R + 7) & ~7ull);
-    const DenseCarve dc = dense_carve(strat, n, key_range, o, L.G);
-    const PartPlan& pp = dc.pp;
-    const bool parts = dc.parts;
+    DenseCarve dc = dense_carve(strat, n, key_range, o, L.G, (uint32_t)job->n_cu, true);
+    if (dc.vparts && !scratch_fits(job, dc.bytes)) dc = dense_carve(strat, n, key_range, o, L.G, (uint32_t)job->n_cu, false);
     const uint64_t o_blk = dc.o_blk, o_cp = dc.o_cp, o_vp = dc.o_vp, o_ph = dc.o_ph, o_pk = dc.o_pk;
     st = scratch(dc.bytes);
     if (st != MR_OK) return st;
@@ -1340,14 +1352,15 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
       L.cnt_part = reinterpret_cast<uint32_t*>(sc + o_cp);
       L.val_part = sc + o_vp;
       MR_HIP(int_enqueue_lds_array(L, job->stream));
-    } else if (parts) {
-      MR_HIP(int_enqueue_global_array_tiles(L, pp, reinterpret_cast<uint32_t*>(sc + o_ph), reinterpret_cast<uint16_t*>(sc + o_pk),
-                                            job->stream));
+    } else if (dc.vparts) {
+      MR_HIP(int_enqueue_global_array_vp(L, dc.vp, reinterpret_cast<uint32_t*>(sc + o_ph), reinterpret_cast<uint16_t*>(sc + o_pk),
+                                         reinterpret_cast<uint32_t*>(sc + dc.o_pv), reinterpret_cast<uint32_t*>(sc + dc.o_tot),
+                                         job->stream));
     } else {
       MR_HIP(int_enqueue_global_array(L, job->stream));
     }
     if (job->cfg.timing) MR_HIP(hipEventRecord(job->ev3, job->stream));
-    MR_HIP(int_enqueue_dense_out(L, true, parts, job->stream));
+    MR_HIP(int_enqueue_dense_out(L, true, dc.vparts ? &dc.vp : nullptr, reinterpret_cast<uint32_t*>(sc + dc.o_tot), job->stream));
   }
   // The hash container without a table size of its own: inputs of few keys
   // stay in the LDS caches and a small table; the others are radix sorted.
@@ -1799,7 +1812,7 @@ extern "C" mr_status mr_workspace_bytes(const mr_job_config* cfg, mr_map_kind ki
         RegionSum t = r;
         if (c == MR_STRAT_LDS_ARRAY || c == MR_STRAT_GLOBAL_ARRAY) {
           t.add(key_range * 12 + 8);
-          t.add(dense_carve(c, ne, key_range, op, G).bytes);
+          t.add(dense_carve(c, ne, key_range, op, G, (uint32_t)n_cu, true).bytes);
         } else if (c == MR_STRAT_HASH) {
           const IntHashNeed h = int_hash_need(&tmp, kind, n, ne, key_range, op);
           if (h.slots) t.add(h.slots * kIntSlotBytes);
@@ -2263,7 +2276,8 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
     for (uint32_t q = 0; q < ni; ++q) strat[q] = job->cfg.strategy;
   }
   // the rule for the items the selector left to it; the regions for the largest item
-  uint64_t dense_b = 0, dense_r = 0, table_s = 0, scratch_b = 0;
+  // (scratch_full: with the partitions that a small caller workspace goes without)
+  uint64_t dense_b = 0, dense_r = 0, table_s = 0, scratch_b = 0, scratch_full = 0;
   for (uint32_t q = 0; q < ni; ++q) {
     const mr_batch_item& it = items[ii[q]];
     const uint32_t op = (uint32_t)it.op;
@@ -2278,7 +2292,8 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
     if (strat[q] == MR_STRAT_LDS_ARRAY || strat[q] == MR_STRAT_GLOBAL_ARRAY) {
       dense_r = std::max(dense_r, it.key_range);
       dense_b = std::max(dense_b, it.key_range * 12 + 8);
-      scratch_b = std::max(scratch_b, dense_carve(strat[q], n, it.key_range, op, G).bytes);
+      scratch_b = std::max(scratch_b, dense_carve(strat[q], n, it.key_range, op, G, (uint32_t)job->n_cu, false).bytes);
+      scratch_full = std::max(scratch_full, dense_carve(strat[q], n, it.key_range, op, G, (uint32_t)job->n_cu, true).bytes);
     } else if (strat[q] == MR_STRAT_HASH) {
       const IntHashNeed h = int_hash_need(job, it.kind, it.input_bytes, n, it.key_range, op);
       table_s = std::max(table_s, h.slots);
@@ -2304,6 +2319,7 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
       MR_HIP(hipMemsetAsync(static_cast<uint8_t*>(job->int_table) + table_s * 4, 0, table_s * 16, s));
     }
   }
+  if (scratch_full > scratch_b && scratch_fits(job, scratch_full)) scratch_b = scratch_full;
   if (scratch_b) {
     st = int_ensure(job, kRegScratch, &job->int_scratch, &job->int_scratch_bytes, scratch_b, -1);
     if (st != MR_OK) return st;

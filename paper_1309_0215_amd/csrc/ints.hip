@@ -16,6 +16,8 @@
 //                keys fit the CAS word, so claim and compare are one step.
 //   SORT         LSD radix sort of the pairs, then a segmented reduce (sort.hip).
 // Every container ends in a compaction to distinct keys in ascending order.
+#include <algorithm>
+
 #include "common.h"
 #include "launch.h"
 
@@ -190,255 +192,423 @@ __global__ __launch_bounds__(256) void k_global_array(IntIn in, uint32_t R, uint
 }
 
 // ----------------------------------------------------------------------------
-// global array over a large range, filled by key-range partitions (COUNT)
+// global array filled by key-range partitions
 //
-// Device-scope atomics run far below the load rate, so a large array is not
-// updated element by element. Instead each tile of elements is ordered by
-// 2^15-key range in LDS and written where it stands, as the elements' low 15
-// bits, with the start of each range's run in the tile; then one workgroup
-// per range counts that range's runs of every tile in an LDS array and
-// writes the range's counts once. Every array entry is written exactly once;
-// no global atomics on the array.
+// Device-scope atomics run far below the load rate (and serialise on a
+// frequent key), so the array is not updated element by element. Each tile of
+// elements is ordered by 2^kb-key range in LDS and written where it stands
+// (16-bit offsets, and 32-bit values unless the op counts) with the start of
+// each range's run; then workgroups reduce the ranges' runs of every tile in
+// LDS arrays. A range is split over as many workgroups as its share of the
+// elements asks for, so that neither few ranges nor a frequent key leaves the
+// work to a few CUs: a range of one workgroup is stored once, a split range is
+// merged into the dense arrays with atomics on neighbouring words.
 // ----------------------------------------------------------------------------
-constexpr uint32_t kPartBits = 15;
-constexpr uint32_t kPartKeys = 1u << kPartBits;  // keys per range: LDS counters of one workgroup (128 KB)
-constexpr uint32_t kMaxParts = 2048;             // ranges (key range up to 2^26)
-constexpr uint32_t kPartTile = 16384;            // elements per tile (a multiple of 8)
-constexpr uint32_t kPartThreads = 1024;
-static_assert(kPartTile % (4 * kPartThreads) == 0, "a held tile is whole 16-byte vectors, the same number per thread");
+constexpr uint32_t kVpPer = 16;                // elements per thread of the tile kernel
+constexpr uint32_t kVpMaxParts = 2048;         // ranges
 constexpr uint32_t kCompTile = 2048;  // keys per block of the ordered compaction of dense arrays (256 threads x 8)
-static_assert(kPartKeys % kCompTile == 0, "a key range holds whole compaction blocks");
 
-// Element i of a tile: keys are read 4 at a time (one 16-byte load) when the
-// input is plain keys; pairs are read one by one.
-template <typename F>
-MR_DEV void for_tile_keys(const IntIn& in, uint64_t base, F&& f) {
-  if (!in.kv && ((uintptr_t)in.p & 15u) == 0) {
-    const uint64_t end = base + kPartTile < in.n ? base + kPartTile : in.n;
-    const uint64_t nv = end > base ? (end - base) / 4 : 0;  // whole vectors
-    const uint4* v = reinterpret_cast<const uint4*>(in.p + base);
-    // loads in batches of kTileBatch per lane, issued before any of them is used
-    constexpr uint32_t kTileBatch = 4;
-    uint64_t q = threadIdx.x;
-    for (; q + (kTileBatch - 1) * blockDim.x < nv; q += kTileBatch * blockDim.x) {
-      uint4 x[kTileBatch];
+// Threads of the tile kernel: 16,384-element tiles for counting, 8,192 where
+// the staged values take twice the keys' LDS.
+constexpr uint32_t vp_threads(uint32_t op) { return op == 0 ? 1024 : 512; }
+constexpr uint32_t vp_tile(uint32_t op) { return vp_threads(op) * kVpPer; }
+// Threads of the fill: counting takes up to 128 KB of LDS, one workgroup per CU.
+constexpr uint32_t vp_fill_threads(uint32_t op) { return op == 0 ? 1024 : 512; }
+
+template <int OP>
+__global__ __launch_bounds__(vp_threads(OP), OP == 0 ? 8 : 6) void k_vp_tile(IntIn in, uint64_t R, uint32_t kb, uint32_t P,
+                                                            uint32_t* __restrict__ runs, uint16_t* __restrict__ pk,
+                                                            uint32_t* __restrict__ pv, uint32_t* __restrict__ flags) {
+  constexpr uint32_t kThreads = vp_threads(OP), kTile = vp_tile(OP);
+  extern __shared__ uint32_t base[];  // [P + 1] counts, then the start of each range's run in the tile
+  __shared__ __attribute__((aligned(16))) uint16_t sk[kTile];
+  __shared__ __attribute__((aligned(16))) uint32_t sv[OP == 0 ? 4 : kTile];
+  __shared__ uint32_t ws[kThreads / kWave];
+  const uint32_t t = blockIdx.x, lane = lane_id(), wv = threadIdx.x / kWave;
+  for (uint32_t q = threadIdx.x; q <= P; q += kThreads) base[q] = 0;
+  const uint64_t e0 = (uint64_t)t * kTile;
+  uint32_t k[kVpPer], v[kVpPer];
+  const uint32_t stride = in.kv ? 2u : 1u;
+  const MR_GLOBAL uint32_t* src = gp(in.p) + e0 * stride;
+  const uint32_t left = in.n - e0 < kTile ? (uint32_t)(in.n - e0) : kTile;
+  uint32_t n_mine = 0;  // this thread's elements: k[0, n_mine)
+  if (OP == 0 && !in.kv && left == kTile && ((uintptr_t)in.p & 15u) == 0) {  // whole 16-byte vectors
+    n_mine = kVpPer;
 #pragma unroll
-      for (uint32_t u = 0; u < kTileBatch; ++u) x[u] = gload16(v + q + u * blockDim.x);
+    for (uint32_t u = 0; u < kVpPer / 4; ++u) {
+      const uint4 x = gload16(in.p + e0 + (u * kThreads + threadIdx.x) * 4);
+      k[4 * u] = x.x;
+      k[4 * u + 1] = x.y;
+      k[4 * u + 2] = x.z;
+      k[4 * u + 3] = x.w;
+    }
+  } else {
 #pragma unroll
-      for (uint32_t u = 0; u < kTileBatch; ++u) {
-        f(x[u].x);
-        f(x[u].y);
-        f(x[u].z);
-        f(x[u].w);
+    for (uint32_t u = 0; u < kVpPer; ++u) {
+      const uint32_t i = u * kThreads + threadIdx.x;
+      k[u] = ~0u;
+      v[u] = 0u;
+      if (i < left) {
+        ++n_mine;
+        k[u] = src[i * stride];
+        if (OP != 0) v[u] = src[i * stride + 1];
       }
     }
-    for (; q < nv; q += blockDim.x) {
-      const uint4 x = gload16(v + q);
-      f(x.x);
-      f(x.y);
-      f(x.z);
-      f(x.w);
-    }
-    for (uint64_t i = base + nv * 4 + threadIdx.x; i < end; i += blockDim.x) f(in.p[i]);
-  } else {
-    for (uint32_t q = threadIdx.x; q < kPartTile; q += blockDim.x) {
-      const uint64_t i = base + q;
-      if (i >= in.n) break;
-      uint32_t k, v;
-      load_elem(in, i, k, v);
-      f(k);
-    }
   }
-}
-
-// Dynamic LDS of k_part_tile: the range arrays, sized by P, so that for
-// P <= 1024 two workgroups fit a CU (one streams its tile while the other
-// scans its counts or writes its row).
-constexpr uint32_t part_tile_lds(uint32_t P) { return (2 * P + 1) * 4; }
-
-// Tile t writes its elements' in-range offsets ordered by range to
-// part[t * kPartTile, ...) and the start of each range's run in the tile to
-// runs[t * (P + 1) + p] (entry P: the tile's element count), both as whole
-// contiguous rows.
-__global__ __launch_bounds__(kPartThreads) void k_part_tile(IntIn in, uint64_t R, uint32_t P, uint32_t* __restrict__ runs,
-                                                            uint16_t* __restrict__ part, uint32_t* __restrict__ flags) {
-  extern __shared__ uint32_t ranges[];
-  uint32_t* const lbase = ranges;         // [P + 1] start of each range's run in the tile (and the end)
-  uint32_t* const lpos = ranges + P + 1;  // [P] counts, then the next free place of each range's run
-  __shared__ __attribute__((aligned(16))) uint16_t sk[kPartTile];  // staged offsets, ordered by range
-  __shared__ uint32_t wsum[kPartThreads / kWave];
-  const uint32_t t = blockIdx.x;
-  for (uint32_t q = threadIdx.x; q < P; q += blockDim.x) lpos[q] = 0u;
   __syncthreads();
-  // A whole tile of aligned plain keys is held in registers between the count
-  // and the placing (four 16-byte vectors per thread); other tiles are read
-  // twice.
-  constexpr uint32_t kHeld = kPartTile / 4 / kPartThreads;
-  const bool held = !in.kv && ((uintptr_t)in.p & 15u) == 0 && (uint64_t)(t + 1) * kPartTile <= in.n &&
-                    blockDim.x == kPartThreads;
-  uint4 x[kHeld];
-  // 1. the tile's count of each range
+  // Counts of the ranges. With values each element keeps its rank within its
+  // range's run; counting takes its place with a second atomic instead, since
+  // the ranks would cost the registers of the second workgroup per CU.
   bool bad = false;
-  auto count = [&](uint32_t k) {
-    if (k < R) atomicAdd(&lpos[k >> kPartBits], 1u);
-    else bad = true;
-  };
-  if (held) {
-    const uint4* v = reinterpret_cast<const uint4*>(in.p + (uint64_t)t * kPartTile);
+  uint32_t rank[OP == 0 ? 1 : kVpPer];
 #pragma unroll
-    for (uint32_t u = 0; u < kHeld; ++u) x[u] = gload16(v + threadIdx.x + u * kPartThreads);
-#pragma unroll
-    for (uint32_t u = 0; u < kHeld; ++u) {
-      count(x[u].x);
-      count(x[u].y);
-      count(x[u].z);
-      count(x[u].w);
+  for (uint32_t u = 0; u < kVpPer; ++u) {
+    if (k[u] < R) {
+      const uint32_t r = atomicAdd(&base[k[u] >> kb], 1u);
+      if (OP != 0) rank[u] = r;
+    } else {
+      bad |= u < n_mine;
     }
-  } else {
-    for_tile_keys(in, (uint64_t)t * kPartTile, count);
   }
   if (bad) atomicOr(flags, kFlagBadInput);
   __syncthreads();
-  // 2. run starts: exclusive scan of the counts (P <= kMaxParts: kPer per thread)
-  constexpr uint32_t kPer = kMaxParts / kPartThreads;
+  constexpr uint32_t kPer = kVpMaxParts / kThreads;  // ranges per thread
   uint32_t c[kPer], sum = 0;
 #pragma unroll
   for (uint32_t q = 0; q < kPer; ++q) {
     const uint32_t r = threadIdx.x * kPer + q;
-    c[q] = r < P ? lpos[r] : 0u;
+    c[q] = r < P ? base[r] : 0u;
     sum += c[q];
   }
-  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
   const uint32_t incl = wave_incl_scan(sum);
-  if (lane == kWave - 1) wsum[wv] = incl;
+  if (lane == kWave - 1) ws[wv] = incl;
   __syncthreads();
-  uint32_t pre = 0, m = 0;
-  for (uint32_t w = 0; w < kPartThreads / kWave; ++w) {
-    if (w < wv) pre += wsum[w];
-    m += wsum[w];
+  uint32_t run = incl - sum, m = 0;
+  for (uint32_t w = 0; w < kThreads / kWave; ++w) {
+    if (w < wv) run += ws[w];
+    m += ws[w];
   }
-  uint32_t run = pre + incl - sum;
 #pragma unroll
   for (uint32_t q = 0; q < kPer; ++q) {
     const uint32_t r = threadIdx.x * kPer + q;
-    if (r < P) {
-      lbase[r] = run;
-      lpos[r] = run;
-    }
+    if (r < P) base[r] = run;
     run += c[q];
   }
-  if (threadIdx.x == 0) lbase[P] = m;
+  if (threadIdx.x == 0) base[P] = m;
   __syncthreads();
   uint32_t* const row = runs + (uint64_t)t * (P + 1);
-  for (uint32_t q = threadIdx.x; q <= P; q += blockDim.x) row[q] = lbase[q];
-  // 3. each element to its place
-  auto place = [&](uint32_t k) {
-    if (k < R) sk[atomicAdd(&lpos[k >> kPartBits], 1u)] = (uint16_t)(k & (kPartKeys - 1));
-  };
-  if (held) {
+  for (uint32_t q = threadIdx.x; q <= P; q += kThreads) row[q] = base[q];
+  if (OP == 0) __syncthreads();
 #pragma unroll
-    for (uint32_t u = 0; u < kHeld; ++u) {
-      place(x[u].x);
-      place(x[u].y);
-      place(x[u].z);
-      place(x[u].w);
-    }
-  } else {
-    for_tile_keys(in, (uint64_t)t * kPartTile, place);
+  for (uint32_t u = 0; u < kVpPer; ++u) {
+    if (k[u] >= R) continue;
+    const uint32_t at = OP == 0 ? atomicAdd(&base[k[u] >> kb], 1u) : base[k[u] >> kb] + rank[u];
+    sk[at] = (uint16_t)(k[u] & ((1u << kb) - 1));
+    if (OP != 0) sv[at] = OP == 1 ? v[u] : enc_minmax(OP, v[u]);
   }
   __syncthreads();
-  // 4. the staged offsets as one row, eight per 16-byte store
-  uint16_t* const dst = part + (uint64_t)t * kPartTile;
-  for (uint32_t i = threadIdx.x; i * 8u < m; i += blockDim.x) {
-    if (i * 8u + 8u <= m) {
-      gstore16(dst + i * 8u, *reinterpret_cast<const uint4*>(&sk[i * 8u]));
-    } else {
-      for (uint32_t e = i * 8u; e < m; ++e) dst[e] = sk[e];
+  // (rows are whole tiles: the words past the tile's elements are written too and never used)
+  for (uint32_t i = threadIdx.x; i * 8 < m; i += kThreads)
+    gstore16(pk + e0 + i * 8, *reinterpret_cast<const uint4*>(&sk[i * 8]));
+  if (OP != 0)
+    for (uint32_t i = threadIdx.x; i * 4 < m; i += kThreads)
+      gstore16(pv + e0 + i * 4, *reinterpret_cast<const uint4*>(&sv[i * 4]));
+}
+
+// Elements of each range in each of gridDim.y slices of the tiles:
+// tot[slice * P + p]. (Adding them up with atomics in k_vp_tile, on the few
+// words of 128 ranges, took 60 us of its 85 on 8 M pairs.)
+constexpr uint32_t kVpTotThreads = 1024;
+constexpr uint32_t kVpMaxSlices = 16;
+
+__global__ __launch_bounds__(kVpTotThreads) void k_vp_totals(const uint32_t* __restrict__ runs, uint32_t P, uint32_t n_tiles,
+                                                             uint32_t* __restrict__ tot) {
+  __shared__ uint32_t s[kVpTotThreads];
+  const uint32_t p = blockIdx.x * kWave + threadIdx.x % kWave;
+  const uint32_t t0 = (uint32_t)((uint64_t)n_tiles * blockIdx.y / gridDim.y);
+  const uint32_t t1 = (uint32_t)((uint64_t)n_tiles * (blockIdx.y + 1) / gridDim.y);
+  uint32_t sum = 0;
+  if (p < P) {
+#pragma unroll 8
+    for (uint32_t t = t0 + threadIdx.x / kWave; t < t1; t += kVpTotThreads / kWave) {
+      const uint32_t* row = runs + (uint64_t)t * (P + 1) + p;
+      sum += row[1] - row[0];
     }
+  }
+  s[threadIdx.x] = sum;
+  __syncthreads();
+  if (threadIdx.x < kWave && p < P) {
+    for (uint32_t q = threadIdx.x + kWave; q < kVpTotThreads; q += kWave) sum += s[q];
+    tot[blockIdx.y * P + p] = sum;
   }
 }
 
-// One workgroup per key range counts the range's runs of every tile in LDS
-// (a thread takes whole tiles: it loads its tiles' run bounds together, then
-// a run's covering 16-byte pieces, up to kFillVecs at once, before it counts
-// them) and writes the range's counts once, with the present keys per
-// compaction block (the ordered compaction's first pass, done here).
-constexpr uint32_t kFillTilesPer = 8;  // tiles a thread takes at a time
-constexpr uint32_t kFillVecs = 12;     // 16-byte pieces of a run loaded before counting
+// Workgroups of range p: one per `split` elements.
+MR_DEV uint32_t vp_parts(const uint32_t* __restrict__ tot, uint32_t slices, uint32_t P, uint32_t p, uint32_t split) {
+  uint32_t c = 0;
+  for (uint32_t y = 0; y < slices; ++y) c += tot[y * P + p];
+  return c <= split ? 1u : (c + split - 1) / split;
+}
 
-__global__ __launch_bounds__(1024) void k_part_fill_tiles(const uint16_t* __restrict__ part, const uint32_t* __restrict__ runs,
-                                                          uint32_t P, uint32_t n_tiles, uint64_t R,
-                                                          uint32_t* __restrict__ dcnt, uint32_t* __restrict__ blk) {
-  __shared__ uint32_t c[kPartKeys + kWave / 2];  // the range's counters, then 32 sinks for entries outside a run
-  // Workgroups are handed to the eight XCDs in turn; neighbouring ranges read
-  // neighbouring words of every tile's run-start row and share the 128-byte
-  // lines where their runs meet, so each XCD takes a contiguous block of
-  // ranges and its L2 serves those lines once. The map is a permutation of
-  // the ranges: another dispatch order costs cache hits, not correctness.
-  const uint32_t p = (P % kXcds == 0u) ? (blockIdx.x % kXcds) * (P / kXcds) + blockIdx.x / kXcds : blockIdx.x;
-  for (uint32_t i = threadIdx.x; i < kPartKeys; i += blockDim.x) c[i] = 0;
+// One workgroup per part of a range (found from the parts' scan). LDS: values
+// [2^kb] (64-bit for SUM), then one presence byte per key; COUNT: the counts;
+// each followed by kVpSinks entries that take the elements of a piece outside
+// the run, so that every piece runs the same branch-free code.
+// kList = false: lpg neighbouring lanes take a tile's run together, one
+// eight-element piece (a 16-byte load of offsets) each, pipelined over steps
+// of kBatch tiles per group.
+// kList = true, for counting over many tiles of short runs: a wave takes 64
+// tiles at a time, lane l loads tile l's run bounds and lists its run's pieces
+// in LDS, and the listed pieces go to the lanes in order, so that every lane
+// has a piece whatever the runs' lengths (2^28 elements over 2^24 keys: 237 us;
+// groups of eight lanes, of which a run of 32 fills five, 277 us of vector and
+// LDS issue). With few tiles per wave the list's chain of loads is not hidden
+// (8 M pairs: 78 us against 35).
+// A range of one workgroup also counts the present keys of its compaction
+// blocks.
+constexpr uint32_t kVpSinks = 32;
+constexpr uint32_t kVpList = 384;  // pieces listed per wave
+constexpr uint32_t vp_fill_lds(uint32_t op, uint32_t kb) { return (op == 0 ? 4 : op == 1 ? 9 : 5) * ((1u << kb) + kVpSinks); }
+
+template <int OP, bool kList>
+__global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uint32_t kb, uint32_t P, uint32_t n_tiles,
+                                                            uint32_t split, uint32_t lpg, const uint32_t* __restrict__ runs,
+                                                            const uint16_t* __restrict__ pk, const uint32_t* __restrict__ pv,
+                                                            const uint32_t* __restrict__ tot, uint32_t slices,
+                                                            uint32_t* __restrict__ dcnt, void* __restrict__ dval,
+                                                            uint32_t* __restrict__ blk) {
+  constexpr uint32_t kThreads = vp_fill_threads(OP);
+  extern __shared__ unsigned long long vp_lds[];
+  constexpr uint32_t kWaves = kThreads / kWave;
+  __shared__ uint32_t ws[kWaves], found[3];
+  __shared__ uint32_t lists[kList ? kWaves : 1][kList ? kVpList : 1];
+  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave, K = 1u << kb;
+  constexpr uint32_t kPer = kVpMaxParts / kThreads;
+  uint32_t parts[kPer], sum = 0;
+#pragma unroll
+  for (uint32_t q = 0; q < kPer; ++q) {
+    const uint32_t r = threadIdx.x * kPer + q;
+    parts[q] = r < P ? vp_parts(tot, slices, P, r, split) : 0u;
+    sum += parts[q];
+  }
+  const uint32_t incl = wave_incl_scan(sum);
+  if (lane == kWave - 1) ws[wv] = incl;
+  if (threadIdx.x == 0) found[2] = 0;
   __syncthreads();
-  const uint32_t sink = kPartKeys + (threadIdx.x & (kWave / 2 - 1));
-  for (uint32_t t0 = 0; t0 < n_tiles; t0 += kFillTilesPer * blockDim.x) {
-    uint32_t b0[kFillTilesPer], b1[kFillTilesPer];
+  uint32_t first = incl - sum, all = 0;
+  for (uint32_t w = 0; w < kThreads / kWave; ++w) {
+    if (w < wv) first += ws[w];
+    all += ws[w];
+  }
+  // Workgroups are handed to the eight XCDs in turn; neighbouring ranges share
+  // the lines where their runs meet and their run starts, so each XCD takes a
+  // contiguous block of parts and its L2 serves those once.
+  const uint32_t each = all / kXcds, whole = each * kXcds;
+  const uint32_t b = blockIdx.x < whole ? blockIdx.x % kXcds * each + blockIdx.x / kXcds : blockIdx.x;
 #pragma unroll
-    for (uint32_t u = 0; u < kFillTilesPer; ++u) {
-      const uint32_t t = t0 + u * blockDim.x + threadIdx.x;
-      b0[u] = b1[u] = 0u;
-      if (t < n_tiles) {
-        const uint32_t* row = runs + (uint64_t)t * (P + 1) + p;
-        b0[u] = *gp(row);
-        b1[u] = *gp(row + 1);
-      }
+  for (uint32_t q = 0; q < kPer; ++q) {
+    if (b >= first && b < first + parts[q]) {
+      found[0] = threadIdx.x * kPer + q;
+      found[1] = b - first;
+      found[2] = parts[q];
     }
-#pragma unroll 1
-    for (uint32_t u = 0; u < kFillTilesPer; ++u) {
-      const uint16_t* src = part + (uint64_t)(t0 + u * blockDim.x + threadIdx.x) * kPartTile;
-      // the run [b0, b1) read as the aligned 16-byte pieces that cover it
-      // (inside the tile's row, whose length is a multiple of 8 entries),
-      // the entries outside it counted in a sink
-      const uint32_t lo = b0[u], hi = b1[u];
-      for (uint32_t v = lo & ~7u; v < hi; v += 8u * kFillVecs) {
-        uint4 x[kFillVecs];
+    first += parts[q];
+  }
+  unsigned long long* const sum64 = vp_lds;
+  uint32_t* const val32 = reinterpret_cast<uint32_t*>(vp_lds);
+  uint8_t* const here = reinterpret_cast<uint8_t*>(vp_lds) + (OP == 1 ? 8u : 4u) * (K + kVpSinks);
+  const uint32_t words = vp_fill_lds(OP, kb) / 4;
+  const uint32_t sink = K + lane % kVpSinks;
+  __syncthreads();
+  const uint32_t p = found[0], part = found[1], np = found[2];
+  if (np == 0) return;  // more workgroups than parts
+  for (uint32_t i = threadIdx.x; i < words; i += kThreads) val32[i] = 0;
+  __syncthreads();
+  const uint32_t t0 = (uint32_t)((uint64_t)n_tiles * part / np), t1 = (uint32_t)((uint64_t)n_tiles * (part + 1) / np);
+  constexpr uint32_t kTile = vp_tile(OP);
+  struct Piece {
+    uint4 k, v0, v1;
+  };
+  auto load = [&](uint64_t at, Piece& x) {  // eight elements from a multiple of 8
+    x.k = gload16(pk + at);
+    if (OP != 0) {
+      x.v0 = gload16(pv + at);
+      x.v1 = gload16(pv + at + 4);
+    }
+  };
+  auto put = [&](uint32_t from, uint32_t upto, const Piece& x) {  // elements [from, upto) of the piece are in the run
+    const uint32_t w[4] = {x.k.x, x.k.y, x.k.z, x.k.w};
+    const uint32_t v[8] = {x.v0.x, x.v0.y, x.v0.z, x.v0.w, x.v1.x, x.v1.y, x.v1.z, x.v1.w};
+    const int32_t in_run = (int32_t)(((1u << upto) - 1u) & ~((1u << from) - 1u));
 #pragma unroll
-        for (uint32_t q = 0; q < kFillVecs; ++q)
-          if (v + 8u * q < hi) x[q] = gload16(src + v + 8u * q);
+    for (uint32_t i = 0; i < 8; ++i) {
+      const uint32_t in = (uint32_t)(in_run << (31 - i) >> 31);  // all ones or zero
+      const uint32_t at = (w[i >> 1] >> (16u * (i & 1u))) & 0xFFFFu;
+      const uint32_t key = (at & in) | (sink & ~in);
+      if (OP == 0) atomicAdd(&val32[key], 1u);
+      if (OP == 1) atomicAdd(&sum64[key], (unsigned long long)v[i]);
+      if (OP >= 2) atomicMax(&val32[key], v[i]);
+      if (OP != 0) here[key] = 1;  // (every writer stores the same byte)
+    }
+  };
+  if constexpr (kList) {
+    uint32_t* const list = lists[wv];
+    auto load_runs = [&](uint32_t tb, uint32_t& lo, uint32_t& hi) {
+      lo = hi = 0;
+      if (lane < kWave && tb + lane < t1) {
+        const uint32_t* row = runs + (uint64_t)(tb + lane) * (P + 1) + p;
+        lo = *gp(row);
+        hi = *gp(row + 1);
+      }
+    };
+    constexpr uint32_t kBatch = OP == 0 ? 6 : 3;  // pieces in flight per lane
+    uint32_t lo, hi, lo1, hi1;
+    load_runs(t0 + wv * kWave, lo, hi);
+    for (uint32_t tb = t0 + wv * kWave; tb < t1; tb += kWaves * kWave, lo = lo1, hi = hi1) {
+      load_runs(tb + kWaves * kWave, lo1, hi1);
+      const uint32_t c = hi > lo ? (hi + 7) / 8 - lo / 8 : 0u;
+      const uint32_t incl = wave_incl_scan(c);
+      const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+      if (total <= kVpList) {
+        // entry: piece (11 bits), from (3), upto (4), tile (6)
+        uint32_t at = incl - c;
+        for (uint32_t q = lo / 8; 8 * q < hi && c; ++q, ++at) {
+          const uint32_t from = lo > 8 * q ? lo - 8 * q : 0u, upto = hi - 8 * q < 8u ? hi - 8 * q : 8u;
+          list[at] = q | from << 11 | upto << 14 | lane << 18;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (uint32_t i0 = 0; i0 < total; i0 += kBatch * kWave) {
+          uint32_t ent[kBatch];
+          Piece x[kBatch];
 #pragma unroll
-        for (uint32_t q = 0; q < kFillVecs; ++q) {
-          const uint32_t e0 = v + 8u * q;
-          if (e0 >= hi) continue;
-          // eight atomics whatever the piece's overlap with the run: an entry
-          // outside it goes to one of the sinks, spread over the banks
-          const uint32_t w[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+          for (uint32_t u = 0; u < kBatch; ++u) {
+            const uint32_t i = i0 + u * kWave + lane;
+            ent[u] = i < total ? list[i] : 0u;  // (a listed piece has upto > 0)
+          }
 #pragma unroll
-          for (uint32_t i = 0; i < 8u; ++i) {
-            const uint32_t key = (w[i >> 1] >> (16u * (i & 1u))) & 0xFFFFu;
-            atomicAdd(&c[e0 + i - lo < hi - lo ? key : sink], 1u);
+          for (uint32_t u = 0; u < kBatch; ++u)
+            if (ent[u]) load((uint64_t)(tb + (ent[u] >> 18)) * kTile + 8 * (ent[u] & 0x7FFu), x[u]);
+#pragma unroll
+          for (uint32_t u = 0; u < kBatch; ++u)
+            if (ent[u]) put(ent[u] >> 11 & 7u, ent[u] >> 14 & 15u, x[u]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      } else {
+        for (uint32_t u = 0; u < kWave && tb + u < t1; ++u) {
+          const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)u);
+          const uint32_t h = (uint32_t)__builtin_amdgcn_readlane((int)hi, (int)u);
+          for (uint32_t q0 = l / 8 + lane; 8 * (q0 - lane) < h; q0 += kBatch * kWave) {
+            Piece x[kBatch];
+#pragma unroll
+            for (uint32_t g = 0; g < kBatch; ++g)
+              if (8 * (q0 + g * kWave) < h) load((uint64_t)(tb + u) * kTile + 8 * (q0 + g * kWave), x[g]);
+#pragma unroll
+            for (uint32_t g = 0; g < kBatch; ++g) {
+              const uint32_t e = 8 * (q0 + g * kWave);
+              if (e < h) put(l > e ? l - e : 0u, h - e < 8u ? h - e : 8u, x[g]);
+            }
           }
         }
       }
     }
+  } else {
+    constexpr uint32_t kBatch = OP == 0 ? 4 : 2;
+    const uint32_t groups = kThreads / lpg, grp = threadIdx.x / lpg, sub = threadIdx.x % lpg;
+    struct Runs {
+      uint32_t lo[kBatch], hi[kBatch];
+    };
+    auto load_runs = [&](uint32_t tb, Runs& r) {
+#pragma unroll
+      for (uint32_t u = 0; u < kBatch; ++u) {
+        const uint32_t t = tb + u * groups + grp;
+        r.lo[u] = r.hi[u] = 0;
+        if (t < t1) {
+          const uint32_t* row = runs + (uint64_t)t * (P + 1) + p;
+          r.lo[u] = *gp(row);
+          r.hi[u] = *gp(row + 1);
+        }
+      }
+    };
+    auto load_pieces = [&](uint32_t tb, const Runs& r, Piece (&x)[kBatch]) {
+#pragma unroll
+      for (uint32_t u = 0; u < kBatch; ++u) {
+        const uint32_t e = (r.lo[u] & ~7u) + 8 * sub;
+        if (e < r.hi[u]) load((uint64_t)(tb + u * groups + grp) * kTile + e, x[u]);
+      }
+    };
+    auto put_in = [&](uint32_t e, uint32_t lo, uint32_t hi, const Piece& x) {
+      put(lo > e ? lo - e : 0u, hi - e < 8u ? hi - e : 8u, x);
+    };
+    const uint32_t step = kBatch * groups;
+    Runs cur, next;
+    Piece x[kBatch], y[kBatch];
+    load_runs(t0, cur);
+    load_runs(t0 + step, next);
+    load_pieces(t0, cur, x);
+    for (uint32_t tb = t0; tb < t1; tb += step) {
+      Runs after;
+      load_pieces(tb + step, next, y);
+      load_runs(tb + 2 * step, after);
+#pragma unroll
+      for (uint32_t u = 0; u < kBatch; ++u) {
+        const uint32_t e = (cur.lo[u] & ~7u) + 8 * sub;
+        if (e < cur.hi[u]) put_in(e, cur.lo[u], cur.hi[u], x[u]);
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < kBatch; ++u) {  // runs longer than the group's pieces
+        const uint64_t e0 = (uint64_t)(tb + u * groups + grp) * kTile;
+        for (uint32_t e = (cur.lo[u] & ~7u) + 8 * (sub + lpg); e < cur.hi[u]; e += 8 * lpg) {
+          Piece z;
+          load(e0 + e, z);
+          put_in(e, cur.lo[u], cur.hi[u], z);
+        }
+      }
+      cur = next;
+      next = after;
+#pragma unroll
+      for (uint32_t u = 0; u < kBatch; ++u) x[u] = y[u];
+    }
   }
   __syncthreads();
-  const uint64_t key0 = (uint64_t)p * kPartKeys;
-  const uint32_t nk = (uint32_t)(R - key0 < kPartKeys ? R - key0 : kPartKeys);
-  for (uint32_t i = threadIdx.x; i < nk; i += blockDim.x) dcnt[key0 + i] = c[i];
-  const uint32_t lane = lane_id();
-  for (uint32_t b = threadIdx.x / kWave; b * kCompTile < nk; b += blockDim.x / kWave) {
-    const uint32_t q1 = (b + 1) * kCompTile < nk ? (b + 1) * kCompTile : nk;
-    uint32_t present = 0;
-    for (uint32_t q = b * kCompTile; q < q1; q += kWave) {
-      const uint32_t i = q + lane;
-      present += (uint32_t)__popcll(__ballot(i < q1 && c[i] != 0));
+  const uint64_t key0 = (uint64_t)p << kb;
+  const uint32_t nk = R - key0 < K ? (uint32_t)(R - key0) : K;
+  if (np == 1) {
+    for (uint32_t i = threadIdx.x; i < nk; i += kThreads) {
+      dcnt[key0 + i] = OP == 0 ? val32[i] : here[i];
+      if (OP == 1) reinterpret_cast<unsigned long long*>(dval)[key0 + i] = sum64[i];
+      if (OP >= 2) reinterpret_cast<uint32_t*>(dval)[key0 + i] = val32[i];
     }
-    if (lane == 0) blk[key0 / kCompTile + b] = present;
+    for (uint32_t q = wv; q * kCompTile < nk; q += kThreads / kWave) {
+      const uint32_t i1 = (q + 1) * kCompTile < nk ? (q + 1) * kCompTile : nk;
+      uint32_t present = 0;
+      for (uint32_t i = q * kCompTile + lane; i - lane < i1; i += kWave)
+        present += popc64(__ballot(i < i1 && (OP == 0 ? val32[i] : here[i]) != 0));
+      if (lane == 0) blk[key0 / kCompTile + q] = present;
+    }
+    return;
+  }
+  for (uint32_t i = threadIdx.x; i < nk; i += kThreads) {  // (the dense arrays are zero before)
+    const uint32_t c = OP == 0 ? val32[i] : here[i];
+    if (!c) continue;
+    if (OP == 0) atomicAdd(&dcnt[key0 + i], c);
+    else dcnt[key0 + i] = 1u;  // (present)
+    if (OP == 1) atomicAdd(&reinterpret_cast<unsigned long long*>(dval)[key0 + i], sum64[i]);
+    if (OP >= 2) atomicMax(&reinterpret_cast<uint32_t*>(dval)[key0 + i], val32[i]);
   }
 }
 
 // ----------------------------------------------------------------------------
 // ordered compaction of dense arrays: keys with count > 0, ascending
 // ----------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_dense_count(const uint32_t* __restrict__ dcnt, uint32_t R, uint32_t* __restrict__ blk) {
+// (tot != NULL: the blocks of ranges of one workgroup are counted already)
+__global__ __launch_bounds__(256) void k_dense_count(const uint32_t* __restrict__ dcnt, uint32_t R, uint32_t* __restrict__ blk,
+                                                     const uint32_t* __restrict__ tot, uint32_t slices, uint32_t P, uint32_t kb,
+                                                     uint32_t split) {
+  if (tot && vp_parts(tot, slices, P, (uint32_t)((uint64_t)blockIdx.x * kCompTile >> kb), split) == 1) return;
   __shared__ uint32_t s;
   if (threadIdx.x == 0) s = 0;
   __syncthreads();
@@ -910,32 +1080,81 @@ hipError_t scan_exclusive_u32(uint32_t* a, uint64_t n, uint32_t* sums, unsigned 
 
 uint64_t scan_sums_count(uint64_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
 
-// Layout of the partitioned fill's scratch for n elements over range R.
-PartPlan part_plan(uint64_t n, uint64_t R) {
-  PartPlan pp{};
-  pp.P = (uint32_t)((R + kPartKeys - 1) / kPartKeys);
-  pp.n_tiles = (uint32_t)((n + kPartTile - 1) / kPartTile);
-  pp.runs = (uint64_t)(pp.P + 1) * pp.n_tiles;
-  pp.part_elems = (uint64_t)pp.n_tiles * kPartTile;
-  pp.usable = R > kPartKeys && pp.P <= kMaxParts && n >= (1ull << 20) && n < (1ull << 32);
-  return pp;
+// Layout of the partitions: ranges of 2^12 keys up to 512 of them (a SUM
+// range's arrays leave room for four workgroups per CU), then the smallest
+// that keeps the ranges at 512 (COUNT, up to 2^15 keys in 128 KB of LDS) or
+// 2048 (values, up to 2^14 keys), so that a tile's run of a range stays long.
+VpPlan vp_plan(uint64_t n, uint64_t R, uint32_t op, uint32_t n_cu) {
+  VpPlan p{};
+  const uint32_t kb_max = op == 0 ? 15 : 14;
+  p.kb = 12;
+  while (p.kb < kb_max && R > (uint64_t)512 << p.kb && (op == 0 || p.kb == 12 || R > (uint64_t)kVpMaxParts << p.kb)) ++p.kb;
+  p.P = (uint32_t)((R + (1ull << p.kb) - 1) >> p.kb);
+  const uint64_t tile = vp_tile(op);
+  p.n_tiles = (uint32_t)((n + tile - 1) / tile);
+  p.elems = (uint64_t)p.n_tiles * tile;
+  p.runs = (uint64_t)p.n_tiles * (p.P + 1);
+  // two workgroups per CU over all ranges; a merged range touches its 2^kb
+  // keys, so four times as many elements at least; and ranges of even shares
+  // (within an eighth) are not split where there are enough of them
+  uint64_t split = std::max<uint64_t>(n / (2 * n_cu), 4ull << p.kb);
+  if (p.P >= 2 * n_cu) split = std::max<uint64_t>(split, n / p.P + n / p.P / 8 + 1024);
+  p.split = (uint32_t)std::min<uint64_t>(split, 1u << 30);
+  p.grid = (uint32_t)(p.P + n / p.split);
+  const uint64_t pieces = n / ((uint64_t)p.P * p.n_tiles + 1) / 8 + 1;  // 16-byte pieces of a run
+  for (p.lpg = 1; p.lpg < vp_fill_threads(op) && pieces > p.lpg; p.lpg *= 2) {}
+  p.list = op == 0 && p.n_tiles >= 8192 && pieces <= 5;
+  p.slices = std::max(1u, std::min(kVpMaxSlices, p.n_tiles / 256));
+  p.usable = p.P <= kVpMaxParts && n >= kVpMin && n < (1ull << 32);
+  return p;
 }
 
-// The tile-major fill: runs [n_tiles][P + 1], part [n_tiles * kPartTile].
-hipError_t int_enqueue_global_array_tiles(const IntLaunch& L, const PartPlan& pp, uint32_t* runs, uint16_t* part,
-                                          hipStream_t s) {
-  const IntIn in{L.in, L.n, L.kv};
-  hipLaunchKernelGGL(k_part_tile, dim3(pp.n_tiles), dim3(kPartThreads), part_tile_lds(pp.P), s, in, L.R, pp.P, runs, part,
-                     L.flags);
-  hipLaunchKernelGGL(k_part_fill_tiles, dim3(pp.P), dim3(1024), 0, s, part, runs, pp.P, pp.n_tiles, L.R, L.dcnt, L.blk);
+template <int OP, bool kList>
+static hipError_t vp_enqueue_fill(const IntLaunch& L, const VpPlan& p, const uint32_t* runs, const uint16_t* pk,
+                                  const uint32_t* pv, const uint32_t* tot, hipStream_t s) {
+  const uint32_t lds = vp_fill_lds(OP, p.kb);
+  if (lds > 32 * 1024) {  // (with the static LDS past 64 KB)
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_vp_fill<OP, kList>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((k_vp_fill<OP, kList>), dim3(p.grid), dim3(vp_fill_threads(OP)), lds, s, L.R, p.kb, p.P, p.n_tiles,
+                     p.split, p.lpg, runs, pk, pv, tot, p.slices, L.dcnt, L.dval, L.blk);
   return hipGetLastError();
 }
 
+template <int OP>
+static hipError_t vp_enqueue(const IntLaunch& L, const VpPlan& p, uint32_t* runs, uint16_t* pk, uint32_t* pv, uint32_t* tot,
+                             hipStream_t s) {
+  hipLaunchKernelGGL(k_vp_tile<OP>, dim3(p.n_tiles), dim3(vp_threads(OP)), (p.P + 1) * 4, s, IntIn{L.in, L.n, L.kv}, L.R, p.kb,
+                     p.P, runs, pk, pv, L.flags);
+  hipLaunchKernelGGL(k_vp_totals, dim3((p.P + kWave - 1) / kWave, p.slices), dim3(kVpTotThreads), 0, s, runs, p.P, p.n_tiles,
+                     tot);
+  if constexpr (OP == 0)
+    if (p.list) return vp_enqueue_fill<0, true>(L, p, runs, pk, pv, tot, s);
+  return vp_enqueue_fill<OP, false>(L, p, runs, pk, pv, tot, s);
+}
+
+hipError_t int_enqueue_global_array_vp(const IntLaunch& L, const VpPlan& p, uint32_t* runs, uint16_t* pk, uint32_t* pv,
+                                       uint32_t* tot, hipStream_t s) {
+  switch (L.op) {
+    case 0: return vp_enqueue<0>(L, p, runs, pk, pv, tot, s);
+    case 1: return vp_enqueue<1>(L, p, runs, pk, pv, tot, s);
+    case 2: return vp_enqueue<2>(L, p, runs, pk, pv, tot, s);
+    default: return vp_enqueue<3>(L, p, runs, pk, pv, tot, s);
+  }
+}
+
 // Compaction of the dense arrays into the outputs; clears them when asked.
-// blk_counted: the blocks' present keys are in L.blk already (partitioned fill).
-hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, bool blk_counted, hipStream_t s) {
+// vp (optional): the partitions that filled them, with their totals.
+hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, const VpPlan* vp, const uint32_t* tot, hipStream_t s) {
   const uint32_t nb = (uint32_t)((L.R + kCompTile - 1) / kCompTile);
-  if (!blk_counted) hipLaunchKernelGGL(k_dense_count, dim3(nb ? nb : 1), dim3(256), 0, s, L.dcnt, L.R, L.blk);
+  if (vp) {
+    hipLaunchKernelGGL(k_dense_count, dim3(nb ? nb : 1), dim3(256), 0, s, L.dcnt, L.R, L.blk, tot, vp->slices, vp->P, vp->kb,
+                       vp->split);
+  } else {
+    hipLaunchKernelGGL(k_dense_count, dim3(nb ? nb : 1), dim3(256), 0, s, L.dcnt, L.R, L.blk, nullptr, 0u, 0u, 0u, 0u);
+  }
   if (nb <= kScanOneMax) hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneWaves * kWave), 0, s, L.blk, nb, L.n_out);
   else hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, L.blk, nb, L.n_out);
   switch (L.op) {

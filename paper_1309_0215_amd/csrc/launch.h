@@ -187,19 +187,26 @@ BloomPlan bloom_plan(uint64_t n_bytes, uint32_t k, uint32_t h, uint64_t m);
 hipError_t bloom_enqueue(const uint8_t* in, uint64_t n_bytes, uint32_t k, uint32_t h, uint64_t m, const BloomPlan& b,
                          uint32_t* hist, uint32_t* scan_sums, unsigned long long* total, uint32_t* part, uint32_t* words,
                          hipStream_t s);
-// global array filled by key-range partitions (COUNT): plan and enqueue
-struct PartPlan {
-  uint32_t P;        // key ranges of 2^15 keys
-  uint32_t n_tiles;  // tiles of elements
-  uint64_t runs;     // (P + 1) * n_tiles run starts
-  uint64_t part_elems;  // n_tiles * tile size: the in-range offsets, tile by tile
-  bool usable;       // range, size and element count suit this fill
-};
-PartPlan part_plan(uint64_t n, uint64_t R);
-hipError_t int_enqueue_global_array_tiles(const IntLaunch& L, const PartPlan& pp, uint32_t* runs, uint16_t* part,
-                                          hipStream_t s);
 hipError_t int_enqueue_global_array(const IntLaunch& L, hipStream_t s);
-hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, bool blk_counted, hipStream_t s);
+// global array filled by key-range partitions, for a range and element count the plan finds usable
+// Fewer elements take atomics on the array: 131,072 uniform pairs over 20,000
+// keys 104 us, 113 us partitioned (three more launches); 262,144 pairs 107 us
+// partitioned whatever the keys, atomics up to 190 us on skewed ones.
+constexpr uint64_t kVpMin = 1ull << 18;
+struct VpPlan {
+  uint32_t kb, P;       // ranges of 2^kb keys
+  uint32_t n_tiles;
+  uint64_t elems, runs; // partitioned elements; (P + 1) run starts per tile
+  uint32_t split, grid; // elements per workgroup of the fill; its workgroups at most
+  uint32_t slices;      // slices of the tiles whose elements are counted per range
+  uint32_t lpg;         // lanes that read a run together
+  bool list;            // counting: runs' pieces listed per wave instead
+  bool usable;
+};
+VpPlan vp_plan(uint64_t n, uint64_t R, uint32_t op, uint32_t n_cu);
+hipError_t int_enqueue_global_array_vp(const IntLaunch& L, const VpPlan& p, uint32_t* runs, uint16_t* pk, uint32_t* pv,
+                                       uint32_t* tot, hipStream_t s);
+hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, const VpPlan* vp, const uint32_t* tot, hipStream_t s);
 hipError_t int_enqueue_hash_map(const IntLaunch& L, hipStream_t s);
 hipError_t int_enqueue_sample(const IntLaunch& L, uint32_t* distinct, hipStream_t s);
 uint32_t int_small_out_max();  // keys int_enqueue_small_out handles

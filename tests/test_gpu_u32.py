@@ -217,3 +217,30 @@ def test_hash_of_few_frequent_keys(torch, n, rare):
         _check(r, keys, None if op == "count" else vals, op)
     # the table is clean for the next job
     _check(_run(torch, _job(STRATS["hash"]), keys[: 1 << 20], vals[: 1 << 20], "max", 0), keys[: 1 << 20], vals[: 1 << 20], "max")
+
+
+# the global array filled by key-range partitions: element counts at its
+# smallest input (2^18; one less takes atomics) and around its tiles (8192
+# pairs, 16,384 counted elements); ranges just past the LDS array's budget, at
+# whole partitions of 2^12 keys, and at the last range of each partition size
+# (2^21, 2^24, 2^25 for values, 2^22, 2^23, 2^26 for counts) and past it
+@pytest.mark.parametrize("n,R", [((1 << 18) - 1, 20_000), (1 << 18, 20_000), ((1 << 18) + 8191, 16_385),
+                                 ((1 << 18) + 8192, 16_384 + 8192), ((1 << 18) + 8193, 1 << 20), (300_000, 1 << 21),
+                                 (300_000, (1 << 21) + 1), (300_000, (1 << 22) + 1), (300_000, (1 << 24) - 1),
+                                 (300_000, (1 << 24) + 1), (280_000, 1 << 25), (280_000, (1 << 25) + 1),
+                                 (280_000, (1 << 26) + 1)])
+@pytest.mark.parametrize("share", [0.0, 0.95])
+def test_global_array_partitions_with_values(torch, n, R, share):
+    """`share` of the elements hold one key, which splits its partition over
+    many workgroups; the others are uniform, both ends of the range present."""
+    rng = np.random.default_rng(n + R)
+    keys = rng.integers(0, R, n).astype(np.uint32)
+    keys[rng.random(n) < share] = R // 3
+    keys[:2] = 0, R - 1
+    vals = rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+    j = _job(STRATS["global_array"])
+    for op in OPS:
+        r = _run(torch, j, keys, vals, op, R)
+        assert r.stats["strategy_used"] == STRATS["global_array"]
+        _check(r, keys, vals, op)
+    _check(_run(torch, j, keys, None, "count", R), keys, None, "count")
