@@ -104,8 +104,11 @@ struct mr_job {
   void* int_table = nullptr;     // keys [cap], counts [cap], values [cap] (64-bit), claimed [cap]
   uint64_t int_table_bytes = 0;  // (int_table_cap: the cap of the layout)
   uint64_t int_table_cap = 0;
-  void* int_small = nullptr;     // flags, counters, side slot
+  void* int_small = nullptr;     // two state blocks (flags, counters, side slot): a job uses one and clears the other
   uint64_t int_small_bytes = 0;
+  uint32_t int_next = 0;         // the block the next job uses
+  bool int_clean = false;        // that block is known to be zero
+  IntPub* h_int = nullptr;       // pinned: state the last job wrote
   void* int_scratch = nullptr;   // partials, sort records, scans
   uint64_t int_scratch_bytes = 0;
   uint64_t int_last_distinct = 0;
@@ -420,6 +423,7 @@ extern "C" mr_status mr_job_destroy(mr_job* job) {
   if (job->gstream) (void)hipStreamSynchronize(job->gstream);
   if (job->gstream) (void)hipStreamDestroy(job->gstream);
   if (job->h_states) (void)hipHostFree(job->h_states);
+  if (job->h_int) (void)hipHostFree(job->h_int);
   if (!job->cws) {  // regions of a caller workspace belong to the caller
     for (void* p : {(void*)job->ws, (void*)job->km_c, job->int_dense, job->int_table, job->int_small, job->int_scratch,
                     job->sel_dev, job->mlp_dev, job->link_dev})
@@ -1098,7 +1102,7 @@ struct IntSmall {
   unsigned long long n_claimed;
   unsigned long long n_out;
   int32_t choice;  // learned container choice (-1: use the rule)
-  uint32_t sampled;  // distinct keys in the sample (hash container)
+  uint32_t pad;
   unsigned long long diff;  // key bits that differ (radix sort)
 };
 
@@ -1160,21 +1164,31 @@ mr_status u32_finish(mr_job* job, mr_output* out, const IntSmall& hs) {
 }
 
 // Scratch layouts of the integer-key containers (offsets in the scratch region).
-struct DenseCarve {  // LDS or global array over n elements and range R, G workgroups
-  uint64_t o_blk = 0, o_cp = 0, o_vp = 0, o_ph = 0, o_pk = 0, o_pv = 0, o_tot = 0, bytes = 0;
+// Workgroups (partial rows) of the LDS array: eight elements per thread, at most two workgroups per CU.
+uint32_t lds_grid(uint64_t n, uint32_t n_cu) {
+  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(2ull * n_cu, (n + 4095) / 4096));
+}
+
+struct DenseCarve {  // LDS or global array over n elements and range R
+  uint64_t o_blk = 0, o_cp = 0, o_vp = 0, o_dc = 0, o_dv = 0, o_ph = 0, o_pk = 0, o_pv = 0, o_tot = 0, bytes = 0;
   bool vparts = false;  // a global array filled by key-range partitions
   VpPlan vp;
 };
 // with_vparts: whether the partitions may be used (without them a global
 // array is filled by atomics, which needs no scratch per element).
-DenseCarve dense_carve(mr_strategy strat, uint64_t n, uint64_t R, uint32_t op, uint32_t G, uint32_t n_cu, bool with_vparts) {
+DenseCarve dense_carve(mr_strategy strat, uint64_t n, uint64_t R, uint32_t op, uint32_t n_cu, bool with_vparts) {
   DenseCarve d;
   Carve c;
+  const uint32_t G = lds_grid(n, n_cu);
   const uint64_t nb = (R + 2047) / 2048;
-  d.o_blk = c.take(4 * (nb + 1));
+  if (strat == MR_STRAT_GLOBAL_ARRAY) d.o_blk = c.take(4 * (nb + 1));
   if (strat == MR_STRAT_LDS_ARRAY) {
     d.o_cp = c.take(4ull * G * R);
     d.o_vp = c.take((op == MR_REDUCE_SUM ? 8ull : 4ull) * G * R);
+    if (!int_lds_direct(R, G)) {  // the partials added up
+      d.o_dc = c.take(4 * R);
+      d.o_dv = c.take((op == MR_REDUCE_SUM ? 8ull : 4ull) * R);
+    }
   }
   if (strat == MR_STRAT_GLOBAL_ARRAY && with_vparts) {
     d.vp = vp_plan(n, R, op, n_cu);
@@ -1291,10 +1305,20 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
 
   mr_status st = MR_OK;
   IntSmall* sm = ctx ? ctx->sm : nullptr;
+  if (!job->h_int) MR_HIP(hipHostMalloc(&job->h_int, sizeof(IntPub), hipHostMallocDefault));
+  IntEnd end{};
   if (!sm) {
-    st = int_ensure(job, kRegSmall, &job->int_small, &job->int_small_bytes, sizeof(IntSmall), 0);
+    bool fresh = false;
+    st = int_ensure(job, kRegSmall, &job->int_small, &job->int_small_bytes, 2 * sizeof(IntSmall), -1, &fresh);
     if (st != MR_OK) return st;
-    sm = static_cast<IntSmall*>(job->int_small);
+    IntSmall* const blocks = static_cast<IntSmall*>(job->int_small);
+    if (fresh || !job->int_clean) MR_HIP(hipMemsetAsync(blocks, 0, 2 * sizeof(IntSmall), job->stream));
+    sm = blocks + job->int_next;
+    job->int_next ^= 1u;
+    job->int_clean = false;  // until this job has cleared the other block
+    end = IntEnd{&sm->flags, job->h_int, reinterpret_cast<uint32_t*>(blocks + job->int_next), sizeof(IntSmall) / 4};
+  } else {
+    MR_HIP(hipMemsetAsync(sm, 0, sizeof(IntSmall), job->stream));
   }
 
   IntLaunch L{};
@@ -1312,6 +1336,7 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
   L.out_keys = static_cast<uint32_t*>(out->keys);
   L.out_vals = out->values;
   L.cap = out->cap_keys;
+  L.end = end;
   L.G = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)job->n_cu * 2, (n + 1023) / 1024));
 
   auto scratch = [&](uint64_t bytes_needed) -> mr_status {
@@ -1319,18 +1344,24 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
   };
   uint32_t retries = 0;
   uint64_t table_cap = 0;
-  {
-    const hipError_t e = hipMemsetAsync(sm, 0, sizeof(IntSmall), job->stream);
-    if (e != hipSuccess) {
-      hipPointerAttribute_t at{};
-      const hipError_t ea = hipPointerGetAttributes(&at, sm);
-      return fail(MR_ERR_HIP, "hipMemsetAsync(state %p, %zu) on stream %p: %s (pointer query: %s, type %d)", (void*)sm,
-                  sizeof(IntSmall), (void*)job->stream, hipGetErrorString(e), hipGetErrorString(ea), (int)at.type);
-    }
-  }
   if (!ctx) MR_HIP(hipEventRecord(job->ev0, job->stream));
 
-  if (strat == MR_STRAT_LDS_ARRAY || strat == MR_STRAT_GLOBAL_ARRAY) {
+  // whether the job's last kernels write its state to h_int (with an end)
+  bool published = strat != MR_STRAT_HASH && !(strat == MR_STRAT_SORT && n == 0);
+  if (strat == MR_STRAT_LDS_ARRAY) {
+    L.G = lds_grid(n, job->n_cu);
+    const DenseCarve dc = dense_carve(strat, n, key_range, o, (uint32_t)job->n_cu, false);
+    st = scratch(dc.bytes);
+    if (st != MR_OK) return st;
+    uint8_t* sc = static_cast<uint8_t*>(job->int_scratch);
+    L.cnt_part = reinterpret_cast<uint32_t*>(sc + dc.o_cp);
+    L.val_part = sc + dc.o_vp;
+    L.dcnt = reinterpret_cast<uint32_t*>(sc + dc.o_dc);
+    L.dval = sc + dc.o_dv;
+    if (job->cfg.timing) MR_HIP(hipEventRecord(job->ev2, job->stream));
+    MR_HIP(int_enqueue_lds_array(L, job->stream));
+    if (job->cfg.timing) MR_HIP(hipEventRecord(job->ev3, job->stream));
+  } else if (strat == MR_STRAT_GLOBAL_ARRAY) {
     // counts [R] then, 8-byte aligned, values [R]: 12 bytes per key plus alignment
     // a new region (or a larger R) starts all zero; the output pass clears what it reads
     bool dense_fresh = false;
@@ -1340,19 +1371,15 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
     if (dense_fresh) job->int_dense_R = key_range;
     L.dcnt = static_cast<uint32_t*>(job->int_dense);
     L.dval = static_cast<uint8_t*>(job->int_dense) + ((4 * job->int_dense_R + 7) & ~7ull);
-    DenseCarve dc = dense_carve(strat, n, key_range, o, L.G, (uint32_t)job->n_cu, true);
-    if (dc.vparts && !scratch_fits(job, dc.bytes)) dc = dense_carve(strat, n, key_range, o, L.G, (uint32_t)job->n_cu, false);
-    const uint64_t o_blk = dc.o_blk, o_cp = dc.o_cp, o_vp = dc.o_vp, o_ph = dc.o_ph, o_pk = dc.o_pk;
+    DenseCarve dc = dense_carve(strat, n, key_range, o, (uint32_t)job->n_cu, true);
+    if (dc.vparts && !scratch_fits(job, dc.bytes)) dc = dense_carve(strat, n, key_range, o, (uint32_t)job->n_cu, false);
+    const uint64_t o_blk = dc.o_blk, o_ph = dc.o_ph, o_pk = dc.o_pk;
     st = scratch(dc.bytes);
     if (st != MR_OK) return st;
     uint8_t* sc = static_cast<uint8_t*>(job->int_scratch);
     L.blk = reinterpret_cast<uint32_t*>(sc + o_blk);
     if (job->cfg.timing) MR_HIP(hipEventRecord(job->ev2, job->stream));
-    if (strat == MR_STRAT_LDS_ARRAY) {
-      L.cnt_part = reinterpret_cast<uint32_t*>(sc + o_cp);
-      L.val_part = sc + o_vp;
-      MR_HIP(int_enqueue_lds_array(L, job->stream));
-    } else if (dc.vparts) {
+    if (dc.vparts) {
       MR_HIP(int_enqueue_global_array_vp(L, dc.vp, reinterpret_cast<uint32_t*>(sc + o_ph), reinterpret_cast<uint16_t*>(sc + o_pk),
                                          reinterpret_cast<uint32_t*>(sc + dc.o_pv), reinterpret_cast<uint32_t*>(sc + dc.o_tot),
                                          job->stream));
@@ -1369,11 +1396,11 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
   IntSmall hs;
   bool have_state = false;  // hs holds the final state already
   if (strat == MR_STRAT_HASH && !own_table && !sorted) {
-    MR_HIP(int_enqueue_sample(L, &sm->sampled, job->stream));
-    MR_HIP(hipMemcpyAsync(&hs, sm, sizeof hs, hipMemcpyDeviceToHost, job->stream));
+    MR_HIP(int_enqueue_sample(L, job->h_int, job->stream));
     MR_HIP(hipStreamSynchronize(job->stream));
-    sorted = hs.sampled > kHashTryKeys;
+    sorted = job->h_int->sampled > kHashTryKeys;
   }
+  published |= sorted && n;
   if (strat == MR_STRAT_HASH && !sorted) {
     // capacity: distinct <= min(n, range); start from the last job's distinct count when larger inputs repeat
     table_cap = own_table ? int_table_slots(job, kind, bytes, n, key_range) : kHashTrySlots;
@@ -1406,8 +1433,16 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
         MR_HIP(int_enqueue_small_out(L, job->stream));
         if (!ctx) MR_HIP(hipEventRecord(job->ev1, job->stream));
       }
-      MR_HIP(hipMemcpyAsync(&hs, sm, sizeof hs, hipMemcpyDeviceToHost, job->stream));
+      const bool pub = !own_table && !ctx;  // int_enqueue_small_out published the state
+      if (!pub) MR_HIP(hipMemcpyAsync(&hs, sm, sizeof hs, hipMemcpyDeviceToHost, job->stream));
       MR_HIP(hipStreamSynchronize(job->stream));
+      if (pub) {
+        hs = IntSmall{};
+        hs.flags = job->h_int->flags;
+        hs.n_out = job->h_int->n_out;
+        hs.n_claimed = job->h_int->n_claimed;
+        job->int_clean = true;
+      }
       const uint64_t nc = hs.n_claimed;
       if (!own_table && !(hs.flags & kFlagTableFull) && nc <= int_small_out_max()) {
         have_state = true;  // the output is written
@@ -1423,7 +1458,7 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
       MR_HIP(int_enqueue_hash_out(L, nc, job->stream));  // gathers and clears the claimed slots
       if (!own_table && (hs.flags & kFlagTableFull)) {
         MR_HIP(hipMemsetAsync(sm, 0, sizeof(IntSmall), job->stream));
-        sorted = true;
+        sorted = published = true;
         table_cap = 0;
         break;
       }
@@ -1476,6 +1511,7 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
     S.out_vals = L.out_vals;
     S.cap = L.cap;
     S.n_out = L.n_out;
+    S.end = end;
     if (job->cfg.timing) MR_HIP(hipEventRecord(job->ev2, job->stream));
     MR_HIP(int_enqueue_sort(S, job->stream));
     if (job->cfg.timing) MR_HIP(hipEventRecord(job->ev3, job->stream));
@@ -1488,8 +1524,14 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
   if (ctx) return MR_OK;  // the batch reads the state back
   if (!have_state) {
     MR_HIP(hipEventRecord(job->ev1, job->stream));
-    MR_HIP(hipMemcpyAsync(&hs, sm, sizeof hs, hipMemcpyDeviceToHost, job->stream));
+    if (!published) MR_HIP(hipMemcpyAsync(&hs, sm, sizeof hs, hipMemcpyDeviceToHost, job->stream));
     MR_HIP(hipStreamSynchronize(job->stream));
+    if (published) {
+      hs = IntSmall{};
+      hs.flags = job->h_int->flags;
+      hs.n_out = job->h_int->n_out;
+      job->int_clean = true;
+    }
   }
   float ms = 0.f;
   MR_HIP(hipEventElapsedTime(&ms, job->ev0, job->ev1));
@@ -1795,8 +1837,7 @@ extern "C" mr_status mr_workspace_bytes(const mr_job_config* cfg, mr_map_kind ki
       const uint64_t ne = n / esz;
       // pairs are planned for SUM (the widest values), keys for COUNT
       const uint32_t op = kind == MR_MAP_U32_KV ? (uint32_t)MR_REDUCE_SUM : (uint32_t)MR_REDUCE_COUNT;
-      const uint32_t G = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)n_cu * 2, (ne + 1023) / 1024));
-      r.add(sizeof(IntSmall));
+      r.add(2 * sizeof(IntSmall));
       std::vector<mr_strategy> cand;
       if (cfg->strategy == MR_STRAT_LEARNED) {
         r.add(4 * sel_floats());
@@ -1811,8 +1852,8 @@ extern "C" mr_status mr_workspace_bytes(const mr_job_config* cfg, mr_map_kind ki
       for (mr_strategy c : cand) {
         RegionSum t = r;
         if (c == MR_STRAT_LDS_ARRAY || c == MR_STRAT_GLOBAL_ARRAY) {
-          t.add(key_range * 12 + 8);
-          t.add(dense_carve(c, ne, key_range, op, G, (uint32_t)n_cu, true).bytes);
+          if (c == MR_STRAT_GLOBAL_ARRAY) t.add(key_range * 12 + 8);
+          t.add(dense_carve(c, ne, key_range, op, (uint32_t)n_cu, true).bytes);
         } else if (c == MR_STRAT_HASH) {
           const IntHashNeed h = int_hash_need(&tmp, kind, n, ne, key_range, op);
           if (h.slots) t.add(h.slots * kIntSlotBytes);
@@ -2178,9 +2219,14 @@ mr_status learned_strategy(mr_job* job, mr_map_kind kind, mr_reduce_op op, const
   uint32_t feas = 0;
   for (int i = 0; i < MR_N_STRATS; ++i)
     if (int_feasible(order[i], R, (uint32_t)op)) feas |= 1u << i;
-  mr_status st = int_ensure(job, kRegSmall, &job->int_small, &job->int_small_bytes, sizeof(IntSmall), 0);
+  bool fresh = false;
+  mr_status st = int_ensure(job, kRegSmall, &job->int_small, &job->int_small_bytes, 2 * sizeof(IntSmall), -1, &fresh);
   if (st != MR_OK) return st;
-  IntSmall* sm = static_cast<IntSmall*>(job->int_small);
+  if (fresh) {
+    MR_HIP(hipMemsetAsync(job->int_small, 0, 2 * sizeof(IntSmall), job->stream));
+    job->int_clean = true;
+  }
+  IntSmall* sm = static_cast<IntSmall*>(job->int_small) + job->int_next;
   st = sel_upload(job);
   if (st != MR_OK) return st;
   float* d = static_cast<float*>(job->sel_dev);
@@ -2211,6 +2257,7 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
   const hipStream_t s = job->stream;
   mr_status st = int_ensure(job, kRegSmall, &job->int_small, &job->int_small_bytes, sizeof(IntSmall) * ni, -1);
   if (st != MR_OK) return st;
+  job->int_clean = false;  // the items' states take the blocks
   IntSmall* sm = static_cast<IntSmall*>(job->int_small);
   MR_HIP(hipMemsetAsync(sm, 0, sizeof(IntSmall) * ni, s));
   std::vector<mr_strategy> strat(ni, MR_STRAT_RULE);
@@ -2288,12 +2335,13 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
       per[ii[q]] = fail(MR_ERR_UNSUPPORTED, "strategy %d is infeasible for item %u", (int)strat[q], ii[q]);
       continue;
     }
-    const uint32_t G = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)job->n_cu * 2, (n + 1023) / 1024));
     if (strat[q] == MR_STRAT_LDS_ARRAY || strat[q] == MR_STRAT_GLOBAL_ARRAY) {
-      dense_r = std::max(dense_r, it.key_range);
-      dense_b = std::max(dense_b, it.key_range * 12 + 8);
-      scratch_b = std::max(scratch_b, dense_carve(strat[q], n, it.key_range, op, G, (uint32_t)job->n_cu, false).bytes);
-      scratch_full = std::max(scratch_full, dense_carve(strat[q], n, it.key_range, op, G, (uint32_t)job->n_cu, true).bytes);
+      if (strat[q] == MR_STRAT_GLOBAL_ARRAY) {
+        dense_r = std::max(dense_r, it.key_range);
+        dense_b = std::max(dense_b, it.key_range * 12 + 8);
+      }
+      scratch_b = std::max(scratch_b, dense_carve(strat[q], n, it.key_range, op, (uint32_t)job->n_cu, false).bytes);
+      scratch_full = std::max(scratch_full, dense_carve(strat[q], n, it.key_range, op, (uint32_t)job->n_cu, true).bytes);
     } else if (strat[q] == MR_STRAT_HASH) {
       const IntHashNeed h = int_hash_need(job, it.kind, it.input_bytes, n, it.key_range, op);
       table_s = std::max(table_s, h.slots);

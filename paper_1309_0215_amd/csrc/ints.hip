@@ -50,64 +50,205 @@ MR_DEV void load_elem(const IntIn& in, uint64_t i, uint32_t& k, uint32_t& v) {
 }
 
 // ----------------------------------------------------------------------------
-// LDS array
+// state of a job
 // ----------------------------------------------------------------------------
-constexpr int kIntThreads = 512;
-
-// Partials layout: cnt_part[g * R + key], val_part[g * R + key] (val for SUM is 64-bit).
-template <int OP>
-__global__ __launch_bounds__(kIntThreads) void k_lds_array(IntIn in, uint32_t R, uint32_t G, uint32_t* __restrict__ cnt_part,
-                                                           void* __restrict__ val_part, uint32_t* __restrict__ flags) {
-  extern __shared__ uint8_t smem[];
-  uint32_t* cnt = reinterpret_cast<uint32_t*>(smem);
-  unsigned long long* sum = reinterpret_cast<unsigned long long*>(smem + ((4ull * R + 7) & ~7ull));
-  uint32_t* mm = reinterpret_cast<uint32_t*>(smem + 4ull * R);
-  for (uint32_t i = threadIdx.x; i < R; i += blockDim.x) {
-    cnt[i] = 0;
-    if (OP == 1) sum[i] = 0;
-    if (OP >= 2) mm[i] = 0;
-  }
-  __syncthreads();
-  const uint64_t lo = in.n * blockIdx.x / G, hi = in.n * (blockIdx.x + 1) / G;
-  bool bad = false;
-  for (uint64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-    uint32_t k, v;
-    load_elem(in, i, k, v);
-    if (k >= R) {
-      bad = true;
-      continue;
-    }
-    atomicAdd(&cnt[k], 1u);
-    if (OP == 1) atomicAdd(&sum[k], (unsigned long long)v);
-    if (OP >= 2) atomicMax(&mm[k], enc_minmax(OP, v));
-  }
-  if (bad) atomicOr(flags, kFlagBadInput);
-  __syncthreads();
-  for (uint32_t i = threadIdx.x; i < R; i += blockDim.x) {
-    cnt_part[(uint64_t)blockIdx.x * R + i] = cnt[i];
-    if (OP == 1) reinterpret_cast<unsigned long long*>(val_part)[(uint64_t)blockIdx.x * R + i] = sum[i];
-    if (OP >= 2) reinterpret_cast<uint32_t*>(val_part)[(uint64_t)blockIdx.x * R + i] = mm[i];
+// The last small kernel of a job writes the job's state to host memory and
+// clears the state block of the next job, so that a job needs neither a fill
+// before its kernels nor a copy after them. Called by a whole workgroup;
+// thread 0 knows n_out.
+MR_DEV void int_publish(const IntEnd& E, unsigned long long n_out, unsigned long long n_claimed) {
+  if (!E.host) return;
+  for (uint32_t i = threadIdx.x; i < E.clear_words; i += blockDim.x) E.clear[i] = 0u;
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(&E.host->n_out, n_out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&E.host->n_claimed, n_claimed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&E.host->flags, *E.flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
-// Dense arrays (count, value) from the partials: one thread per key.
+// ----------------------------------------------------------------------------
+// LDS array
+// ----------------------------------------------------------------------------
+constexpr int kIntThreads = 512;
+constexpr uint32_t kLdsCopiesBytes = 32 * 1024;  // LDS a workgroup may spend on copies of a small array
+
+// LDS words from one array copy to the next: counts (padded to 8 bytes before
+// 64-bit values), then values; with several copies an odd number of values, so
+// that a key's copies lie in different banks.
+static __host__ __device__ uint32_t lds_copy_words(uint32_t R, uint32_t op, uint32_t copies) {
+  if (op == 1) {
+    const uint32_t w = ((R + 1) & ~1u) + 2 * R;
+    return copies > 1 && w % 4 == 0 ? w + 2 : w;
+  }
+  const uint32_t w = op == 0 ? R : 2 * R;
+  return copies > 1 ? w | 1u : w;
+}
+
+// Partials layout: cnt_part[g * R + key], val_part[g * R + key] (val for SUM is 64-bit).
+// A small array is kept in `copies` copies (a power of two), lane l adding to
+// copy l % copies, so that a frequent key serialises 64 / copies lanes;
+// elements are loaded eight at a time. With one copy and a load per step the
+// step on 16 M pairs over 300 keys (SUM, skewed) took 250 us without the pairs'
+// interleaving, 55 us this way.
 template <int OP>
-__global__ __launch_bounds__(256) void k_lds_array_reduce(uint32_t R, uint32_t G, const uint32_t* __restrict__ cnt_part,
-                                                          const void* __restrict__ val_part, uint32_t* __restrict__ dcnt,
-                                                          void* __restrict__ dval) {
-  for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < R; k += gridDim.x * blockDim.x) {
-    uint32_t c = 0;
+__global__ __launch_bounds__(kIntThreads) void k_lds_array(IntIn in, uint32_t R, uint32_t G, uint32_t copies,
+                                                           uint32_t* __restrict__ cnt_part, void* __restrict__ val_part,
+                                                           uint32_t* __restrict__ flags) {
+  extern __shared__ unsigned long long lds_array[];
+  uint32_t* const lds = reinterpret_cast<uint32_t*>(lds_array);
+  const uint32_t words = lds_copy_words(R, OP, copies), off = OP == 1 ? (R + 1) & ~1u : R;  // values start `off` words in
+  for (uint32_t i = threadIdx.x; i < words * copies; i += kIntThreads) lds[i] = 0;
+  __syncthreads();
+  uint32_t* const cnt = lds + (threadIdx.x & (copies - 1)) * words;
+  unsigned long long* const sum = reinterpret_cast<unsigned long long*>(cnt + off);
+  uint32_t* const mm = cnt + off;
+  const uint64_t lo = in.n * blockIdx.x / G, hi = in.n * (blockIdx.x + 1) / G;
+  const uint32_t stride = in.kv ? 2u : 1u;
+  bool bad = false;
+  constexpr uint32_t kBatch = 8;
+  for (uint64_t i0 = lo + threadIdx.x; i0 < hi; i0 += kBatch * kIntThreads) {
+    uint32_t k[kBatch], v[kBatch];
+    const MR_GLOBAL uint32_t* src = gp(in.p) + i0 * stride;
+#pragma unroll
+    for (uint32_t u = 0; u < kBatch; ++u) {
+      k[u] = v[u] = 0;
+      if (i0 + u * kIntThreads < hi) {
+        k[u] = src[u * kIntThreads * stride];
+        if (OP != 0) v[u] = src[u * kIntThreads * stride + 1];
+      }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kBatch; ++u) {
+      if (i0 + u * kIntThreads >= hi) break;
+      if (k[u] >= R) {
+        bad = true;
+        continue;
+      }
+      atomicAdd(&cnt[k[u]], 1u);
+      if (OP == 1) atomicAdd(&sum[k[u]], (unsigned long long)v[u]);
+      if (OP >= 2) atomicMax(&mm[k[u]], enc_minmax(OP, v[u]));
+    }
+  }
+  if (bad) atomicOr(flags, kFlagBadInput);
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < R; i += kIntThreads) {
+    uint32_t c = 0, m = 0;
     unsigned long long s = 0;
-    uint32_t m = 0;
-    for (uint32_t g = 0; g < G; ++g) {
+    for (uint32_t q = 0; q < copies; ++q) {
+      const uint32_t* const a = lds + q * words;
+      c += a[i];
+      if (OP == 1) s += reinterpret_cast<const unsigned long long*>(a + off)[i];
+      if (OP >= 2) m = max(m, a[off + i]);
+    }
+    cnt_part[(uint64_t)blockIdx.x * R + i] = c;
+    if (OP == 1) reinterpret_cast<unsigned long long*>(val_part)[(uint64_t)blockIdx.x * R + i] = s;
+    if (OP >= 2) reinterpret_cast<uint32_t*>(val_part)[(uint64_t)blockIdx.x * R + i] = m;
+  }
+}
+
+// G partial rows added into one: 64 keys per workgroup, each wave a
+// sixteenth of the rows.
+constexpr uint32_t kLdsReduceWaves = 16;
+
+template <int OP>
+__global__ __launch_bounds__(kLdsReduceWaves * kWave) void k_lds_array_reduce(uint32_t R, uint32_t G,
+                                                                              const uint32_t* __restrict__ cnt_part,
+                                                                              const void* __restrict__ val_part,
+                                                                              uint32_t* __restrict__ dcnt,
+                                                                              void* __restrict__ dval) {
+  __shared__ uint32_t wc[kLdsReduceWaves][kWave], wm[kLdsReduceWaves][kWave];
+  __shared__ unsigned long long wsum[kLdsReduceWaves][kWave];
+  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave, k = blockIdx.x * kWave + lane;
+  uint32_t c = 0, m = 0;
+  unsigned long long s = 0;
+  if (k < R) {
+#pragma unroll 8
+    for (uint32_t g = wv; g < G; g += kLdsReduceWaves) {
       c += cnt_part[(uint64_t)g * R + k];
       if (OP == 1) s += reinterpret_cast<const unsigned long long*>(val_part)[(uint64_t)g * R + k];
       if (OP >= 2) m = max(m, reinterpret_cast<const uint32_t*>(val_part)[(uint64_t)g * R + k]);
     }
-    dcnt[k] = c;
-    if (OP == 1) reinterpret_cast<unsigned long long*>(dval)[k] = s;
-    if (OP >= 2) reinterpret_cast<uint32_t*>(dval)[k] = m;
   }
+  wc[wv][lane] = c;
+  if (OP == 1) wsum[wv][lane] = s;
+  if (OP >= 2) wm[wv][lane] = m;
+  __syncthreads();
+  if (wv || k >= R) return;
+  for (uint32_t w = 1; w < kLdsReduceWaves; ++w) {
+    c += wc[w][lane];
+    if (OP == 1) s += wsum[w][lane];
+    if (OP >= 2) m = max(m, wm[w][lane]);
+  }
+  dcnt[k] = c;
+  if (OP == 1) reinterpret_cast<unsigned long long*>(dval)[k] = s;
+  if (OP >= 2) reinterpret_cast<uint32_t*>(dval)[k] = m;
+}
+
+// Output of an LDS array by one workgroup: the G partial rows are added (few
+// of them; many are added by k_lds_array_reduce first and come as one row),
+// the present keys placed by a scan of ballots, and the job's state published.
+// One launch instead of the reduce, the block counts, their scan and the
+// ordered write.
+template <int OP, uint32_t PER>  // keys per thread
+__global__ __launch_bounds__(1024) void k_lds_out(uint32_t R, uint32_t G, const uint32_t* __restrict__ cnt_part,
+                                                  const void* __restrict__ val_part, uint32_t* __restrict__ out_keys,
+                                                  void* __restrict__ out_vals, uint64_t cap,
+                                                  unsigned long long* __restrict__ n_out, IntEnd E) {
+  constexpr uint32_t kWaves = 1024 / kWave;
+  __shared__ uint32_t place[PER * kWaves];  // present keys of (u, wave), then their first place
+  __shared__ uint32_t ws[kWaves];
+  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+  uint32_t c[PER], m[OP >= 2 ? PER : 1];
+  unsigned long long s[OP == 1 ? PER : 1];
+#pragma unroll
+  for (uint32_t u = 0; u < PER; ++u) {
+    c[u] = 0;
+    if (OP == 1) s[u] = 0;
+    if (OP >= 2) m[u] = 0;
+  }
+  constexpr int kRows = PER <= 4 ? 8 / PER : 1;  // rows in flight
+#pragma unroll kRows
+  for (uint32_t g = 0; g < G; ++g) {
+#pragma unroll
+    for (uint32_t u = 0; u < PER; ++u) {
+      const uint32_t k = u * 1024 + threadIdx.x;
+      if (k < R) {
+        c[u] += cnt_part[(uint64_t)g * R + k];
+        if (OP == 1) s[u] += reinterpret_cast<const unsigned long long*>(val_part)[(uint64_t)g * R + k];
+        if (OP >= 2) m[u] = max(m[u], reinterpret_cast<const uint32_t*>(val_part)[(uint64_t)g * R + k]);
+      }
+    }
+  }
+#pragma unroll
+  for (uint32_t u = 0; u < PER; ++u) {
+    const uint64_t b = __ballot(c[u] != 0);
+    if (lane == 0) place[u * kWaves + wv] = popc64(b);
+  }
+  __syncthreads();
+  const uint32_t mine = threadIdx.x < PER * kWaves ? place[threadIdx.x] : 0u;
+  const uint32_t incl = wave_incl_scan(mine);
+  if (lane == kWave - 1) ws[wv] = incl;
+  __syncthreads();
+  uint32_t pre = incl - mine, all = 0;
+  for (uint32_t w = 0; w < kWaves; ++w) {
+    if (w < wv) pre += ws[w];
+    all += ws[w];
+  }
+  if (threadIdx.x < PER * kWaves) place[threadIdx.x] = pre;
+  __syncthreads();
+#pragma unroll
+  for (uint32_t u = 0; u < PER; ++u) {
+    const uint64_t b = __ballot(c[u] != 0);
+    const uint64_t o = place[u * kWaves + wv] + mbcnt(b);
+    if (c[u] && o < cap) {
+      out_keys[o] = u * 1024 + threadIdx.x;
+      if (OP == 0) reinterpret_cast<uint32_t*>(out_vals)[o] = c[u];
+      if (OP == 1) reinterpret_cast<unsigned long long*>(out_vals)[o] = s[u];
+      if (OP >= 2) reinterpret_cast<uint32_t*>(out_vals)[o] = dec_minmax(OP, m[u]);
+    }
+  }
+  if (threadIdx.x == 0) *n_out = all;
+  int_publish(E, all, 0);
 }
 
 // ----------------------------------------------------------------------------
@@ -624,7 +765,8 @@ __global__ __launch_bounds__(256) void k_dense_count(const uint32_t* __restrict_
 }
 
 // Exclusive scan of blk[0, nb) in place by one workgroup; total in *total.
-__global__ __launch_bounds__(1024) void k_scan_small(uint32_t* __restrict__ blk, uint32_t nb, unsigned long long* total) {
+__global__ __launch_bounds__(1024) void k_scan_small(uint32_t* __restrict__ blk, uint32_t nb, unsigned long long* total,
+                                                     IntEnd E) {
   __shared__ uint32_t ws[1024 / kWave];
   uint32_t carry = 0;
   const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
@@ -649,6 +791,7 @@ __global__ __launch_bounds__(1024) void k_scan_small(uint32_t* __restrict__ blk,
     __syncthreads();
   }
   if (threadIdx.x == 0 && total) *total = carry;
+  int_publish(E, carry, 0);
 }
 
 // Write the present keys of a dense array in order and clear the arrays.
@@ -797,7 +940,7 @@ __global__ __launch_bounds__(kIntThreads) void k_int_hash(IntIn in, IntTable T, 
 // which the LDS caches combine, from the others before any pass over them.
 constexpr uint32_t kSampleSize = 8192;
 
-__global__ __launch_bounds__(1024) void k_int_sample(IntIn in, uint32_t* __restrict__ distinct) {
+__global__ __launch_bounds__(1024) void k_int_sample(IntIn in, IntPub* host) {
   constexpr uint32_t S = 2 * kSampleSize;
   __shared__ uint32_t set[S];
   __shared__ uint32_t n;
@@ -825,7 +968,7 @@ __global__ __launch_bounds__(1024) void k_int_sample(IntIn in, uint32_t* __restr
   }
   if (mine) atomicAdd(&n, mine);
   __syncthreads();
-  if (threadIdx.x == 0) *distinct = n;
+  if (threadIdx.x == 0) __hip_atomic_store(&host->sampled, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Output of a table of few keys by one workgroup: the claimed slots' keys are
@@ -837,10 +980,13 @@ constexpr uint32_t kSmallOut = 4096;
 
 template <int OP>
 __global__ __launch_bounds__(1024) void k_int_small_out(IntTable T, uint32_t* __restrict__ out_keys, void* __restrict__ out_vals,
-                                                        uint64_t cap, unsigned long long* __restrict__ n_out) {
+                                                        uint64_t cap, unsigned long long* __restrict__ n_out, IntEnd E) {
   __shared__ unsigned long long e[kSmallOut];
   const unsigned long long nc = *T.n_claimed;
-  if (nc > kSmallOut || (*T.flags & kFlagTableFull)) return;
+  if (nc > kSmallOut || (*T.flags & kFlagTableFull)) {
+    int_publish(E, 0, nc);
+    return;
+  }
   const uint32_t n = (uint32_t)nc;
   uint32_t m = 1;
   while (m < n) m *= 2;
@@ -883,6 +1029,7 @@ __global__ __launch_bounds__(1024) void k_int_small_out(IntTable T, uint32_t* __
     }
     *n_out = n + (side ? 1u : 0u);
   }
+  int_publish(E, n + (*T.side_cnt != 0 ? 1u : 0u), nc);
 }
 
 // Claimed slots -> (key, claim index) pairs and values; slots are cleared for reuse.
@@ -982,24 +1129,59 @@ uint32_t int_lds_array_bytes(uint64_t R, uint32_t op) {
   return (uint32_t)(b < 0xFFFFFFFFull ? b : 0xFFFFFFFFull);
 }
 
-hipError_t int_enqueue_lds_array(const IntLaunch& L, hipStream_t s) {
-  const IntIn in{L.in, L.n, L.kv};
-  const size_t lds = int_lds_array_bytes(L.R, L.op);
-#define LDS_CASE(OP)                                                                                               \
-  case OP:                                                                                                         \
-    hipLaunchKernelGGL(k_lds_array<OP>, dim3(L.G), dim3(kIntThreads), lds, s, in, L.R, L.G, L.cnt_part, L.val_part, \
-                       L.flags);                                                                                   \
-    hipLaunchKernelGGL(k_lds_array_reduce<OP>, dim3(blocks_for(L.R, 256, 4096)), dim3(256), 0, s, L.R, L.G,        \
-                       L.cnt_part, L.val_part, L.dcnt, L.dval);                                                    \
-    break;
-  switch (L.op) {
-    LDS_CASE(0)
-    LDS_CASE(1)
-    LDS_CASE(2)
-    LDS_CASE(3)
+// Copies of the LDS array per workgroup: as many as kLdsCopiesBytes hold, at most 32.
+static uint32_t lds_copies(uint32_t R, uint32_t op) {
+  uint32_t c = 1;
+  while (c < 32 && 2 * c * lds_copy_words(R, op, 2 * c) * 4 <= kLdsCopiesBytes) c *= 2;
+  return c;
+}
+
+// Partial rows the output kernel adds itself: up to 32 rows and kLdsDirect
+// values; more are added by the reduce kernel first (its launch costs 5 us, a
+// row read by one workgroup about 0.1 us).
+constexpr uint64_t kLdsDirect = 64 * 1024;
+
+bool int_lds_direct(uint64_t R, uint32_t G) { return G <= 32 && R * G <= kLdsDirect; }
+
+template <int OP>
+static hipError_t lds_enqueue(const IntLaunch& L, hipStream_t s) {
+  const uint32_t R = (uint32_t)L.R;
+  const uint32_t copies = lds_copies(R, OP);
+  hipLaunchKernelGGL(k_lds_array<OP>, dim3(L.G), dim3(kIntThreads), copies * lds_copy_words(R, OP, copies) * 4, s, IntIn{L.in, L.n, L.kv}, R, L.G, copies,
+                     L.cnt_part, L.val_part, L.flags);
+  const uint32_t* cnt = L.cnt_part;
+  const void* val = L.val_part;
+  uint32_t G = L.G;
+  if (!int_lds_direct(L.R, L.G)) {
+    hipLaunchKernelGGL(k_lds_array_reduce<OP>, dim3((R + kWave - 1) / kWave), dim3(kLdsReduceWaves * kWave), 0, s, R, L.G,
+                       L.cnt_part, L.val_part, L.dcnt, L.dval);
+    cnt = L.dcnt;
+    val = L.dval;
+    G = 1;
   }
-#undef LDS_CASE
+  // (an LDS array holds at most 16,384 counts, 8,192 counts with extrema or 5,461 with sums)
+  constexpr uint32_t kMost = OP == 0 ? 16 : 8;
+  if (R <= 1024) {
+    hipLaunchKernelGGL((k_lds_out<OP, 1>), dim3(1), dim3(1024), 0, s, R, G, cnt, val, L.out_keys, L.out_vals, L.cap, L.n_out,
+                       L.end);
+  } else if (R <= 4096) {
+    hipLaunchKernelGGL((k_lds_out<OP, 4>), dim3(1), dim3(1024), 0, s, R, G, cnt, val, L.out_keys, L.out_vals, L.cap, L.n_out,
+                       L.end);
+  } else {
+    hipLaunchKernelGGL((k_lds_out<OP, kMost>), dim3(1), dim3(1024), 0, s, R, G, cnt, val, L.out_keys, L.out_vals, L.cap,
+                       L.n_out, L.end);
+  }
   return hipGetLastError();
+}
+
+// Map, reduce and ordered output.
+hipError_t int_enqueue_lds_array(const IntLaunch& L, hipStream_t s) {
+  switch (L.op) {
+    case 0: return lds_enqueue<0>(L, s);
+    case 1: return lds_enqueue<1>(L, s);
+    case 2: return lds_enqueue<2>(L, s);
+    default: return lds_enqueue<3>(L, s);
+  }
 }
 
 hipError_t int_enqueue_global_array(const IntLaunch& L, hipStream_t s) {
@@ -1027,7 +1209,7 @@ constexpr uint32_t kScanOneBatch = 8;   // steps loaded and scanned together
 constexpr uint64_t kScanOneMax = (uint64_t)kScanOneWaves * kWave * kScanOneSteps;
 
 __global__ __launch_bounds__(kScanOneWaves * kWave) void k_scan_one(uint32_t* __restrict__ a, uint32_t n,
-                                                                   unsigned long long* total) {
+                                                                   unsigned long long* total, IntEnd E) {
   __shared__ uint32_t ws[kScanOneWaves];
   const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
   const uint32_t steps = (n + kScanOneWaves * kWave - 1) / (kScanOneWaves * kWave);  // <= kScanOneSteps
@@ -1063,17 +1245,19 @@ __global__ __launch_bounds__(kScanOneWaves * kWave) void k_scan_one(uint32_t* __
     }
   }
   if (threadIdx.x == 0 && total) *total = all;
+  int_publish(E, all, 0);
 }
 
 // Exclusive scan of a[0, n) in place; the sum of all entries into *total.
-hipError_t scan_exclusive_u32(uint32_t* a, uint64_t n, uint32_t* sums, unsigned long long* total, hipStream_t s) {
+hipError_t scan_exclusive_u32(uint32_t* a, uint64_t n, uint32_t* sums, unsigned long long* total, hipStream_t s,
+                              const IntEnd& E) {
   if (n <= kScanOneMax) {
-    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneWaves * kWave), 0, s, a, (uint32_t)n, total);
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneWaves * kWave), 0, s, a, (uint32_t)n, total, E);
     return hipGetLastError();
   }
   const uint32_t sb = (uint32_t)((n + kScanTile - 1) / kScanTile);
   hipLaunchKernelGGL(k_scan_blocks, dim3(sb ? sb : 1), dim3(256), 0, s, a, n, sums);
-  hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, sums, sb ? sb : 1, total);
+  hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, sums, sb ? sb : 1, total, E);
   hipLaunchKernelGGL(k_scan_apply, dim3(sb ? sb : 1), dim3(256), 0, s, a, n, sums);
   return hipGetLastError();
 }
@@ -1155,8 +1339,8 @@ hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, const VpPlan* v
   } else {
     hipLaunchKernelGGL(k_dense_count, dim3(nb ? nb : 1), dim3(256), 0, s, L.dcnt, L.R, L.blk, nullptr, 0u, 0u, 0u, 0u);
   }
-  if (nb <= kScanOneMax) hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneWaves * kWave), 0, s, L.blk, nb, L.n_out);
-  else hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, L.blk, nb, L.n_out);
+  if (nb <= kScanOneMax) hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneWaves * kWave), 0, s, L.blk, nb, L.n_out, L.end);
+  else hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, L.blk, nb, L.n_out, L.end);
   switch (L.op) {
     case 0: hipLaunchKernelGGL(k_dense_write<0>, dim3(nb ? nb : 1), dim3(256), 0, s, L.dcnt, L.dval, L.R, L.blk, L.out_keys, L.out_vals, L.cap, clear); break;
     case 1: hipLaunchKernelGGL(k_dense_write<1>, dim3(nb ? nb : 1), dim3(256), 0, s, L.dcnt, L.dval, L.R, L.blk, L.out_keys, L.out_vals, L.cap, clear); break;
@@ -1181,8 +1365,8 @@ hipError_t int_enqueue_hash_map(const IntLaunch& L, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t int_enqueue_sample(const IntLaunch& L, uint32_t* distinct, hipStream_t s) {
-  hipLaunchKernelGGL(k_int_sample, dim3(1), dim3(1024), 0, s, IntIn{L.in, L.n, L.kv}, distinct);
+hipError_t int_enqueue_sample(const IntLaunch& L, IntPub* host, hipStream_t s) {
+  hipLaunchKernelGGL(k_int_sample, dim3(1), dim3(1024), 0, s, IntIn{L.in, L.n, L.kv}, host);
   return hipGetLastError();
 }
 
@@ -1191,10 +1375,10 @@ uint32_t int_small_out_max() { return kSmallOut; }
 hipError_t int_enqueue_small_out(const IntLaunch& L, hipStream_t s) {
   IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.max_probes, L.side_cnt, L.side_val, L.flags};
   switch (L.op) {
-    case 0: hipLaunchKernelGGL(k_int_small_out<0>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out); break;
-    case 1: hipLaunchKernelGGL(k_int_small_out<1>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out); break;
-    case 2: hipLaunchKernelGGL(k_int_small_out<2>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out); break;
-    case 3: hipLaunchKernelGGL(k_int_small_out<3>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out); break;
+    case 0: hipLaunchKernelGGL(k_int_small_out<0>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out, L.end); break;
+    case 1: hipLaunchKernelGGL(k_int_small_out<1>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out, L.end); break;
+    case 2: hipLaunchKernelGGL(k_int_small_out<2>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out, L.end); break;
+    case 3: hipLaunchKernelGGL(k_int_small_out<3>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out, L.end); break;
   }
   return hipGetLastError();
 }

@@ -85,6 +85,19 @@ hipError_t rgb_graph_build(hipGraph_t g, const uint8_t* in, uint64_t n, uint32_t
                            unsigned long long* out, hipEvent_t all0, hipEvent_t map0, hipEvent_t map1,
                            hipEvent_t all1);
 
+// End of an integer-key job: its state goes to host memory, and the other
+// state block is cleared for the next job. host == NULL: not done.
+struct IntPub {  // pinned host memory
+  uint32_t flags, sampled;
+  unsigned long long n_out, n_claimed;
+};
+struct IntEnd {
+  const uint32_t* flags;
+  IntPub* host;
+  uint32_t* clear;
+  uint32_t clear_words;
+};
+
 // Integer-key jobs: one launch description shared by the four containers.
 struct IntLaunch {
   const uint32_t* in;
@@ -119,6 +132,7 @@ struct IntLaunch {
   void* out_vals;
   uint64_t cap;
   unsigned long long* n_out;  // device: number of distinct keys
+  IntEnd end;
 };
 
 // Radix sort of all elements and the reduce of the runs (sort.hip).
@@ -148,6 +162,7 @@ struct SortLaunch {
   void* out_vals;
   uint64_t cap;
   unsigned long long* n_out;
+  IntEnd end;
 };
 hipError_t int_enqueue_sort(const SortLaunch& L, hipStream_t s);
 // in: n pairs (key, index into vals); writes keys ascending and their values
@@ -168,8 +183,10 @@ hipError_t keys64_enqueue_sort(const Keys64Sort& L, hipStream_t s);
 uint32_t keys64_sorted_bits(uint32_t bits);
 
 hipError_t int_enqueue_lds_array(const IntLaunch& L, hipStream_t s);
+bool int_lds_direct(uint64_t R, uint32_t G);  // whether its output needs no reduced arrays (dcnt, dval)
 // device-wide exclusive scan of uint32 counts (sums: scan_sums_count(n) entries)
-hipError_t scan_exclusive_u32(uint32_t* a, uint64_t n, uint32_t* sums, unsigned long long* total, hipStream_t s);
+hipError_t scan_exclusive_u32(uint32_t* a, uint64_t n, uint32_t* sums, unsigned long long* total, hipStream_t s,
+                              const IntEnd& E = IntEnd{});
 uint64_t scan_sums_count(uint64_t n);
 
 // Bloom filter build: plan and enqueue (see bloom.hip)
@@ -208,7 +225,7 @@ hipError_t int_enqueue_global_array_vp(const IntLaunch& L, const VpPlan& p, uint
                                        uint32_t* tot, hipStream_t s);
 hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, const VpPlan* vp, const uint32_t* tot, hipStream_t s);
 hipError_t int_enqueue_hash_map(const IntLaunch& L, hipStream_t s);
-hipError_t int_enqueue_sample(const IntLaunch& L, uint32_t* distinct, hipStream_t s);
+hipError_t int_enqueue_sample(const IntLaunch& L, IntPub* host, hipStream_t s);  // -> host->sampled
 uint32_t int_small_out_max();  // keys int_enqueue_small_out handles
 hipError_t int_enqueue_small_out(const IntLaunch& L, hipStream_t s);
 hipError_t int_enqueue_hash_out(const IntLaunch& L, uint64_t n_claimed_host, hipStream_t s);

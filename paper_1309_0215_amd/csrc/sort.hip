@@ -535,7 +535,7 @@ static hipError_t rs_reduce_per(const RsData<E>& D, uint32_t bits, const SortLau
   const uint64_t n_chunks = radix_plan(D.n).n_chunks;
   const uint32_t g = (uint32_t)((n_chunks + kRunThreads / kWave - 1) / (kRunThreads / kWave));
   hipLaunchKernelGGL((k_runs_count<E, PER>), dim3(g), dim3(kRunThreads), 0, s, D, bits, L.heads);
-  const hipError_t e = scan_exclusive_u32(L.heads, n_chunks, L.scan_sums, L.n_out, s);
+  const hipError_t e = scan_exclusive_u32(L.heads, n_chunks, L.scan_sums, L.n_out, s, L.end);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_runs_write<E, OP, PER>), dim3(g), dim3(kRunThreads), 0, s, D, bits, L.heads, L.out_keys, L.out_vals,
                      L.cap, L.lead);

@@ -244,3 +244,44 @@ def test_global_array_partitions_with_values(torch, n, R, share):
         assert r.stats["strategy_used"] == STRATS["global_array"]
         _check(r, keys, vals, op)
     _check(_run(torch, j, keys, None, "count", R), keys, None, "count")
+
+
+# the LDS array: one workgroup's elements and one more, 32 partial rows (added
+# by the output kernel) and 33 (by the reduce kernel); arrays of 1 to 32
+# copies, and the last sizes of the output kernel's 1, 4 and most keys per thread
+@pytest.mark.parametrize("n", [1, 4096, 4097, 32 * 4096, 32 * 4096 + 1])
+@pytest.mark.parametrize("R", [1, 2, 16, 1024, 1025, 4096, 4097, 5461])
+def test_lds_array_edges(torch, n, R):
+    rng = np.random.default_rng(n + R)
+    keys = rng.integers(0, R, n).astype(np.uint32)
+    keys[rng.random(n) < 0.5] = R - 1
+    vals = rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+    j = _job(STRATS["lds_array"])
+    for op in OPS:
+        if op == "sum" and R > 5460:
+            continue
+        r = _run(torch, j, keys, None if op == "count" else vals, op, R)
+        assert r.stats["strategy_used"] == STRATS["lds_array"]
+        _check(r, keys, None if op == "count" else vals, op)
+
+
+@pytest.mark.parametrize("op,R", [("count", 16_384), ("min", 8192), ("max", 8192), ("sum", 5460)])
+def test_lds_array_largest_ranges(torch, op, R):
+    keys, vals = gen.u32_keys(51, 300_000, R, 0.3, with_values=True)
+    r = _run(torch, _job(STRATS["lds_array"]), keys, None if op == "count" else vals, op, R)
+    _check(r, keys, None if op == "count" else vals, op)
+
+
+def test_states_after_rejected_and_short_calls(torch):
+    """A job clears its next state as it ends: calls that end in an error, or
+    whose outputs are too small, leave the next call's state clean."""
+    from paper_1309_0215_amd import Job, MRError
+    keys, vals = gen.u32_keys(61, 300_000, 3000, 0.5, with_values=True)
+    for strat in STRATS.values():
+        j = Job(device=0, strategy=strat)
+        for _ in range(3):
+            with pytest.raises(MRError):
+                _run(torch, j, keys, None, "count", 100)
+            _check(_run(torch, j, keys, vals, "sum", 3000), keys, vals, "sum")
+            kt = torch.from_numpy(keys.view(np.int32)).to("cuda:0")
+            _check(j.u32(kt, key_range=3000, cap_keys=5), keys, None, "count")  # retried at the size needed
