@@ -262,6 +262,14 @@ mr_status mr_workspace_bytes(const mr_job_config* cfg, mr_map_kind kind, uint64_
 mr_status mr_run(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_input, uint64_t input_bytes,
                  const uint64_t* d_record_offsets, uint64_t n_records, uint64_t key_range, mr_output* out);
 
+/* mr_run of MR_MAP_U32_KV with the n keys and the n values in two arrays
+ * instead of interleaved pairs (device pointers, uint32, read only): same
+ * outputs, workspace and errors, and no pass that interleaves them first.
+ * MR_ERR_UNSUPPORTED for a job created with MR_STRAT_LEARNED, whose features
+ * are computed from interleaved pairs. */
+mr_status mr_run_pairs(mr_job* job, mr_reduce_op op, const uint32_t* d_keys, const uint32_t* d_values, uint64_t n,
+                       uint64_t key_range, mr_output* out);
+
 /* RGB histogram (MR_MAP_RGB_HIST with MR_REDUCE_COUNT) for callers that
  * cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid allocation. Same result as mr_run: d_bins

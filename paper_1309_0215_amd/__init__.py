@@ -347,10 +347,16 @@ class Job:
     def u32(self, keys, values=None, op: int = L.REDUCE_COUNT, key_range: int = 0, cap_keys: int | None = None):
         """keys: int32 CUDA tensor (uint32 bit pattern); values likewise or None.
 
-        With values the input is interleaved (key, value) pairs, as mr_run expects."""
+        One-dimensional 32-bit keys and values go to mr_run_pairs as they are; others, and those of a job
+        with the learned selector, are interleaved to (key, value) pairs, as mr_run expects."""
         torch = self.torch
         dev = f"cuda:{self.device}"
-        if values is not None:
+        vals = None
+        if (values is not None and self.cfg.strategy != L.STRAT_LEARNED and keys.dim() == 1 and keys.is_cuda and
+                keys.element_size() == 4 and values.element_size() == 4 and values.shape == keys.shape and
+                values.device == keys.device):
+            data, vals = keys.view(torch.int32).contiguous(), values.view(torch.int32).contiguous()
+        elif values is not None:
             data = torch.stack([keys.view(torch.int32), values.view(torch.int32)], dim=1).contiguous()
             kind = L.MAP_U32_KV
         else:
@@ -365,7 +371,10 @@ class Job:
             v = torch.empty(max(cap_keys, 1), dtype=torch.int64 if wide else torch.int32, device=dev)
             o = L.Output()
             o.keys, o.values, o.cap_keys = k.data_ptr(), v.data_ptr(), cap_keys
-            st = self.lib.mr_run(self.h, kind, op, data.data_ptr(), data.numel() * 4, None, 0, key_range, C.byref(o))
+            if vals is not None:
+                st = self.lib.mr_run_pairs(self.h, op, data.data_ptr(), vals.data_ptr(), n, key_range, C.byref(o))
+            else:
+                st = self.lib.mr_run(self.h, kind, op, data.data_ptr(), data.numel() * 4, None, 0, key_range, C.byref(o))
             if st == L.MR_ERR_CAPACITY and o.n_keys > cap_keys:
                 cap_keys = int(o.n_keys)
                 continue

@@ -27,7 +27,7 @@ EXPORTS = [
     "mr_status_str", "mr_last_error", "mr_job_create", "mr_job_destroy", "mr_run", "mr_batch_run",
     "mr_job_features", "mr_selector_set", "mr_selector_predict", "mr_mlp_forward", "mr_mlp_loss_backward",
     "mr_mlp_adam", "mr_tune_set", "mr_rgb_hist_static", "mr_workspace_bytes", "mr_selector_load",
-    "mr_selector_train", "mr_hash_words",
+    "mr_selector_train", "mr_hash_words", "mr_run_pairs",
 ]
 
 
@@ -152,6 +152,8 @@ def load(required: bool = True):
     lib.mr_job_destroy.argtypes = [P]
     lib.mr_run.restype = I32
     lib.mr_run.argtypes = [P, C.c_int, C.c_int, P, U64, P, U64, U64, C.POINTER(Output)]
+    lib.mr_run_pairs.restype = I32
+    lib.mr_run_pairs.argtypes = [P, C.c_int, P, P, U64, U64, C.POINTER(Output)]
     lib.mr_batch_run.restype = I32
     lib.mr_batch_run.argtypes = [P, C.POINTER(BatchItem), U32, C.POINTER(Output)]
     lib.mr_tune_set.restype = I32

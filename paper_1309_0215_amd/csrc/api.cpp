@@ -1279,8 +1279,10 @@ struct U32Ctx {
   IntSmall* sm;        // this item's state (device)
 };
 
+// d_values: the values of MR_MAP_U32_KV in an array of their own (d_input then
+// holds the keys alone; bytes still counts 8 per pair), or NULL for interleaved pairs.
 mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_input, uint64_t bytes, uint64_t key_range,
-                  mr_output* out, const U32Ctx* ctx = nullptr) {
+                  mr_output* out, const U32Ctx* ctx = nullptr, const void* d_values = nullptr) {
   const uint32_t esz = kind == MR_MAP_U32_KV ? 8 : 4;
   if (bytes % esz) return fail(MR_ERR_INVALID_ARG, "input length %llu is not a multiple of %u", (unsigned long long)bytes, esz);
   if (kind == MR_MAP_U32_KEYS && op != MR_REDUCE_COUNT) return fail(MR_ERR_UNSUPPORTED, "plain keys support COUNT only");
@@ -1324,7 +1326,8 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
   IntLaunch L{};
   L.in = static_cast<const uint32_t*>(d_input);
   L.n = n;
-  L.kv = kind == MR_MAP_U32_KV;
+  L.stride = kind == MR_MAP_U32_KV && !d_values ? 2 : 1;
+  L.vals_in = kind != MR_MAP_U32_KV ? nullptr : d_values ? static_cast<const uint32_t*>(d_values) : L.in + 1;
   L.op = o;
   L.R = key_range;
   L.debug_hash = job->cfg.debug_hash;
@@ -1470,6 +1473,8 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
       }
       SortLaunch S{};
       S.in = reinterpret_cast<const uint32_t*>(L.pairs);
+      S.vals_in = S.in + 1;
+      S.stride = 2;
       S.n = nc;
       S.op = o;
       S.flags = L.flags;
@@ -1494,7 +1499,8 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
     SortLaunch S{};
     S.in = L.in;
     S.n = n;
-    S.kv = L.kv;
+    S.vals_in = L.vals_in;
+    S.stride = L.stride;
     S.op = o;
     S.R = key_range;
     S.bits = key_range ? bits_for(key_range) : 32;
@@ -1757,6 +1763,26 @@ extern "C" mr_status mr_run(mr_job* job, mr_map_kind kind, mr_reduce_op op, cons
     default:
       return fail(MR_ERR_INVALID_ARG, "unknown map kind %d", (int)kind);
   }
+  out->stats.device_allocs = job->call_allocs;
+  out->stats.workspace_needed = job->cws_need;
+  out->status = s;
+  return s;
+}
+
+extern "C" mr_status mr_run_pairs(mr_job* job, mr_reduce_op op, const uint32_t* d_keys, const uint32_t* d_values, uint64_t n,
+                                  uint64_t key_range, mr_output* out) {
+  if (!job || !out) return fail(MR_ERR_INVALID_ARG, "NULL job or output");
+  if (n && (!d_keys || !d_values)) return fail(MR_ERR_INVALID_ARG, "NULL input");
+  if ((uintptr_t)d_values % 4) return fail(MR_ERR_INVALID_ARG, "integer input must be 4-byte aligned");
+  if (n >= (1ull << 32)) return fail(MR_ERR_UNSUPPORTED, "integer inputs must have fewer than 2^32 elements");
+  if (job->cfg.strategy == MR_STRAT_LEARNED)
+    return fail(MR_ERR_UNSUPPORTED, "the selector's features are computed from interleaved pairs");
+  ScopedDevice sd(job->device);
+  out->stats = mr_stats{};
+  out->status = MR_OK;
+  arena_begin(job, kFamU32);
+  // (no values to read: the pointer only tells the layout)
+  const mr_status s = run_u32(job, MR_MAP_U32_KV, op, d_keys, 8 * n, key_range, out, nullptr, n ? d_values : d_keys);
   out->stats.device_allocs = job->call_allocs;
   out->stats.workspace_needed = job->cws_need;
   out->status = s;

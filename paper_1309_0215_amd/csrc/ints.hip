@@ -32,21 +32,20 @@ MR_DEV uint32_t dec_minmax(int op, uint32_t v) { return op == 2 ? ~v : v; }
 // ----------------------------------------------------------------------------
 // element access
 // ----------------------------------------------------------------------------
+// Element i: key p[i * stride], value v[i * stride] (v == NULL: every value is
+// 1). Interleaved pairs have stride 2 and v = p + 1.
 struct IntIn {
-  const uint32_t* p;  // keys, or interleaved (key, value) pairs
-  uint64_t n;         // elements
-  uint32_t kv;        // 1 when values are present
+  const uint32_t* p;
+  const uint32_t* v;
+  uint64_t n;
+  uint32_t stride;
 };
 
+static IntIn int_in(const IntLaunch& L) { return {L.in, L.vals_in, L.n, L.stride}; }
+
 MR_DEV void load_elem(const IntIn& in, uint64_t i, uint32_t& k, uint32_t& v) {
-  if (in.kv) {
-    const uint2 e = reinterpret_cast<const uint2*>(in.p)[i];
-    k = e.x;
-    v = e.y;
-  } else {
-    k = in.p[i];
-    v = 1u;
-  }
+  k = in.p[i * in.stride];
+  v = in.v ? in.v[i * in.stride] : 1u;
 }
 
 // ----------------------------------------------------------------------------
@@ -103,18 +102,19 @@ __global__ __launch_bounds__(kIntThreads) void k_lds_array(IntIn in, uint32_t R,
   unsigned long long* const sum = reinterpret_cast<unsigned long long*>(cnt + off);
   uint32_t* const mm = cnt + off;
   const uint64_t lo = in.n * blockIdx.x / G, hi = in.n * (blockIdx.x + 1) / G;
-  const uint32_t stride = in.kv ? 2u : 1u;
+  const uint32_t stride = in.stride;
   bool bad = false;
   constexpr uint32_t kBatch = 8;
   for (uint64_t i0 = lo + threadIdx.x; i0 < hi; i0 += kBatch * kIntThreads) {
     uint32_t k[kBatch], v[kBatch];
-    const MR_GLOBAL uint32_t* src = gp(in.p) + i0 * stride;
+    const MR_GLOBAL uint32_t* kp = gp(in.p) + i0 * stride;
+    const MR_GLOBAL uint32_t* vp = gp(in.v) + i0 * stride;
 #pragma unroll
     for (uint32_t u = 0; u < kBatch; ++u) {
       k[u] = v[u] = 0;
       if (i0 + u * kIntThreads < hi) {
-        k[u] = src[u * kIntThreads * stride];
-        if (OP != 0) v[u] = src[u * kIntThreads * stride + 1];
+        k[u] = kp[u * kIntThreads * stride];
+        if (OP != 0) v[u] = vp[u * kIntThreads * stride];
       }
     }
 #pragma unroll
@@ -369,11 +369,12 @@ __global__ __launch_bounds__(vp_threads(OP), OP == 0 ? 8 : 6) void k_vp_tile(Int
   for (uint32_t q = threadIdx.x; q <= P; q += kThreads) base[q] = 0;
   const uint64_t e0 = (uint64_t)t * kTile;
   uint32_t k[kVpPer], v[kVpPer];
-  const uint32_t stride = in.kv ? 2u : 1u;
-  const MR_GLOBAL uint32_t* src = gp(in.p) + e0 * stride;
+  const uint32_t stride = in.stride;
+  const MR_GLOBAL uint32_t* kp = gp(in.p) + e0 * stride;
+  const MR_GLOBAL uint32_t* vp = gp(in.v) + e0 * stride;
   const uint32_t left = in.n - e0 < kTile ? (uint32_t)(in.n - e0) : kTile;
   uint32_t n_mine = 0;  // this thread's elements: k[0, n_mine)
-  if (OP == 0 && !in.kv && left == kTile && ((uintptr_t)in.p & 15u) == 0) {  // whole 16-byte vectors
+  if (OP == 0 && stride == 1 && left == kTile && ((uintptr_t)in.p & 15u) == 0) {  // whole 16-byte vectors
     n_mine = kVpPer;
 #pragma unroll
     for (uint32_t u = 0; u < kVpPer / 4; ++u) {
@@ -391,8 +392,8 @@ __global__ __launch_bounds__(vp_threads(OP), OP == 0 ? 8 : 6) void k_vp_tile(Int
       v[u] = 0u;
       if (i < left) {
         ++n_mine;
-        k[u] = src[i * stride];
-        if (OP != 0) v[u] = src[i * stride + 1];
+        k[u] = kp[i * stride];
+        if (OP != 0) v[u] = vp[i * stride];
       }
     }
   }
@@ -951,7 +952,7 @@ __global__ __launch_bounds__(1024) void k_int_sample(IntIn in, IntPub* host) {
 #pragma unroll
   for (uint32_t u = 0; u < kPer; ++u) {
     const uint64_t q = u * 1024 + threadIdx.x;
-    k[u] = in.p[(q * in.n / kSampleSize) * (in.kv ? 2 : 1)];
+    k[u] = in.p[(q * in.n / kSampleSize) * in.stride];
   }
   __syncthreads();
   uint32_t mine = 0;
@@ -1147,7 +1148,7 @@ template <int OP>
 static hipError_t lds_enqueue(const IntLaunch& L, hipStream_t s) {
   const uint32_t R = (uint32_t)L.R;
   const uint32_t copies = lds_copies(R, OP);
-  hipLaunchKernelGGL(k_lds_array<OP>, dim3(L.G), dim3(kIntThreads), copies * lds_copy_words(R, OP, copies) * 4, s, IntIn{L.in, L.n, L.kv}, R, L.G, copies,
+  hipLaunchKernelGGL(k_lds_array<OP>, dim3(L.G), dim3(kIntThreads), copies * lds_copy_words(R, OP, copies) * 4, s, int_in(L), R, L.G, copies,
                      L.cnt_part, L.val_part, L.flags);
   const uint32_t* cnt = L.cnt_part;
   const void* val = L.val_part;
@@ -1185,7 +1186,7 @@ hipError_t int_enqueue_lds_array(const IntLaunch& L, hipStream_t s) {
 }
 
 hipError_t int_enqueue_global_array(const IntLaunch& L, hipStream_t s) {
-  const IntIn in{L.in, L.n, L.kv};
+  const IntIn in = int_in(L);
   const uint32_t g = blocks_for(L.n, 256, 8192);
   switch (L.op) {
     case 0: hipLaunchKernelGGL(k_global_array<0>, dim3(g), dim3(256), 0, s, in, L.R, L.dcnt, L.dval, L.flags); break;
@@ -1310,7 +1311,7 @@ static hipError_t vp_enqueue_fill(const IntLaunch& L, const VpPlan& p, const uin
 template <int OP>
 static hipError_t vp_enqueue(const IntLaunch& L, const VpPlan& p, uint32_t* runs, uint16_t* pk, uint32_t* pv, uint32_t* tot,
                              hipStream_t s) {
-  hipLaunchKernelGGL(k_vp_tile<OP>, dim3(p.n_tiles), dim3(vp_threads(OP)), (p.P + 1) * 4, s, IntIn{L.in, L.n, L.kv}, L.R, p.kb,
+  hipLaunchKernelGGL(k_vp_tile<OP>, dim3(p.n_tiles), dim3(vp_threads(OP)), (p.P + 1) * 4, s, int_in(L), L.R, p.kb,
                      p.P, runs, pk, pv, L.flags);
   hipLaunchKernelGGL(k_vp_totals, dim3((p.P + kWave - 1) / kWave, p.slices), dim3(kVpTotThreads), 0, s, runs, p.P, p.n_tiles,
                      tot);
@@ -1351,7 +1352,7 @@ hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, const VpPlan* v
 }
 
 hipError_t int_enqueue_hash_map(const IntLaunch& L, hipStream_t s) {
-  const IntIn in{L.in, L.n, L.kv};
+  const IntIn in = int_in(L);
   IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.max_probes, L.side_cnt, L.side_val, L.flags};
 #define HASH_CASE(OP) \
   case OP: hipLaunchKernelGGL((k_int_hash<OP, 12>), dim3(L.G), dim3(kIntThreads), 0, s, in, T, L.G, L.debug_hash, L.R); break;
@@ -1366,7 +1367,7 @@ hipError_t int_enqueue_hash_map(const IntLaunch& L, hipStream_t s) {
 }
 
 hipError_t int_enqueue_sample(const IntLaunch& L, IntPub* host, hipStream_t s) {
-  hipLaunchKernelGGL(k_int_sample, dim3(1), dim3(1024), 0, s, IntIn{L.in, L.n, L.kv}, host);
+  hipLaunchKernelGGL(k_int_sample, dim3(1), dim3(1024), 0, s, int_in(L), host);
   return hipGetLastError();
 }
 

@@ -100,9 +100,10 @@ struct IntEnd {
 
 // Integer-key jobs: one launch description shared by the four containers.
 struct IntLaunch {
-  const uint32_t* in;
+  const uint32_t* in;   // keys
+  const uint32_t* vals_in;  // values (NULL: keys alone, every value 1)
+  uint32_t stride;      // words from one key, and one value, to the next
   uint64_t n;           // elements
-  uint32_t kv;          // 1 = interleaved (key, value) pairs
   uint32_t op;          // 0 COUNT, 1 SUM, 2 MIN, 3 MAX
   uint64_t R;           // declared key range (0 = none)
   uint32_t G;           // workgroups of the map kernels
@@ -147,7 +148,8 @@ RadixPlan radix_plan(uint64_t n);
 struct SortLaunch {
   const uint32_t* in;
   uint64_t n;              // elements, below 2^32
-  uint32_t kv, op;         // as in IntLaunch
+  const uint32_t* vals_in;   // as in IntLaunch
+  uint32_t stride, op;
   uint64_t R;              // declared key range (0 = none)
   uint32_t bits;           // key bits that can differ
   uint32_t* flags;

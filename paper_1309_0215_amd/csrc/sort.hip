@@ -42,8 +42,10 @@ MR_DEV bool rs_skip(uint64_t diff, uint32_t shift) { return shift && !((diff >> 
 // Where the data of a pass is: the input, or one of the two buffers.
 template <typename E>
 struct RsData {
-  const void* in;     // first pass: elements, or (stride 2) the keys of interleaved pairs
-  uint32_t stride;    // in units of the key, for E = uint32_t
+  // first pass: uint64 elements; or uint32 keys, and for pairs values, `stride` words apart
+  const void* in;
+  const uint32_t* vals;
+  uint32_t stride;
   uint64_t n;
   E *a, *b;
   unsigned long long* diff;  // differing key bits (first pass writes, later ones read)
@@ -59,8 +61,7 @@ MR_DEV uint32_t rs_in<uint32_t>(const RsData<uint32_t>& D, uint64_t i) {
 }
 template <>
 MR_DEV uint2 rs_in<uint2>(const RsData<uint2>& D, uint64_t i) {
-  const MR_GLOBAL uint32_t* p = gp(reinterpret_cast<const uint32_t*>(D.in)) + 2 * i;  // (4-byte aligned input)
-  return make_uint2(p[0], p[1]);
+  return make_uint2(gp(reinterpret_cast<const uint32_t*>(D.in))[i * D.stride], gp(D.vals)[i * D.stride]);
 }
 
 template <typename E>
@@ -556,11 +557,11 @@ hipError_t int_enqueue_sort(const SortLaunch& L, hipStream_t s) {
   if (!L.n) return hipSuccess;
   const uint32_t bits = whole_digits(L.bits);
   if (L.op == 0) {  // the keys alone
-    const RsData<uint32_t> D{L.in, L.kv ? 2u : 1u, L.n, static_cast<uint32_t*>(L.buf0), static_cast<uint32_t*>(L.buf1), L.diff};
+    const RsData<uint32_t> D{L.in, nullptr, L.stride, L.n, static_cast<uint32_t*>(L.buf0), static_cast<uint32_t*>(L.buf1), L.diff};
     const hipError_t e = rs_sort(D, bits, L.hist, L.tot, L.R, L.flags, s);
     return e != hipSuccess ? e : rs_reduce<uint32_t, 0>(D, bits, L, s);
   }
-  const RsData<uint2> D{L.in, 1u, L.n, static_cast<uint2*>(L.buf0), static_cast<uint2*>(L.buf1), L.diff};
+  const RsData<uint2> D{L.in, L.vals_in, L.stride, L.n, static_cast<uint2*>(L.buf0), static_cast<uint2*>(L.buf1), L.diff};
   const hipError_t e = rs_sort(D, bits, L.hist, L.tot, L.R, L.flags, s);
   if (e != hipSuccess) return e;
   switch (L.op) {
@@ -586,7 +587,7 @@ __global__ __launch_bounds__(256) void k_pairs_out(RsData<uint2> D, uint32_t bit
 
 hipError_t pairs_enqueue_out(const SortLaunch& L, const unsigned long long* vals, hipStream_t s) {
   if (!L.n) return hipSuccess;
-  const RsData<uint2> D{L.in, 1u, L.n, static_cast<uint2*>(L.buf0), static_cast<uint2*>(L.buf1), L.diff};
+  const RsData<uint2> D{L.in, L.vals_in, L.stride, L.n, static_cast<uint2*>(L.buf0), static_cast<uint2*>(L.buf1), L.diff};
   const hipError_t e = rs_sort(D, 32, L.hist, L.tot, 0, L.flags, s);
   if (e != hipSuccess) return e;
   const uint64_t g = (L.n + 255) / 256;
@@ -597,7 +598,7 @@ hipError_t pairs_enqueue_out(const SortLaunch& L, const unsigned long long* vals
 
 hipError_t keys64_enqueue_sort(const Keys64Sort& L, hipStream_t s) {
   if (!L.n) return hipSuccess;
-  const RsData<unsigned long long> D{L.in, 1u, L.n, L.buf0, L.buf1, L.diff};
+  const RsData<unsigned long long> D{L.in, nullptr, 1u, L.n, L.buf0, L.buf1, L.diff};
   return rs_sort(D, whole_digits(L.bits), L.hist, L.tot, 0, nullptr, s);
 }
 

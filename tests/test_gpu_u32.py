@@ -285,3 +285,52 @@ def test_states_after_rejected_and_short_calls(torch):
             _check(_run(torch, j, keys, vals, "sum", 3000), keys, vals, "sum")
             kt = torch.from_numpy(keys.view(np.int32)).to("cuda:0")
             _check(j.u32(kt, key_range=3000, cap_keys=5), keys, None, "count")  # retried at the size needed
+
+
+@pytest.mark.parametrize("strat", list(STRATS))
+def test_separate_and_interleaved_pairs_agree(torch, strat):
+    """mr_run_pairs (keys and values in two arrays, 4 bytes past a 16-byte
+    boundary) against mr_run on interleaved pairs and the oracle; the binding
+    interleaves what is not one-dimensional, and strided input."""
+    import ctypes as C
+    from paper_1309_0215_amd import _lib as L
+    R = 3000
+    keys, vals = gen.u32_keys(71, 300_002, R, 0.8, with_values=True)
+    kt, vt = (torch.from_numpy(x.view(np.int32)).to("cuda:0") for x in (keys, vals))
+    j = _job(STRATS[strat])
+    inter = torch.stack([kt, vt], dim=1).contiguous()
+    for op in OPS:
+        r = j.u32(kt[1:], vt[1:], op=OPS[op], key_range=R)
+        _check(r, keys[1:], vals[1:], op)
+        ko = torch.empty(R, dtype=torch.int32, device="cuda:0")
+        vo = torch.empty(R, dtype=torch.int64 if op == "sum" else torch.int32, device="cuda:0")
+        o = L.Output()
+        o.keys, o.values, o.cap_keys = ko.data_ptr(), vo.data_ptr(), R
+        L.check(j.lib.mr_run(j.h, L.MAP_U32_KV, OPS[op], inter.data_ptr(), inter.numel() * 4, None, 0, R, C.byref(o)))
+        nk = int(o.n_keys)
+        _check(type(r)(ko[:nk], vo[:nk], {}), keys, vals, op)
+    _check(j.u32(kt[::2], vt[::2], op=OPS["sum"], key_range=R), keys[::2], vals[::2], "sum")
+    half = len(keys) // 2
+    a = j.u32(kt.view(half, 2), vt.view(half, 2), op=OPS["max"], key_range=1 << 32 if strat in ("hash", "sort") else 0) \
+        if strat in ("hash", "sort") else None
+    if a is not None:  # stacked along dim 1: (k0, k1), (v0, v1) per row
+        two = np.stack([keys.reshape(half, 2), vals.reshape(half, 2)], axis=1).reshape(-1, 2)
+        _check(a, np.ascontiguousarray(two[:, 0]), np.ascontiguousarray(two[:, 1]), "max")
+
+
+def test_pairs_entry_rejects_what_mr_run_rejects(torch):
+    import ctypes as C
+    from paper_1309_0215_amd import Job, _lib as L
+    j = _job(STRATS["sort"])
+    k = torch.zeros(16, dtype=torch.int32, device="cuda:0")
+    o = L.Output()
+    o.keys, o.values, o.cap_keys = k.data_ptr(), k.data_ptr(), 16
+    run = j.lib.mr_run_pairs
+    assert run(None, 1, k.data_ptr(), k.data_ptr(), 4, 0, C.byref(o)) == L.MR_ERR_INVALID_ARG
+    assert run(j.h, 1, None, k.data_ptr(), 4, 0, C.byref(o)) == L.MR_ERR_INVALID_ARG
+    assert run(j.h, 1, k.data_ptr() + 2, k.data_ptr(), 4, 0, C.byref(o)) == L.MR_ERR_INVALID_ARG
+    assert run(j.h, 1, k.data_ptr(), k.data_ptr() + 1, 4, 0, C.byref(o)) == L.MR_ERR_INVALID_ARG
+    assert run(j.h, 9, k.data_ptr(), k.data_ptr(), 4, 0, C.byref(o)) == L.MR_ERR_INVALID_ARG
+    assert run(j.h, 1, k.data_ptr(), k.data_ptr(), 1 << 32, 0, C.byref(o)) == L.MR_ERR_UNSUPPORTED
+    assert run(Job(device=0, strategy=1).h, 1, k.data_ptr(), k.data_ptr(), 4, 0, C.byref(o)) == L.MR_ERR_UNSUPPORTED
+    assert run(j.h, 1, None, None, 0, 0, C.byref(o)) == L.MR_OK and o.n_keys == 0
