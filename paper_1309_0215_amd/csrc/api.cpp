@@ -1661,17 +1661,15 @@ mr_status run_kmeans(mr_job* job, const void* d_input, uint64_t bytes, mr_output
   return MR_OK;
 }
 
-// Bloom filter scratch: per (range, tile) counts, their scan, the total, the positions.
+// Bloom filter scratch: each tile's row of sub-range starts, the tiles' positions.
 struct BloomCarve {
-  uint64_t o_hist, o_sums, o_tot, o_part, bytes;
+  uint64_t o_rows, o_part, bytes;
 };
 BloomCarve bloom_carve(const BloomPlan& b) {
   BloomCarve r;
   Carve c;
-  r.o_hist = c.take(4ull * std::max<uint64_t>(b.H, 1));
-  r.o_sums = c.take(4ull * scan_sums_count(b.H));
-  r.o_tot = c.take(8);
-  r.o_part = c.take(4ull * b.part_words);
+  r.o_rows = c.take(bloom_row_bytes(b));
+  r.o_part = c.take(bloom_part_bytes(b));
   r.bytes = c.off;
   return r;
 }
@@ -1691,16 +1689,14 @@ mr_status run_bloom(mr_job* job, mr_reduce_op op, const void* d_input, uint64_t 
   if (out->cap_keys < b.n_words)
     return fail(MR_ERR_CAPACITY, "the Bloom filter needs %llu words", (unsigned long long)b.n_words);
   const BloomCarve bc = bloom_carve(b);
-  const uint64_t o_hist = bc.o_hist, o_sums = bc.o_sums, o_tot = bc.o_tot, o_part = bc.o_part;
   mr_status st = ensure_ws(job, bc.bytes);
   if (st != MR_OK) return st;
   job->table_clean_bytes = 0;  // this scratch overwrites the word table region
   job->graph_valid = false;
   uint8_t* ws = job->ws;
   MR_HIP(hipEventRecord(job->ev0, job->stream));
-  MR_HIP(bloom_enqueue(static_cast<const uint8_t*>(d_input), bytes, k, h, m, b, reinterpret_cast<uint32_t*>(ws + o_hist),
-                       reinterpret_cast<uint32_t*>(ws + o_sums), reinterpret_cast<unsigned long long*>(ws + o_tot),
-                       reinterpret_cast<uint32_t*>(ws + o_part), static_cast<uint32_t*>(out->values), job->stream));
+  MR_HIP(bloom_enqueue(static_cast<const uint8_t*>(d_input), bytes, k, h, m, b, reinterpret_cast<uint32_t*>(ws + bc.o_rows),
+                       reinterpret_cast<uint16_t*>(ws + bc.o_part), static_cast<uint32_t*>(out->values), job->stream));
   MR_HIP(hipEventRecord(job->ev1, job->stream));
   MR_HIP(hipStreamSynchronize(job->stream));
   float ms = 0.f;

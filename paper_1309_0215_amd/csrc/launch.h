@@ -195,17 +195,20 @@ uint64_t scan_sums_count(uint64_t n);
 struct BloomPlan {
   uint64_t n_kmers;      // k-mers of the input
   uint64_t n_words;      // uint32 words of the m-bit filter
-  uint32_t P;            // position ranges of 2^18 bits
-  uint32_t n_tiles;      // tiles of the count and scatter passes
-  uint64_t H;            // P * n_tiles range counts
   uint64_t max_entries;  // positions emitted at most (n_kmers * h)
-  uint64_t part_words;   // uint32 words of the position buffer
-  bool ok;               // parameters and sizes within the kernels' limits
+  // 0 tiles: few positions, set by device atomics
+  uint32_t n_tiles, cap;  // tiles, positions a tile holds at most
+  uint32_t sb, S;         // bits of a sub-range's size, sub-ranges
+  uint32_t per, grid;     // sub-ranges per range, ranges
+  uint32_t row_words;     // words of a tile's row of sub-range starts (16-bit)
+  uint32_t lpg;           // lanes that take a tile's run of a range together
+  bool ok;                // parameters and sizes within the kernels' limits
 };
 BloomPlan bloom_plan(uint64_t n_bytes, uint32_t k, uint32_t h, uint64_t m);
+uint64_t bloom_row_bytes(const BloomPlan& b);
+uint64_t bloom_part_bytes(const BloomPlan& b);
 hipError_t bloom_enqueue(const uint8_t* in, uint64_t n_bytes, uint32_t k, uint32_t h, uint64_t m, const BloomPlan& b,
-                         uint32_t* hist, uint32_t* scan_sums, unsigned long long* total, uint32_t* part, uint32_t* words,
-                         hipStream_t s);
+                         uint32_t* rows, uint16_t* part, uint32_t* words, hipStream_t s);
 hipError_t int_enqueue_global_array(const IntLaunch& L, hipStream_t s);
 // global array filled by key-range partitions, for a range and element count the plan finds usable
 // Fewer elements take atomics on the array: 131,072 uniform pairs over 20,000

@@ -105,3 +105,32 @@ def test_capacity_is_reported(torch):
     o.values, o.cap_keys = w.data_ptr(), 10
     st = job.lib.mr_run(job.h, L.MAP_BLOOM, L.REDUCE_COUNT, d.data_ptr(), 1000, None, 0, 1000, C.byref(o))
     assert st == L.MR_ERR_CAPACITY and o.n_keys == 32
+
+
+# positions below and at the 2^14 where tiles begin; one k-mer over a whole
+# tile; each tile shape (8, 4 and 2 batches, one batch); sub-ranges of 32 bits
+# (three of them) to 2^16 bits, one to nine per range, two rounds of ranges; an
+# input that is not 4-byte aligned; bytes that are no bases in every word
+@pytest.mark.parametrize("n,m,k,h,n_rate,shift", [
+    ((1 << 14) - 1, 5_000_011, 1, 1, 0, 0),
+    (1 << 14, 5_000_011, 1, 1, 0, 1),
+    ((1 << 14) + 3, 1 << 29, 4, 1, 0, 0),
+    (32768 * 9 + 1, 70_001, 16, 1, 1e-3, 2),
+    (131072 + 8, 77, 9, 2, 1e-2, 0),
+    (16384 * 11 + 30, 40_000, 31, 2, 1e-3, 3),
+    (150_001, 1 << 24, 20, 3, 0.03, 1),
+    (100_003, (1 << 26) + 1, 32, 4, 1e-3, 0),
+    (70_000, (1 << 28) - 31, 11, 5, 1e-3, 0),
+    (4096 * 17 + 24, 320_000_000, 25, 6, 0.2, 2),
+    (4096 * 12 + 19, 1 << 29, 20, 8, 1e-3, 0),
+])
+def test_tiles_and_ranges_at_their_edges(torch, n, m, k, h, n_rate, shift):
+    from paper_1309_0215_amd import Job
+    s = np.ascontiguousarray(gen.dna(n % 1000 + k, n + shift, n_rate=n_rate), np.uint8)
+    d = torch.from_numpy(s).to("cuda:0")[shift:]
+    ew, _ = oracle.bloom(s[shift:], m, k, h)
+    job = Job(device=0, bloom_k=k, bloom_hashes=h)
+    for _ in range(2):  # the second call finds the first one's scratch
+        words, st = job.bloom(d, m)
+        assert np.array_equal(words.cpu().numpy().view(np.uint32), ew)
+        assert st["n_items"] == n - k + 1
