@@ -814,22 +814,31 @@ __global__ __launch_bounds__(kMapThreads) void k_words_map(const WordJob* __rest
 // records of its flush queue and of every map workgroup's miss sub-queue by
 // (job, key) in an LDS table and inserts each summed key into its job's table,
 // so that the keys every workgroup meets no longer meet on one global slot
-// from every workgroup. The records are taken in rounds of one per thread
-// (the next round's record is loaded meanwhile); after a round that leaves
-// the table more than half full, the table is flushed into the global tables
-// (one insert per summed key, all threads at once) and cleared, so records
-// never fall back to one global insert each. A round adds at most blockDim
-// keys, which keeps the table below three quarters full.
+// from every workgroup. The records are taken in rounds of kPartUnroll per
+// thread (the next round's records are loaded meanwhile). Most find their key
+// in its home group, by straight-line code; the others take the full insert.
+// When as many claims as since the last look at the fill would leave the table
+// more than three quarters full, it is flushed into the global tables (one
+// insert per summed key, all threads at once) and cleared, so that few records
+// meet a full group and fall back to a global insert each. The looks, which
+// take two barriers, are up to eight rounds apart while few keys are new.
+// Bound by the chain of LDS reads of a round on the one workgroup that the
+// table leaves room for on a CU: 17 M records over 50,000 keys (512 MiB of
+// text) 129 us; one record a round by the full insert, a look after each and a
+// search of all segments for each record 210 us; four records a round 137 us
+// (the registers spill).
 constexpr uint32_t kMaxMapGrid = 1024;  // map workgroups (miss sub-queues per partition)
+constexpr uint32_t kPartUnroll = 2;     // records per thread and round
+constexpr uint32_t kPartHints = 2048;   // blocks of records whose first segment is kept
 template <int L>
 __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __restrict__ jobs, uint32_t debug_hash) {
   constexpr uint32_t kSlots = LdsTable<L>::kSlots;
-  static_assert(kSlots / 2 + kMapThreads <= kSlots / 4 * 3, "a round cannot fill the table");
   __shared__ LdsTable<L> T;
   __shared__ uint32_t s_job[kSlots];
   // first record of each segment: map workgroup w's 32-byte sub-queue (w),
   // then its 16-byte one (G + w)
   __shared__ uint32_t s_pre[2 * kMaxMapGrid + 1];
+  __shared__ uint16_t s_hint[kPartHints + 1];
   __shared__ uint32_t s_used;
   const WordJob& Q = jobs[0];  // the queues (shared by the jobs of a batch)
   const uint32_t p = blockIdx.x;
@@ -858,37 +867,39 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
   if (threadIdx.x == 0) s_pre[NS] = carry;
   __syncthreads();
   const uint32_t total = carry;
-  // record r of the partition: the last segment starting at or before it.
-  // A thread's records only move forward, so the search gallops on from its
-  // previous segment (steps 1, 2, 4, ...) and then bisects.
-  // record r of the partition: the last segment starting at or before it.
-  // A thread's records only move forward, so the search gallops on from its
-  // previous segment (steps 1, 2, 4, ...) and then bisects. The record's two
-  // 16-byte halves are loaded (the second is zero for a 16-byte record; the
-  // caller decodes by `wide`).
-  uint32_t seg = 0;
-  auto load_rec = [&](uint32_t r, uint4& a, uint4& b, bool& wide) {
-    uint32_t lo = seg, hi = seg + 1, step = 1;  // s_pre[lo] <= r < total = s_pre[NS]
-    while (hi < NS && s_pre[hi] <= r) {
-      lo = hi;
-      step <<= 1;
-      hi = lo + step;
-    }
-    if (hi > NS) hi = NS;
+  // the segment of the first record of every block of 2^hb records
+  uint32_t hb = 6;
+  while ((total >> hb) >= kPartHints) ++hb;
+  const uint32_t n_hints = total ? ((total - 1) >> hb) + 1 : 0;
+  for (uint32_t i = threadIdx.x; i < n_hints; i += blockDim.x) {
+    const uint32_t r = i << hb;
+    uint32_t lo = 0, hi = NS;
     while (hi - lo > 1) {
       const uint32_t mid = (lo + hi) >> 1;
       if (s_pre[mid] <= r) lo = mid; else hi = mid;
     }
-    seg = lo;
-    const uint32_t e = r - s_pre[seg];
-    wide = seg < G;
+    s_hint[i] = (uint16_t)lo;
+  }
+  if (threadIdx.x == 0) s_hint[n_hints] = (uint16_t)(NS - 1);
+  __syncthreads();
+  // Record r of the partition, in the last segment starting at or before it.
+  // Its two 16-byte halves are loaded (the second is zero for a 16-byte
+  // record; the caller decodes by `wide`).
+  auto load_rec = [&](uint32_t r, uint4& a, uint4& b, bool& wide) {
+    uint32_t lo = s_hint[r >> hb], hi = (uint32_t)s_hint[(r >> hb) + 1] + 1;
+    while (hi - lo > 1) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (s_pre[mid] <= r) lo = mid; else hi = mid;
+    }
+    const uint32_t e = r - s_pre[lo];
+    wide = lo < G;
+    b = make_uint4(0, 0, 0, 0);
     if (wide) {
-      const FlushRec* rp = reinterpret_cast<const FlushRec*>(Q.mq) + ((uint64_t)p * G + seg) * Q.mq_cap + e;
+      const FlushRec* rp = reinterpret_cast<const FlushRec*>(Q.mq) + ((uint64_t)p * G + lo) * Q.mq_cap + e;
       a = gload16(&rp->k);
       b = gload16(&rp->off);
     } else {
-      a = gload16(reinterpret_cast<const uint4*>(Q.sq) + ((uint64_t)p * G + (seg - G)) * Q.sq_cap + e);
-      b = make_uint4(0, 0, 0, 0);
+      a = gload16(reinterpret_cast<const uint4*>(Q.sq) + ((uint64_t)p * G + (lo - G)) * Q.sq_cap + e);
     }
   };
   // a summed key into its job's table: with the table split into partition
@@ -897,10 +908,8 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
     if (J.region_log2) g_insert<true, true>(J, 0, 0, off, len, h, k, v, debug_hash);
     else g_insert<true>(J, 0, 0, off, len, h, k, v, debug_hash);
   };
-  auto consume = [&](uint4 k, uint4 m) -> bool {  // m: off, len, count, job; true: claimed a slot
-    const uint32_t hk = lds_hash32(k, m.y, debug_hash);
-    // the LDS placement mixes in the job; the global table takes the key's own hash
-    const uint32_t h32 = hk ^ (m.w * 0x9E3779B1u);
+  // the full insert, for a record whose key its home group does not show; true: claimed a slot
+  auto consume = [&](uint32_t hk, uint32_t h32, uint4 k, uint4 m) -> bool {  // m: off, len, count, job
     const uint32_t tg = (h32 & 0xFFFFFFC0u) | (m.y << 1);
     int r = 1;
     for (uint32_t spin = 0; r == 1; ++spin) {
@@ -926,27 +935,93 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
       T.tag[i] = 0u;
     }
   };
-  uint4 na = make_uint4(0, 0, 0, 0), nb = make_uint4(0, 0, 0, 0);
-  bool nwide = true;
-  if (threadIdx.x < total) load_rec(threadIdx.x, na, nb, nwide);
-  for (uint32_t base = 0; base < total; base += blockDim.x) {
-    const bool have = base + threadIdx.x < total;
-    // this round's record as (key, {offset, length, count, job})
-    const uint4 k = nwide ? na : make_uint4(na.x, na.y, 0u, 0u);
-    const uint4 m = nwide ? nb : make_uint4(na.z, na.w & 15u, (na.w >> 4) & 0xFFFu, na.w >> 16);
-    const uint32_t nx = base + blockDim.x + threadIdx.x;
-    if (nx < total) load_rec(nx, na, nb, nwide);
-    const bool claimed = have && consume(k, m);
-    // the round's claims, one LDS add per wave
-    const uint32_t nc = popc64(__ballot(claimed));
-    if (lane == 0 && nc) atomicAdd(&s_used, nc);
+  uint4 na[kPartUnroll], nb[kPartUnroll];
+  bool nwide[kPartUnroll];
+  auto load_round = [&](uint32_t base) {
+#pragma unroll
+    for (uint32_t u = 0; u < kPartUnroll; ++u) {
+      const uint32_t r = base + u * kMapThreads + threadIdx.x;
+      na[u] = nb[u] = make_uint4(0, 0, 0, 0);
+      nwide[u] = true;
+      if (r < total) load_rec(r, na[u], nb[u], nwide[u]);
+    }
+  };
+  load_round(0);
+  uint32_t rounds = 0, period = 1, before = 0;  // since the last look at the fill; rounds between looks; the fill then
+  for (uint32_t base = 0; base < total; base += kPartUnroll * kMapThreads) {
+    // this round's records as (key, {offset, length, count, job})
+    uint4 k[kPartUnroll], m[kPartUnroll];
+    bool have[kPartUnroll];
+#pragma unroll
+    for (uint32_t u = 0; u < kPartUnroll; ++u) {
+      have[u] = base + u * kMapThreads + threadIdx.x < total;
+      k[u] = nwide[u] ? na[u] : make_uint4(na[u].x, na[u].y, 0u, 0u);
+      m[u] = nwide[u] ? nb[u] : make_uint4(na[u].z, na[u].w & 15u, (na[u].w >> 4) & 0xFFFu, na[u].w >> 16);
+    }
+    load_round(base + kPartUnroll * kMapThreads);
+    // Home group: one 16-byte tag read, then the key and job of the slot whose
+    // ready tag matches (read whether or not one does). Straight-line code, so
+    // that the LDS reads of one record overlap those of the others.
+    constexpr uint32_t kGroupMask = kSlots / 4 - 1;
+    uint32_t hk[kPartUnroll], h32[kPartUnroll], slot[kPartUnroll];
+    uint4 t4[kPartUnroll];
+    bool hit[kPartUnroll];
+#pragma unroll
+    for (uint32_t u = 0; u < kPartUnroll; ++u) {
+      hk[u] = lds_hash32(k[u], m[u].y, debug_hash);
+      // the LDS placement mixes in the job; the global table takes the key's own hash
+      h32[u] = hk[u] ^ (m[u].w * 0x9E3779B1u);
+      t4[u] = reinterpret_cast<const uint4*>(T.tag)[h32[u] & kGroupMask];
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kPartUnroll; ++u) {
+      const uint32_t tq = (h32[u] & 0xFFFFFFC0u) | (m[u].y << 1) | 1u;
+      const uint32_t c3 = t4[u].w == tq ? 3u : 4u;
+      const uint32_t c2 = t4[u].z == tq ? 2u : c3;
+      const uint32_t c1 = t4[u].y == tq ? 1u : c2;
+      const uint32_t c = t4[u].x == tq ? 0u : c1;
+      hit[u] = have[u] & (c < 4u);
+      slot[u] = 4u * (h32[u] & kGroupMask) + (c & 3u);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");  // key bytes and jobs after the ready tags
+    uint4 kk[kPartUnroll];
+    uint32_t kj[kPartUnroll];
+#pragma unroll
+    for (uint32_t u = 0; u < kPartUnroll; ++u) {
+      kk[u] = T.key[slot[u]];
+      kj[u] = s_job[slot[u]];
+    }
+    uint32_t nc = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < kPartUnroll; ++u) {
+      hit[u] &= (key_diff(kk[u], k[u]) | (kj[u] ^ m[u].w)) == 0u;
+      if (hit[u]) atomicAdd(&T.cnt[slot[u]], m[u].z);
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kPartUnroll; ++u) {
+      const bool todo = have[u] & !hit[u];
+      if (__ballot(todo)) {
+        bool claimed = false;
+        if (todo) claimed = consume(hk[u], h32[u], k[u], m[u]);
+        nc += popc64(__ballot(claimed));
+      }
+    }
+    if (lane == 0 && nc) atomicAdd(&s_used, nc);  // the round's claims, one LDS add per wave
+    if (++rounds < period) continue;              // (the same in every wave)
     __syncthreads();
-    const bool full = s_used > kSlots / 2;  // uniform: read after the barrier
+    const uint32_t used = s_used, claims = used - before;
     __syncthreads();
-    if (full) {
+    rounds = 0;
+    // as many claims again would leave the table more than three quarters full
+    if (used + claims > kSlots / 4 * 3) {
       flush();
       if (threadIdx.x == 0) s_used = 0;
       __syncthreads();
+      before = 0;
+      period = 1;
+    } else {
+      before = used;
+      period = claims > kSlots / 16 ? 1u : period < 8 ? 2 * period : period;
     }
   }
   __syncthreads();
