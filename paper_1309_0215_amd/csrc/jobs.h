@@ -15,6 +15,8 @@ enum : uint32_t {
 };
 
 
+constexpr uint32_t kMaxWordParts = 256;  // partitions of the two-phase reduce (the top 8 hash bits)
+
 // Per-job state the kernels update in device memory. Zeroed by the host
 // before each run (one memset of the whole state array).
 struct JobState {
@@ -22,13 +24,18 @@ struct JobState {
   uint64_t valid_hi;               // one past the last input byte inside a record
   unsigned long long n_recs;       // distinct keys found by the compaction
   unsigned long long key_bytes;    // total output key bytes (words)
-  unsigned long long claims;       // table slots claimed by the map
+  unsigned long long table_recs;   // records the compaction has taken from the table, after the staged ones
   uint32_t flags;                  // kFlag* bits
   uint32_t nb;                     // sort buckets
   uint32_t bucket_base;            // first global bucket of this job
   uint32_t rtile_base;             // first record tile of this job
   uint32_t sort_spills;            // sort buckets too large for LDS (sorted in global memory)
   uint32_t pad;
+  // Jobs with partition queues: a bit per partition whose keys the table holds
+  // any of, and per partition with a key of up to 16 bytes there from the map
+  // (the partition's sums then have to meet it in the table).
+  uint32_t in_table[kMaxWordParts / 32];
+  uint32_t in_table_map[kMaxWordParts / 32];
 };
 
 static_assert(sizeof(JobState) % 8 == 0, "JobState is cleared as 32-bit words");
@@ -82,8 +89,6 @@ struct WordJob {
   // kernel only partition p's workgroup writes region p
   uint32_t region_log2;
 };
-
-constexpr uint32_t kMaxWordParts = 256;  // partitions of the two-phase reduce (the top 8 hash bits)
 
 // Compacted table entry of a word, ordered by (p, len) then tail bytes.
 struct WRec {

@@ -32,6 +32,8 @@
 #include "jobs.h"
 #include "launch.h"
 
+#include <algorithm>
+
 namespace mr {
 
 // ----------------------------------------------------------------------------
@@ -265,6 +267,15 @@ MR_DEV bool g_insert(const WordJob& J, uint64_t vlo, uint64_t vhi, uint64_t off,
   return false;
 }
 
+// Sets the bit of the partition of hash h in one of the job's partition maps;
+// a read first, since an atomic on one word from many workgroups is slow.
+MR_DEV void mark_part(const WordJob& J, uint32_t* map, uint64_t h) {
+  if (!J.mq) return;
+  const uint32_t p = (uint32_t)(h >> J.part_shift), bit = 1u << (p & 31u);
+  if (!(__hip_atomic_load(gp(&map[p >> 5]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit))
+    __hip_atomic_fetch_or(gp(&map[p >> 5]), bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ----------------------------------------------------------------------------
 // prep: validate record offsets and publish the valid byte range
 // ----------------------------------------------------------------------------
@@ -441,8 +452,11 @@ MR_DEV void lds_flush_parts(LdsTable<L>& T, const WordJob& J, uint32_t job, uint
       const uint32_t len = (tg >> 1) & 31u;
       const uint4 k = T.key[i];
       const uint64_t h = key_hash16(k, len, debug_hash);
-      if (!queue_append(J, mfill, sfill, (uint32_t)(h >> J.part_shift), k, T.off[i], len, T.cnt[i], job))
+      if (!queue_append(J, mfill, sfill, (uint32_t)(h >> J.part_shift), k, T.off[i], len, T.cnt[i], job)) {
+        mark_part(J, J.st->in_table, h);
+        mark_part(J, J.st->in_table_map, h);
         g_insert<true>(J, vlo, vhi, T.off[i], len, h, k, T.cnt[i], debug_hash);
+      }
     }
     T.tag[i] = 0u;
   }
@@ -681,13 +695,16 @@ __global__ __launch_bounds__(kMapThreads) void k_words_map(const WordJob* __rest
       auto miss = [&](bool lng, uint32_t off, uint32_t len, uint32_t h, uint4 k, uint32_t v) {
         if (lng) {
           const uint64_t wlen = word_length_slow(J, vlo, vhi, off);
-          g_insert<false>(J, vlo, vhi, off, wlen, key_hash_global(J.in, off, wlen, debug_hash), make_uint4(0, 0, 0, 0),
-                          1u, debug_hash);
+          const uint64_t wh = key_hash_global(J.in, off, wlen, debug_hash);
+          mark_part(J, J.st->in_table, wh);
+          g_insert<false>(J, vlo, vhi, off, wlen, wh, make_uint4(0, 0, 0, 0), 1u, debug_hash);
           return;
         }
         const uint64_t h64 = hash_from32(h);
         // into this workgroup's sub-queue of the key's partition
         if (J.mq && queue_append(J, s_mfill, s_sfill, (uint32_t)(h64 >> J.part_shift), k, off, len, v, j)) return;
+        mark_part(J, J.st->in_table, h64);
+        mark_part(J, J.st->in_table_map, h64);
         g_insert<true>(J, vlo, vhi, off, len, h64, k, v, debug_hash);
       };
       // the home-group lookup could not decide: the full insert, retried
@@ -830,20 +847,25 @@ __global__ __launch_bounds__(kMapThreads) void k_words_map(const WordJob* __rest
 constexpr uint32_t kMaxMapGrid = 1024;  // map workgroups (miss sub-queues per partition)
 constexpr uint32_t kPartUnroll = 2;     // records per thread and round
 constexpr uint32_t kPartHints = 2048;   // blocks of records whose first segment is kept
+// Jobs of a batch whose records the partitions stage (more take the tables)
+constexpr uint32_t kDirectJobs = 1024;
 template <int L>
-__global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __restrict__ jobs, uint32_t debug_hash) {
+__global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __restrict__ jobs, uint32_t n_jobs, uint32_t debug_hash,
+                                                             uint32_t* __restrict__ staged,
+                                                             unsigned long long* __restrict__ staged_bytes) {
   constexpr uint32_t kSlots = LdsTable<L>::kSlots;
+  static_assert(2 * kDirectJobs <= 2 * kMaxMapGrid, "two counters per job take the segments' place");
   __shared__ LdsTable<L> T;
   __shared__ uint32_t s_job[kSlots];
   // first record of each segment: map workgroup w's 32-byte sub-queue (w),
   // then its 16-byte one (G + w)
   __shared__ uint32_t s_pre[2 * kMaxMapGrid + 1];
   __shared__ uint16_t s_hint[kPartHints + 1];
-  __shared__ uint32_t s_used;
+  __shared__ uint32_t s_used, s_flushed;
   const WordJob& Q = jobs[0];  // the queues (shared by the jobs of a batch)
   const uint32_t p = blockIdx.x;
   for (uint32_t i = threadIdx.x; i < kSlots; i += blockDim.x) T.tag[i] = 0u;
-  if (threadIdx.x == 0) s_used = 0;
+  if (threadIdx.x == 0) s_used = s_flushed = 0;
   // exclusive prefix of the segment sizes, blockDim at a time
   __shared__ uint32_t s_wsum[kMapThreads / kWave];
   const uint32_t G = Q.mq_grid, NS = 2 * G;
@@ -905,6 +927,8 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
   // a summed key into its job's table: with the table split into partition
   // regions, this workgroup is the region's only writer
   auto insert = [&](const WordJob& J, uint32_t off, uint32_t len, uint64_t h, uint4 k, uint32_t v) {
+    mark_part(J, J.st->in_table, h);
+    s_flushed = 1;
     if (J.region_log2) g_insert<true, true>(J, 0, 0, off, len, h, k, v, debug_hash);
     else g_insert<true>(J, 0, 0, off, len, h, k, v, debug_hash);
   };
@@ -923,14 +947,30 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
     if (r == 2) insert(jobs[m.w], m.x, m.y, hash_from32(hk), k, m.z);
     return r == 4;
   };
-  // the summed keys into their jobs' tables; the table is cleared
-  auto flush = [&]() {
+  // The summed keys into their jobs' tables; the table is cleared. At the end
+  // (last), a partition whose keys of a job are all here writes their records
+  // to its stretch of the job's staging area instead; s_cnt and s_bytes count
+  // them and their bytes per job, from kNotDirect where that must not be.
+  uint32_t* const s_cnt = s_pre;
+  uint32_t* const s_bytes = s_pre + kDirectJobs;
+  constexpr uint32_t kNotDirect = 0x80000000u;
+  auto flush = [&](bool last) {
     for (uint32_t i = threadIdx.x; i < kSlots; i += blockDim.x) {
       const uint32_t tg = T.tag[i];
       if (tg & 1u) {
-        const uint32_t len = (tg >> 1) & 31u;
+        const uint32_t len = (tg >> 1) & 31u, j = s_job[i];
         const uint4 k = T.key[i];
-        insert(jobs[s_job[i]], T.off[i], len, key_hash16(k, len, debug_hash), k, T.cnt[i]);
+        const WordJob& J = jobs[j];
+        const uint32_t room = (uint32_t)(J.cap / kMaxWordParts);
+        const uint32_t at = last ? atomicAdd(&s_cnt[j], 1u) : kNotDirect;
+        if (at < room) {
+          atomicAdd(&s_bytes[j], len);
+          WRec* r = reinterpret_cast<WRec*>(J.recs2) + (uint64_t)p * room + at;
+          gstore16(r, make_uint4(bswap32(k.x), bswap32(k.y), bswap32(k.z), bswap32(k.w)));
+          gstore16(reinterpret_cast<uint8_t*>(r) + 16, make_uint4(len, T.off[i], T.cnt[i], 0u));
+        } else {
+          insert(J, T.off[i], len, key_hash16(k, len, debug_hash), k, T.cnt[i]);
+        }
       }
       T.tag[i] = 0u;
     }
@@ -1014,7 +1054,7 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
     rounds = 0;
     // as many claims again would leave the table more than three quarters full
     if (used + claims > kSlots / 4 * 3) {
-      flush();
+      flush(false);
       if (threadIdx.x == 0) s_used = 0;
       __syncthreads();
       before = 0;
@@ -1025,7 +1065,23 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
     }
   }
   __syncthreads();
-  flush();
+  if (n_jobs > kDirectJobs) {
+    flush(false);
+    return;
+  }
+  // the table must hold no key of this partition: neither the map's nor an earlier flush's
+  for (uint32_t j = threadIdx.x; j < n_jobs; j += blockDim.x) {
+    s_cnt[j] = s_flushed || (gp(jobs[j].st)->in_table_map[p >> 5] >> (p & 31u) & 1u) ? kNotDirect : 0u;
+    s_bytes[j] = 0;
+  }
+  __syncthreads();
+  flush(true);
+  __syncthreads();
+  for (uint32_t j = threadIdx.x; j < n_jobs; j += blockDim.x) {
+    const uint32_t room = (uint32_t)(jobs[j].cap / kMaxWordParts), c = s_cnt[j];
+    staged[j * kMaxWordParts + p] = c & kNotDirect ? 0u : c < room ? c : room;
+    staged_bytes[j * kMaxWordParts + p] = s_bytes[j];
+  }
 }
 
 // ----------------------------------------------------------------------------
@@ -1046,22 +1102,89 @@ MR_DEV unsigned long long compact_entry(const WordJob& J, uint64_t i) {
   return w;
 }
 
-// Work item = `item` slots of one job's table, 1024 or 4096 (tables are
+// The first n_direct * 256 work items gather the staged records: item
+// (job, partition) adds up the counts of the partitions before its own and
+// copies its records to their place, without an atomic (the places used to
+// come from one counter per job, at about 35 ns an update: 40 us of 512).
+// Then work item = `item` slots of one job's table, 1024 or 4096 (tables are
 // powers of two >= 4096 slots at 4096-aligned arena offsets, so no item
-// straddles two tables). Pass 1 counts the entries, one atomic reserves their
-// places, pass 2 writes the records and clears the slots.
+// straddles two tables), where the table holds anything. Pass 1 counts the
+// entries, one atomic reserves their places after the staged records, pass 2
+// writes the records and clears the slots.
 __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob* __restrict__ jobs, uint32_t n_jobs,
+                                                                   uint32_t n_direct, const uint32_t* __restrict__ staged,
+                                                                   const unsigned long long* __restrict__ staged_bytes,
                                                                    uint64_t total_slots, uint32_t item) {
   __shared__ uint32_t s_cnt, s_pos;
   __shared__ unsigned long long s_base, s_bytes;
+  __shared__ uint32_t w_before[kCompactThreads / kWave], w_all[kCompactThreads / kWave];
+  __shared__ unsigned long long w_bytes[kCompactThreads / kWave];
+  static_assert(kCompactThreads == kMaxWordParts, "one thread per partition's count");
+  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+  // staged records of job j before partition p, and in all
+  auto staged_sums = [&](uint32_t j, uint32_t p, uint32_t& before, uint32_t& all) {
+    const uint32_t c = gp(staged)[j * kMaxWordParts + threadIdx.x];
+    const uint32_t ib = wave_incl_scan(threadIdx.x < p ? c : 0u), ia = wave_incl_scan(c);
+    __syncthreads();  // the previous use has been read
+    if (lane == kWave - 1) {
+      w_before[wv] = ib;
+      w_all[wv] = ia;
+    }
+    __syncthreads();
+    before = all = 0;
+    for (uint32_t w = 0; w < kCompactThreads / kWave; ++w) {
+      before += w_before[w];
+      all += w_all[w];
+    }
+  };
+  const uint64_t n_gather = (uint64_t)n_direct * kMaxWordParts;
+  for (uint64_t g = blockIdx.x; g < n_gather; g += gridDim.x) {
+    const uint32_t j = (uint32_t)(g / kMaxWordParts), p = (uint32_t)(g % kMaxWordParts);
+    const WordJob& J = jobs[j];
+    uint32_t before, all;
+    staged_sums(j, p, before, all);
+    const uint32_t n = gp(staged)[j * kMaxWordParts + p];
+    const uint8_t* from = reinterpret_cast<const uint8_t*>(reinterpret_cast<const WRec*>(J.recs2) + p * (J.cap / kMaxWordParts));
+    uint8_t* to = reinterpret_cast<uint8_t*>(reinterpret_cast<WRec*>(J.recs) + before);
+    for (uint32_t i = threadIdx.x; i < 2 * n; i += kCompactThreads) gstore16(to + 16ull * i, gload16(from + 16ull * i));
+    if (p == 0) {
+      unsigned long long y = gp(staged_bytes)[j * kMaxWordParts + threadIdx.x];
+#pragma unroll
+      for (int o = kWave / 2; o; o >>= 1) y += __shfl_xor(y, o);
+      if (lane == 0) w_bytes[wv] = y;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        for (uint32_t w = 1; w < kCompactThreads / kWave; ++w) y += w_bytes[w];
+        atomicAdd(&J.st->n_recs, (unsigned long long)all);
+        atomicAdd(&J.st->key_bytes, y);
+      }
+    }
+  }
   for (uint64_t t0 = (uint64_t)blockIdx.x * item; t0 < total_slots; t0 += (uint64_t)gridDim.x * item) {
     uint32_t lo = 0, hi = n_jobs;
     while (hi - lo > 1) {
       const uint32_t mid = (lo + hi) >> 1;
       if (jobs[mid].slot_base <= t0) lo = mid; else hi = mid;
     }
+    const bool direct = lo < n_direct;
     const WordJob& J = jobs[lo];
     const uint64_t i0 = t0 - J.slot_base;
+    uint32_t before = 0, first = 0;
+    if (direct) {
+      // the partitions whose region these slots touch (without regions, all) have no key in the table
+      const uint32_t p0 = J.region_log2 ? (uint32_t)(i0 >> J.region_log2) : 0u;
+      const uint32_t p1 = J.region_log2 ? (uint32_t)((i0 + item - 1) >> J.region_log2) : kMaxWordParts - 1;
+      uint32_t any = 0;
+#pragma unroll
+      for (uint32_t w = 0; w < kMaxWordParts / 32; ++w) {
+        uint32_t bits = gp(J.st)->in_table[w];
+        if (w == p0 / 32) bits &= ~0u << (p0 & 31u);
+        if (w == p1 / 32) bits &= ~0u >> (31u - (p1 & 31u));
+        any |= w >= p0 / 32 && w <= p1 / 32 ? bits : 0u;
+      }
+      if (!any) continue;
+      staged_sums(lo, 0, before, first);
+    }
     if (threadIdx.x == 0) {
       s_cnt = 0;
       s_pos = 0;
@@ -1072,8 +1195,17 @@ __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob
     for (uint32_t q = threadIdx.x; q < item; q += kCompactThreads) mine += compact_entry(J, i0 + q) ? 1u : 0u;
     if (mine) atomicAdd(&s_cnt, mine);
     __syncthreads();
-    if (threadIdx.x == 0) s_base = s_cnt ? atomicAdd(&J.st->n_recs, (unsigned long long)s_cnt) : 0ull;
+    // Staged and table records together may pass the table's slots, which the
+    // record arrays are sized by: the table has to grow then. (Reservations
+    // only grow, so those that fit stay without a gap.)
+    if (threadIdx.x == 0 && s_cnt) {
+      const unsigned long long at = first + atomicAdd(&J.st->table_recs, (unsigned long long)s_cnt);
+      s_base = at + s_cnt <= J.cap ? at : ~0ull;
+      if (s_base == at) atomicAdd(&J.st->n_recs, (unsigned long long)s_cnt);
+      else atomicOr(&J.st->flags, kFlagTableFull);
+    }
     __syncthreads();
+    if (s_cnt && s_base == ~0ull) continue;
     unsigned long long bytes = 0;
     for (uint32_t q = threadIdx.x; q < item; q += kCompactThreads) {
       const uint64_t i = i0 + q;
@@ -1978,16 +2110,18 @@ hipError_t words_enqueue_map(const WordsLaunch& L, hipStream_t s) {
   }
 #undef MR_MAP_CASE
 #undef MR_MAP_LAUNCH
-  if (L.n_parts) hipLaunchKernelGGL((k_words_parts<12>), dim3(L.n_parts), dim3(kMapThreads), 0, s, L.jobs, L.debug_hash);
+  if (L.n_parts) hipLaunchKernelGGL((k_words_parts<12>), dim3(L.n_parts), dim3(kMapThreads), 0, s, L.jobs, L.n_jobs, L.debug_hash,
+                                    L.bucket_start, L.bucket_bstart);
   return hipGetLastError();
 }
 
 hipError_t words_enqueue_reduce(const WordsLaunch& L, hipStream_t s) {
   const uint32_t item = L.total_slots <= (1ull << 20) ? kCompactSmall : kCompactLarge;
-  const uint64_t tiles = (L.total_slots + item - 1) / item;
+  const uint32_t n_direct = L.n_parts && L.n_jobs <= kDirectJobs ? L.n_jobs : 0;
+  const uint64_t tiles = std::max<uint64_t>((L.total_slots + item - 1) / item, (uint64_t)n_direct * kMaxWordParts);
   const uint32_t cgrid = (uint32_t)(tiles < 4096 ? tiles : 4096);
-  hipLaunchKernelGGL(k_words_compact, dim3(cgrid ? cgrid : 1), dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, L.total_slots,
-                     item);
+  hipLaunchKernelGGL(k_words_compact, dim3(cgrid ? cgrid : 1), dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, n_direct,
+                     L.bucket_start, L.bucket_bstart, L.total_slots, item);
   if (L.n_jobs <= kRankJobs) {
     // plans the sort itself
     hipLaunchKernelGGL(k_sort_ranks, dim3(L.sort_grid), dim3(kSortThreads), 0, s, L.jobs, L.n_jobs, L.totals,

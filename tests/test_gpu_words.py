@@ -365,3 +365,45 @@ def test_sort_spill_path(torch):
     res = Job(device=0).words(_dev(torch, buf))
     assert res.stats["sort_spills"] > 0
     _check(res, buf)
+
+
+def _distinct(rng, n, lens, sep=32):
+    """n distinct words of lengths drawn from lens, each once and some again, in random order."""
+    letters = rng.integers(97, 123, (n, max(lens))).astype(np.uint8)
+    words = list({letters[i, :int(rng.choice(lens))].tobytes() for i in range(n)})
+    words += [words[i] for i in rng.integers(0, len(words), n // 2)]
+    order = rng.permutation(len(words))
+    return np.frombuffer(bytes([sep]).join(words[i] for i in order) + bytes([sep]), np.uint8)
+
+
+# The partitions stage their sums' records where no key of theirs is in the
+# table: few words (most partitions empty); more of one partition than its
+# stretch of a small table's staging area; staged and table records that fill
+# the record arrays or pass them (a larger table); words longer than 16 bytes
+# beside staged ones; queues that overflow in the map; partitions flushed while
+# they sum.
+@pytest.mark.parametrize("n,lens,slots,lds", [
+    (1, [3], 0, 4096), (40, [1, 2, 16], 4096, 256), (2_100, [9], 4096, 4096), (3_900, [6, 12], 4096, 4096),
+    (4_090, [7], 4096, 256), (4_300, [7], 4096, 4096), (20_000, [5, 16, 17, 40], 0, 1024), (3_000, [17, 33, 8], 4096, 4096),
+    (150_000, [3], 0, 256), (900_000, [8, 9], 1 << 22, 4096),
+])
+def test_staged_records_and_table_records(torch, n, lens, slots, lds):
+    from paper_1309_0215_amd import Job
+    rng = np.random.default_rng(n)
+    buf = _distinct(rng, n, lens)
+    if lens == [3]:
+        buf = np.concatenate([buf] * (1 if n == 1 else 8))
+    d = _dev(torch, buf)
+    j = Job(device=0, table_slots=slots, lds_slots=lds)
+    for _ in range(3):  # the later calls find the first one's table and scratch, and replay its launches
+        _check(j.words(d), buf)
+    _check(Job(device=0, table_slots=slots, lds_slots=lds).words_batch([d, d[: len(buf) // 2]])[0], buf)
+
+
+@pytest.mark.parametrize("n_jobs", [1024, 1025])
+def test_batches_around_the_most_jobs_that_stage(torch, n_jobs):
+    from paper_1309_0215_amd import Job
+    bufs = [gen.text(500 + i, 200 + i % 700, V=20 + i % 60, s=0.8) for i in range(n_jobs)]
+    res = Job(device=0).words_batch([_dev(torch, b) for b in bufs])
+    for r, b in zip(res, bufs):
+        _check(r, b)
