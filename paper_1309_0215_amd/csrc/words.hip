@@ -834,8 +834,8 @@ __global__ __launch_bounds__(kMapThreads) void k_words_map(const WordJob* __rest
 // from every workgroup. The records are taken in rounds of kPartUnroll per
 // thread (the next round's records are loaded meanwhile). Most find their key
 // in its home group, by straight-line code; the others take the full insert.
-// When as many claims as since the last look at the fill would leave the table
-// more than three quarters full, it is flushed into the global tables (one
+// When half as many claims as since the last look at the fill would leave the
+// table more than seven eighths full, it is flushed into the global tables (one
 // insert per summed key, all threads at once) and cleared, so that few records
 // meet a full group and fall back to a global insert each. The looks, which
 // take two barriers, are up to eight rounds apart while few keys are new.
@@ -861,11 +861,13 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
   // then its 16-byte one (G + w)
   __shared__ uint32_t s_pre[2 * kMaxMapGrid + 1];
   __shared__ uint16_t s_hint[kPartHints + 1];
-  __shared__ uint32_t s_used, s_flushed;
+  __shared__ uint32_t s_used;
+  __shared__ uint32_t s_tabled[kDirectJobs / 32];  // a bit per job with a key of this partition in its table from here
   const WordJob& Q = jobs[0];  // the queues (shared by the jobs of a batch)
   const uint32_t p = blockIdx.x;
   for (uint32_t i = threadIdx.x; i < kSlots; i += blockDim.x) T.tag[i] = 0u;
-  if (threadIdx.x == 0) s_used = s_flushed = 0;
+  if (threadIdx.x == 0) s_used = 0;
+  if (threadIdx.x < kDirectJobs / 32) s_tabled[threadIdx.x] = 0;
   // exclusive prefix of the segment sizes, blockDim at a time
   __shared__ uint32_t s_wsum[kMapThreads / kWave];
   const uint32_t G = Q.mq_grid, NS = 2 * G;
@@ -926,9 +928,9 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
   };
   // a summed key into its job's table: with the table split into partition
   // regions, this workgroup is the region's only writer
-  auto insert = [&](const WordJob& J, uint32_t off, uint32_t len, uint64_t h, uint4 k, uint32_t v) {
-    mark_part(J, J.st->in_table, h);
-    s_flushed = 1;
+  auto insert = [&](uint32_t j, uint32_t off, uint32_t len, uint64_t h, uint4 k, uint32_t v) {
+    const WordJob& J = jobs[j];
+    if (j < kDirectJobs) atomicOr(&s_tabled[j >> 5], 1u << (j & 31u));
     if (J.region_log2) g_insert<true, true>(J, 0, 0, off, len, h, k, v, debug_hash);
     else g_insert<true>(J, 0, 0, off, len, h, k, v, debug_hash);
   };
@@ -943,8 +945,9 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
         r = 0;
       }
     }
-    // the key's probe groups are full (rare below three quarters load)
-    if (r == 2) insert(jobs[m.w], m.x, m.y, hash_from32(hk), k, m.z);
+    // The key's probe groups are full (rare below three quarters load). They
+    // stay so until a flush: the key is in the job's table or here, not in both.
+    if (r == 2) insert(m.w, m.x, m.y, hash_from32(hk), k, m.z);
     return r == 4;
   };
   // The summed keys into their jobs' tables; the table is cleared. At the end
@@ -969,7 +972,7 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
           gstore16(r, make_uint4(bswap32(k.x), bswap32(k.y), bswap32(k.z), bswap32(k.w)));
           gstore16(reinterpret_cast<uint8_t*>(r) + 16, make_uint4(len, T.off[i], T.cnt[i], 0u));
         } else {
-          insert(J, T.off[i], len, key_hash16(k, len, debug_hash), k, T.cnt[i]);
+          insert(j, T.off[i], len, key_hash16(k, len, debug_hash), k, T.cnt[i]);
         }
       }
       T.tag[i] = 0u;
@@ -987,6 +990,7 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
     }
   };
   load_round(0);
+  bool flushed = false;
   uint32_t rounds = 0, period = 1, before = 0;  // since the last look at the fill; rounds between looks; the fill then
   for (uint32_t base = 0; base < total; base += kPartUnroll * kMapThreads) {
     // this round's records as (key, {offset, length, count, job})
@@ -1052,9 +1056,10 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
     const uint32_t used = s_used, claims = used - before;
     __syncthreads();
     rounds = 0;
-    // as many claims again would leave the table more than three quarters full
-    if (used + claims > kSlots / 4 * 3) {
+    // half as many claims again would leave the table more than seven eighths full
+    if (used + claims / 2 > kSlots / 8 * 7) {
       flush(false);
+      flushed = true;
       if (threadIdx.x == 0) s_used = 0;
       __syncthreads();
       before = 0;
@@ -1071,7 +1076,7 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
   }
   // the table must hold no key of this partition: neither the map's nor an earlier flush's
   for (uint32_t j = threadIdx.x; j < n_jobs; j += blockDim.x) {
-    s_cnt[j] = s_flushed || (gp(jobs[j].st)->in_table_map[p >> 5] >> (p & 31u) & 1u) ? kNotDirect : 0u;
+    s_cnt[j] = flushed || (gp(jobs[j].st)->in_table_map[p >> 5] >> (p & 31u) & 1u) ? kNotDirect : 0u;
     s_bytes[j] = 0;
   }
   __syncthreads();
@@ -1081,6 +1086,7 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
     const uint32_t room = (uint32_t)(jobs[j].cap / kMaxWordParts), c = s_cnt[j];
     staged[j * kMaxWordParts + p] = c & kNotDirect ? 0u : c < room ? c : room;
     staged_bytes[j * kMaxWordParts + p] = s_bytes[j];
+    if (s_tabled[j >> 5] >> (j & 31u) & 1u) mark_part(jobs[j], jobs[j].st->in_table, (uint64_t)p << jobs[j].part_shift);
   }
 }
 
