@@ -299,11 +299,18 @@ mr_status ensure_ws(mr_job* job, uint64_t bytes) {
   return MR_OK;
 }
 
+// Pinned host memory that the last kernel of a job writes its results to: the
+// states of n jobs, then kHostTail 64-bit values.
+constexpr uint32_t kHostTail = 4;
+unsigned long long* host_tail(mr_job* job) { return reinterpret_cast<unsigned long long*>(job->h_states + job->h_states_cap); }
+
 mr_status ensure_host_states(mr_job* job, uint32_t n) {
   if (n <= job->h_states_cap) return MR_OK;
   if (job->h_states) (void)hipHostFree(job->h_states);
   job->h_states = nullptr;
-  MR_HIP(hipHostMalloc(&job->h_states, sizeof(JobState) * n, hipHostMallocDefault));
+  job->h_states_cap = 0;
+  // (kernels of earlier calls write there, and every call waits for its own)
+  MR_HIP(hipHostMalloc(&job->h_states, sizeof(JobState) * n + 8 * kHostTail, hipHostMallocDefault));
   job->h_states_cap = n;
   return MR_OK;
 }
@@ -603,9 +610,12 @@ mr_status words_pass(mr_job* job, std::vector<WordItem>& items, std::vector<JobS
   mr_status st = ensure_ws(job, p.c.off);
   if (st != MR_OK) return st;
   uint8_t* ws = job->ws;
+  st = ensure_host_states(job, n);
+  if (st != MR_OK) return st;
   // identity of the launch sequence: a captured graph replays only for the same one
   uint64_t key = 0xCBF29CE484222325ull;
   key = fnv_mix(key, (uint64_t)ws);
+  key = fnv_mix(key, (uint64_t)job->h_states);
   key = fnv_mix(key, n);
   key = fnv_mix(key, (uint64_t)lds_log2);
   key = fnv_mix(key, grid_cap);
@@ -641,9 +651,6 @@ mr_status words_pass(mr_job* job, std::vector<WordItem>& items, std::vector<JobS
     MR_HIP(hipEventRecord(job->ev0, s));
     MR_HIP(hipGraphLaunch(job->graph, s));
     MR_HIP(hipEventRecord(job->ev1, s));
-    st = ensure_host_states(job, n);
-    if (st != MR_OK) return st;
-    MR_HIP(hipMemcpyAsync(job->h_states, ws + p.o_states, sizeof(JobState) * n, hipMemcpyDeviceToHost, s));
     MR_HIP(hipStreamSynchronize(s));
     states.assign(job->h_states, job->h_states + n);
     float ms = 0.f;
@@ -731,7 +738,9 @@ mr_status words_pass(mr_job* job, std::vector<WordItem>& items, std::vector<JobS
   L.bucket_fill = reinterpret_cast<uint32_t*>(ws + p.o_bucket_fill);
 
   L.states = reinterpret_cast<JobState*>(ws + p.o_states);
+  L.pub.r[0] = PubRange{L.states, job->h_states, (uint32_t)(sizeof(JobState) / 4 * n)};
   if (lb) {
+    L.pub.r[1] = PubRange{lb->n_marks, host_tail(job), 2};
     L.links = true;
     L.link_grid = (uint32_t)std::max(1, job->n_cu * 8);
     L.link_marks = lb->marks;
@@ -776,15 +785,9 @@ mr_status words_pass(mr_job* job, std::vector<WordItem>& items, std::vector<JobS
     MR_HIP(words_enqueue_reduce(L, s));
     MR_HIP(hipEventRecord(job->ev1, s));
   }
-  // (with markers, their count comes back in the same round trip, in the
-  // pinned buffer's entry past the states)
-  st = ensure_host_states(job, n + (lb ? 1u : 0u));
-  if (st != MR_OK) return st;
-  MR_HIP(hipMemcpyAsync(job->h_states, ws + p.o_states, sizeof(JobState) * n, hipMemcpyDeviceToHost, s));
-  if (lb) MR_HIP(hipMemcpyAsync(&job->h_states[n], lb->n_marks, 8, hipMemcpyDeviceToHost, s));
   MR_HIP(hipStreamSynchronize(s));
   states.assign(job->h_states, job->h_states + n);
-  if (lb) std::memcpy(&lb->h_n_marks, &job->h_states[n], 8);
+  if (lb) lb->h_n_marks = *host_tail(job);
   float ms = 0.f;
   MR_HIP(hipEventElapsedTime(&ms, job->ev0, job->ev1));
   *gpu_ms = ms;
@@ -986,14 +989,12 @@ mr_status run_links(mr_job* job, mr_reduce_op op, const void* d_input, uint64_t 
   // their size and the error flag are checked after the one synchronisation
   MR_HIP(links_enqueue_write(P, out->list_ids, out->cap_list_ids, out->list_offsets,
                              static_cast<uint32_t*>(out->values), job->stream));
-  unsigned long long tv[2] = {0, 0};
-  uint32_t flags = 0;
-  MR_HIP(hipMemcpyAsync(&tv[0], P.total, 8, hipMemcpyDeviceToHost, job->stream));
-  MR_HIP(hipMemcpyAsync(&tv[1], P.n_valid, 8, hipMemcpyDeviceToHost, job->stream));
-  MR_HIP(hipMemcpyAsync(&flags, P.flags, 4, hipMemcpyDeviceToHost, job->stream));
+  unsigned long long* const tv = host_tail(job);
+  tv[2] = 0;
+  MR_HIP(publish_enqueue(Publish{{{P.total, &tv[0], 2}, {P.n_valid, &tv[1], 2}, {P.flags, &tv[2], 1}}}, job->stream));
   MR_HIP(hipEventRecord(job->ev1, job->stream));
   MR_HIP(hipStreamSynchronize(job->stream));
-  if (flags) return fail(MR_ERR_HIP, "internal error: a link's URL is missing from the sorted URLs");
+  if (tv[2]) return fail(MR_ERR_HIP, "internal error: a link's URL is missing from the sorted URLs");
   out->n_list_ids = tv[0];
   out->stats.n_items = tv[1];
   if (tv[0] > out->cap_list_ids)
@@ -1634,13 +1635,15 @@ mr_status run_kmeans(mr_job* job, const void* d_input, uint64_t bytes, mr_output
   L.sums = out->sums;
   L.counts = out->counts;
   L.cent = out->centroids;
-  unsigned long long flags[2] = {0, 0};  // rechecks, tiny (matrix-core path)
+  st = ensure_host_states(job, 1);
+  if (st != MR_OK) return st;
+  unsigned long long* const flags = host_tail(job);  // rechecks, tiny (matrix-core path)
+  flags[0] = flags[1] = 0;
   for (int pass = 0; pass < 2; ++pass) {
-    if (L.mfma) MR_HIP(hipMemsetAsync(L.n_recheck, 0, 16, job->stream));
     MR_HIP(hipEventRecord(job->ev0, job->stream));
     MR_HIP(km_enqueue(L, job->stream, job->cfg.timing ? job->ev2 : nullptr, job->cfg.timing ? job->ev3 : nullptr));
     MR_HIP(hipEventRecord(job->ev1, job->stream));
-    if (L.mfma) MR_HIP(hipMemcpyAsync(flags, L.n_recheck, 16, hipMemcpyDeviceToHost, job->stream));
+    if (L.mfma) MR_HIP(publish_enqueue(Publish{{{L.n_recheck, flags, 4}}}, job->stream));
     MR_HIP(hipStreamSynchronize(job->stream));
     // coordinates too small for the matrix-core path's exact split: the
     // generic path redoes the step (it writes every output again)

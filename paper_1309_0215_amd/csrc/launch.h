@@ -7,6 +7,19 @@
 
 namespace mr {
 
+// Small results to pinned host memory at the end of a job's kernels: ranges of
+// 32-bit words (unused: 0 words), copied by a kernel, so that a job needs no
+// copy after its last one.
+struct PubRange {
+  const void* from;
+  void* to;
+  uint32_t words;
+};
+struct Publish {
+  PubRange r[3];
+};
+hipError_t publish_enqueue(const Publish& P, hipStream_t s);
+
 struct WordsLaunch {
   const WordJob* jobs;        // device array [n_jobs]
   const uint64_t* tile_base;  // device array [n_jobs + 1]
@@ -26,6 +39,7 @@ struct WordsLaunch {
   unsigned long long* bucket_bstart;
   uint32_t* bucket_fill;
   JobState* states;           // device [n_jobs]
+  Publish pub;                // states (and markers found) to host memory
   uint32_t n_parts;            // partitions of the two-phase reduce through partition queues (0: none)
   // Reverse Index map instead of the word map (one job)
   bool links;
