@@ -714,10 +714,13 @@ mr_status words_pass(mr_job* job, std::vector<WordItem>& items, std::vector<JobS
                         : 0u;
     any_rec |= it.rec != nullptr;
   }
-  MR_HIP(hipMemcpyAsync(ws + p.o_jobs, hj.data(), sizeof(WordJob) * n, hipMemcpyHostToDevice, s));
-  MR_HIP(hipMemcpyAsync(ws + p.o_tile_base, p.tile_base.data(), 8 * (n + 1), hipMemcpyHostToDevice, s));
-
   WordsLaunch L{};
+  if (n == 1) {
+    L.one = hj[0];
+  } else {
+    MR_HIP(hipMemcpyAsync(ws + p.o_jobs, hj.data(), sizeof(WordJob) * n, hipMemcpyHostToDevice, s));
+    MR_HIP(hipMemcpyAsync(ws + p.o_tile_base, p.tile_base.data(), 8 * (n + 1), hipMemcpyHostToDevice, s));
+  }
   L.jobs = reinterpret_cast<const WordJob*>(ws + p.o_jobs);
   L.tile_base = reinterpret_cast<const uint64_t*>(ws + p.o_tile_base);
   L.n_jobs = n;

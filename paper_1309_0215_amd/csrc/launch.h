@@ -24,6 +24,7 @@ struct WordsLaunch {
   const WordJob* jobs;        // device array [n_jobs]
   const uint64_t* tile_base;  // device array [n_jobs + 1]
   uint32_t n_jobs;
+  WordJob one;                // the descriptor of a single job, which the preparation kernel stores
   uint64_t total_tiles;
   uint64_t total_slots;       // sum of table capacities
   uint32_t map_grid;

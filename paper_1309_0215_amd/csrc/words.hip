@@ -280,6 +280,24 @@ MR_DEV void mark_part(const WordJob& J, uint32_t* map, uint64_t h) {
 // prep: validate record offsets and publish the valid byte range
 // ----------------------------------------------------------------------------
 
+// A single job's descriptor comes as a kernel argument: two copies from
+// pageable memory before the first kernel cost about 20 us of a call. Stores
+// it with its tile bases, clears the state and publishes the whole input as
+// the valid range (k_words_prep narrows it to the records, if there are any).
+__global__ __launch_bounds__(kWave) void k_words_one(WordJob J, WordJob* __restrict__ job, uint64_t* __restrict__ tile_base,
+                                                     uint64_t total_tiles) {
+  uint32_t* st = reinterpret_cast<uint32_t*>(J.st);
+  for (uint32_t i = threadIdx.x; i < (uint32_t)(sizeof(JobState) / 4); i += kWave) st[i] = 0u;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    *job = J;
+    tile_base[0] = 0;
+    tile_base[1] = total_tiles;
+    J.st->valid_lo = 0;
+    J.st->valid_hi = J.n;
+  }
+}
+
 // Without record offsets one block per job (blockIdx.y) clears the job's
 // state and publishes its whole input as the valid range: the state's only
 // writer here, so no separate clearing launch is needed. With them the states
@@ -2086,8 +2104,11 @@ hipError_t publish_enqueue(const Publish& P, hipStream_t s) {
 }
 
 hipError_t words_enqueue_zero_states(const WordsLaunch& L, hipStream_t s) {
-  // without record offsets the prep kernel clears each job's state itself
-  if (L.any_records) hipLaunchKernelGGL(k_zero_states, dim3(1), dim3(256), 0, s, L.states, L.n_jobs);
+  // (without record offsets the prep kernel clears each job's state itself)
+  if (L.n_jobs == 1)
+    hipLaunchKernelGGL(k_words_one, dim3(1), dim3(kWave), 0, s, L.one, const_cast<WordJob*>(L.jobs),
+                       const_cast<uint64_t*>(L.tile_base), L.total_tiles);
+  else if (L.any_records) hipLaunchKernelGGL(k_zero_states, dim3(1), dim3(256), 0, s, L.states, L.n_jobs);
   return hipGetLastError();
 }
 
@@ -2095,7 +2116,7 @@ hipError_t words_enqueue_prep(const WordsLaunch& L, hipStream_t s) {
   if (L.any_records) {
     dim3 g(64, L.n_jobs);
     hipLaunchKernelGGL(k_words_prep, g, dim3(256), 0, s, L.jobs, L.n_jobs, 0u);
-  } else {
+  } else if (L.n_jobs > 1) {
     dim3 g(1, L.n_jobs);
     hipLaunchKernelGGL(k_words_prep, g, dim3(64), 0, s, L.jobs, L.n_jobs, 1u);
   }
