@@ -1570,9 +1570,10 @@ KmCarve km_carve(uint32_t k, uint32_t d, uint32_t G, bool generic) {
   r.bytes = c.off;
   return r;
 }
-// Workgroups (partials) of the matrix-core path at d = 32, k = 64.
+// Workgroups (partials) of the matrix-core path at d = 32, k = 64: one per CU,
+// twelve groups of 32 points each at least.
 uint32_t km_grid(uint64_t N, int n_cu) {
-  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)n_cu * 3, (N + 127) / 128));
+  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)n_cu, (N + 383) / 384));
 }
 // Scratch of a step. The matrix-core path's includes the generic path's,
 // which redoes a step on coordinates outside its exact split (with as many

@@ -52,7 +52,7 @@ MR_DEV void split_bf16x3(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
   lo = bf16_bits(__float_as_uint(r2) >> 16);
 }
 
-constexpr int kKmThreads = 256;  // 4 waves
+constexpr int kKmThreads = 768;  // 12 waves
 
 // Nonzero float32 magnitudes below 2^-100 (bit patterns 1 .. kTinyBits - 1):
 // their bfloat16 pieces can fall below the normal range, where the split
@@ -101,6 +101,9 @@ __global__ __launch_bounds__(kWave) void k_km_prep(const float* __restrict__ C, 
 // Assignment + local sums for d = 32, k = 64.
 constexpr int kKmFlushIters = 16;  // wave iterations between float32 -> float64 flushes of the sums
 
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
 MR_DEV void load_group(const float* __restrict__ X, uint64_t N, uint64_t g, uint64_t groups, uint32_t col, uint32_t h,
                        float (&xs)[16]) {
   const uint64_t p = g * 32 + col;
@@ -121,14 +124,77 @@ MR_DEV void load_group(const float* __restrict__ X, uint64_t N, uint64_t g, uint
   }
 }
 
-// Each wave takes groups of 32 points. Lane (col, h) holds dims 16h..16h+15
-// of point col (B operand of the score contraction) and centroid rows col and
-// 32 + col come from LDS (A operand). After the argmin, the per-cluster sums
-// are a second contraction S[c][d] += sum_p [a_p = c] x[p][d]: the one-hot
-// assignment is the A operand (clusters x points), the points transposed
-// through LDS are the B operand (points x dims), and the float32 sums stay in
-// the accumulators until they are flushed into float64 LDS sums.
-__global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_km_mfma(const float* __restrict__ X, uint64_t N, const float* __restrict__ C,
+// Eight consecutive values as their three pieces (split_bf16x3), packed in pairs.
+MR_DEV void split8_bf16x3(const float* x, uint4& hi, uint4& mid, uint4& lo) {
+  uint32_t* const ph = &hi.x;
+  uint32_t* const pm = &mid.x;
+  uint32_t* const pl = &lo.x;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    uint32_t u0[2], u1[2], u2[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const float v = x[2 * j + e];
+      u0[e] = __float_as_uint(v);
+      const float r1 = v - __uint_as_float(u0[e] & 0xFFFF0000u);
+      u1[e] = __float_as_uint(r1);
+      u2[e] = __float_as_uint(r1 - __uint_as_float(u1[e] & 0xFFFF0000u));
+    }
+    ph[j] = __builtin_amdgcn_perm(u0[1], u0[0], 0x07060302u);  // the upper halves
+    pm[j] = __builtin_amdgcn_perm(u1[1], u1[0], 0x07060302u);
+    pl[j] = __builtin_amdgcn_perm(u2[1], u2[0], 0x07060302u);
+  }
+}
+
+MR_DEV bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
+
+// The larger of two float32 values (plain fmaxf first quiets each operand that
+// it cannot show to be quiet; a NaN gives the other value either way).
+MR_DEV float max_f32(float a, float b) {
+  float m;
+  asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
+  return m;
+}
+
+// 0x3F80 (1.0 in bfloat16) in each half of a that equals the half of c, else 0:
+// the compiler turns the plain form into a compare and a select per half.
+MR_DEV uint32_t one_hot2(uint32_t a, uint32_t c) {
+  const uint32_t x = a ^ c, one = 0x00010001u, unit = 0x3F803F80u, less = 0xC080C080u;
+  uint32_t m, o;
+  asm("v_pk_min_u16 %0, %1, %2" : "=v"(m) : "v"(x), "v"(one));
+  asm("v_pk_mad_u16 %0, %1, %2, %3" : "=v"(o) : "v"(m), "v"(less), "v"(unit));
+  return o;
+}
+
+// The values that lanes l and l ^ 32 hold, in both lanes alike.
+MR_DEV void pair_values(uint32_t v, uint32_t& lower, uint32_t& upper) {
+  const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  lower = r[0];
+  upper = r[1];
+}
+
+// Each wave takes groups of 32 points. Lane (col, h) holds dims 8h..8h+7 and
+// 16+8h..16+8h+7 of point col (B operand of the score contraction) and
+// centroid rows col and 32 + col come from LDS (A operand); the accumulators
+// start at -|c|^2 / 2, so that the largest of them is the nearest centroid.
+// After the argmax, the per-cluster sums are a second contraction
+// S[c][d] += sum_p [a_p = c] x[p][d]: the one-hot assignment is the A operand
+// (clusters x points), and the points' pieces, stored for it as they were split
+// for the first and read transposed, are the B operand (points x dims); the
+// float32 sums stay in the accumulators until they are flushed into float64
+// LDS sums.
+// Bound by vector instructions beside the matrix cores. A score keeps its
+// accumulator's place within its block of 16 in the four low mantissa bits, so
+// that best and second best take an and-or, a maximum and a median a score. One
+// workgroup of twelve waves per CU holds the centroids and the float64 sums
+// once and leaves room for three waves per SIMD. 16.8 M points: 790 us (the
+// matrix cores are busy for 590,000 of 1.38 M clocks, vector instructions take
+// 920,000; the clock falls to 1.6..1.8 GHz). With four-wave workgroups, two of
+// which were resident, a second split of the transposed float32 values, indices
+// carried beside the scores and 715 vector instructions a group of 32 points
+// instead of 450: 1,080 us. Collecting the near ties and deciding 64 at a time
+// over all centroids: 804 us.
+__global__ __launch_bounds__(kKmThreads) void k_km_mfma(const float* __restrict__ X, uint64_t N, const float* __restrict__ C,
                                                         const float* __restrict__ cn_g, const double* __restrict__ cmax_g,
                                                         int32_t* __restrict__ assign, double* __restrict__ part_sum,
                                                         uint32_t* __restrict__ part_cnt, unsigned long long* __restrict__ n_recheck,
@@ -136,73 +202,89 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(3, 3
   constexpr int D = 32, K = 64, W = kKmThreads / kWave;
   __shared__ double s64[K * D];
   __shared__ uint32_t scnt[K];
-  __shared__ float sC[K * D];
-  __shared__ float sCn[K];
+  __shared__ __attribute__((aligned(16))) float sC[K * D];
+  __shared__ __attribute__((aligned(16))) float sCn[K];  // -|c|^2 / 2
   // centroid pieces (hi, mid, lo) as A operands: sCp[piece][row][...] holds
   // the row's four 8-dim chunks, chunk c at position c ^ ((row / 4) % 4), so
   // that the 16 lanes of one 16-byte read (rows r..r+15) meet 16 different
   // bank groups
-  __shared__ __bf16 sCp[3][K][D];
-  // per wave: x transposed, xt[w][row(d)][p] = x[p][d] with row(d) =
-  // 16 (d / 16) + 2 (d % 8) + (d / 8) % 2 (the two lanes of a pair write rows
-  // of different parity, hence different banks), and the assignments,
-  // ab[w][p] = a_p (-1 for no point)
-  __shared__ float xt[W][32][32];
-  __shared__ int32_t ab[W][32];
+  __shared__ __attribute__((aligned(16))) __bf16 sCp[3][K][D];
+  // per wave: the points' pieces, laid out alike, and the assignments (no
+  // cluster for no point)
+  __shared__ __attribute__((aligned(16))) uint4 xp[W][3][32][4];
+  __shared__ __attribute__((aligned(16))) uint16_t ab[W][32];
+  __shared__ uint32_t s_rechecks;
   for (int i = threadIdx.x; i < K * D; i += blockDim.x) {
     s64[i] = 0.0;
     sC[i] = C[i];
     const int r = i / D, e = ((((i % D) / 8) ^ ((r / 4) % 4)) * 8) + i % 8;
     split_bf16x3(C[i], sCp[0][r][e], sCp[1][r][e], sCp[2][r][e]);
   }
+  if (threadIdx.x == 0) s_rechecks = 0;
   if (threadIdx.x < K) {
     scnt[threadIdx.x] = 0;
-    sCn[threadIdx.x] = cn_g[threadIdx.x];
+    sCn[threadIdx.x] = -0.5f * cn_g[threadIdx.x];
   }
   __syncthreads();
 
   const uint32_t lane = lane_id();
   const uint32_t wv = threadIdx.x / kWave;
-  const uint32_t h = lane >> 5;     // which half of the dims (0: 0..15, 1: 16..31)
+  const uint32_t h = lane >> 5;     // which half of the dims (0: 0..7 and 16..23, 1: 8..15 and 24..31)
   const uint32_t col = lane & 31u;  // point within the 32-point group / centroid row within a block
   const float cmax = (float)*cmax_g;
   const float u = 5.9604645e-08f;                     // 2^-24
-  // float32 accumulation of the piece products: 12 instructions of 16 products
-  // each per score, counted as 48 sequential additions (with margin)
-  const float gam = 48.f * u / (1.f - 48.f * u);
+  // Error of t = x . c - |c|^2 / 2 as computed. Float32 accumulation of the
+  // start value and the piece products: 12 instructions of 16 products each
+  // per score, counted as 49 sequential additions (with margin), each relative
+  // to |c|^2 / 2 + |x| |c|; the place in the low four mantissa bits, 15 units
+  // of the last place at most; the norm's own rounding; the dropped products.
+  const float gam = 49.f * u / (1.f - 49.f * u);
+  const float place = 1.9073486e-06f;                 // 2^-19
   const float drop = 9.5367432e-07f;                  // 2^-20: the three dropped piece products
-  const float e_c = 8.f * u * cmax * cmax;            // centroid-norm rounding, both scores, x2 margin
-  const float e_x = 8.f * (gam + u + drop) * cmax;    // times |x|: dot products and the subtraction
+  // both scores, x2 margin
+  const float e_c = 2.f * (gam + place + u) * cmax * cmax;
+  const float e_x = 4.f * (gam + place + drop) * cmax;  // times |x|
 
   const uint32_t waves_total = gridDim.x * W;
   const uint32_t wave_g = blockIdx.x * W + wv;
   const uint64_t groups = (N + 31) / 32;
   const uint64_t iters = (groups + waves_total - 1) / waves_total;  // uniform across the grid
-  unsigned long long rechecks = 0;
-  uint32_t tmin = 0xFFFFFFFFu;  // min over this lane's coordinates of (|bits| - 1): zero stays above every tiny value
+  uint32_t rechecks = 0;
+  bool any_tiny = false;
   f32x16 sum0 = {}, sum1 = {};  // cluster rows 0..31 and 32..63 x dims (float32, since the last flush)
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
 
-  float xs[16], xn[16];
-  load_group(X, N, wave_g, groups, col, h, xs);
-  for (uint64_t it = 0; it < iters; ++it) {
+  // one group, in xs; the next group's loads go into xn and are in flight meanwhile
+  auto group = [&](uint64_t it, float (&xs)[16], float (&xn)[16]) {
     const uint64_t g = it * waves_total + wave_g;
     const uint64_t p = g * 32 + col;
     const bool valid = g < groups && p < N;
-    // the next group's loads are in flight while this group is computed
     load_group(X, N, g + waves_total, groups, col, h, xn);
-    f32x16 acc0 = {}, acc1 = {};
+    f32x16 acc0, acc1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {  // register r of lane (col, h) is row 8 (r / 4) + 4 h + r % 4 (+ 32 for acc1)
+      const f32x4 c0 = *reinterpret_cast<const f32x4*>(&sCn[8 * q + 4 * h]);
+      const f32x4 c1 = *reinterpret_cast<const f32x4*>(&sCn[32 + 8 * q + 4 * h]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        acc0[4 * q + r] = c0[r];
+        acc1[4 * q + r] = c1[r];
+      }
+    }
 #pragma unroll
     for (int kc = 0; kc < 2; ++kc) {
       // B: dims 16 kc + 8h + j of point col (xs[8 kc + j]) as three pieces
-      bf16x8 xh, xm, xl;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        __bf16 vh, vm, vl;
-        split_bf16x3(xs[8 * kc + j], vh, vm, vl);
-        xh[j] = vh;
-        xm[j] = vm;
-        xl[j] = vl;
-      }
+      uint4 ph, pm, pl;
+      split8_bf16x3(xs + 8 * kc, ph, pm, pl);
+      const uint32_t at = (2 * kc + h) ^ ((col / 4) % 4);
+      xp[wv][0][col][at] = ph;
+      xp[wv][1][col][at] = pm;
+      xp[wv][2][col][at] = pl;
+      const bf16x8 xh = as_bf16x8(ph), xm = as_bf16x8(pm), xl = as_bf16x8(pl);
 #pragma unroll
       for (int blk = 0; blk < 2; ++blk) {
         // A: centroid row blk * 32 + col, the same 8 dims
@@ -221,58 +303,63 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(3, 3
         if (blk) acc1 = acc; else acc0 = acc;
       }
     }
+    // coordinates below 2^-100: zeros are set apart only where there is one
+    float amin = fabsf(xs[0]);
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
-      const uint32_t b = (__float_as_uint(xs[t]) & 0x7FFFFFFFu) - 1u;
-      tmin = b < tmin ? b : tmin;
+    for (int t = 1; t < 16; ++t) amin = fminf(amin, fabsf(xs[t]));
+    if (__any(amin < __uint_as_float(kTinyBits))) {
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        const uint32_t b = __float_as_uint(xs[t]) & 0x7FFFFFFFu;
+        any_tiny |= b != 0u && b < kTinyBits;
+      }
     }
     // |x| for the bound
     float nx = 0.f;
 #pragma unroll
     for (int s = 0; s < 16; ++s) nx = fmaf(xs[s], xs[s], nx);
-    nx += __shfl_xor(nx, 32);
-    nx = sqrtf(nx);
-    // scores of this lane's 32 rows, then best and second best; rows are
-    // visited in increasing index order, so a strict < keeps the lowest index
-    float sc[32];
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        sc[b * 16 + r] = sCn[b * 32 + 8 * (r / 4) + 4 * (int)h + (r % 4)] - 2.f * (b ? acc1[r] : acc0[r]);
-    float b1 = INFINITY, b2 = INFINITY;
-    int i1 = 0;
+    uint32_t lo, up;
+    pair_values(__float_as_uint(nx), lo, up);
+    nx = sqrtf(__uint_as_float(lo) + __uint_as_float(up));
+    // best and second best of this lane's 16 rows of each block
+    float b1[2], b2[2];
+    uint32_t sc[2][16];
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
+      b1[b] = b2[b] = -INFINITY;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int idx = b * 32 + 8 * (r / 4) + 4 * (int)h + (r % 4);
-        const float v = sc[b * 16 + r];
-        const bool better = v < b1;
-        b2 = better ? b1 : (v < b2 ? v : b2);
-        i1 = better ? idx : i1;
-        b1 = better ? v : b1;
+        const uint32_t v = (__float_as_uint(b ? acc1[r] : acc0[r]) & ~15u) | (uint32_t)r;
+        sc[b][r] = v;
+        b2[b] = __builtin_amdgcn_fmed3f(b1[b], b2[b], __uint_as_float(v));
+        b1[b] = max_f32(b1[b], __uint_as_float(v));
       }
     }
+    const float l1 = fmaxf(b1[0], b1[1]);
+    const float l2 = fmaxf(fminf(b1[0], b1[1]), fmaxf(b2[0], b2[1]));
+    const uint32_t r = __float_as_uint(l1) & 15u;
+    const uint32_t lrow = (b1[1] > b1[0] ? 32u : 0u) + 8 * (r / 4) + 4 * h + r % 4;
     // combine with the partner lane (other 32 rows of the same point)
-    const float o1 = __shfl_xor(b1, 32), o2 = __shfl_xor(b2, 32);
-    const int oi = __shfl_xor(i1, 32);
-    const bool other = o1 < b1 || (o1 == b1 && oi < i1);
-    const float best = other ? o1 : b1;
-    const float second = other ? (b1 < o2 ? b1 : o2) : (b2 < o1 ? b2 : o1);
-    int bi = other ? oi : i1;
-    // Near tie: every float32 score is within eps/2 of its exact value, so the
-    // exact argmin is among the rows scoring <= best + eps. Those candidates
+    uint32_t lo1, up1, lo2, up2, rlo, rup;
+    pair_values(__float_as_uint(l1), lo1, up1);
+    pair_values(__float_as_uint(l2), lo2, up2);
+    pair_values(lrow, rlo, rup);
+    const float f1 = __uint_as_float(lo1), g1 = __uint_as_float(up1);
+    const float best = fmaxf(f1, g1);
+    const float second = fmaxf(fminf(f1, g1), fmaxf(__uint_as_float(lo2), __uint_as_float(up2)));
+    int bi = (int)(g1 > f1 ? rup : rlo);
+    // Near tie: every score is within eps/2 of its exact value, so the exact
+    // nearest is among the rows scoring >= best - eps. Those candidates
     // (usually two) are decided again in float64 from the direct form; both
     // lanes of the pair take part, each for its own rows.
     const float eps = e_c + e_x * nx;
-    const bool need = valid && !(second - best > eps);
+    const bool need = valid && !(best - second > eps);
     if (__any(need)) {
       uint32_t cand = 0;
       if (need) {
-        const float thr = best + eps;
+        const float thr = best - eps;
 #pragma unroll
-        for (int t = 0; t < 32; ++t) cand |= (sc[t] <= thr ? 1u : 0u) << t;
+        for (int t = 0; t < 32; ++t) cand |= (__uint_as_float(sc[t / 16][t % 16]) >= thr ? 1u : 0u) << t;
       }
       // the partner's half of the point: this lane then holds all 32 dims
       float xo[16];
@@ -291,8 +378,8 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(3, 3
         double dj = 0.0;
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-          const uint32_t g = q < 4 ? h : 1u - h;
-          const f32x4 c = *reinterpret_cast<const f32x4*>(sC + idx * D + 16 * ((q % 4) / 2) + 8 * g + 4 * (q % 2));
+          const uint32_t g2 = q < 4 ? h : 1u - h;
+          const f32x4 c = *reinterpret_cast<const f32x4*>(sC + idx * D + 16 * ((q % 4) / 2) + 8 * g2 + 4 * (q % 2));
           const float* xv = q < 4 ? xs + 4 * q : xo + 4 * (q - 4);
           float x0 = xv[0], x1 = xv[1], x2 = xv[2], x3 = xv[3];
           // keeps the float64 conversions of x inside this rare loop (hoisted
@@ -319,71 +406,72 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(3, 3
         bi = bj;
         if (h == 0) ++rechecks;
       }
+      bi = __shfl(bi, (int)col);  // lane col (h = 0) decided for both halves
     }
-    bi = __shfl(bi, (int)col);  // lane col (h = 0) decided for both halves
     if (valid && h == 0) {
       assign[p] = bi;
-      atomicAdd(&scnt[bi], 1u);
+      if ((uint32_t)bi < (uint32_t)K) atomicAdd(&scnt[bi], 1u);  // (a point with a NaN has no cluster)
     }
-    // update: x transposed through LDS, one-hot assignments as the A operand
+    if (h == 0) ab[wv][col] = valid ? (uint16_t)bi : 0xFFFFu;
+    wave_sync();
+    // Update. 16 points per instruction: lane (col, h) supplies A[col][8h + j]
+    // = [a_p = blk * 32 + col] and B[8h + j][col] = x[p][col] (as three pieces)
+    // for the points p = 16 kc + 8h + j, j = 0..7. A transposing read takes
+    // four rows (points) of 16 columns (dims) per 16 lanes: lane l names the
+    // eight bytes of row l / 4, columns 4 (l % 4) .., and receives column l of
+    // the four rows.
+    const uint32_t c0 = col * 0x10001u, c1 = c0 + 0x200020u;
 #pragma unroll
-    for (int t = 0; t < 16; ++t) xt[wv][16 * (t / 8) + 2 * (t % 8) + h][col] = xs[t];  // xs[t] is dim 16 (t / 8) + 8h + t % 8
-    if (h == 0) ab[wv][col] = valid ? bi : -1;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    {
-      // 16 points per instruction: lane (col, h) supplies A[col][8h + j] =
-      // [a_p = blk * 32 + col] and B[8h + j][col] = x[p][col] (as three
-      // pieces) for the points p = 16 kc + 8h + j, j = 0..7
-      const float* xrow = &xt[wv][16 * (col / 16) + 2 * (col % 8) + (col / 8) % 2][0];
+    for (int kc = 0; kc < 2; ++kc) {
+      const uint4 aw = *reinterpret_cast<const uint4*>(&ab[wv][16 * kc + 8 * h]);
+      const uint32_t a4[4] = {aw.x, aw.y, aw.z, aw.w};
+      uint32_t o0[4], o1[4];
 #pragma unroll
-      for (int kc = 0; kc < 2; ++kc) {
-        const f32x4 xa = *reinterpret_cast<const f32x4*>(xrow + 16 * kc + 8 * h);
-        const f32x4 xb = *reinterpret_cast<const f32x4*>(xrow + 16 * kc + 8 * h + 4);
-        const int4 aa = *reinterpret_cast<const int4*>(&ab[wv][16 * kc + 8 * h]);
-        const int4 ac = *reinterpret_cast<const int4*>(&ab[wv][16 * kc + 8 * h + 4]);
-        const float xv[8] = {xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w};
-        const int av[8] = {aa.x, aa.y, aa.z, aa.w, ac.x, ac.y, ac.z, ac.w};
-        bf16x8 ph, pm, pl, o0, o1;
+      for (int j = 0; j < 4; ++j) {
+        o0[j] = one_hot2(a4[j], c0);
+        o1[j] = one_hot2(a4[j], c1);
+      }
+      const bf16x8 v0 = as_bf16x8(make_uint4(o0[0], o0[1], o0[2], o0[3]));
+      const bf16x8 v1 = as_bf16x8(make_uint4(o1[0], o1[1], o1[2], o1[3]));
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          __bf16 vh, vm, vl;
-          split_bf16x3(xv[j], vh, vm, vl);
-          ph[j] = vh;
-          pm[j] = vm;
-          pl[j] = vl;
-          o0[j] = bf16_bits(av[j] == (int)col ? 0x3F80u : 0u);
-          o1[j] = bf16_bits(av[j] == (int)(32 + col) ? 0x3F80u : 0u);
+      for (int piece = 0; piece < 3; ++piece) {
+        s16x4 half[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const uint32_t p0 = 16 * kc + 8 * h + 4 * q, l = lane & 15u;
+          const uint32_t chunk = (2 * (col / 16) + (l % 4) / 2) ^ ((p0 / 4) % 4);
+          half[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (lds_s16x4*)(reinterpret_cast<short*>(&xp[wv][piece][p0 + l / 4][chunk]) + 4 * (l % 2)));
         }
-        sum0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o0, ph, sum0, 0, 0, 0);
-        sum1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o1, ph, sum1, 0, 0, 0);
-        sum0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o0, pm, sum0, 0, 0, 0);
-        sum1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o1, pm, sum1, 0, 0, 0);
-        sum0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o0, pl, sum0, 0, 0, 0);
-        sum1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o1, pl, sum1, 0, 0, 0);
+        const uint2 x0 = __builtin_bit_cast(uint2, half[0]), x1 = __builtin_bit_cast(uint2, half[1]);
+        const bf16x8 xv = as_bf16x8(make_uint4(x0.x, x0.y, x1.x, x1.y));
+        sum0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v0, xv, sum0, 0, 0, 0);
+        sum1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v1, xv, sum1, 0, 0, 0);
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
     if ((it + 1) % kKmFlushIters == 0 || it + 1 == iters) {
       // D layout: register r of lane (col, h) is cluster 8 (r / 4) + 4 h + r % 4 (+ 32 for sum1), dim col
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int c = 8 * (r / 4) + 4 * (int)h + (r % 4);
-        atomicAdd(&s64[c * D + col], (double)sum0[r]);
-        atomicAdd(&s64[(32 + c) * D + col], (double)sum1[r]);
+      for (int q = 0; q < 16; ++q) {
+        const int c = 8 * (q / 4) + 4 * (int)h + (q % 4);
+        atomicAdd(&s64[c * D + col], (double)sum0[q]);
+        atomicAdd(&s64[(32 + c) * D + col], (double)sum1[q]);
       }
       sum0 = f32x16{};
       sum1 = f32x16{};
     }
-#pragma unroll
-    for (int s = 0; s < 16; ++s) xs[s] = xn[s];
+  };
+  float xa[16], xb[16];
+  load_group(X, N, wave_g, groups, col, h, xa);
+  for (uint64_t it = 0; it < iters; it += 2) {
+    group(it, xa, xb);
+    if (it + 1 < iters) group(it + 1, xb, xa);
   }
+  if (rechecks) atomicAdd(&s_rechecks, rechecks);
   __syncthreads();
-  if (rechecks) atomicAdd(n_recheck, rechecks);
-  if (tmin < kTinyBits - 1u) atomicOr(tiny, 1ull);
+  if (threadIdx.x == 0 && s_rechecks) atomicAdd(n_recheck, (unsigned long long)s_rechecks);
+  if (any_tiny) atomicOr(tiny, 1ull);
   for (int i = threadIdx.x; i < K * D; i += blockDim.x) part_sum[(uint64_t)blockIdx.x * K * D + i] = s64[i];
   if (threadIdx.x < K) part_cnt[(uint64_t)blockIdx.x * K + threadIdx.x] = scnt[threadIdx.x];
 }

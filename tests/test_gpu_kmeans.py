@@ -228,3 +228,50 @@ def test_full_config_16m(torch):
         worst_rel = max(worst_rel, float((err[big] / np.abs(S[big])).max(initial=0.0)))
     print(f"largest plain relative sum error {worst_rel:.3e}")
     assert st["km_rechecked"] < len(X) // 100
+
+
+# d = 32, k = 64 around a workgroup's twelve groups of 32 points, one and two
+# passes of 256 workgroups, with what its rules turn on: zeros among the
+# coordinates, points midway between two centroids (decided in float64), equal
+# centroids (the lowest index), scores of both signs and of any size
+@pytest.mark.parametrize("n,kind", [
+    (383, "zeros"), (384, "ties"), (385, "ties"), (98_304, "zeros"), (98_305, "far"), (200_003, "ties"), (150_000, "near"),
+])
+def test_mfma_path_edges(torch, n, kind):
+    rng = np.random.default_rng(n)
+    Cn = rng.normal(size=(64, 32)).astype(np.float32)
+    X = (Cn[rng.integers(0, 64, n)] + rng.normal(size=(n, 32)) * 0.3).astype(np.float32)
+    if kind == "zeros":
+        X[rng.random(X.shape) < 0.7] = 0.0
+        Cn[rng.random(Cn.shape) < 0.5] = 0.0
+    elif kind == "ties":
+        Cn[40:] = Cn[:24]
+        Cn = np.round(Cn * 8) / 8
+        i, j = rng.integers(0, 64, n), rng.integers(0, 64, n)
+        X = ((Cn[i] + Cn[j]) / 2).astype(np.float32)  # exact
+    elif kind == "far":  # a common offset: norms far above the distances
+        Cn += 100.0
+        X += 100.0
+    else:  # centroids within float32 rounding of each other
+        Cn = (Cn[:1] + rng.normal(size=(64, 32)) * 1e-6).astype(np.float32)
+        X = (Cn[:1] + rng.normal(size=(n, 32)) * 1e-3).astype(np.float32)
+    a, s, c, cent, st = _run(torch, X, Cn)
+    assert st["strategy_used"] == 1  # the matrix-core path
+    if kind == "ties":
+        assert np.array_equal(a, oracle.kmeans_distances(X, Cn).argmin(axis=1))
+    else:
+        _check_assign(X, Cn, a)
+    _check_update(X, Cn, a, s, c, cent)
+
+
+def test_mfma_path_points_that_are_no_numbers(torch):
+    """The other points keep their clusters and the counts leave such points out."""
+    rng = np.random.default_rng(5)
+    Cn = rng.normal(size=(64, 32)).astype(np.float32)
+    X = (Cn[rng.integers(0, 64, 5_000)] + rng.normal(size=(5_000, 32)) * 0.3).astype(np.float32)
+    bad = np.arange(17, 5_000, 97)
+    X[bad, bad % 32] = np.where(bad % 2, np.nan, np.inf)
+    a, s, c, cent, st = _run(torch, X, Cn)
+    ok = np.setdiff1d(np.arange(5_000), bad)
+    _check_assign(X, Cn, a, ok)
+    assert np.array_equal(c, np.bincount(a[ok], minlength=64) + np.bincount(a[bad][a[bad] < 64], minlength=64))
