@@ -1059,43 +1059,68 @@ __global__ __launch_bounds__(256) void k_int_gather(IntTable T, uint2* __restric
 // Device-wide exclusive scan of a (in place): per-block sums, scan of sums, add back.
 constexpr uint32_t kScanTile = 4096;
 
-__global__ __launch_bounds__(256) void k_scan_blocks(const uint32_t* __restrict__ a, uint64_t n, uint32_t* __restrict__ sums) {
-  __shared__ uint32_t s;
-  if (threadIdx.x == 0) s = 0;
-  __syncthreads();
-  uint32_t c = 0;
-  const uint64_t base = (uint64_t)blockIdx.x * kScanTile;
-  for (uint32_t q = threadIdx.x; q < kScanTile; q += blockDim.x)
-    if (base + q < n) c += a[base + q];
-  atomicAdd(&s, c);
-  __syncthreads();
-  if (threadIdx.x == 0) sums[blockIdx.x] = s;
+// The tile's entries of this thread, 16 in a row, all in flight at once (one
+// after the other, with a barrier each: 8.1 and 12.9 us for 308,000 entries,
+// now 2.7 and 3.2).
+constexpr uint32_t kScanThreads = 256, kScanPer = kScanTile / kScanThreads;
+MR_DEV void scan_load(const uint32_t* __restrict__ a, uint64_t n, uint64_t at, uint32_t (&x)[kScanPer]) {
+  if (at + kScanPer <= n && ((uintptr_t)a & 15u) == 0) {
+#pragma unroll
+    for (uint32_t q = 0; q < kScanPer; q += 4) {
+      const uint4 v = gload16(a + at + q);
+      x[q] = v.x;
+      x[q + 1] = v.y;
+      x[q + 2] = v.z;
+      x[q + 3] = v.w;
+    }
+  } else {
+#pragma unroll
+    for (uint32_t q = 0; q < kScanPer; ++q) x[q] = at + q < n ? gp(a)[at + q] : 0u;
+  }
 }
 
-__global__ __launch_bounds__(256) void k_scan_apply(uint32_t* __restrict__ a, uint64_t n, const uint32_t* __restrict__ sums) {
-  __shared__ uint32_t ws[256 / kWave];
-  const uint64_t base = (uint64_t)blockIdx.x * kScanTile;
-  uint32_t carry = sums[blockIdx.x];
-  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
-  for (uint32_t q0 = 0; q0 < kScanTile; q0 += blockDim.x) {
-    const uint64_t i = base + q0 + threadIdx.x;
-    const uint32_t x = i < n ? a[i] : 0u;
-    uint32_t inc = x;
+__global__ __launch_bounds__(kScanThreads) void k_scan_blocks(const uint32_t* __restrict__ a, uint64_t n,
+                                                              uint32_t* __restrict__ sums) {
+  __shared__ uint32_t ws[kScanThreads / kWave];
+  uint32_t x[kScanPer], c = 0;
+  scan_load(a, n, (uint64_t)blockIdx.x * kScanTile + threadIdx.x * kScanPer, x);
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const uint32_t t = __shfl_up(inc, o);
-      if (lane >= (uint32_t)o) inc += t;
-    }
-    if (lane == kWave - 1) ws[wv] = inc;
-    __syncthreads();
-    uint32_t pre = carry, tot = 0;
-    for (uint32_t w = 0; w < blockDim.x / kWave; ++w) {
-      if (w < wv) pre += ws[w];
-      tot += ws[w];
-    }
-    if (i < n) a[i] = pre + inc - x;
-    carry += tot;
-    __syncthreads();
+  for (uint32_t q = 0; q < kScanPer; ++q) c += x[q];
+  const uint32_t incl = wave_incl_scan(c);
+  if (lane_id() == kWave - 1) ws[threadIdx.x / kWave] = incl;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t s = 0;
+    for (uint32_t w = 0; w < kScanThreads / kWave; ++w) s += ws[w];
+    sums[blockIdx.x] = s;
+  }
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_apply(uint32_t* __restrict__ a, uint64_t n, const uint32_t* __restrict__ sums) {
+  __shared__ uint32_t ws[kScanThreads / kWave];
+  const uint64_t at = (uint64_t)blockIdx.x * kScanTile + threadIdx.x * kScanPer;
+  uint32_t run = sums[blockIdx.x], x[kScanPer], c = 0;
+  scan_load(a, n, at, x);
+#pragma unroll
+  for (uint32_t q = 0; q < kScanPer; ++q) c += x[q];
+  const uint32_t incl = wave_incl_scan(c), wv = threadIdx.x / kWave;
+  if (lane_id() == kWave - 1) ws[wv] = incl;
+  __syncthreads();
+  for (uint32_t w = 0; w < wv; ++w) run += ws[w];
+  run += incl - c;
+#pragma unroll
+  for (uint32_t q = 0; q < kScanPer; ++q) {
+    const uint32_t y = x[q];
+    x[q] = run;
+    run += y;
+  }
+  if (at + kScanPer <= n && ((uintptr_t)a & 15u) == 0) {
+#pragma unroll
+    for (uint32_t q = 0; q < kScanPer; q += 4) gstore16(a + at + q, make_uint4(x[q], x[q + 1], x[q + 2], x[q + 3]));
+  } else {
+#pragma unroll
+    for (uint32_t q = 0; q < kScanPer; ++q)
+      if (at + q < n) gp(a)[at + q] = x[q];
   }
 }
 
@@ -1257,9 +1282,9 @@ hipError_t scan_exclusive_u32(uint32_t* a, uint64_t n, uint32_t* sums, unsigned 
     return hipGetLastError();
   }
   const uint32_t sb = (uint32_t)((n + kScanTile - 1) / kScanTile);
-  hipLaunchKernelGGL(k_scan_blocks, dim3(sb ? sb : 1), dim3(256), 0, s, a, n, sums);
+  hipLaunchKernelGGL(k_scan_blocks, dim3(sb ? sb : 1), dim3(kScanThreads), 0, s, a, n, sums);
   hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, sums, sb ? sb : 1, total, E);
-  hipLaunchKernelGGL(k_scan_apply, dim3(sb ? sb : 1), dim3(256), 0, s, a, n, sums);
+  hipLaunchKernelGGL(k_scan_apply, dim3(sb ? sb : 1), dim3(kScanThreads), 0, s, a, n, sums);
   return hipGetLastError();
 }
 

@@ -1944,10 +1944,10 @@ int words_max_lds_log2() { return 12; }
 // ----------------------------------------------------------------------------
 
 constexpr uint32_t kLinkMaxUrl = 4095;
-constexpr uint32_t kLinkFindThreads = 256;
-constexpr uint32_t kLinkGroup = 64;   // input bytes per lane per step (four 16-byte chunks)
-constexpr uint32_t kLinkBuf = 4096;   // marker offsets staged per workgroup
-constexpr uint32_t kLinkStepMax = kLinkFindThreads * (kLinkGroup / 9 + 1);  // markers one step can add
+constexpr uint32_t kLinkFindThreads = 1024;
+constexpr uint32_t kLinkBlocks = 2;   // 16-byte blocks per lane and step
+constexpr uint32_t kLinkBuf = 512;    // marker offsets staged per wave
+constexpr uint32_t kLinkStepMax = kWave * kLinkBlocks * 2;  // markers a wave can add in a step (nine bytes each)
 constexpr uint32_t kMarkW0 = 0x6820613Cu;  // '<' 'a' ' ' 'h'
 constexpr uint32_t kMarkW1 = 0x3D666572u;  // 'r' 'e' 'f' '='
 constexpr uint32_t kMarkW2 = 0x22u;        // '"'
@@ -1973,55 +1973,112 @@ __global__ void k_links_zero(unsigned long long* n_marks) {
 
 // Input offsets of every marker inside the valid byte range of job 0. Marks
 // past mark_cap are counted but not stored (the caller grows the list and
-// runs again).
-__global__ __launch_bounds__(kLinkFindThreads) void k_links_find(const WordJob* __restrict__ jobs, uint32_t* __restrict__ marks,
-                                                                 unsigned long long* __restrict__ n_marks, uint64_t mark_cap) {
-  __shared__ uint32_t buf[kLinkBuf];
-  __shared__ uint32_t cnt;
+// runs again). Bound by the read of the input: 1 GiB in 227 us, 4.7 TB/s. A wave reads
+// neighbouring blocks, takes the bytes after a block from the next lane, and
+// looks closer only at a '<' with an 'a' behind it; no barrier until the end.
+// (Four blocks a lane of its own, every '<' compared in full, and a barrier and
+// a common buffer per step of 256 threads: 276 us.)
+__global__ __launch_bounds__(kLinkFindThreads, 8) void k_links_find(const WordJob* __restrict__ jobs, uint32_t* __restrict__ marks,
+                                                                    unsigned long long* __restrict__ n_marks, uint64_t mark_cap) {
+  constexpr uint32_t kWaves = kLinkFindThreads / kWave;
+  __shared__ uint32_t bufs[kWaves][kLinkBuf];
+  __shared__ uint32_t cnts[kWaves];
   __shared__ unsigned long long base;
   const WordJob J = jobs[0];
   const uint64_t a_in = (uint64_t)J.in;
   const uint64_t a0 = a_in + J.st->valid_lo, a1 = a_in + J.st->valid_hi;
-  const uint64_t g0 = a0 / kLinkGroup, g1 = (a1 + kLinkGroup - 1) / kLinkGroup;
-  if (threadIdx.x == 0) cnt = 0;
-  __syncthreads();
-  auto flush = [&]() {
-    if (threadIdx.x == 0) base = cnt ? atomicAdd(n_marks, (unsigned long long)cnt) : 0ull;
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < cnt; i += blockDim.x)
-      if (base + i < mark_cap) marks[base + i] = buf[i];
-    __syncthreads();
-    if (threadIdx.x == 0) cnt = 0;
-    __syncthreads();
+  const uint64_t b0 = a0 / 16, b1 = (a1 + 15) / 16;  // blocks
+  const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+  uint32_t* const buf = bufs[wv];
+  uint32_t* const cnt = &cnts[wv];
+  if (lane == 0) *cnt = 0;
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   };
-  // the step base is the same for every lane of the workgroup, so all lanes meet every barrier
-  for (uint64_t step = g0 + (uint64_t)blockIdx.x * blockDim.x; step < g1; step += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t g = step + threadIdx.x;
-    if (g < g1) {
-      const uint64_t ga = g * kLinkGroup;
-      uint4 blk[5];  // the group and the block after it (for markers that cross the group's end)
+  wave_sync();
+  // this lane's blocks of the wave's stretch of a step, and the block after the stretch
+  auto load = [&](uint64_t step, uint4 (&blk)[kLinkBlocks + 1]) {
+    const uint64_t first = step + __builtin_amdgcn_readfirstlane(wv) * (kWave * kLinkBlocks);
+    if (first >= b0 && first + kWave * kLinkBlocks < b1) {  // the same for all lanes
+      const uint8_t* at = reinterpret_cast<const uint8_t*>(first * 16);
 #pragma unroll
-      for (int c = 0; c < 5; ++c) blk[c] = load_block(a0, a1, ga + 16ull * c);
+      for (uint32_t u = 0; u < kLinkBlocks; ++u) blk[u] = gload16(at + (u * kWave + lane) * 16);
+      blk[kLinkBlocks] = gload16(at + kWave * kLinkBlocks * 16);
+    } else {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        uint32_t cand = byte_candidates16(blk[c], '<');
-        if (!cand) continue;
-        const uint32_t w[8] = {blk[c].x, blk[c].y, blk[c].z, blk[c].w, blk[c + 1].x, blk[c + 1].y, blk[c + 1].z, blk[c + 1].w};
-        while (cand) {
-          const uint32_t sb = __builtin_ctz(cand);
-          cand &= cand - 1;
-          const uint64_t pa = ga + 16ull * c + sb;
+      for (uint32_t u = 0; u < kLinkBlocks; ++u) blk[u] = load_block(a0, a1, (first + u * kWave + lane) * 16);
+      blk[kLinkBlocks] = load_block(a0, a1, (first + kWave * kLinkBlocks) * 16);
+    }
+  };
+  // (the steps are the same for every lane, which the lane shifts need)
+  const uint64_t per_step = (uint64_t)kLinkFindThreads * kLinkBlocks;
+  uint64_t step = b0 + blockIdx.x * per_step;
+  uint4 next[kLinkBlocks + 1];
+  load(step, next);
+  for (; step < b1; step += gridDim.x * per_step) {
+    uint4 blk[kLinkBlocks + 1];
+#pragma unroll
+    for (uint32_t u = 0; u <= kLinkBlocks; ++u) blk[u] = next[u];
+    load(step + gridDim.x * per_step, next);
+    uint32_t any = 0;
+    uint2 after[kLinkBlocks];  // the first eight bytes of the block after
+    auto hits = [&](uint32_t u, uint32_t i) {  // top bits of the word's bytes that are '<' with an 'a' behind them
+      const uint32_t w[5] = {blk[u].x, blk[u].y, blk[u].z, blk[u].w, after[u].x};
+      const uint32_t d = (w[i] ^ 0x3C3C3C3Cu) | (__builtin_amdgcn_alignbyte(w[i + 1], w[i], 1) ^ 0x61616161u);
+      return ~(((d & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | d) & 0x80808080u;  // the zero bytes of d
+    };
+#pragma unroll
+    for (uint32_t u = 0; u < kLinkBlocks; ++u) {
+      after[u].x = from_next_lane(blk[u].x, (uint32_t)__builtin_amdgcn_readfirstlane((int)blk[u + 1].x));
+      after[u].y = from_next_lane(blk[u].y, (uint32_t)__builtin_amdgcn_readfirstlane((int)blk[u + 1].y));
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i) any |= hits(u, i);
+    }
+    if (any) {
+#pragma unroll
+      for (uint32_t u = 0; u < kLinkBlocks; ++u) {
+        const uint32_t w[8] = {blk[u].x, blk[u].y, blk[u].z, blk[u].w, after[u].x, after[u].y, 0u, 0u};
+        const uint64_t at = (step + wv * (kWave * kLinkBlocks) + u * kWave + lane) * 16;
+        // the top bits of the four words' bytes as one mask: byte b of the block is bit b
+        uint32_t m = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) m |= (((hits(u, i) >> 7) * 0x10204080u) >> 28) << (4 * i);
+        for (; m; m &= m - 1) {
+          const uint32_t sb = __builtin_ctz(m);
+          const uint64_t pa = at + sb;
           if (pa < a0 || pa + 9 > a1) continue;
           const uint4 k = extract16(w, sb, 9);
-          if (k.x == kMarkW0 && k.y == kMarkW1 && k.z == kMarkW2) buf[atomicAdd(&cnt, 1u)] = (uint32_t)(pa - a_in);
+          if (k.x == kMarkW0 && k.y == kMarkW1 && k.z == kMarkW2) buf[atomicAdd(cnt, 1u)] = (uint32_t)(pa - a_in);
         }
       }
     }
-    __syncthreads();
-    if (cnt > kLinkBuf - kLinkStepMax) flush();
+    if (__ballot(any)) {
+      wave_sync();
+      const uint32_t c = *cnt;
+      if (c > kLinkBuf - kLinkStepMax) {  // the wave's buffer may not take another step
+        unsigned long long at = 0;
+        if (lane == 0) at = atomicAdd(n_marks, (unsigned long long)c);
+        at = __shfl(at, 0);
+        for (uint32_t i = lane; i < c; i += kWave)
+          if (at + i < mark_cap) marks[at + i] = buf[i];
+        wave_sync();
+        if (lane == 0) *cnt = 0;
+        wave_sync();
+      }
+    }
   }
+  // what is left, in one place for the workgroup: an update of the one counter takes about 35 ns
   __syncthreads();
-  flush();
+  uint32_t before = 0, all = 0;
+  for (uint32_t w = 0; w < kWaves; ++w) {
+    if (w < wv) before += cnts[w];
+    all += cnts[w];
+  }
+  if (threadIdx.x == 0 && all) base = atomicAdd(n_marks, (unsigned long long)all);
+  __syncthreads();
+  for (uint32_t i = lane; i < *cnt; i += kWave)
+    if (base + before + i < mark_cap) marks[base + before + i] = buf[i];
 }
 
 // One lane per marker: the record, the closing quote, the table insert and
@@ -2126,7 +2183,7 @@ hipError_t words_enqueue_prep(const WordsLaunch& L, hipStream_t s) {
 hipError_t words_enqueue_map(const WordsLaunch& L, hipStream_t s) {
   if (L.links) {
     hipLaunchKernelGGL(k_links_zero, dim3(1), dim3(64), 0, s, L.link_n);
-    hipLaunchKernelGGL(k_links_find, dim3(L.link_grid), dim3(kLinkFindThreads), 0, s, L.jobs, L.link_marks, L.link_n,
+    hipLaunchKernelGGL(k_links_find, dim3((L.link_grid + 3) / 4), dim3(kLinkFindThreads), 0, s, L.jobs, L.link_marks, L.link_n,
                        L.link_cap);
     hipLaunchKernelGGL(k_links_insert, dim3(L.link_grid), dim3(256), 0, s, L.jobs, L.link_marks, L.link_n, L.link_cap,
                        L.link_pair_slot, L.link_pair_file, L.debug_hash);

@@ -139,3 +139,22 @@ def test_capacity_and_bad_offsets(torch):
     with pytest.raises(MRError) as e:
         job.links(d, _dev(torch, bad.view(np.int64)))
     assert e.value.status == -1
+
+
+# a wave's stretch of 2 KiB and a workgroup's of 32 KiB: markers across every
+# boundary between blocks, lanes, stretches and steps, stretches full of them
+# (more than a wave's buffer takes in a few steps), '<a' that is no marker, and
+# inputs that begin and end anywhere in a block
+@pytest.mark.parametrize("shift,size,every", [(0, 70_000, 2039), (5, 70_000, 1021), (13, 33_000, 11), (3, 2_100_000, 13), (0, 9, 9), (15, 10, 9)])
+def test_markers_across_blocks_and_full_stretches(torch, shift, size, every):
+    buf = np.frombuffer(b"<a hr" * (size // 5 + 1), np.uint8)[:size].copy()
+    mark = np.frombuffer(b'<a href="u"', np.uint8)
+    for at in range(0, size, every):
+        buf[at:at + 11] = mark[:size - at]
+    big = torch.zeros(size + 64, dtype=torch.uint8, device="cuda:0")
+    big[shift:shift + size] = _dev(torch, buf)
+    from paper_1309_0215_amd import Job
+    res = Job(device=0).links(big[shift:shift + size])
+    want = oracle.links(buf)
+    assert res.items() == want.items()
+    assert res.stats["n_items"] == int(want.counts.sum())
