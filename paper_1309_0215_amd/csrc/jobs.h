@@ -31,11 +31,6 @@ struct JobState {
   uint32_t rtile_base;             // first record tile of this job
   uint32_t sort_spills;            // sort buckets too large for LDS (sorted in global memory)
   uint32_t pad;
-  // Jobs with partition queues: a bit per partition whose keys the table holds
-  // any of, and per partition with a key of up to 16 bytes there from the map
-  // (the partition's sums then have to meet it in the table).
-  uint32_t in_table[kMaxWordParts / 32];
-  uint32_t in_table_map[kMaxWordParts / 32];
 };
 
 static_assert(sizeof(JobState) % 8 == 0, "JobState is cleared as 32-bit words");
@@ -56,7 +51,11 @@ struct WordJob {
   void* recs;                // compacted records [cap]
   void* recs2;               // bucket-ordered records [cap]
   uint32_t* rec_bucket;      // bucket of each compacted record [cap]
-  void* splitters;           // sort splitters [kMaxBuckets - 1]
+  // sort splitters [kMaxBuckets - 1]; until the sort, of a job with partition
+  // queues, a bit per partition whose keys the table holds any of, then a bit
+  // per partition with a key of up to 16 bytes there from the map (the
+  // partition's sums then have to meet it in the table)
+  void* splitters;
   uint8_t* out_key_bytes;    // outputs (device), may be NULL when capacities are 0
   uint64_t* out_key_offsets;
   uint32_t* out_values;

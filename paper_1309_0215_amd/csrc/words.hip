@@ -267,6 +267,11 @@ MR_DEV bool g_insert(const WordJob& J, uint64_t vlo, uint64_t vhi, uint64_t off,
   return false;
 }
 
+// The job's two partition maps (WordJob::splitters).
+constexpr uint32_t kPartMapWords = kMaxWordParts / 32;
+MR_DEV uint32_t* in_table(const WordJob& J) { return static_cast<uint32_t*>(J.splitters); }
+MR_DEV uint32_t* in_table_map(const WordJob& J) { return static_cast<uint32_t*>(J.splitters) + kPartMapWords; }
+
 // Sets the bit of the partition of hash h in one of the job's partition maps;
 // a read first, since an atomic on one word from many workgroups is slow.
 MR_DEV void mark_part(const WordJob& J, uint32_t* map, uint64_t h) {
@@ -288,6 +293,7 @@ __global__ __launch_bounds__(kWave) void k_words_one(WordJob J, WordJob* __restr
                                                      uint64_t total_tiles) {
   uint32_t* st = reinterpret_cast<uint32_t*>(J.st);
   for (uint32_t i = threadIdx.x; i < (uint32_t)(sizeof(JobState) / 4); i += kWave) st[i] = 0u;
+  if (threadIdx.x < 2 * kPartMapWords) in_table(J)[threadIdx.x] = 0u;
   __syncthreads();
   if (threadIdx.x == 0) {
     *job = J;
@@ -307,6 +313,7 @@ __global__ void k_words_prep(const WordJob* __restrict__ jobs, uint32_t n_jobs, 
   const uint32_t j = blockIdx.y;
   if (j >= n_jobs) return;
   const WordJob J = jobs[j];
+  if (blockIdx.x == 0 && threadIdx.x < 2 * kPartMapWords) in_table(J)[threadIdx.x] = 0u;
   if (clear) {
     uint32_t* w = reinterpret_cast<uint32_t*>(J.st);
     for (uint32_t i = threadIdx.x; i < (uint32_t)(sizeof(JobState) / 4); i += blockDim.x) w[i] = 0u;
@@ -471,8 +478,8 @@ MR_DEV void lds_flush_parts(LdsTable<L>& T, const WordJob& J, uint32_t job, uint
       const uint4 k = T.key[i];
       const uint64_t h = key_hash16(k, len, debug_hash);
       if (!queue_append(J, mfill, sfill, (uint32_t)(h >> J.part_shift), k, T.off[i], len, T.cnt[i], job)) {
-        mark_part(J, J.st->in_table, h);
-        mark_part(J, J.st->in_table_map, h);
+        mark_part(J, in_table(J), h);
+        mark_part(J, in_table_map(J), h);
         g_insert<true>(J, vlo, vhi, T.off[i], len, h, k, T.cnt[i], debug_hash);
       }
     }
@@ -714,15 +721,15 @@ __global__ __launch_bounds__(kMapThreads) void k_words_map(const WordJob* __rest
         if (lng) {
           const uint64_t wlen = word_length_slow(J, vlo, vhi, off);
           const uint64_t wh = key_hash_global(J.in, off, wlen, debug_hash);
-          mark_part(J, J.st->in_table, wh);
+          mark_part(J, in_table(J), wh);
           g_insert<false>(J, vlo, vhi, off, wlen, wh, make_uint4(0, 0, 0, 0), 1u, debug_hash);
           return;
         }
         const uint64_t h64 = hash_from32(h);
         // into this workgroup's sub-queue of the key's partition
         if (J.mq && queue_append(J, s_mfill, s_sfill, (uint32_t)(h64 >> J.part_shift), k, off, len, v, j)) return;
-        mark_part(J, J.st->in_table, h64);
-        mark_part(J, J.st->in_table_map, h64);
+        mark_part(J, in_table(J), h64);
+        mark_part(J, in_table_map(J), h64);
         g_insert<true>(J, vlo, vhi, off, len, h64, k, v, debug_hash);
       };
       // the home-group lookup could not decide: the full insert, retried
@@ -1094,7 +1101,7 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
   }
   // the table must hold no key of this partition: neither the map's nor an earlier flush's
   for (uint32_t j = threadIdx.x; j < n_jobs; j += blockDim.x) {
-    s_cnt[j] = flushed || (gp(jobs[j].st)->in_table_map[p >> 5] >> (p & 31u) & 1u) ? kNotDirect : 0u;
+    s_cnt[j] = flushed || (gp(in_table_map(jobs[j]))[p >> 5] >> (p & 31u) & 1u) ? kNotDirect : 0u;
     s_bytes[j] = 0;
   }
   __syncthreads();
@@ -1104,7 +1111,7 @@ __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __re
     const uint32_t room = (uint32_t)(jobs[j].cap / kMaxWordParts), c = s_cnt[j];
     staged[j * kMaxWordParts + p] = c & kNotDirect ? 0u : c < room ? c : room;
     staged_bytes[j * kMaxWordParts + p] = s_bytes[j];
-    if (s_tabled[j >> 5] >> (j & 31u) & 1u) mark_part(jobs[j], jobs[j].st->in_table, (uint64_t)p << jobs[j].part_shift);
+    if (s_tabled[j >> 5] >> (j & 31u) & 1u) mark_part(jobs[j], in_table(jobs[j]), (uint64_t)p << jobs[j].part_shift);
   }
 }
 
@@ -1200,8 +1207,8 @@ __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob
       const uint32_t p1 = J.region_log2 ? (uint32_t)((i0 + item - 1) >> J.region_log2) : kMaxWordParts - 1;
       uint32_t any = 0;
 #pragma unroll
-      for (uint32_t w = 0; w < kMaxWordParts / 32; ++w) {
-        uint32_t bits = gp(J.st)->in_table[w];
+      for (uint32_t w = 0; w < kPartMapWords; ++w) {
+        uint32_t bits = gp(in_table(J))[w];
         if (w == p0 / 32) bits &= ~0u << (p0 & 31u);
         if (w == p1 / 32) bits &= ~0u >> (31u - (p1 & 31u));
         any |= w >= p0 / 32 && w <= p1 / 32 ? bits : 0u;
