@@ -1268,11 +1268,20 @@ uint64_t int_table_slots(const mr_job* job, mr_map_kind kind, uint64_t bytes, ui
 struct IntHashNeed {
   uint64_t slots, scratch;
 };
-IntHashNeed int_hash_need(const mr_job* job, mr_map_kind kind, uint64_t bytes, uint64_t n, uint64_t R, uint32_t op) {
-  if (int_own_table(job)) return {int_table_slots(job, kind, bytes, n, R), hash_carve(R ? std::min(n, R) : n).bytes};
+IntHashNeed int_hash_need(const mr_job* job, mr_map_kind kind, uint64_t bytes, uint64_t n, uint64_t R, uint32_t op,
+                          bool own_table) {
+  if (own_table) return {int_table_slots(job, kind, bytes, n, R), hash_carve(R ? std::min(n, R) : n).bytes};
   const uint64_t sort = sort_carve(n, op).bytes;
   if (n < kHashTryMin) return {0, sort};
   return {kHashTrySlots, std::max(sort, hash_carve(kHashTrySlots).bytes)};
+}
+
+// Whether a table and then a scratch region of these sizes fit what a caller
+// workspace has left (library memory grows as needed).
+bool hash_fits(const mr_job* job, const IntHashNeed& h) {
+  if (!job->cws) return true;
+  const uint64_t at = align_up(align_up(job->cws_off, 256) + h.slots * kIntSlotBytes, h.slots ? 256 : 1);
+  return at + h.scratch <= job->cws_bytes;
 }
 
 // A batched integer item: the batch decides the container, gives the item
@@ -1280,6 +1289,7 @@ IntHashNeed int_hash_need(const mr_job* job, mr_map_kind kind, uint64_t bytes, u
 struct U32Ctx {
   mr_strategy strat;   // the container to run
   bool sel_used;       // the learned selector chose it
+  bool own_table;      // the hash container with a table for all keys
   IntSmall* sm;        // this item's state (device)
 };
 
@@ -1397,8 +1407,13 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
     MR_HIP(int_enqueue_dense_out(L, true, dc.vparts ? &dc.vp : nullptr, reinterpret_cast<uint32_t*>(sc + dc.o_tot), job->stream));
   }
   // The hash container without a table size of its own: inputs of few keys
-  // stay in the LDS caches and a small table; the others are radix sorted.
-  const bool own_table = strat == MR_STRAT_HASH && int_own_table(job);
+  // stay in the LDS caches and a small table; the others are radix sorted. A
+  // caller workspace that holds a table for a declared range but not the sort
+  // takes the table (5 M keys of 1,000: 120 KB against 40 MB).
+  bool own_table = strat == MR_STRAT_HASH && (ctx ? ctx->own_table : int_own_table(job));
+  if (strat == MR_STRAT_HASH && !own_table && !ctx)
+    own_table = !hash_fits(job, int_hash_need(job, kind, bytes, n, key_range, o, false)) &&
+                hash_fits(job, int_hash_need(job, kind, bytes, n, key_range, o, true));
   bool sorted = strat == MR_STRAT_SORT || (strat == MR_STRAT_HASH && !own_table && n < kHashTryMin);
   IntSmall hs;
   bool have_state = false;  // hs holds the final state already
@@ -1558,11 +1573,11 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
 struct KmCarve {
   uint64_t o_cn, o_cmax, o_nr, o_ps, o_pc, bytes;
 };
-KmCarve km_carve(uint32_t k, uint32_t d, uint32_t G, bool generic) {
+KmCarve km_carve(uint32_t k, uint32_t d, uint32_t G, bool generic, bool direct = false) {
   KmCarve r;
   Carve c;
-  const uint64_t nkb = (k + 31) / 32, packed = generic ? nkb * ((d + 7) / 8) * 1024 : 0;
-  r.o_cn = c.take(4ull * nkb * 32);
+  const uint64_t nkb = (k + 31) / 32, packed = generic && !direct ? nkb * ((d + 7) / 8) * 1024 : 0;
+  r.o_cn = c.take(direct ? 0 : 4ull * nkb * 32);
   r.o_cmax = c.take(8 * nkb);
   r.o_nr = c.take(16);
   r.o_ps = c.take(std::max<uint64_t>(8ull * G * k * d, packed));
@@ -1618,10 +1633,16 @@ mr_status run_kmeans(mr_job* job, const void* d_input, uint64_t bytes, mr_output
       L.upd.G /= 2;
       want = km_carve(k, d, L.upd.G, true).bytes;
     }
+    // or runs without the packed centroids; what fits neither reports the full need
+    if (!L.mfma && want > room) {
+      const uint64_t least = km_carve(k, d, 1, true, true).bytes;
+      L.direct = least <= room;
+      want = L.direct ? least : km_bytes(N, k, d, job->n_cu, false);
+    }
   }
   mr_status st = ensure_ws(job, want);
   if (st != MR_OK) return st;
-  while (L.upd.G > 1 && km_carve(k, d, L.upd.G, true).bytes > want) L.upd.G /= 2;  // (a redone matrix-core step)
+  while (!L.direct && L.upd.G > 1 && km_carve(k, d, L.upd.G, true).bytes > want) L.upd.G /= 2;  // (a redone matrix-core step)
   job->table_clean_bytes = 0;  // this scratch overwrites the word table region
   job->graph_valid = false;
   uint8_t* ws = job->ws;
@@ -1634,7 +1655,7 @@ mr_status run_kmeans(mr_job* job, const void* d_input, uint64_t bytes, mr_output
     L.cp = reinterpret_cast<float*>(ws + kc.o_ps);
     L.part_cnt = reinterpret_cast<uint32_t*>(ws + kc.o_pc);
   };
-  place(L.mfma ? km_carve(k, d, L.G, false) : km_carve(k, d, L.upd.G, true));
+  place(L.mfma ? km_carve(k, d, L.G, false) : km_carve(k, d, L.upd.G, true, L.direct));
   L.assign = out->assign;
   L.sums = out->sums;
   L.counts = out->counts;
@@ -1884,7 +1905,7 @@ extern "C" mr_status mr_workspace_bytes(const mr_job_config* cfg, mr_map_kind ki
           if (c == MR_STRAT_GLOBAL_ARRAY) t.add(key_range * 12 + 8);
           t.add(dense_carve(c, ne, key_range, op, (uint32_t)n_cu, true).bytes);
         } else if (c == MR_STRAT_HASH) {
-          const IntHashNeed h = int_hash_need(&tmp, kind, n, ne, key_range, op);
+          const IntHashNeed h = int_hash_need(&tmp, kind, n, ne, key_range, op, int_own_table(&tmp));
           if (h.slots) t.add(h.slots * kIntSlotBytes);
           t.add(h.scratch);
         } else {
@@ -2353,7 +2374,8 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
   }
   // the rule for the items the selector left to it; the regions for the largest item
   // (scratch_full: with the partitions that a small caller workspace goes without)
-  uint64_t dense_b = 0, dense_r = 0, table_s = 0, scratch_b = 0, scratch_full = 0;
+  uint64_t dense_b = 0, dense_r = 0, scratch_b = 0, scratch_full = 0;
+  IntHashNeed hash_h{0, 0}, hash_g{0, 0};  // the hash items' need, and with a table for all keys
   for (uint32_t q = 0; q < ni; ++q) {
     const mr_batch_item& it = items[ii[q]];
     const uint32_t op = (uint32_t)it.op;
@@ -2372,9 +2394,10 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
       scratch_b = std::max(scratch_b, dense_carve(strat[q], n, it.key_range, op, (uint32_t)job->n_cu, false).bytes);
       scratch_full = std::max(scratch_full, dense_carve(strat[q], n, it.key_range, op, (uint32_t)job->n_cu, true).bytes);
     } else if (strat[q] == MR_STRAT_HASH) {
-      const IntHashNeed h = int_hash_need(job, it.kind, it.input_bytes, n, it.key_range, op);
-      table_s = std::max(table_s, h.slots);
-      scratch_b = std::max(scratch_b, h.scratch);
+      const IntHashNeed h = int_hash_need(job, it.kind, it.input_bytes, n, it.key_range, op, int_own_table(job));
+      const IntHashNeed g = int_hash_need(job, it.kind, it.input_bytes, n, it.key_range, op, true);
+      hash_h = {std::max(hash_h.slots, h.slots), std::max(hash_h.scratch, h.scratch)};
+      hash_g = {std::max(hash_g.slots, g.slots), std::max(hash_g.scratch, g.scratch)};
     } else {
       scratch_b = std::max(scratch_b, sort_carve(n, op).bytes);
     }
@@ -2385,6 +2408,11 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
     if (st != MR_OK) return st;
     if (fresh) job->int_dense_R = dense_r;
   }
+  hash_h.scratch = std::max(hash_h.scratch, scratch_b);
+  hash_g.scratch = std::max(hash_g.scratch, scratch_b);
+  const bool own_table = int_own_table(job) || (!hash_fits(job, hash_h) && hash_fits(job, hash_g));
+  scratch_b = own_table ? hash_g.scratch : hash_h.scratch;
+  const uint64_t table_s = own_table ? hash_g.slots : hash_h.slots;
   if (table_s) {
     bool fresh = false;
     st = dev_region(job, kRegTable, &job->int_table, &job->int_table_bytes, table_s * kIntSlotBytes, table_s * kIntSlotBytes,
@@ -2407,7 +2435,7 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
   for (uint32_t q = 0; q < ni; ++q) {
     if (per[ii[q]] != MR_OK) continue;
     const mr_batch_item& it = items[ii[q]];
-    const U32Ctx ctx{strat[q], chosen[q] != 0, sm + q};
+    const U32Ctx ctx{strat[q], chosen[q] != 0, own_table, sm + q};
     st = run_u32(job, it.kind, it.op, it.d_input, it.input_bytes, it.key_range, &outs[ii[q]], &ctx);
     if (st == MR_ERR_HIP) return st;
     per[ii[q]] = st;

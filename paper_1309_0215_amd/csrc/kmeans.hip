@@ -879,6 +879,42 @@ __global__ __launch_bounds__(kFinalWaves * kWave) void k_km_final(const double* 
   }
 }
 
+// Any d, k in a caller workspace that the packed centroids do not fit (few
+// dimensions or clusters, whose single partial is smaller than they are): a
+// thread per point, float64 direct distances, sums by atomics on one partial.
+// (500,000 points, d = 64, k = 100: 48.7 ms, the packed path 0.19 ms.)
+__global__ void k_km_clear(double* __restrict__ sum, uint64_t n_sum, uint32_t* __restrict__ cnt, uint32_t k) {
+  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n_sum; i += (uint64_t)gridDim.x * blockDim.x) {
+    sum[i] = 0.0;
+    if (i < k) cnt[i] = 0u;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_km_direct(const float* __restrict__ X, uint64_t N, const float* __restrict__ C,
+                                                   uint32_t k, uint32_t d, int32_t* __restrict__ assign,
+                                                   double* __restrict__ sum, uint32_t* __restrict__ cnt) {
+  for (uint64_t p = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; p < N; p += (uint64_t)gridDim.x * blockDim.x) {
+    const float* const x = X + p * d;
+    double bd = INFINITY;
+    uint32_t bj = 0;
+    for (uint32_t j = 0; j < k; ++j) {
+      double s = 0.0;
+#pragma unroll 1
+      for (uint32_t t = 0; t < d; ++t) {
+        const double e = (double)x[t] - (double)C[(uint64_t)j * d + t];
+        s += e * e;
+      }
+      if (s < bd) {
+        bd = s;
+        bj = j;
+      }
+    }
+    assign[p] = (int32_t)bj;
+    atomicAdd(&cnt[bj], 1u);
+    for (uint32_t t = 0; t < d; ++t) atomicAdd(&sum[(uint64_t)bj * d + t], (double)x[t]);
+  }
+}
+
 static hipError_t km_enqueue_generic(const KmLaunch& L, hipStream_t s) {
   const uint32_t dq = (L.d + 7) / 8, nkb = (L.k + 31) / 32;
   if (L.N) {
@@ -906,11 +942,16 @@ static hipError_t km_enqueue_generic(const KmLaunch& L, hipStream_t s) {
 }
 
 hipError_t km_enqueue(const KmLaunch& L, hipStream_t s, hipEvent_t map0, hipEvent_t map1) {
-  if (L.mfma) hipLaunchKernelGGL(k_km_prep, dim3(1), dim3(kWave), 0, s, L.C, L.cn, L.cmax, L.n_recheck, L.tiny);
+  if (L.direct)
+    hipLaunchKernelGGL(k_km_clear, dim3(256), dim3(256), 0, s, L.part_sum, (uint64_t)L.k * L.d, L.part_cnt, L.k);
+  else if (L.mfma) hipLaunchKernelGGL(k_km_prep, dim3(1), dim3(kWave), 0, s, L.C, L.cn, L.cmax, L.n_recheck, L.tiny);
   else
     hipLaunchKernelGGL(k_km_pack, dim3((L.k + 31) / 32), dim3(256), 0, s, L.C, L.k, L.d, (L.d + 7) / 8, L.cp, L.cn, L.cmax);
   if (map0) (void)hipEventRecord(map0, s);
-  if (L.mfma) {
+  if (L.direct) {
+    const uint64_t b = std::max<uint64_t>(1, std::min<uint64_t>((L.N + 255) / 256, 4096));
+    hipLaunchKernelGGL(k_km_direct, dim3((uint32_t)b), dim3(256), 0, s, L.X, L.N, L.C, L.k, L.d, L.assign, L.part_sum, L.part_cnt);
+  } else if (L.mfma) {
     hipLaunchKernelGGL(k_km_mfma, dim3(L.G), dim3(kKmThreads), 0, s, L.X, L.N, L.C, L.cn, L.cmax, L.assign, L.part_sum,
                        L.part_cnt, L.n_recheck, L.tiny);
   } else {
@@ -920,7 +961,7 @@ hipError_t km_enqueue(const KmLaunch& L, hipStream_t s, hipEvent_t map0, hipEven
   if (map1) (void)hipEventRecord(map1, s);
   const uint64_t kd = (uint64_t)L.k * L.d;
   hipLaunchKernelGGL(k_km_final, dim3((uint32_t)((kd + kWave - 1) / kWave)), dim3(kFinalWaves * kWave), 0, s, L.part_sum, L.part_cnt,
-                     L.mfma ? L.G : L.upd.G, L.k, L.d, L.C, L.sums, L.counts, L.cent);
+                     L.direct ? 1u : L.mfma ? L.G : L.upd.G, L.k, L.d, L.C, L.sums, L.counts, L.cent);
   return hipGetLastError();
 }
 

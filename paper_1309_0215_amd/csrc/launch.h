@@ -270,6 +270,7 @@ struct KmLaunch {
   KmUpdPlan upd;        // generic path
   uint32_t G;           // workgroups of the assignment kernel (matrix-core path at d = 32, k = 64)
   bool mfma;            // d == 32, k == 64 and X 16-byte aligned
+  bool direct;          // a caller workspace too small for the packed centroids
   int32_t* assign;      // [N]
   double* part_sum;     // [G][k][d] (generic path: upd.G partials)
   uint32_t* part_cnt;   // [G][k]

@@ -275,3 +275,21 @@ def test_mfma_path_points_that_are_no_numbers(torch):
     ok = np.setdiff1d(np.arange(5_000), bad)
     _check_assign(X, Cn, a, ok)
     assert np.array_equal(c, np.bincount(a[ok], minlength=64) + np.bincount(a[bad][a[bad] < 64], minlength=64))
+
+
+# caller workspaces that hold one partial but not the packed centroids (few
+# dimensions, or few clusters): a thread per point decides in float64
+@pytest.mark.parametrize("n,d,k", [(1, 1, 1), (1_000, 2, 64), (5_001, 3, 1024), (777, 256, 2), (20_000, 5, 7)])
+def test_smallest_workspaces(torch, n, d, k):
+    from paper_1309_0215_amd import Job
+    X, Cn = gen.kmeans(n, n=max(n, k), d=d, k=k)
+    X = X[:n].copy()
+    up = lambda b: (b + 255) // 256 * 256
+    ws = torch.empty(up(4 * k * d) + 512 + up(8 * k * d) + 4 * k, dtype=torch.uint8, device="cuda:0")
+    job = Job(device=0, km_centroids=torch.from_numpy(Cn).to("cuda:0"), workspace=ws)
+    for _ in range(2):
+        a, s, c, cent, st = job.kmeans(torch.from_numpy(X).to("cuda:0"))
+        assert st["device_allocs"] == 0
+        a, s, c, cent = a.cpu().numpy(), s.cpu().numpy(), c.cpu().numpy().view(np.uint32), cent.cpu().numpy()
+        _check_assign(X, Cn, a)
+        _check_update(X, Cn, a, s, c, cent)

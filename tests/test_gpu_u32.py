@@ -334,3 +334,23 @@ def test_pairs_entry_rejects_what_mr_run_rejects(torch):
     assert run(j.h, 1, k.data_ptr(), k.data_ptr(), 1 << 32, 0, C.byref(o)) == L.MR_ERR_UNSUPPORTED
     assert run(Job(device=0, strategy=1).h, 1, k.data_ptr(), k.data_ptr(), 4, 0, C.byref(o)) == L.MR_ERR_UNSUPPORTED
     assert run(j.h, 1, None, None, 0, 0, C.byref(o)) == L.MR_OK and o.n_keys == 0
+
+
+# a caller workspace that holds a table for the declared range but not the
+# sort of all elements
+@pytest.mark.parametrize("n,R,op", [(20_011, 1_000, "count"), (300_000, 1_000, "sum"), (1 << 20, 20_000, "count"), (1_200_007, 300, "max")])
+def test_hash_table_in_a_small_workspace(torch, n, R, op):
+    from paper_1309_0215_amd import Job, _lib as L
+    rng = np.random.default_rng(n)
+    keys = torch.from_numpy(rng.integers(0, R, n).astype(np.int32)).to("cuda:0")
+    vals = torch.from_numpy(rng.integers(0, 1 << 31, n).astype(np.int32)).to("cuda:0") if op != "count" else None
+    code = {"count": L.REDUCE_COUNT, "sum": L.REDUCE_SUM, "max": L.REDUCE_MAX}[op]
+    want = Job(device=0, strategy=L.STRAT_SORT).u32(keys, vals, op=code, key_range=R)
+    slots = max(4096, 1 << (2 * R - 1).bit_length())
+    ws = torch.empty(4096 + 20 * slots + 128 * R + 8192, dtype=torch.uint8, device="cuda:0")
+    assert ws.numel() < 4 * n + 20 * slots or n < 100_000
+    job = Job(device=0, strategy=L.STRAT_HASH, workspace=ws)
+    for _ in range(2):
+        r = job.u32(keys, vals, op=code, key_range=R)
+        assert r.stats["device_allocs"] == 0 and r.stats["strategy_used"] == L.STRAT_HASH
+        assert torch.equal(r.keys, want.keys) and torch.equal(r.values, want.values)
