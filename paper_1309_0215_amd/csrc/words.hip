@@ -2225,7 +2225,10 @@ hipError_t words_enqueue_map(const WordsLaunch& L, hipStream_t s) {
 }
 
 hipError_t words_enqueue_reduce(const WordsLaunch& L, hipStream_t s) {
-  const uint32_t item = L.total_slots <= (1ull << 20) ? kCompactSmall : kCompactLarge;
+  // (with staged records few slots hold a key, and an item's time is its chain
+  // of loads: the two items of one partition in a table of 2^21 slots 33 us at
+  // 4096 slots each, 13 at 1024)
+  const uint32_t item = L.total_slots <= (L.n_parts ? 1ull << 22 : 1ull << 20) ? kCompactSmall : kCompactLarge;
   const uint32_t n_direct = L.n_parts && L.n_jobs <= kDirectJobs ? L.n_jobs : 0;
   const uint64_t tiles = std::max<uint64_t>((L.total_slots + item - 1) / item, (uint64_t)n_direct * kMaxWordParts);
   const uint32_t cgrid = (uint32_t)(tiles < 4096 ? tiles : 4096);
