@@ -231,7 +231,13 @@ __global__ __launch_bounds__(kKmThreads) void k_km_mfma(const float* __restrict_
   const uint32_t wv = threadIdx.x / kWave;
   const uint32_t h = lane >> 5;     // which half of the dims (0: 0..7 and 16..23, 1: 8..15 and 24..31)
   const uint32_t col = lane & 31u;  // point within the 32-point group / centroid row within a block
-  const float cmax = (float)*cmax_g;
+  // Where squares, products or sums of them fall below the normal range, each
+  // of a score's some 400 operations is off by 2^-126 at most, and the place
+  // by 15 x 2^-149: 2^-112 covers both scores. (Without it equal scores of
+  // zero differed by their places alone.) The floor stands for norms whose
+  // squares vanish: 32 coordinates below 2^-63 have norms below 2^-60.
+  constexpr float kAbs = 1.9259299e-34f, kFloor = 3.4694470e-18f;  // 2^-112, 2^-58
+  const float cmax = (float)*cmax_g + kFloor;
   const float u = 5.9604645e-08f;                     // 2^-24
   // Error of t = x . c - |c|^2 / 2 as computed. Float32 accumulation of the
   // start value and the piece products: 12 instructions of 16 products each
@@ -242,7 +248,7 @@ __global__ __launch_bounds__(kKmThreads) void k_km_mfma(const float* __restrict_
   const float place = 1.9073486e-06f;                 // 2^-19
   const float drop = 9.5367432e-07f;                  // 2^-20: the three dropped piece products
   // both scores, x2 margin
-  const float e_c = 2.f * (gam + place + u) * cmax * cmax;
+  const float e_c = 2.f * (gam + place + u) * cmax * cmax + kAbs;
   const float e_x = 4.f * (gam + place + drop) * cmax;  // times |x|
 
   const uint32_t waves_total = gridDim.x * W;
@@ -320,7 +326,7 @@ __global__ __launch_bounds__(kKmThreads) void k_km_mfma(const float* __restrict_
     for (int s = 0; s < 16; ++s) nx = fmaf(xs[s], xs[s], nx);
     uint32_t lo, up;
     pair_values(__float_as_uint(nx), lo, up);
-    nx = sqrtf(__uint_as_float(lo) + __uint_as_float(up));
+    nx = sqrtf(__uint_as_float(lo) + __uint_as_float(up)) + kFloor;
     // best and second best of this lane's 16 rows of each block
     float b1[2], b2[2];
     uint32_t sc[2][16];

@@ -293,3 +293,29 @@ def test_smallest_workspaces(torch, n, d, k):
         a, s, c, cent = a.cpu().numpy(), s.cpu().numpy(), c.cpu().numpy().view(np.uint32), cent.cpu().numpy()
         _check_assign(X, Cn, a)
         _check_update(X, Cn, a, s, c, cent)
+
+
+def _signed(rng, shape, lo, hi):
+    """Magnitudes uniform in [lo, hi), either sign."""
+    return (rng.uniform(lo, hi, shape) * rng.choice([-1.0, 1.0], shape)).astype(np.float32)
+
+
+# Where squares and products leave float32 at its lower end, every point is
+# decided in float64: the assignments are the oracle's, the lowest index on
+# equal distances. (Magnitudes within a factor of two, so that none is below
+# 2^-100, from where on the step is not the matrix-core path's. Distances drawn
+# at random differ by far more than the 32 roundings of 2^-53 they are summed
+# with.)
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("scale", [0.0, 1e-15, 1e-17, 1e-18, 1e-19, 1e-20, 1e-22, 1e-25, 1e-29])
+def test_underflow_of_squares_and_products(torch, scale, offset):
+    """scale 0: all centroids zero and ordinary points, so that every centroid
+    is as near as any other."""
+    rng = np.random.default_rng(11)
+    Cn = _signed(rng, (64, 32), scale, 2 * scale)
+    X = _signed(rng, (5_003, 32), scale or 1.0, 2 * (scale or 1.0))
+    X[-64:] = Cn
+    a, s, c, cent, st = _run(torch, X, Cn, offset=offset)
+    assert st["strategy_used"] == (0 if offset else 1)
+    assert np.array_equal(a, oracle.kmeans_distances(X, Cn).argmin(axis=1))
+    _check_update(X, Cn, a, s, c, cent)
