@@ -149,7 +149,8 @@ MR_DEV void split8_bf16x3(const float* x, uint4& hi, uint4& mid, uint4& lo) {
 MR_DEV bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // The larger of two float32 values (plain fmaxf first quiets each operand that
-// it cannot show to be quiet; a NaN gives the other value either way).
+// it cannot show to be quiet). A quiet NaN gives the other value; a signalling
+// one gives a NaN here.
 MR_DEV float max_f32(float a, float b) {
   float m;
   asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
@@ -236,7 +237,7 @@ __global__ __launch_bounds__(kKmThreads) void k_km_mfma(const float* __restrict_
   // by 15 x 2^-149: 2^-112 covers both scores. (Without it equal scores of
   // zero differed by their places alone.) The floor stands for norms whose
   // squares vanish: 32 coordinates below 2^-63 have norms below 2^-60.
-  constexpr float kAbs = 1.9259299e-34f, kFloor = 3.4694470e-18f;  // 2^-112, 2^-58
+  constexpr float kAbs = 1.9259299e-34f, kFloor = 3.4694470e-18f, kHuge = 1.3292280e+36f;  // 2^-112, 2^-58, 2^120
   const float cmax = (float)*cmax_g + kFloor;
   const float u = 5.9604645e-08f;                     // 2^-24
   // Error of t = x . c - |c|^2 / 2 as computed. Float32 accumulation of the
@@ -250,6 +251,10 @@ __global__ __launch_bounds__(kKmThreads) void k_km_mfma(const float* __restrict_
   // both scores, x2 margin
   const float e_c = 2.f * (gam + place + u) * cmax * cmax + kAbs;
   const float e_x = 4.f * (gam + place + drop) * cmax;  // times |x|
+  // Points from this norm on have squares or products that could pass the
+  // float32 range: no score of theirs counts (an infinite one with its place
+  // is no number any more), nor of a point that has no norm.
+  const float n_max = cmax * cmax < kHuge ? kHuge / cmax : 0.f;
 
   const uint32_t waves_total = gridDim.x * W;
   const uint32_t wave_g = blockIdx.x * W + wv;
@@ -359,13 +364,15 @@ __global__ __launch_bounds__(kKmThreads) void k_km_mfma(const float* __restrict_
     // (usually two) are decided again in float64 from the direct form; both
     // lanes of the pair take part, each for its own rows.
     const float eps = e_c + e_x * nx;
-    const bool need = valid && !(best - second > eps);
+    const bool ranged = nx < n_max;
+    const bool need = valid && !(best - second > eps && ranged);
     if (__any(need)) {
       uint32_t cand = 0;
       if (need) {
         const float thr = best - eps;
 #pragma unroll
         for (int t = 0; t < 32; ++t) cand |= (__uint_as_float(sc[t / 16][t % 16]) >= thr ? 1u : 0u) << t;
+        if (!ranged) cand = ~0u;
       }
       // the partner's half of the point: this lane then holds all 32 dims
       float xo[16];

@@ -319,3 +319,24 @@ def test_underflow_of_squares_and_products(torch, scale, offset):
     assert st["strategy_used"] == (0 if offset else 1)
     assert np.array_equal(a, oracle.kmeans_distances(X, Cn).argmin(axis=1))
     _check_update(X, Cn, a, s, c, cent)
+
+
+# The same at float32's upper end: |c|^2 past it, or the products alone. (Where
+# points are far longer than centroids, all distances round to |x|^2 and the
+# nearest centroid is any within the acceptance limit.)
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("x,c", [(1.0, 1e18), (1.0, 1e19), (1.0, 1e20), (1e18, 1e18), (1e20, 1e20), (1e20, 1.0), (1e30, 1e10),
+                                 (1e10, 1e30), (1e33, 1e33)])
+def test_overflow_of_squares_and_products(torch, x, c, offset):
+    rng = np.random.default_rng(12)
+    Cn = _signed(rng, (64, 32), c, 2 * c)
+    X = _signed(rng, (5_003, 32), x, 2 * x)
+    X[-64:] = Cn
+    a, s, n, cent, st = _run(torch, X, Cn, offset=offset)
+    assert st["strategy_used"] == (0 if offset else 1)
+    if x <= c:
+        assert np.array_equal(a, oracle.kmeans_distances(X, Cn).argmin(axis=1))
+    else:
+        assert a.min() >= 0 and a.max() < 64
+        _check_assign(X, Cn, a)
+    _check_update(X, Cn, a, s, n, cent)
