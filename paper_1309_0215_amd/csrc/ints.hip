@@ -489,7 +489,7 @@ __global__ __launch_bounds__(kVpTotThreads) void k_vp_totals(const uint32_t* __r
 MR_DEV uint32_t vp_parts(const uint32_t* __restrict__ tot, uint32_t slices, uint32_t P, uint32_t p, uint32_t split) {
   uint32_t c = 0;
   for (uint32_t y = 0; y < slices; ++y) c += tot[y * P + p];
-  return c <= split ? 1u : (c + split - 1) / split;
+  return c <= split ? 1u : (c - 1) / split + 1;  // (c may be close to 2^32)
 }
 
 // One workgroup per part of a range (found from the parts' scan). LDS: values

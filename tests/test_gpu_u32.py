@@ -354,3 +354,14 @@ def test_hash_table_in_a_small_workspace(torch, n, R, op):
         r = job.u32(keys, vals, op=code, key_range=R)
         assert r.stats["device_allocs"] == 0 and r.stats["strategy_used"] == L.STRAT_HASH
         assert torch.equal(r.keys, want.keys) and torch.equal(r.values, want.values)
+
+
+def test_global_array_of_nearly_2_32_keys_in_one_range(torch):
+    """The most elements an input may have (16 GiB of keys), all but one in one
+    key range: its share over the elements of a workgroup is rounded up."""
+    n, R = (1 << 32) - 1, 20_000
+    keys = torch.full((n,), 3, dtype=torch.int32, device="cuda:0")
+    keys[-1] = R - 1
+    r = _job(STRATS["global_array"]).u32(keys, key_range=R)
+    assert r.keys.tolist() == [3, R - 1]
+    assert [x & 0xFFFFFFFF for x in r.values.tolist()] == [n - 1, 1]
