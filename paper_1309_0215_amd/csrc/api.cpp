@@ -1243,17 +1243,28 @@ SortCarve sort_carve(uint64_t n, uint32_t op) {
 // The hash container keeps a growing table of its own when the job fixes the
 // table's size or forces collisions. Otherwise an input of kHashTryMin
 // elements and more is sampled: with at most kHashTryKeys distinct keys among
-// 8192 elements it goes through the LDS caches and a table of kHashTrySlots
-// slots; all others (and any that fills that table) are radix sorted.
+// 8192 elements, and at most kHashTryAll estimated in all, it goes through the
+// LDS caches and a table of hash_try_slots; all others (and any that claims
+// half that table) are radix sorted.
 // Measured on 16 M elements, count: 16 keys 127 us through the caches and
 // about 350 us sorted; 1 M keys 387 us sorted and 2,490 us through the caches
 // and a table of 2^25 slots (atomics on its slots). On 1.1 M elements 92 and
 // 180 us; on 100,000 elements the sort takes 125 us and a table, with its host
 // round trip and ordered output, 190 us, so smaller inputs are not sampled.
+// A key beside the frequent ones costs a claim and atomics that no cache
+// merges: 8 M elements of which a tenth are keys of their own take 245 us
+// sorted, and took 1,740 us through a table of 2^18 slots that filled up; 2^26
+// elements with 400,000 such keys take 890 us through 2^21 slots and about
+// 1,100 us sorted (2,390 us through 2^18 slots and sorted then).
 constexpr uint64_t kHashTryMin = 1ull << 20;
-constexpr uint64_t kHashTrySlots = 1ull << 18;
 constexpr uint32_t kHashTryKeys = 1024;
+constexpr uint32_t kHashTryAll = 4096;
 constexpr uint64_t kHashTryProbes = 256;
+// Slots for half as many keys as one element in 64 (84 MB at most).
+constexpr uint64_t kHashTryLeast = 1ull << 18, kHashTryMost = 1ull << 22;
+uint64_t hash_try_slots(uint64_t n) {
+  return std::min(kHashTryMost, std::max(kHashTryLeast, next_pow2((n + 31) / 32)));
+}
 bool int_own_table(const mr_job* job) { return job->cfg.table_slots || job->cfg.debug_hash; }
 
 // Initial slots of the integer hash table for n elements and range R.
@@ -1264,16 +1275,22 @@ uint64_t int_table_slots(const mr_job* job, mr_map_kind kind, uint64_t bytes, ui
   return std::max<uint64_t>(4096, next_pow2((uint64_t)std::ceil(std::min<uint64_t>(bound, 1ull << 24) / lf)));
 }
 
+// The hash container's table: one for all keys, or the one that sampled
+// inputs of few keys go through (small: of the least slots, where a caller
+// workspace has no room for more).
+enum class HashTable { kTry, kTrySmall, kOwn };
+
 // Table slots (0: no table) and scratch bytes of the hash container.
 struct IntHashNeed {
   uint64_t slots, scratch;
 };
 IntHashNeed int_hash_need(const mr_job* job, mr_map_kind kind, uint64_t bytes, uint64_t n, uint64_t R, uint32_t op,
-                          bool own_table) {
-  if (own_table) return {int_table_slots(job, kind, bytes, n, R), hash_carve(R ? std::min(n, R) : n).bytes};
+                          HashTable t) {
+  if (t == HashTable::kOwn) return {int_table_slots(job, kind, bytes, n, R), hash_carve(R ? std::min(n, R) : n).bytes};
   const uint64_t sort = sort_carve(n, op).bytes;
   if (n < kHashTryMin) return {0, sort};
-  return {kHashTrySlots, std::max(sort, hash_carve(kHashTrySlots).bytes)};
+  const uint64_t slots = t == HashTable::kTrySmall ? kHashTryLeast : hash_try_slots(n);
+  return {slots, std::max(sort, hash_carve(slots).bytes)};
 }
 
 // Whether a table and then a scratch region of these sizes fit what a caller
@@ -1284,12 +1301,21 @@ bool hash_fits(const mr_job* job, const IntHashNeed& h) {
   return at + h.scratch <= job->cws_bytes;
 }
 
+// The table a caller workspace has room for: the wanted one, or a smaller or
+// growing one that fits where that does not (need(t): its sizes).
+template <typename Need>
+HashTable hash_table_that_fits(const mr_job* job, HashTable want, const Need& need) {
+  if (want == HashTable::kOwn || hash_fits(job, need(want))) return want;
+  if (hash_fits(job, need(HashTable::kTrySmall))) return HashTable::kTrySmall;
+  return hash_fits(job, need(HashTable::kOwn)) ? HashTable::kOwn : want;
+}
+
 // A batched integer item: the batch decides the container, gives the item
 // its own state slot and reads the states back once for all items.
 struct U32Ctx {
   mr_strategy strat;   // the container to run
   bool sel_used;       // the learned selector chose it
-  bool own_table;      // the hash container with a table for all keys
+  HashTable table;     // of the hash container
   IntSmall* sm;        // this item's state (device)
 };
 
@@ -1410,22 +1436,22 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
   // stay in the LDS caches and a small table; the others are radix sorted. A
   // caller workspace that holds a table for a declared range but not the sort
   // takes the table (5 M keys of 1,000: 120 KB against 40 MB).
-  bool own_table = strat == MR_STRAT_HASH && (ctx ? ctx->own_table : int_own_table(job));
-  if (strat == MR_STRAT_HASH && !own_table && !ctx)
-    own_table = !hash_fits(job, int_hash_need(job, kind, bytes, n, key_range, o, false)) &&
-                hash_fits(job, int_hash_need(job, kind, bytes, n, key_range, o, true));
+  HashTable table = ctx ? ctx->table : int_own_table(job) ? HashTable::kOwn : HashTable::kTry;
+  if (strat == MR_STRAT_HASH && !ctx)
+    table = hash_table_that_fits(job, table, [&](HashTable t) { return int_hash_need(job, kind, bytes, n, key_range, o, t); });
+  const bool own_table = strat == MR_STRAT_HASH && table == HashTable::kOwn;
   bool sorted = strat == MR_STRAT_SORT || (strat == MR_STRAT_HASH && !own_table && n < kHashTryMin);
   IntSmall hs;
   bool have_state = false;  // hs holds the final state already
   if (strat == MR_STRAT_HASH && !own_table && !sorted) {
     MR_HIP(int_enqueue_sample(L, job->h_int, job->stream));
     MR_HIP(hipStreamSynchronize(job->stream));
-    sorted = job->h_int->sampled > kHashTryKeys;
+    sorted = job->h_int->sampled > kHashTryKeys || job->h_int->estimate > kHashTryAll;
   }
   published |= sorted && n;
   if (strat == MR_STRAT_HASH && !sorted) {
     // capacity: distinct <= min(n, range); start from the last job's distinct count when larger inputs repeat
-    table_cap = own_table ? int_table_slots(job, kind, bytes, n, key_range) : kHashTrySlots;
+    table_cap = int_hash_need(job, kind, bytes, n, key_range, o, table).slots;
     for (;;) {
       {
         // a new table region is laid out for table_cap slots: keys start as
@@ -1448,6 +1474,7 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
       L.claimed = reinterpret_cast<uint32_t*>(tb + 16 * C);
       L.t_cap = table_cap;  // use a prefix of the allocation (kept clean as a whole)
       L.max_probes = own_table ? table_cap : kHashTryProbes;
+      L.max_claims = own_table ? table_cap : table_cap / 2;
       if (job->cfg.timing) MR_HIP(hipEventRecord(job->ev2, job->stream));
       MR_HIP(int_enqueue_hash_map(L, job->stream));
       if (job->cfg.timing) MR_HIP(hipEventRecord(job->ev3, job->stream));
@@ -1905,7 +1932,8 @@ extern "C" mr_status mr_workspace_bytes(const mr_job_config* cfg, mr_map_kind ki
           if (c == MR_STRAT_GLOBAL_ARRAY) t.add(key_range * 12 + 8);
           t.add(dense_carve(c, ne, key_range, op, (uint32_t)n_cu, true).bytes);
         } else if (c == MR_STRAT_HASH) {
-          const IntHashNeed h = int_hash_need(&tmp, kind, n, ne, key_range, op, int_own_table(&tmp));
+          const IntHashNeed h =
+              int_hash_need(&tmp, kind, n, ne, key_range, op, int_own_table(&tmp) ? HashTable::kOwn : HashTable::kTry);
           if (h.slots) t.add(h.slots * kIntSlotBytes);
           t.add(h.scratch);
         } else {
@@ -2375,7 +2403,7 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
   // the rule for the items the selector left to it; the regions for the largest item
   // (scratch_full: with the partitions that a small caller workspace goes without)
   uint64_t dense_b = 0, dense_r = 0, scratch_b = 0, scratch_full = 0;
-  IntHashNeed hash_h{0, 0}, hash_g{0, 0};  // the hash items' need, and with a table for all keys
+  IntHashNeed hash_need[3] = {};  // the hash items' need with each kind of table
   for (uint32_t q = 0; q < ni; ++q) {
     const mr_batch_item& it = items[ii[q]];
     const uint32_t op = (uint32_t)it.op;
@@ -2394,10 +2422,11 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
       scratch_b = std::max(scratch_b, dense_carve(strat[q], n, it.key_range, op, (uint32_t)job->n_cu, false).bytes);
       scratch_full = std::max(scratch_full, dense_carve(strat[q], n, it.key_range, op, (uint32_t)job->n_cu, true).bytes);
     } else if (strat[q] == MR_STRAT_HASH) {
-      const IntHashNeed h = int_hash_need(job, it.kind, it.input_bytes, n, it.key_range, op, int_own_table(job));
-      const IntHashNeed g = int_hash_need(job, it.kind, it.input_bytes, n, it.key_range, op, true);
-      hash_h = {std::max(hash_h.slots, h.slots), std::max(hash_h.scratch, h.scratch)};
-      hash_g = {std::max(hash_g.slots, g.slots), std::max(hash_g.scratch, g.scratch)};
+      for (HashTable t : {HashTable::kTry, HashTable::kTrySmall, HashTable::kOwn}) {
+        const IntHashNeed h = int_hash_need(job, it.kind, it.input_bytes, n, it.key_range, op, t);
+        IntHashNeed& all = hash_need[(int)t];
+        all = {std::max(all.slots, h.slots), std::max(all.scratch, h.scratch)};
+      }
     } else {
       scratch_b = std::max(scratch_b, sort_carve(n, op).bytes);
     }
@@ -2408,11 +2437,11 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
     if (st != MR_OK) return st;
     if (fresh) job->int_dense_R = dense_r;
   }
-  hash_h.scratch = std::max(hash_h.scratch, scratch_b);
-  hash_g.scratch = std::max(hash_g.scratch, scratch_b);
-  const bool own_table = int_own_table(job) || (!hash_fits(job, hash_h) && hash_fits(job, hash_g));
-  scratch_b = own_table ? hash_g.scratch : hash_h.scratch;
-  const uint64_t table_s = own_table ? hash_g.slots : hash_h.slots;
+  for (IntHashNeed& h : hash_need) h.scratch = std::max(h.scratch, scratch_b);
+  const HashTable table = hash_table_that_fits(job, int_own_table(job) ? HashTable::kOwn : HashTable::kTry,
+                                               [&](HashTable t) { return hash_need[(int)t]; });
+  scratch_b = hash_need[(int)table].scratch;
+  const uint64_t table_s = hash_need[(int)table].slots;
   if (table_s) {
     bool fresh = false;
     st = dev_region(job, kRegTable, &job->int_table, &job->int_table_bytes, table_s * kIntSlotBytes, table_s * kIntSlotBytes,
@@ -2435,7 +2464,7 @@ mr_status batch_ints_enqueue(mr_job* job, const mr_batch_item* items, const std:
   for (uint32_t q = 0; q < ni; ++q) {
     if (per[ii[q]] != MR_OK) continue;
     const mr_batch_item& it = items[ii[q]];
-    const U32Ctx ctx{strat[q], chosen[q] != 0, own_table, sm + q};
+    const U32Ctx ctx{strat[q], chosen[q] != 0, table, sm + q};
     st = run_u32(job, it.kind, it.op, it.d_input, it.input_bytes, it.key_range, &outs[ii[q]], &ctx);
     if (st == MR_ERR_HIP) return st;
     per[ii[q]] = st;

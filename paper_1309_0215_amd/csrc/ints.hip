@@ -849,6 +849,7 @@ struct IntTable {
   uint32_t* claimed;          // slots claimed, in claim order
   unsigned long long* n_claimed;
   uint64_t max_probes;        // slots an insert looks at before the table counts as full
+  uint64_t max_claims;        // slots claimed before it does
   uint32_t* side_cnt;         // key 0xFFFFFFFF: count and value
   void* side_val;
   uint32_t* flags;
@@ -876,7 +877,9 @@ MR_DEV void g_int_insert(const IntTable& T, uint32_t k, uint32_t c, unsigned lon
     if (cur == kEmptyKey) {
       cur = atomicCAS(&T.keys[i], kEmptyKey, k);
       if (cur == kEmptyKey) {
-        T.claimed[wave_claim(T.n_claimed)] = (uint32_t)i;
+        const uint64_t at = wave_claim(T.n_claimed);
+        T.claimed[at] = (uint32_t)i;
+        if (at >= T.max_claims) atomicOr(T.flags, kFlagTableFull);
         apply_global<OP>(T, i, c, s, mm);
         return;
       }
@@ -906,70 +909,107 @@ __global__ __launch_bounds__(kIntThreads) void k_int_hash(IntIn in, IntTable T, 
   }
   __syncthreads();
   const uint64_t lo = in.n * blockIdx.x / G, hi = in.n * (blockIdx.x + 1) / G;
-  for (uint64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-    uint32_t k, v;
-    load_elem(in, i, k, v);
-    if (R && k >= R) atomicOr(T.flags, kFlagBadInput);
-    bool done = false;
-    if (k != kEmptyKey) {
-      uint32_t s = (uint32_t)(debug_hash ? 0ull : hash_u32(k)) & (S - 1);
+  // A full table ends the pass (it is then cleared, and another way taken):
+  // the job's flags are read every kLook elements of a thread and looked at
+  // when as many more are done.
+  constexpr uint32_t kLook = 32;
+  uint32_t fl = 0;
+  for (uint64_t i0 = lo + threadIdx.x; i0 < hi && !(fl & kFlagTableFull); i0 += (uint64_t)kLook * blockDim.x) {
+    fl = __hip_atomic_load(T.flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t i1 = hi - i0 < (uint64_t)kLook * blockDim.x ? hi : i0 + (uint64_t)kLook * blockDim.x;
+    for (uint64_t i = i0; i < i1; i += blockDim.x) {
+      uint32_t k, v;
+      load_elem(in, i, k, v);
+      if (R && k >= R) atomicOr(T.flags, kFlagBadInput);
+      bool done = false;
+      if (k != kEmptyKey) {
+        uint32_t s = (uint32_t)(debug_hash ? 0ull : hash_u32(k)) & (S - 1);
 #pragma unroll 1
-      for (int p = 0; p < 16; ++p) {
-        uint32_t cur = lk[s];
-        if (cur == kEmptyKey) cur = atomicCAS(&lk[s], kEmptyKey, k);
-        if (cur == kEmptyKey || cur == k) {
-          atomicAdd(&lc[s], 1u);
-          if (OP == 1) atomicAdd(&ls[s], (unsigned long long)v);
-          if (OP >= 2) atomicMax(&lm[s], enc_minmax(OP, v));
-          done = true;
-          break;
+        for (int p = 0; p < 16; ++p) {
+          uint32_t cur = lk[s];
+          if (cur == kEmptyKey) cur = atomicCAS(&lk[s], kEmptyKey, k);
+          if (cur == kEmptyKey || cur == k) {
+            atomicAdd(&lc[s], 1u);
+            if (OP == 1) atomicAdd(&ls[s], (unsigned long long)v);
+            if (OP >= 2) atomicMax(&lm[s], enc_minmax(OP, v));
+            done = true;
+            break;
+          }
+          s = (s + 1) & (S - 1);
         }
-        s = (s + 1) & (S - 1);
       }
+      if (!done) g_int_insert<OP>(T, k, 1u, v, enc_minmax(OP, v), debug_hash);
     }
-    if (!done) g_int_insert<OP>(T, k, 1u, v, enc_minmax(OP, v), debug_hash);
   }
   __syncthreads();
+  if (fl & kFlagTableFull) return;
   for (uint32_t s = threadIdx.x; s < S; s += blockDim.x) {
     if (lk[s] != kEmptyKey && lc[s])
       g_int_insert<OP>(T, lk[s], lc[s], OP == 1 ? ls[s] : 0ull, OP >= 2 ? lm[s] : 0u, debug_hash);
   }
 }
 
-// Distinct keys among kSampleSize elements spread evenly over the input
-// (counted in an LDS hash set by one workgroup): tells inputs of few keys,
-// which the LDS caches combine, from the others before any pass over them.
+// Distinct keys among kSampleSize elements, one from each of as many equal
+// stretches of the input at a place that varies from stretch to stretch (keys
+// that recur with the stretches are met like others), counted in an LDS hash
+// set by one workgroup; and an estimate of the distinct keys of the whole
+// input from the keys met once (f1) and twice (f2), the lower bound of Chao:
+// d + f1 (f1 - 1) / (2 (f2 + 1)). They tell inputs of few keys, which the LDS
+// caches combine, from the others before any pass over them.
 constexpr uint32_t kSampleSize = 8192;
 
 __global__ __launch_bounds__(1024) void k_int_sample(IntIn in, IntPub* host) {
   constexpr uint32_t S = 2 * kSampleSize;
-  __shared__ uint32_t set[S];
-  __shared__ uint32_t n;
-  for (uint32_t i = threadIdx.x; i < S; i += blockDim.x) set[i] = kEmptyKey;
-  if (threadIdx.x == 0) n = 0;
+  __shared__ __attribute__((aligned(16))) uint32_t set[S], met[S];
+  __shared__ uint32_t n[3];  // keys met, met once, met twice
+  for (uint32_t i = threadIdx.x * 4; i < S; i += blockDim.x * 4) {
+    *reinterpret_cast<uint4*>(&set[i]) = make_uint4(kEmptyKey, kEmptyKey, kEmptyKey, kEmptyKey);
+    *reinterpret_cast<uint4*>(&met[i]) = make_uint4(0, 0, 0, 0);
+  }
+  if (threadIdx.x < 3) n[threadIdx.x] = 0;
   constexpr uint32_t kPer = kSampleSize / 1024;
+  const uint32_t stretch = (uint32_t)(in.n / kSampleSize);  // (at least 1)
   uint32_t k[kPer];
 #pragma unroll
   for (uint32_t u = 0; u < kPer; ++u) {
     const uint64_t q = u * 1024 + threadIdx.x;
-    k[u] = in.p[(q * in.n / kSampleSize) * in.stride];
+    k[u] = in.p[(q * in.n / kSampleSize + __umulhi((uint32_t)fmix64(q + 1), stretch)) * in.stride];
   }
   __syncthreads();
-  uint32_t mine = 0;
 #pragma unroll
   for (uint32_t u = 0; u < kPer; ++u) {
     if (k[u] == kEmptyKey) continue;
     uint32_t s = (uint32_t)hash_u32(k[u]) & (S - 1);
     for (;;) {  // (the set has twice the slots: a free one is met)
       const uint32_t cur = atomicCAS(&set[s], kEmptyKey, k[u]);
-      if (cur == kEmptyKey) ++mine;
       if (cur == kEmptyKey || cur == k[u]) break;
       s = (s + 1) & (S - 1);
     }
+    atomicAdd(&met[s], 1u);
   }
-  if (mine) atomicAdd(&n, mine);
   __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_store(&host->sampled, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  // (the counts below 2^16 of a wave's 1024 slots in the halves of one sum)
+  uint32_t all = 0, few = 0;
+  for (uint32_t i = threadIdx.x * 4; i < S; i += blockDim.x * 4) {
+    const uint4 m = *reinterpret_cast<const uint4*>(&met[i]);
+    all += (m.x != 0) + (m.y != 0) + (m.z != 0) + (m.w != 0);
+    few += (m.x == 1) + (m.y == 1) + (m.z == 1) + (m.w == 1);
+    few += (uint32_t)((m.x == 2) + (m.y == 2) + (m.z == 2) + (m.w == 2)) << 16;
+  }
+  all = wave_incl_scan(all);
+  few = wave_incl_scan(few);
+  if (lane_id() == kWave - 1) {
+    atomicAdd(&n[0], all);
+    atomicAdd(&n[1], few & 0xFFFFu);
+    atomicAdd(&n[2], few >> 16);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint32_t f1 = n[1];
+    __hip_atomic_store(&host->sampled, n[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&host->estimate, n[0] + (f1 ? f1 * (f1 - 1) / (2 * (n[2] + 1)) : 0u), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 // Output of a table of few keys by one workgroup: the claimed slots' keys are
@@ -1378,7 +1418,7 @@ hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, const VpPlan* v
 
 hipError_t int_enqueue_hash_map(const IntLaunch& L, hipStream_t s) {
   const IntIn in = int_in(L);
-  IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.max_probes, L.side_cnt, L.side_val, L.flags};
+  IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.max_probes, L.max_claims, L.side_cnt, L.side_val, L.flags};
 #define HASH_CASE(OP) \
   case OP: hipLaunchKernelGGL((k_int_hash<OP, 12>), dim3(L.G), dim3(kIntThreads), 0, s, in, T, L.G, L.debug_hash, L.R); break;
   switch (L.op) {
@@ -1399,7 +1439,7 @@ hipError_t int_enqueue_sample(const IntLaunch& L, IntPub* host, hipStream_t s) {
 uint32_t int_small_out_max() { return kSmallOut; }
 
 hipError_t int_enqueue_small_out(const IntLaunch& L, hipStream_t s) {
-  IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.max_probes, L.side_cnt, L.side_val, L.flags};
+  IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.max_probes, L.max_claims, L.side_cnt, L.side_val, L.flags};
   switch (L.op) {
     case 0: hipLaunchKernelGGL(k_int_small_out<0>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out, L.end); break;
     case 1: hipLaunchKernelGGL(k_int_small_out<1>, dim3(1), dim3(1024), 0, s, T, L.out_keys, L.out_vals, L.cap, L.n_out, L.end); break;
@@ -1410,7 +1450,7 @@ hipError_t int_enqueue_small_out(const IntLaunch& L, hipStream_t s) {
 }
 
 hipError_t int_enqueue_hash_out(const IntLaunch& L, uint64_t n_claimed_host, hipStream_t s) {
-  IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.max_probes, L.side_cnt, L.side_val, L.flags};
+  IntTable T{L.t_keys, L.t_cnt, L.t_val, L.t_cap, L.claimed, L.n_claimed, L.max_probes, L.max_claims, L.side_cnt, L.side_val, L.flags};
   const uint64_t n = n_claimed_host;
   const uint32_t g = blocks_for(n, 256, 4096);
   switch (L.op) {

@@ -103,7 +103,7 @@ hipError_t rgb_graph_build(hipGraph_t g, const uint8_t* in, uint64_t n, uint32_t
 // End of an integer-key job: its state goes to host memory, and the other
 // state block is cleared for the next job. host == NULL: not done.
 struct IntPub {  // pinned host memory
-  uint32_t flags, sampled;
+  uint32_t flags, sampled, estimate, pad;
   unsigned long long n_out, n_claimed;
 };
 struct IntEnd {
@@ -138,6 +138,7 @@ struct IntLaunch {
   uint32_t* claimed;
   unsigned long long* n_claimed;
   uint64_t max_probes;  // slots an insert looks at before the table counts as full
+  uint64_t max_claims;  // slots claimed before it does
   uint32_t* side_cnt;
   void* side_val;
   // hash output: (key, index) pairs and values of the claimed slots
@@ -245,7 +246,7 @@ hipError_t int_enqueue_global_array_vp(const IntLaunch& L, const VpPlan& p, uint
                                        uint32_t* tot, hipStream_t s);
 hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, const VpPlan* vp, const uint32_t* tot, hipStream_t s);
 hipError_t int_enqueue_hash_map(const IntLaunch& L, hipStream_t s);
-hipError_t int_enqueue_sample(const IntLaunch& L, IntPub* host, hipStream_t s);  // -> host->sampled
+hipError_t int_enqueue_sample(const IntLaunch& L, IntPub* host, hipStream_t s);  // -> host->sampled, estimate (n at least 8192)
 uint32_t int_small_out_max();  // keys int_enqueue_small_out handles
 hipError_t int_enqueue_small_out(const IntLaunch& L, hipStream_t s);
 hipError_t int_enqueue_hash_out(const IntLaunch& L, uint64_t n_claimed_host, hipStream_t s);

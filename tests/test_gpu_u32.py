@@ -365,3 +365,58 @@ def test_global_array_of_nearly_2_32_keys_in_one_range(torch):
     r = _job(STRATS["global_array"]).u32(keys, key_range=R)
     assert r.keys.tolist() == [3, R - 1]
     assert [x & 0xFFFFFFFF for x in r.values.tolist()] == [n - 1, 1]
+
+
+def _frequent_and_rare(torch, n, rare):
+    """n keys: 500 frequent ones, and `rare` others once each; (keys, counts of the frequent)."""
+    g = torch.Generator(device="cuda:0").manual_seed(n + rare)
+    k = torch.randint(0, 500, (n,), generator=g, device="cuda:0")
+    at = torch.randperm(n, generator=g, device="cuda:0")[:rare]
+    k[at] = 1000 + torch.arange(rare, device="cuda:0") * 13
+    return k.int(), torch.bincount(k[k < 500], minlength=500)
+
+
+# Few frequent keys and rare ones: as many as the table has room for, far more
+# than the small table of short inputs (its slots follow the input's length),
+# and so many that the sample's estimate sends the input to the sort.
+@pytest.mark.parametrize("n,rare,slots", [(1 << 26, 400_000, 1 << 21), (1 << 24, 80_000, 1 << 19), ((1 << 24) + 1, 80_000, 1 << 20),
+                                          (1 << 24, 600_000, 0)])
+def test_hash_of_frequent_and_rare_keys(torch, n, rare, slots):
+    keys, freq = _frequent_and_rare(torch, n, rare)
+    r = _job(STRATS["hash"]).u32(keys, cap_keys=rare + 1000)
+    assert r.stats["table_slots"] == slots
+    assert torch.equal(r.keys[:500], torch.arange(500, device="cuda:0").int())
+    assert torch.equal(r.keys[500:], (1000 + torch.arange(rare, device="cuda:0") * 13).int())
+    assert torch.equal(r.values[:500].long(), freq)
+    assert (r.values[500:] == 1).all()
+
+
+def test_hash_table_that_fills(torch):
+    """Keys met twice in the sample lower its estimate: the input takes the
+    table, more than half its slots are claimed, and it is sorted after all;
+    the table is clean for the next job."""
+    rng = np.random.default_rng(3)
+    n, rare = 6_000_000, 250_000
+    keys = rng.integers(0, 250, n).astype(np.uint32)
+    some = rng.permutation(n)
+    keys[some[:1_300_000]] = 1000 + rng.integers(0, 800, 1_300_000)
+    keys[some[-rare:]] = 5000 + np.arange(rare, dtype=np.uint32) * 13
+    vals = rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+    j = _job(STRATS["hash"])
+    for op in OPS:
+        r = _run(torch, j, keys, None if op == "count" else vals, op, 0)
+        _check(r, keys, None if op == "count" else vals, op)
+        few = keys[:1 << 20] % 250
+        r = _run(torch, j, few, vals[:1 << 20], "sum", 0)
+        assert r.stats["table_slots"] == 1 << 18
+        _check(r, few, vals[:1 << 20], "sum")
+
+
+def test_hash_of_keys_that_recur_with_a_sample(torch):
+    """One key at every 2048th place of 2^24, every other element its own key."""
+    n = 1 << 24
+    keys = torch.arange(n, device="cuda:0").int()
+    keys[::2048] = 5
+    r = _job(STRATS["hash"]).u32(keys, cap_keys=n)
+    k, c = torch.unique(keys, return_counts=True)
+    assert torch.equal(r.keys, k) and torch.equal(r.values.long(), c)
