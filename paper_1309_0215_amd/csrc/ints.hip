@@ -485,10 +485,20 @@ __global__ __launch_bounds__(kVpTotThreads) void k_vp_totals(const uint32_t* __r
   }
 }
 
-// Workgroups of range p: one per `split` elements.
-MR_DEV uint32_t vp_parts(const uint32_t* __restrict__ tot, uint32_t slices, uint32_t P, uint32_t p, uint32_t split) {
-  uint32_t c = 0;
-  for (uint32_t y = 0; y < slices; ++y) c += tot[y * P + p];
+// Workgroups of range p: one per `split` of its elements; and whether they are
+// spread evenly over the slices of the tiles (a single slice of fewer than 128
+// tiles does not tell: finding the shares there cost 10 us and gained nothing).
+MR_DEV uint32_t vp_parts(const uint32_t* __restrict__ tot, uint32_t slices, uint32_t P, uint32_t p, uint32_t split,
+                         uint32_t* elems = nullptr, bool* even = nullptr) {
+  uint32_t c = 0, most = 0;
+#pragma unroll 4
+  for (uint32_t y = 0; y < slices; ++y) {
+    const uint32_t x = tot[y * P + p];
+    c += x;
+    most = x > most ? x : most;
+  }
+  if (elems) *elems = c;
+  if (even) *even = (uint64_t)most * slices <= c + (uint64_t)c / 2;
   return c <= split ? 1u : (c - 1) / split + 1;  // (c may be close to 2^32)
 }
 
@@ -496,9 +506,12 @@ MR_DEV uint32_t vp_parts(const uint32_t* __restrict__ tot, uint32_t slices, uint
 // [2^kb] (64-bit for SUM), then one presence byte per key; COUNT: the counts;
 // each followed by kVpSinks entries that take the elements of a piece outside
 // the run, so that every piece runs the same branch-free code.
-// kList = false: lpg neighbouring lanes take a tile's run together, one
-// eight-element piece (a 16-byte load of offsets) each, pipelined over steps
-// of kBatch tiles per group.
+// The parts of a range that is spread unevenly over the tiles (sorted input)
+// take equal shares of its elements instead of its tiles.
+// kList = false: neighbouring lanes take a tile's run together, one
+// eight-element piece (a 16-byte load of offsets) each, as many lanes as the
+// part's mean run has pieces, pipelined over steps of kBatch tiles per group;
+// runs far above the mean are left for whole waves afterwards.
 // kList = true, for counting over many tiles of short runs: a wave takes 64
 // tiles at a time, lane l loads tile l's run bounds and lists its run's pieces
 // in LDS, and the listed pieces go to the lanes in order, so that every lane
@@ -514,7 +527,7 @@ constexpr uint32_t vp_fill_lds(uint32_t op, uint32_t kb) { return (op == 0 ? 4 :
 
 template <int OP, bool kList>
 __global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uint32_t kb, uint32_t P, uint32_t n_tiles,
-                                                            uint32_t split, uint32_t lpg, const uint32_t* __restrict__ runs,
+                                                            uint32_t split, const uint32_t* __restrict__ runs,
                                                             const uint16_t* __restrict__ pk, const uint32_t* __restrict__ pv,
                                                             const uint32_t* __restrict__ tot, uint32_t slices,
                                                             uint32_t* __restrict__ dcnt, void* __restrict__ dval,
@@ -522,20 +535,24 @@ __global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uin
   constexpr uint32_t kThreads = vp_fill_threads(OP);
   extern __shared__ unsigned long long vp_lds[];
   constexpr uint32_t kWaves = kThreads / kWave;
-  __shared__ uint32_t ws[kWaves], found[3];
+  // range, part, parts, elements, whether they are spread evenly; bounds of an uneven part; runs left for whole waves
+  constexpr uint32_t kFound = 8;
+  __shared__ uint32_t ws[kWaves], found[kFound];
   __shared__ uint32_t lists[kList ? kWaves : 1][kList ? kVpList : 1];
   const uint32_t lane = lane_id(), wv = threadIdx.x / kWave, K = 1u << kb;
   constexpr uint32_t kPer = kVpMaxParts / kThreads;
-  uint32_t parts[kPer], sum = 0;
+  const uint32_t per = (P + kThreads - 1) / kThreads;  // ranges per thread
+  uint32_t parts[kPer], elems[kPer], sum = 0;
+  bool even[kPer];
 #pragma unroll
   for (uint32_t q = 0; q < kPer; ++q) {
-    const uint32_t r = threadIdx.x * kPer + q;
-    parts[q] = r < P ? vp_parts(tot, slices, P, r, split) : 0u;
+    const uint32_t r = threadIdx.x * per + q;
+    parts[q] = q < per && r < P ? vp_parts(tot, slices, P, r, split, &elems[q], &even[q]) : 0u;
     sum += parts[q];
   }
   const uint32_t incl = wave_incl_scan(sum);
   if (lane == kWave - 1) ws[wv] = incl;
-  if (threadIdx.x == 0) found[2] = 0;
+  if (threadIdx.x < kFound) found[threadIdx.x] = 0;
   __syncthreads();
   uint32_t first = incl - sum, all = 0;
   for (uint32_t w = 0; w < kThreads / kWave; ++w) {
@@ -550,9 +567,11 @@ __global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uin
 #pragma unroll
   for (uint32_t q = 0; q < kPer; ++q) {
     if (b >= first && b < first + parts[q]) {
-      found[0] = threadIdx.x * kPer + q;
+      found[0] = threadIdx.x * per + q;
       found[1] = b - first;
       found[2] = parts[q];
+      found[3] = elems[q];
+      found[4] = even[q];
     }
     first += parts[q];
   }
@@ -566,7 +585,34 @@ __global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uin
   if (np == 0) return;  // more workgroups than parts
   for (uint32_t i = threadIdx.x; i < words; i += kThreads) val32[i] = 0;
   __syncthreads();
-  const uint32_t t0 = (uint32_t)((uint64_t)n_tiles * part / np), t1 = (uint32_t)((uint64_t)n_tiles * (part + 1) / np);
+  uint32_t t0 = (uint32_t)((uint64_t)n_tiles * part / np), t1 = (uint32_t)((uint64_t)n_tiles * (part + 1) / np);
+  if (np > 1 && !found[4]) {
+    // equal shares of the elements: a bound is the number of tiles with fewer than so many elements before them
+    const uint32_t c0 = (uint32_t)((uint64_t)found[3] * part / np), c1 = (uint32_t)((uint64_t)found[3] * (part + 1) / np);
+    const uint32_t each_t = (n_tiles + kThreads - 1) / kThreads, a = threadIdx.x * each_t;
+    const uint32_t z = a + each_t < n_tiles ? a + each_t : n_tiles;
+    auto run = [&](uint32_t t) {
+      const uint32_t* row = runs + (uint64_t)t * (P + 1) + p;
+      return *gp(row + 1) - *gp(row);
+    };
+    uint32_t mine = 0;
+    for (uint32_t t = a; t < z; ++t) mine += run(t);
+    const uint32_t upto = wave_incl_scan(mine);
+    if (lane == kWave - 1) ws[wv] = upto;
+    __syncthreads();
+    uint32_t before = upto - mine, n0 = 0, n1 = 0;
+    for (uint32_t w = 0; w < wv; ++w) before += ws[w];
+    for (uint32_t t = a; t < z && before < c1; ++t) {
+      n0 += before < c0;
+      ++n1;
+      before += run(t);
+    }
+    if (n0) atomicAdd(&found[5], n0);
+    if (n1) atomicAdd(&found[6], n1);
+    __syncthreads();
+    t0 = found[5];
+    t1 = found[6];
+  }
   constexpr uint32_t kTile = vp_tile(OP);
   struct Piece {
     uint4 k, v0, v1;
@@ -659,7 +705,14 @@ __global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uin
     }
   } else {
     constexpr uint32_t kBatch = OP == 0 ? 4 : 2;
-    const uint32_t groups = kThreads / lpg, grp = threadIdx.x / lpg, sub = threadIdx.x % lpg;
+    // lanes per run: the pieces of the part's mean run
+    const uint32_t pieces = t1 > t0 ? found[3] / np / (t1 - t0) / 8 + 1 : 1;
+    uint32_t lpg_log2 = 0;
+    while ((1u << lpg_log2) < kThreads && pieces > 1u << lpg_log2) ++lpg_log2;
+    const uint32_t lpg = 1u << lpg_log2, groups = kThreads >> lpg_log2, grp = threadIdx.x >> lpg_log2;
+    const uint32_t sub = threadIdx.x & (lpg - 1);
+    // runs of more pieces than a few rounds of the group are left for whole waves
+    auto left = [&](uint32_t lo, uint32_t hi) { return lpg < kWave && (hi + 7) / 8 - lo / 8 > 4 * lpg; };
     struct Runs {
       uint32_t lo[kBatch], hi[kBatch];
     };
@@ -702,6 +755,10 @@ __global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uin
       }
 #pragma unroll
       for (uint32_t u = 0; u < kBatch; ++u) {  // runs longer than the group's pieces
+        if (left(cur.lo[u], cur.hi[u])) {
+          found[7] = 1;
+          continue;
+        }
         const uint64_t e0 = (uint64_t)(tb + u * groups + grp) * kTile;
         for (uint32_t e = (cur.lo[u] & ~7u) + 8 * (sub + lpg); e < cur.hi[u]; e += 8 * lpg) {
           Piece z;
@@ -713,6 +770,32 @@ __global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uin
       next = after;
 #pragma unroll
       for (uint32_t u = 0; u < kBatch; ++u) x[u] = y[u];
+    }
+    __syncthreads();
+    if (found[7]) {
+      // The rest of the long runs. (A wave finds them among 64 tiles at a time.)
+      for (uint32_t tb = t0 + wv * kWave; tb < t1; tb += kWaves * kWave) {
+        uint32_t lo = 0, hi = 0;
+        if (tb + lane < t1) {
+          const uint32_t* row = runs + (uint64_t)(tb + lane) * (P + 1) + p;
+          lo = *gp(row);
+          hi = *gp(row + 1);
+        }
+        for (uint64_t m = __ballot(left(lo, hi)); m; m &= m - 1) {
+          const int u = __builtin_ctzll(m);
+          const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)lo, u), h = (uint32_t)__builtin_amdgcn_readlane((int)hi, u);
+          const uint64_t e0 = (uint64_t)(tb + u) * kTile;
+          for (uint32_t e = (l & ~7u) + 8 * (lpg + lane); e - 8 * lane < h; e += 8 * kWave * kBatch) {
+            Piece z[kBatch];
+#pragma unroll
+            for (uint32_t g = 0; g < kBatch; ++g)
+              if (e + 8 * kWave * g < h) load(e0 + e + 8 * kWave * g, z[g]);
+#pragma unroll
+            for (uint32_t g = 0; g < kBatch; ++g)
+              if (e + 8 * kWave * g < h) put_in(e + 8 * kWave * g, l, h, z[g]);
+          }
+        }
+      }
     }
   }
   __syncthreads();
@@ -1345,16 +1428,15 @@ VpPlan vp_plan(uint64_t n, uint64_t R, uint32_t op, uint32_t n_cu) {
   p.elems = (uint64_t)p.n_tiles * tile;
   p.runs = (uint64_t)p.n_tiles * (p.P + 1);
   // two workgroups per CU over all ranges; a merged range touches its 2^kb
-  // keys, so four times as many elements at least; and ranges of even shares
+  // keys, so twice as many elements at least; and ranges of even shares
   // (within an eighth) are not split where there are enough of them
-  uint64_t split = std::max<uint64_t>(n / (2 * n_cu), 4ull << p.kb);
+  uint64_t split = std::max<uint64_t>(n / (2 * n_cu), 2ull << p.kb);
   if (p.P >= 2 * n_cu) split = std::max<uint64_t>(split, n / p.P + n / p.P / 8 + 1024);
   p.split = (uint32_t)std::min<uint64_t>(split, 1u << 30);
   p.grid = (uint32_t)(p.P + n / p.split);
   const uint64_t pieces = n / ((uint64_t)p.P * p.n_tiles + 1) / 8 + 1;  // 16-byte pieces of a run
-  for (p.lpg = 1; p.lpg < vp_fill_threads(op) && pieces > p.lpg; p.lpg *= 2) {}
   p.list = op == 0 && p.n_tiles >= 8192 && pieces <= 5;
-  p.slices = std::max(1u, std::min(kVpMaxSlices, p.n_tiles / 256));
+  p.slices = std::max(1u, std::min(kVpMaxSlices, p.n_tiles / 64));
   p.usable = p.P <= kVpMaxParts && n >= kVpMin && n < (1ull << 32);
   return p;
 }
@@ -1369,7 +1451,7 @@ static hipError_t vp_enqueue_fill(const IntLaunch& L, const VpPlan& p, const uin
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((k_vp_fill<OP, kList>), dim3(p.grid), dim3(vp_fill_threads(OP)), lds, s, L.R, p.kb, p.P, p.n_tiles,
-                     p.split, p.lpg, runs, pk, pv, tot, p.slices, L.dcnt, L.dval, L.blk);
+                     p.split, runs, pk, pv, tot, p.slices, L.dcnt, L.dval, L.blk);
   return hipGetLastError();
 }
 

@@ -237,7 +237,6 @@ struct VpPlan {
   uint64_t elems, runs; // partitioned elements; (P + 1) run starts per tile
   uint32_t split, grid; // elements per workgroup of the fill; its workgroups at most
   uint32_t slices;      // slices of the tiles whose elements are counted per range
-  uint32_t lpg;         // lanes that read a run together
   bool list;            // counting: runs' pieces listed per wave instead
   bool usable;
 };

@@ -420,3 +420,28 @@ def test_hash_of_keys_that_recur_with_a_sample(torch):
     r = _job(STRATS["hash"]).u32(keys, cap_keys=n)
     k, c = torch.unique(keys, return_counts=True)
     assert torch.equal(r.keys, k) and torch.equal(r.values.long(), c)
+
+
+# key ranges that the tiles of the input share unevenly: all of a range in a
+# few whole tiles (sorted keys), in some tiles and not in others, or in a stretch
+# of the input beside uniform keys; ranges of one workgroup and of several
+@pytest.mark.parametrize("n", [300_000, 1_100_000, 2_200_000])
+@pytest.mark.parametrize("R", [1 << 15, 1 << 20, 1 << 24])
+@pytest.mark.parametrize("kind", ["sorted", "blocks", "stretch", "one"])
+def test_global_array_of_unevenly_spread_keys(torch, n, R, kind):
+    rng = np.random.default_rng(n + R)
+    keys = rng.integers(0, R, n)
+    if kind == "sorted":
+        keys.sort()
+    elif kind == "blocks":
+        at = np.arange(n) // 16_384 % 8  # one eighth of the tiles holds the first keys alone
+        keys[at == 3] %= 3000
+    elif kind == "stretch":
+        keys[n // 2: n // 2 + n // 4] = R // 2 + rng.integers(0, 50, n // 4)
+    else:
+        keys[:] = R - 1
+    keys = keys.astype(np.uint32)
+    vals = rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+    j = _job(STRATS["global_array"])
+    for op in OPS:
+        _check(_run(torch, j, keys, None if op == "count" else vals, op, R), keys, None if op == "count" else vals, op)
