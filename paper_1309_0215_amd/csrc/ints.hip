@@ -1437,7 +1437,7 @@ VpPlan vp_plan(uint64_t n, uint64_t R, uint32_t op, uint32_t n_cu) {
   const uint64_t pieces = n / ((uint64_t)p.P * p.n_tiles + 1) / 8 + 1;  // 16-byte pieces of a run
   p.list = op == 0 && p.n_tiles >= 8192 && pieces <= 5;
   p.slices = std::max(1u, std::min(kVpMaxSlices, p.n_tiles / 64));
-  p.usable = p.P <= kVpMaxParts && n >= kVpMin && n < (1ull << 32);
+  p.usable = p.P <= kVpMaxParts && n >= kVpMin && n < (1ull << 32) && (op == 0 || R < kVpSparse * n);
   return p;
 }
 

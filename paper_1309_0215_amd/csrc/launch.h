@@ -228,9 +228,15 @@ hipError_t bloom_enqueue(const uint8_t* in, uint64_t n_bytes, uint32_t k, uint32
 hipError_t int_enqueue_global_array(const IntLaunch& L, hipStream_t s);
 // global array filled by key-range partitions, for a range and element count the plan finds usable
 // Fewer elements take atomics on the array: 131,072 uniform pairs over 20,000
-// keys 104 us, 113 us partitioned (three more launches); 262,144 pairs 107 us
-// partitioned whatever the keys, atomics up to 190 us on skewed ones.
+// keys 104 us, 113 us partitioned (three more launches); 262,144 pairs 70 to
+// 110 us partitioned whatever the keys, atomics 65 to 340 us on skewed ones.
 constexpr uint64_t kVpMin = 1ull << 18;
+// So do elements with values on so many times as many keys, since the ranges'
+// counts and values are all written whatever they hold: 2^18 pairs over 2^25
+// keys, SUM, 178 us by atomics and 280 us partitioned, 2^19 pairs 209 and
+// 304 us, 2^21 pairs 405 and 360 us. (Counts alone are level there: 2^18 over
+// 2^26 keys 255 and 258 us.)
+constexpr uint64_t kVpSparse = 64;
 struct VpPlan {
   uint32_t kb, P;       // ranges of 2^kb keys
   uint32_t n_tiles;

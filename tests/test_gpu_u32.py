@@ -445,3 +445,18 @@ def test_global_array_of_unevenly_spread_keys(torch, n, R, kind):
     j = _job(STRATS["global_array"])
     for op in OPS:
         _check(_run(torch, j, keys, None if op == "count" else vals, op, R), keys, None if op == "count" else vals, op)
+
+
+# pairs on 64 times as many keys, where atomics on the array take the
+# partitions' place, and one pair more; the last range of the largest
+# partitions of values (2^25 keys) and past it
+@pytest.mark.parametrize("n,R", [(1 << 18, 1 << 24), ((1 << 18) + 1, 1 << 24), (600_000, 1 << 25), (600_000, (1 << 25) + 1)])
+def test_global_array_of_few_pairs_on_many_keys(torch, n, R):
+    rng = np.random.default_rng(n)
+    keys = rng.integers(0, R, n).astype(np.uint32)
+    keys[:2] = 0, R - 1
+    vals = rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+    j = _job(STRATS["global_array"])
+    for op in OPS:
+        for _ in range(2):  # the arrays are clean for the next job
+            _check(_run(torch, j, keys, vals, op, R), keys, vals, op)
