@@ -874,6 +874,9 @@ constexpr uint32_t kPartUnroll = 2;     // records per thread and round
 constexpr uint32_t kPartHints = 2048;   // blocks of records whose first segment is kept
 // Jobs of a batch whose records the partitions stage (more take the tables)
 constexpr uint32_t kDirectJobs = 1024;
+// Items that gather staged records: a job's 256 partitions take one each, or
+// four, 16, ... together, until the jobs of a launch need no more than this.
+constexpr uint32_t kGatherItems = 4096;
 template <int L>
 __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __restrict__ jobs, uint32_t n_jobs, uint32_t debug_hash,
                                                              uint32_t* __restrict__ staged,
@@ -1133,52 +1136,64 @@ MR_DEV unsigned long long compact_entry(const WordJob& J, uint64_t i) {
   return w;
 }
 
-// The first n_direct * 256 work items gather the staged records: item
-// (job, partition) adds up the counts of the partitions before its own and
-// copies its records to their place, without an atomic (the places used to
-// come from one counter per job, at about 35 ns an update: 40 us of 512).
+// The first work items gather the staged records: an item takes kMaxWordParts /
+// gather partitions of one job, places its partitions' counts by a scan of all
+// of the job's, and copies their records there, without an atomic (the places
+// used to come from one counter per job, at about 35 ns an update: 40 us of
+// 512). A job has as many items as leave each four, 16, ... partitions where
+// there are many jobs (1000 jobs of 4 KiB: 159 us with 256 items each, 14 with four).
 // Then work item = `item` slots of one job's table, 1024 or 4096 (tables are
 // powers of two >= 4096 slots at 4096-aligned arena offsets, so no item
 // straddles two tables), where the table holds anything. Pass 1 counts the
 // entries, one atomic reserves their places after the staged records, pass 2
 // writes the records and clears the slots.
 __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob* __restrict__ jobs, uint32_t n_jobs,
-                                                                   uint32_t n_direct, const uint32_t* __restrict__ staged,
+                                                                   uint32_t n_direct, uint32_t gather,
+                                                                   const uint32_t* __restrict__ staged,
                                                                    const unsigned long long* __restrict__ staged_bytes,
                                                                    uint64_t total_slots, uint32_t item) {
   __shared__ uint32_t s_cnt, s_pos;
   __shared__ unsigned long long s_base, s_bytes;
-  __shared__ uint32_t w_before[kCompactThreads / kWave], w_all[kCompactThreads / kWave];
+  __shared__ uint32_t s_at[kMaxWordParts + 1];  // staged records of the job before each partition
+  __shared__ uint32_t w_all[kCompactThreads / kWave];
   __shared__ unsigned long long w_bytes[kCompactThreads / kWave];
   static_assert(kCompactThreads == kMaxWordParts, "one thread per partition's count");
   const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
-  // staged records of job j before partition p, and in all
-  auto staged_sums = [&](uint32_t j, uint32_t p, uint32_t& before, uint32_t& all) {
+  // staged records of job j before partition threadIdx.x, and in all
+  auto staged_sums = [&](uint32_t j, uint32_t& before, uint32_t& all) {
     const uint32_t c = gp(staged)[j * kMaxWordParts + threadIdx.x];
-    const uint32_t ib = wave_incl_scan(threadIdx.x < p ? c : 0u), ia = wave_incl_scan(c);
+    const uint32_t incl = wave_incl_scan(c);
     __syncthreads();  // the previous use has been read
-    if (lane == kWave - 1) {
-      w_before[wv] = ib;
-      w_all[wv] = ia;
-    }
+    if (lane == kWave - 1) w_all[wv] = incl;
     __syncthreads();
-    before = all = 0;
+    before = incl - c;
+    all = 0;
     for (uint32_t w = 0; w < kCompactThreads / kWave; ++w) {
-      before += w_before[w];
+      if (w < wv) before += w_all[w];
       all += w_all[w];
     }
   };
-  const uint64_t n_gather = (uint64_t)n_direct * kMaxWordParts;
+  const uint64_t n_gather = (uint64_t)n_direct * gather;
   for (uint64_t g = blockIdx.x; g < n_gather; g += gridDim.x) {
-    const uint32_t j = (uint32_t)(g / kMaxWordParts), p = (uint32_t)(g % kMaxWordParts);
+    const uint32_t j = (uint32_t)(g / gather), each = kMaxWordParts / gather, p0 = (uint32_t)(g % gather) * each;
     const WordJob& J = jobs[j];
     uint32_t before, all;
-    staged_sums(j, p, before, all);
-    const uint32_t n = gp(staged)[j * kMaxWordParts + p];
-    const uint8_t* from = reinterpret_cast<const uint8_t*>(reinterpret_cast<const WRec*>(J.recs2) + p * (J.cap / kMaxWordParts));
-    uint8_t* to = reinterpret_cast<uint8_t*>(reinterpret_cast<WRec*>(J.recs) + before);
-    for (uint32_t i = threadIdx.x; i < 2 * n; i += kCompactThreads) gstore16(to + 16ull * i, gload16(from + 16ull * i));
-    if (p == 0) {
+    staged_sums(j, before, all);
+    s_at[threadIdx.x] = before;
+    if (threadIdx.x == 0) s_at[kMaxWordParts] = all;
+    __syncthreads();
+    const uint32_t room = (uint32_t)(J.cap / kMaxWordParts), r0 = s_at[p0], r1 = s_at[p0 + each];
+    // half records, in the job's order; the last partition that starts at or before a record has it
+    for (uint32_t i = 2 * r0 + threadIdx.x; i < 2 * r1; i += kCompactThreads) {
+      uint32_t lo = p0, hi = p0 + each;
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (s_at[mid] <= i / 2) lo = mid; else hi = mid;
+      }
+      const uint64_t from = 2 * ((uint64_t)lo * room - s_at[lo]) + i;
+      gstore16(reinterpret_cast<uint4*>(J.recs) + i, gload16(reinterpret_cast<const uint4*>(J.recs2) + from));
+    }
+    if (p0 == 0) {
       unsigned long long y = gp(staged_bytes)[j * kMaxWordParts + threadIdx.x];
 #pragma unroll
       for (int o = kWave / 2; o; o >>= 1) y += __shfl_xor(y, o);
@@ -1214,7 +1229,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob
         any |= w >= p0 / 32 && w <= p1 / 32 ? bits : 0u;
       }
       if (!any) continue;
-      staged_sums(lo, 0, before, first);
+      staged_sums(lo, before, first);
     }
     if (threadIdx.x == 0) {
       s_cnt = 0;
@@ -2230,9 +2245,11 @@ hipError_t words_enqueue_reduce(const WordsLaunch& L, hipStream_t s) {
   // 4096 slots each, 13 at 1024)
   const uint32_t item = L.total_slots <= (L.n_parts ? 1ull << 22 : 1ull << 20) ? kCompactSmall : kCompactLarge;
   const uint32_t n_direct = L.n_parts && L.n_jobs <= kDirectJobs ? L.n_jobs : 0;
-  const uint64_t tiles = std::max<uint64_t>((L.total_slots + item - 1) / item, (uint64_t)n_direct * kMaxWordParts);
+  uint32_t gather = kMaxWordParts;
+  while (gather > 1 && (uint64_t)n_direct * gather > kGatherItems) gather /= 4;
+  const uint64_t tiles = std::max<uint64_t>((L.total_slots + item - 1) / item, (uint64_t)n_direct * gather);
   const uint32_t cgrid = (uint32_t)(tiles < 4096 ? tiles : 4096);
-  hipLaunchKernelGGL(k_words_compact, dim3(cgrid ? cgrid : 1), dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, n_direct,
+  hipLaunchKernelGGL(k_words_compact, dim3(cgrid ? cgrid : 1), dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, n_direct, gather,
                      L.bucket_start, L.bucket_bstart, L.total_slots, item);
   if (L.n_jobs <= kRankJobs) {
     // plans the sort itself

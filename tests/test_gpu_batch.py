@@ -121,3 +121,27 @@ def test_full_batched_config_matches_per_job_runs(torch):
         exp = list(ex.map(oracle.words, bufs))
     for i in range(len(bufs)):
         assert _oracle_equal(batched[i], bufs[i], exp=exp[i]), i
+
+
+# the compaction's items take all, four, 16, ... or one of a job's 256 staged
+# partitions each, by the number of jobs; past 1024 jobs the tables take the
+# records' place
+@pytest.mark.parametrize("n", [2, 16, 17, 64, 65, 256, 257, 1024, 1025])
+def test_batches_of_many_jobs(torch, n):
+    """A few jobs of many words among small ones, some empty or of one word."""
+    from paper_1309_0215_amd import Job
+    base = [gen.text(i, 300 + 97 * i, V=20 + i, s=0.8) for i in range(30)]
+    base[5], base[6] = np.zeros(0, np.uint8), np.frombuffer(b" one ", np.uint8)
+    base[7] = np.frombuffer(b"a much longer word than sixteen bytes and others", np.uint8)
+    want = [oracle.words(b) for b in base]
+    pick = [i % 30 for i in range(n)]
+    big = gen.text(77, 400_000, V=30_000, s=0.6)
+    bufs = [base[i] for i in pick]
+    exps = [want[i] for i in pick]
+    for at in {1, n - 1}:
+        bufs[at], exps[at] = big, oracle.words(big)
+    dev = [_dev(torch, b) if len(b) else torch.empty(0, dtype=torch.uint8, device="cuda:0") for b in bufs]
+    job = Job(device=0)
+    for _ in range(3):
+        for r, b, e in zip(job.words_batch(dev), bufs, exps):
+            assert _oracle_equal(r, b, exp=e)
