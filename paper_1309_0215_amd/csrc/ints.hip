@@ -1063,12 +1063,14 @@ __global__ __launch_bounds__(1024) void k_int_sample(IntIn in, IntPub* host) {
   for (uint32_t u = 0; u < kPer; ++u) {
     if (k[u] == kEmptyKey) continue;
     uint32_t s = (uint32_t)hash_u32(k[u]) & (S - 1);
+    // (reads first: atomics on a frequent key's slot queue)
     for (;;) {  // (the set has twice the slots: a free one is met)
-      const uint32_t cur = atomicCAS(&set[s], kEmptyKey, k[u]);
+      uint32_t cur = __hip_atomic_load(&set[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (cur == kEmptyKey) cur = atomicCAS(&set[s], kEmptyKey, k[u]);
       if (cur == kEmptyKey || cur == k[u]) break;
       s = (s + 1) & (S - 1);
     }
-    atomicAdd(&met[s], 1u);
+    if (__hip_atomic_load(&met[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < 3) atomicAdd(&met[s], 1u);
   }
   __syncthreads();
   // (the counts below 2^16 of a wave's 1024 slots in the halves of one sum)
