@@ -895,7 +895,8 @@ constexpr uint32_t kPartHints = 2048;   // blocks of records whose first segment
 constexpr uint32_t kDirectJobs = 1024;
 // Items that gather staged records: a job's 256 partitions take one each, or
 // four, 16, ... together, until the jobs of a launch need no more than this.
-constexpr uint32_t kGatherItems = 4096;
+constexpr uint32_t kGatherItems = 1024;
+constexpr uint32_t kCompactGroup = 4;  // items of a large table compacted together
 template <int L>
 __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __restrict__ jobs, uint32_t n_jobs, uint32_t debug_hash,
                                                              uint32_t* __restrict__ staged,
@@ -1163,9 +1164,13 @@ MR_DEV unsigned long long compact_entry(const WordJob& J, uint64_t i) {
 // there are many jobs (1000 jobs of 4 KiB: 159 us with 256 items each, 14 with four).
 // Then work item = `item` slots of one job's table, 1024 or 4096 (tables are
 // powers of two >= 4096 slots at 4096-aligned arena offsets, so no item
-// straddles two tables), where the table holds anything. Pass 1 counts the
-// entries, one atomic reserves their places after the staged records, pass 2
-// writes the records and clears the slots.
+// straddles two tables), where the table holds anything; kGroup items of one
+// job far from each other are taken together, so that neither the few items
+// of a few partitions with keys in the table nor the atomics of many are the
+// work of one workgroup or one counter. Pass 1 counts the entries, one atomic
+// reserves their places after the staged records, pass 2 writes the records
+// and clears the slots.
+template <uint32_t kGroup>
 __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob* __restrict__ jobs, uint32_t n_jobs,
                                                                    uint32_t n_direct, uint32_t gather,
                                                                    const uint32_t* __restrict__ staged,
@@ -1225,7 +1230,9 @@ __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob
       }
     }
   }
-  for (uint64_t t0 = (uint64_t)blockIdx.x * item; t0 < total_slots; t0 += (uint64_t)gridDim.x * item) {
+  const uint64_t n_groups = (total_slots + item - 1) / item / kGroup;  // (kGroup 1, or a divisor of the items of one job)
+  for (uint64_t t = blockIdx.x; t < n_groups; t += gridDim.x) {
+    const uint64_t t0 = t * item;
     uint32_t lo = 0, hi = n_jobs;
     while (hi - lo > 1) {
       const uint32_t mid = (lo + hi) >> 1;
@@ -1234,20 +1241,28 @@ __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob
     const bool direct = lo < n_direct;
     const WordJob& J = jobs[lo];
     const uint64_t i0 = t0 - J.slot_base;
-    uint32_t before = 0, first = 0;
+    const uint64_t apart = n_groups * item;  // from one item of the group to the next
+    uint32_t before = 0, first = 0, with_keys = (1u << kGroup) - 1u;  // the group's items
     if (direct) {
-      // the partitions whose region these slots touch (without regions, all) have no key in the table
-      const uint32_t p0 = J.region_log2 ? (uint32_t)(i0 >> J.region_log2) : 0u;
-      const uint32_t p1 = J.region_log2 ? (uint32_t)((i0 + item - 1) >> J.region_log2) : kMaxWordParts - 1;
-      uint32_t any = 0;
+      uint32_t map[kPartMapWords];
 #pragma unroll
-      for (uint32_t w = 0; w < kPartMapWords; ++w) {
-        uint32_t bits = gp(in_table(J))[w];
-        if (w == p0 / 32) bits &= ~0u << (p0 & 31u);
-        if (w == p1 / 32) bits &= ~0u >> (31u - (p1 & 31u));
-        any |= w >= p0 / 32 && w <= p1 / 32 ? bits : 0u;
+      for (uint32_t w = 0; w < kPartMapWords; ++w) map[w] = gp(in_table(J))[w];
+      for (uint32_t g = 0; g < kGroup; ++g) {
+        // the partitions whose region these slots touch (without regions, all) have no key in the table
+        const uint64_t i = i0 + g * apart;
+        const uint32_t p0 = J.region_log2 ? (uint32_t)(i >> J.region_log2) : 0u;
+        const uint32_t p1 = J.region_log2 ? (uint32_t)((i + item - 1) >> J.region_log2) : kMaxWordParts - 1;
+        uint32_t any = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < kPartMapWords; ++w) {
+          uint32_t bits = map[w];
+          if (w == p0 / 32) bits &= ~0u << (p0 & 31u);
+          if (w == p1 / 32) bits &= ~0u >> (31u - (p1 & 31u));
+          any |= w >= p0 / 32 && w <= p1 / 32 ? bits : 0u;
+        }
+        if (!any) with_keys &= ~(1u << g);
       }
-      if (!any) continue;
+      if (!with_keys) continue;
       staged_sums(lo, before, first);
     }
     if (threadIdx.x == 0) {
@@ -1257,7 +1272,9 @@ __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob
     }
     __syncthreads();
     uint32_t mine = 0;
-    for (uint32_t q = threadIdx.x; q < item; q += kCompactThreads) mine += compact_entry(J, i0 + q) ? 1u : 0u;
+    for (uint32_t g = 0; g < kGroup; ++g)
+      if (with_keys >> g & 1u)
+        for (uint32_t q = threadIdx.x; q < item; q += kCompactThreads) mine += compact_entry(J, i0 + g * apart + q) ? 1u : 0u;
     if (mine) atomicAdd(&s_cnt, mine);
     __syncthreads();
     // Staged and table records together may pass the table's slots, which the
@@ -1272,25 +1289,28 @@ __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob
     __syncthreads();
     if (s_cnt && s_base == ~0ull) continue;
     unsigned long long bytes = 0;
-    for (uint32_t q = threadIdx.x; q < item; q += kCompactThreads) {
-      const uint64_t i = i0 + q;
-      const unsigned long long w = compact_entry(J, i);
-      if (!w) continue;
-      const uint32_t cnt = J.tc[i];
-      J.tw[i] = 0ull;
-      J.tc[i] = 0u;
-      const uint64_t off = w >> 32;
-      uint64_t len = (w >> 16) & 0xFFFFull;
-      if (len == 0xFFFFull) len = word_length_slow(J, J.st->valid_lo, J.st->valid_hi, off);
-      const uint4 k = load_key16(J.in, off, (uint32_t)(len < 16 ? len : 16));
-      WRec r;
-      r.p[0] = bswap32(k.x); r.p[1] = bswap32(k.y); r.p[2] = bswap32(k.z); r.p[3] = bswap32(k.w);
-      r.len = (uint32_t)len;
-      r.off = (uint32_t)off;
-      r.cnt = cnt;
-      r.pad = (uint32_t)i;  // the table slot, for callers that map slots to output ranks
-      reinterpret_cast<WRec*>(J.recs)[s_base + atomicAdd(&s_pos, 1u)] = r;
-      bytes += len;
+    for (uint32_t g = 0; g < kGroup; ++g) {
+      if (!(with_keys >> g & 1u)) continue;
+      for (uint32_t q = threadIdx.x; q < item; q += kCompactThreads) {
+        const uint64_t i = i0 + g * apart + q;
+        const unsigned long long w = compact_entry(J, i);
+        if (!w) continue;
+        const uint32_t cnt = J.tc[i];
+        J.tw[i] = 0ull;
+        J.tc[i] = 0u;
+        const uint64_t off = w >> 32;
+        uint64_t len = (w >> 16) & 0xFFFFull;
+        if (len == 0xFFFFull) len = word_length_slow(J, J.st->valid_lo, J.st->valid_hi, off);
+        const uint4 k = load_key16(J.in, off, (uint32_t)(len < 16 ? len : 16));
+        WRec r;
+        r.p[0] = bswap32(k.x); r.p[1] = bswap32(k.y); r.p[2] = bswap32(k.z); r.p[3] = bswap32(k.w);
+        r.len = (uint32_t)len;
+        r.off = (uint32_t)off;
+        r.cnt = cnt;
+        r.pad = (uint32_t)i;  // the table slot, for callers that map slots to output ranks
+        reinterpret_cast<WRec*>(J.recs)[s_base + atomicAdd(&s_pos, 1u)] = r;
+        bytes += len;
+      }
     }
     if (bytes) atomicAdd(&s_bytes, bytes);
     __syncthreads();
@@ -2266,10 +2286,18 @@ hipError_t words_enqueue_reduce(const WordsLaunch& L, hipStream_t s) {
   const uint32_t n_direct = L.n_parts && L.n_jobs <= kDirectJobs ? L.n_jobs : 0;
   uint32_t gather = kMaxWordParts;
   while (gather > 1 && (uint64_t)n_direct * gather > kGatherItems) gather /= 4;
-  const uint64_t tiles = std::max<uint64_t>((L.total_slots + item - 1) / item, (uint64_t)n_direct * gather);
-  const uint32_t cgrid = (uint32_t)(tiles < 4096 ? tiles : 4096);
-  hipLaunchKernelGGL(k_words_compact, dim3(cgrid ? cgrid : 1), dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, n_direct, gather,
-                     L.bucket_start, L.bucket_bstart, L.total_slots, item);
+  // (1.6 M distinct words of 20 bytes, a table of 2^22 slots: 165 us with an
+  // atomic per item of 1024, 91 in groups of four; 512 MiB of text, whose table
+  // holds few keys: 13 and 15 us)
+  const uint32_t group = n_direct == 1 && L.total_slots >= 512ull * item ? kCompactGroup : 1u;
+  const uint64_t tiles = std::max<uint64_t>((L.total_slots + item - 1) / item / group, (uint64_t)n_direct * gather);
+  const dim3 cgrid((uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(tiles, 4096)));
+  if (group == 1)
+    hipLaunchKernelGGL(k_words_compact<1>, cgrid, dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, n_direct, gather,
+                       L.bucket_start, L.bucket_bstart, L.total_slots, item);
+  else
+    hipLaunchKernelGGL(k_words_compact<kCompactGroup>, cgrid, dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, n_direct, gather,
+                       L.bucket_start, L.bucket_bstart, L.total_slots, item);
   if (L.n_jobs <= kRankJobs) {
     // plans the sort itself
     hipLaunchKernelGGL(k_sort_ranks, dim3(L.sort_grid), dim3(kSortThreads), 0, s, L.jobs, L.n_jobs, L.totals,
