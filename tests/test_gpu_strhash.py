@@ -63,3 +63,12 @@ def test_empty_and_all_separators(job):
         d = _dev(buf) if len(buf) else torch.empty(0, dtype=torch.uint8, device="cuda:0")
         h, sched, _ = job.hash_words(d, schedule=True)
         assert h.numel() == 0 and sched.numel() == 0
+
+
+# the word starts per 16-byte chunk are scanned by one workgroup up to 65,536
+# chunks (64 steps of 64 per wave), by three kernels past it, in tiles of 4096
+@pytest.mark.parametrize("n", [65_536 * 16 - 1, 65_536 * 16, 65_536 * 16 + 1, 69_632 * 16, 69_632 * 16 + 1])
+def test_scans_at_the_one_workgroup_limit(job, n):
+    buf = gen.text(32, n, V=4000, s=0.9, lmin=1, lmax=20)
+    h, _, _ = job.hash_words(_dev(buf))
+    assert np.array_equal(h.cpu().numpy().view(np.uint64), oracle.word_hashes(buf))

@@ -460,3 +460,40 @@ def test_global_array_of_few_pairs_on_many_keys(torch, n, R):
     for op in OPS:
         for _ in range(2):  # the arrays are clean for the next job
             _check(_run(torch, j, keys, vals, op, R), keys, vals, op)
+
+
+def _reduced(torch, keys, vals, op):
+    """Distinct keys ascending and their reduced values, in 64 bits."""
+    k, inv, n = torch.unique(keys.long() & 0xFFFFFFFF, return_inverse=True, return_counts=True)
+    if op == "count":
+        return k, n
+    v = vals.long() & 0xFFFFFFFF
+    if op == "sum":
+        return k, torch.zeros_like(k).index_add_(0, inv, v)
+    return k, torch.zeros_like(k).scatter_reduce_(0, inv, v, "a" + op, include_self=False)
+
+
+# Inputs past 2^20 elements take tiles of 8192 (one whole tile more, one element
+# of the next, one short of it) and chunks of 1024; 2^26 and one more fill the
+# chunk counts' scan by one workgroup (65,536) and pass it.
+@pytest.mark.parametrize("n,kinds", [((1 << 20) + d, ("one", "own", "some")) for d in (1, 1023, 1024, 1025, 8191, 8192, 8193)]
+                         + [((1 << 26) + d, ("runs",)) for d in (0, 1)])
+def test_sort_of_large_inputs_at_tile_and_chunk_edges(torch, n, kinds):
+    g = torch.Generator(device="cuda:0").manual_seed(n)
+    i = torch.arange(n, device="cuda:0")
+    vals = torch.randint(-(1 << 31), 1 << 31, (n,), generator=g, device="cuda:0").int()
+    for kind in kinds:
+        if kind == "one":
+            k = torch.full_like(i, 0xFFFFFFFF)
+        elif kind == "own":
+            k = i * 2654435761 % (1 << 32)
+        elif kind == "some":
+            k = torch.randint(0, 50, (n,), generator=g, device="cuda:0") ** 4
+        else:  # runs of 1500, longer than a chunk, out of order
+            k = (i // 1500 * 7919) % 65_536
+        keys = torch.where(k >= 1 << 31, k - (1 << 32), k).int()
+        for op in OPS if n < 1 << 26 else ("count", "sum"):
+            r = _job(STRATS["sort"]).u32(keys, None if op == "count" else vals, op=OPS[op], cap_keys=n if kind == "own" else 65_536)
+            k, v = _reduced(torch, keys, vals, op)
+            assert torch.equal(r.keys.long() & 0xFFFFFFFF, k)
+            assert torch.equal(r.values.long() if op == "sum" else r.values.long() & 0xFFFFFFFF, v)
