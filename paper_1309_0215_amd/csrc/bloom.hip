@@ -338,8 +338,10 @@ template <uint32_t H>
 static hipError_t bloom_tiles(const uint8_t* in, uint64_t n_bytes, uint32_t k, uint32_t m, const BloomPlan& b, uint32_t* rows,
                               uint16_t* part, hipStream_t s) {
   const uint32_t lds = 2 * b.cap + 4 * b.S;
+  // (the most any filter takes: calls on other threads set the same)
+  constexpr uint32_t kMost = 2 * bloom_batches(H) * kBloomBatch * H + 4 * kBloomMaxSubs;
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_bloom_tile<H>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMost);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_bloom_tile<H>, dim3(b.n_tiles), dim3(kBloomThreads), lds, s, in, n_bytes, b.n_kmers, k, m, b.sb, b.S,
                      b.row_words, rows, part);
@@ -367,6 +369,9 @@ hipError_t bloom_enqueue(const uint8_t* in, uint64_t n_bytes, uint32_t k, uint32
     case 7: e = bloom_tiles<7>(in, n_bytes, k, mb, b, rows, part, s); break;
     case 8: e = bloom_tiles<8>(in, n_bytes, k, mb, b, rows, part, s); break;
   }
+  if (e != hipSuccess) return e;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_bloom_fill), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)(kBloomMaxPer << (kBloomSubBits - 3)));
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_bloom_fill, dim3(b.grid), dim3(kBloomFillThreads), b.per << (b.sb - 3), s, part, rows, b.row_words,
                      b.n_tiles, b.cap, b.sb, b.per, b.lpg, b.n_words, words);

@@ -523,6 +523,7 @@ MR_DEV uint32_t vp_parts(const uint32_t* __restrict__ tot, uint32_t slices, uint
 // blocks.
 constexpr uint32_t kVpSinks = 32;
 constexpr uint32_t kVpList = 384;  // pieces listed per wave
+constexpr uint32_t vp_max_kb(uint32_t op) { return op == 0 ? 15 : 14; }
 constexpr uint32_t vp_fill_lds(uint32_t op, uint32_t kb) { return (op == 0 ? 4 : op == 1 ? 9 : 5) * ((1u << kb) + kVpSinks); }
 
 template <int OP, bool kList>
@@ -1421,7 +1422,7 @@ uint64_t scan_sums_count(uint64_t n) { return (n + kScanTile - 1) / kScanTile + 
 // 2048 (values, up to 2^14 keys), so that a tile's run of a range stays long.
 VpPlan vp_plan(uint64_t n, uint64_t R, uint32_t op, uint32_t n_cu) {
   VpPlan p{};
-  const uint32_t kb_max = op == 0 ? 15 : 14;
+  const uint32_t kb_max = vp_max_kb(op);
   p.kb = 12;
   while (p.kb < kb_max && R > (uint64_t)512 << p.kb && (op == 0 || p.kb == 12 || R > (uint64_t)kVpMaxParts << p.kb)) ++p.kb;
   p.P = (uint32_t)((R + (1ull << p.kb) - 1) >> p.kb);
@@ -1447,9 +1448,9 @@ template <int OP, bool kList>
 static hipError_t vp_enqueue_fill(const IntLaunch& L, const VpPlan& p, const uint32_t* runs, const uint16_t* pk,
                                   const uint32_t* pv, const uint32_t* tot, hipStream_t s) {
   const uint32_t lds = vp_fill_lds(OP, p.kb);
-  if (lds > 32 * 1024) {  // (with the static LDS past 64 KB)
+  if (lds > 32 * 1024) {  // (with the static LDS past 64 KB; the most any range takes: calls on other threads set the same)
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_vp_fill<OP, kList>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)vp_fill_lds(OP, vp_max_kb(OP)));
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((k_vp_fill<OP, kList>), dim3(p.grid), dim3(vp_fill_threads(OP)), lds, s, L.R, p.kb, p.P, p.n_tiles,
