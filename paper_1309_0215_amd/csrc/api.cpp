@@ -1736,7 +1736,7 @@ mr_status run_bloom(mr_job* job, mr_reduce_op op, const void* d_input, uint64_t 
   if (k > 32 || h > 8) return fail(MR_ERR_INVALID_ARG, "Bloom filter k-mer length %u (1..32) or hash count %u (1..8)", k, h);
   if (m == 0) return fail(MR_ERR_INVALID_ARG, "the Bloom filter needs its size in bits as key_range");
   if (m > (1ull << 29)) return fail(MR_ERR_UNSUPPORTED, "Bloom filters of more than 2^29 bits are not supported");
-  const BloomPlan b = bloom_plan(bytes, k, h, m);
+  const BloomPlan b = bloom_plan(bytes, k, h, m, (uint32_t)job->n_cu);
   if (!b.ok) return fail(MR_ERR_UNSUPPORTED, "Bloom filter input too large (%llu positions)", (unsigned long long)b.max_entries);
   out->n_keys = b.n_words;
   out->key_bytes_used = 0;
@@ -1904,7 +1904,7 @@ extern "C" mr_status mr_workspace_bytes(const mr_job_config* cfg, mr_map_kind ki
       const uint32_t k = cfg->bloom_k ? cfg->bloom_k : 20u, h = cfg->bloom_hashes ? cfg->bloom_hashes : 7u;
       if (!key_range || key_range > (1ull << 29) || k > 32 || h > 8)
         return fail(MR_ERR_INVALID_ARG, "the Bloom filter needs 1 <= key_range <= 2^29 bits, k <= 32, hashes <= 8");
-      const BloomPlan b = bloom_plan(n, k, h, key_range);
+      const BloomPlan b = bloom_plan(n, k, h, key_range, (uint32_t)n_cu);
       r.add(bloom_carve(b).bytes);
       break;
     }

@@ -32,7 +32,7 @@ constexpr uint32_t kBloomSubBitsMin = 5;      // a sub-range is whole words
 constexpr uint32_t kBloomSubsWanted = 1024;   // smaller sub-ranges up to this many: counters that seldom meet
 constexpr uint32_t kBloomMaxSubs = 8192;      // m up to 2^29 bits
 constexpr uint32_t kBloomMaxPer = 9;          // sub-ranges per range: 72 KB of LDS, two workgroups per CU
-constexpr uint32_t kBloomFillSlots = 512;     // fill workgroups resident at once (two on each of 256 CUs)
+constexpr uint32_t kBloomFillPerCu = 2;       // fill workgroups resident at once on a CU
 constexpr uint32_t kBloomThreads = 1024;
 constexpr uint32_t kBloomBatch = 4 * kBloomThreads;  // k-mers staged at once, four per thread
 constexpr uint32_t kBloomMaxK = 32;
@@ -304,7 +304,7 @@ __global__ void k_bloom_zero_words(uint32_t* __restrict__ words, uint64_t n) {
   for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) words[i] = 0u;
 }
 
-BloomPlan bloom_plan(uint64_t n_bytes, uint32_t k, uint32_t h, uint64_t m) {
+BloomPlan bloom_plan(uint64_t n_bytes, uint32_t k, uint32_t h, uint64_t m, uint32_t n_cu) {
   BloomPlan b{};
   b.ok = k >= 1 && k <= kBloomMaxK && h >= 1 && h <= kBloomMaxH && m >= 1 && m <= (uint64_t)kBloomMaxSubs << kBloomSubBits;
   if (!b.ok) return b;
@@ -317,8 +317,9 @@ BloomPlan bloom_plan(uint64_t n_bytes, uint32_t k, uint32_t h, uint64_t m) {
   while (b.sb < kBloomSubBits && ((m - 1) >> b.sb) + 1 > kBloomSubsWanted) ++b.sb;
   b.S = (uint32_t)((m - 1) >> b.sb) + 1;
   // as few sub-ranges per range as fill the chip in whole rounds of workgroups
-  const uint32_t rounds = (b.S + kBloomFillSlots * kBloomMaxPer - 1) / (kBloomFillSlots * kBloomMaxPer);
-  b.per = (b.S + kBloomFillSlots * rounds - 1) / (kBloomFillSlots * rounds);
+  const uint32_t slots = kBloomFillPerCu * n_cu;
+  const uint32_t rounds = (b.S + slots * kBloomMaxPer - 1) / (slots * kBloomMaxPer);
+  b.per = (b.S + slots * rounds - 1) / (slots * rounds);
   b.grid = (b.S + b.per - 1) / b.per;
   const uint32_t tile = bloom_batches(h) * kBloomBatch;
   b.cap = tile * h;

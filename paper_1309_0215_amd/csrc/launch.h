@@ -220,7 +220,7 @@ struct BloomPlan {
   uint32_t lpg;           // lanes that take a tile's run of a range together
   bool ok;                // parameters and sizes within the kernels' limits
 };
-BloomPlan bloom_plan(uint64_t n_bytes, uint32_t k, uint32_t h, uint64_t m);
+BloomPlan bloom_plan(uint64_t n_bytes, uint32_t k, uint32_t h, uint64_t m, uint32_t n_cu);
 uint64_t bloom_row_bytes(const BloomPlan& b);
 uint64_t bloom_part_bytes(const BloomPlan& b);
 hipError_t bloom_enqueue(const uint8_t* in, uint64_t n_bytes, uint32_t k, uint32_t h, uint64_t m, const BloomPlan& b,
