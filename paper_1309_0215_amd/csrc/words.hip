@@ -895,7 +895,7 @@ constexpr uint32_t kPartHints = 2048;   // blocks of records whose first segment
 constexpr uint32_t kDirectJobs = 1024;
 // Items that gather staged records: a job's 256 partitions take one each, or
 // four, 16, ... together, until the jobs of a launch need no more than this.
-constexpr uint32_t kGatherItems = 1024;
+constexpr uint32_t kGatherItems = 4096;
 constexpr uint32_t kCompactGroup = 4;  // items of a large table compacted together
 template <int L>
 __global__ __launch_bounds__(kMapThreads) void k_words_parts(const WordJob* __restrict__ jobs, uint32_t n_jobs, uint32_t debug_hash,
@@ -1156,12 +1156,13 @@ MR_DEV unsigned long long compact_entry(const WordJob& J, uint64_t i) {
   return w;
 }
 
-// The first work items gather the staged records: an item takes kMaxWordParts /
-// gather partitions of one job, places its partitions' counts by a scan of all
-// of the job's, and copies their records there, without an atomic (the places
-// used to come from one counter per job, at about 35 ns an update: 40 us of
-// 512). A job has as many items as leave each four, 16, ... partitions where
-// there are many jobs (1000 jobs of 4 KiB: 159 us with 256 items each, 14 with four).
+// The first work items gather the staged records: each of a job's
+// 2^gather_log2 items takes its share of the 256 partitions, finds their
+// places by a scan of all counts of the job, and copies their records there,
+// without an atomic (the places used to come from one counter per job, at
+// about 35 ns an update: 40 us of 512). Where there are many jobs an item
+// takes four, 16, ... partitions (1000 jobs of 4 KiB: 159 us with 256 items a
+// job, 15 with four; 16 jobs of 64 KiB to 16 MiB 9 us with 256, 11 with 64).
 // Then work item = `item` slots of one job's table, 1024 or 4096 (tables are
 // powers of two >= 4096 slots at 4096-aligned arena offsets, so no item
 // straddles two tables), where the table holds anything; kGroup items of one
@@ -1172,49 +1173,54 @@ MR_DEV unsigned long long compact_entry(const WordJob& J, uint64_t i) {
 // and clears the slots.
 template <uint32_t kGroup>
 __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob* __restrict__ jobs, uint32_t n_jobs,
-                                                                   uint32_t n_direct, uint32_t gather,
+                                                                   uint32_t n_direct, uint32_t gather_log2,
                                                                    const uint32_t* __restrict__ staged,
                                                                    const unsigned long long* __restrict__ staged_bytes,
                                                                    uint64_t total_slots, uint32_t item) {
   __shared__ uint32_t s_cnt, s_pos;
   __shared__ unsigned long long s_base, s_bytes;
-  __shared__ uint32_t s_at[kMaxWordParts + 1];  // staged records of the job before each partition
+  __shared__ uint32_t s_at[kMaxWordParts];
   __shared__ uint32_t w_all[kCompactThreads / kWave];
   __shared__ unsigned long long w_bytes[kCompactThreads / kWave];
-  static_assert(kCompactThreads == kMaxWordParts, "one thread per partition's count");
+  static_assert(kCompactThreads == kMaxWordParts && kMaxWordParts == 256, "one thread per partition's count");
   const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
-  // staged records of job j before partition threadIdx.x, and in all
-  auto staged_sums = [&](uint32_t j, uint32_t& before, uint32_t& all) {
+  // Staged records of job j: s_at[q] those before partition q in its wave's 64,
+  // of[w] those before wave w's, of[4] all.
+  constexpr uint32_t kWaves = kCompactThreads / kWave;
+  uint32_t of[kWaves + 1];
+  auto staged_sums = [&](uint32_t j) {
     const uint32_t c = gp(staged)[j * kMaxWordParts + threadIdx.x];
     const uint32_t incl = wave_incl_scan(c);
     __syncthreads();  // the previous use has been read
+    s_at[threadIdx.x] = incl - c;
     if (lane == kWave - 1) w_all[wv] = incl;
     __syncthreads();
-    before = incl - c;
-    all = 0;
-    for (uint32_t w = 0; w < kCompactThreads / kWave; ++w) {
-      if (w < wv) before += w_all[w];
-      all += w_all[w];
-    }
+    of[0] = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kWaves; ++w) of[w + 1] = of[w] + w_all[w];
   };
-  const uint64_t n_gather = (uint64_t)n_direct * gather;
+  auto at = [&](uint32_t q) {  // staged records before partition q, up to all
+    if (q == kMaxWordParts) return of[kWaves];
+    uint32_t base = 0;
+#pragma unroll
+    for (uint32_t w = 1; w < kWaves; ++w) base = q >= w * kWave ? of[w] : base;
+    return base + s_at[q];
+  };
+  const uint64_t n_gather = (uint64_t)n_direct << gather_log2;
   for (uint64_t g = blockIdx.x; g < n_gather; g += gridDim.x) {
-    const uint32_t j = (uint32_t)(g / gather), each = kMaxWordParts / gather, p0 = (uint32_t)(g % gather) * each;
+    const uint32_t j = (uint32_t)(g >> gather_log2), each = kMaxWordParts >> gather_log2;
+    const uint32_t p0 = ((uint32_t)g & ((1u << gather_log2) - 1u)) * each;
     const WordJob& J = jobs[j];
-    uint32_t before, all;
-    staged_sums(j, before, all);
-    s_at[threadIdx.x] = before;
-    if (threadIdx.x == 0) s_at[kMaxWordParts] = all;
-    __syncthreads();
-    const uint32_t room = (uint32_t)(J.cap / kMaxWordParts), r0 = s_at[p0], r1 = s_at[p0 + each];
+    staged_sums(j);
+    const uint32_t room = (uint32_t)(J.cap / kMaxWordParts), r0 = at(p0), r1 = at(p0 + each);
     // half records, in the job's order; the last partition that starts at or before a record has it
     for (uint32_t i = 2 * r0 + threadIdx.x; i < 2 * r1; i += kCompactThreads) {
       uint32_t lo = p0, hi = p0 + each;
       while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
-        if (s_at[mid] <= i / 2) lo = mid; else hi = mid;
+        if (at(mid) <= i / 2) lo = mid; else hi = mid;
       }
-      const uint64_t from = 2 * ((uint64_t)lo * room - s_at[lo]) + i;
+      const uint64_t from = 2 * ((uint64_t)lo * room - (each > 1 ? at(lo) : r0)) + i;
       gstore16(reinterpret_cast<uint4*>(J.recs) + i, gload16(reinterpret_cast<const uint4*>(J.recs2) + from));
     }
     if (p0 == 0) {
@@ -1225,7 +1231,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob
       __syncthreads();
       if (threadIdx.x == 0) {
         for (uint32_t w = 1; w < kCompactThreads / kWave; ++w) y += w_bytes[w];
-        atomicAdd(&J.st->n_recs, (unsigned long long)all);
+        atomicAdd(&J.st->n_recs, (unsigned long long)of[kWaves]);
         atomicAdd(&J.st->key_bytes, y);
       }
     }
@@ -1242,7 +1248,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob
     const WordJob& J = jobs[lo];
     const uint64_t i0 = t0 - J.slot_base;
     const uint64_t apart = n_groups * item;  // from one item of the group to the next
-    uint32_t before = 0, first = 0, with_keys = (1u << kGroup) - 1u;  // the group's items
+    uint32_t first = 0, with_keys = (1u << kGroup) - 1u;  // the group's items
     if (direct) {
       uint32_t map[kPartMapWords];
 #pragma unroll
@@ -1263,7 +1269,8 @@ __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob
         if (!any) with_keys &= ~(1u << g);
       }
       if (!with_keys) continue;
-      staged_sums(lo, before, first);
+      staged_sums(lo);
+      first = of[kWaves];
     }
     if (threadIdx.x == 0) {
       s_cnt = 0;
@@ -2284,19 +2291,19 @@ hipError_t words_enqueue_reduce(const WordsLaunch& L, hipStream_t s) {
   // 4096 slots each, 13 at 1024)
   const uint32_t item = L.total_slots <= (L.n_parts ? 1ull << 22 : 1ull << 20) ? kCompactSmall : kCompactLarge;
   const uint32_t n_direct = L.n_parts && L.n_jobs <= kDirectJobs ? L.n_jobs : 0;
-  uint32_t gather = kMaxWordParts;
-  while (gather > 1 && (uint64_t)n_direct * gather > kGatherItems) gather /= 4;
+  uint32_t gather_log2 = 8;  // (kMaxWordParts)
+  while (gather_log2 && (uint64_t)n_direct << gather_log2 > kGatherItems) gather_log2 -= 2;
   // (1.6 M distinct words of 20 bytes, a table of 2^22 slots: 165 us with an
   // atomic per item of 1024, 91 in groups of four; 512 MiB of text, whose table
   // holds few keys: 13 and 15 us)
   const uint32_t group = n_direct == 1 && L.total_slots >= 512ull * item ? kCompactGroup : 1u;
-  const uint64_t tiles = std::max<uint64_t>((L.total_slots + item - 1) / item / group, (uint64_t)n_direct * gather);
+  const uint64_t tiles = std::max<uint64_t>((L.total_slots + item - 1) / item / group, (uint64_t)n_direct << gather_log2);
   const dim3 cgrid((uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(tiles, 4096)));
   if (group == 1)
-    hipLaunchKernelGGL(k_words_compact<1>, cgrid, dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, n_direct, gather,
+    hipLaunchKernelGGL(k_words_compact<1>, cgrid, dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, n_direct, gather_log2,
                        L.bucket_start, L.bucket_bstart, L.total_slots, item);
   else
-    hipLaunchKernelGGL(k_words_compact<kCompactGroup>, cgrid, dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, n_direct, gather,
+    hipLaunchKernelGGL(k_words_compact<kCompactGroup>, cgrid, dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, n_direct, gather_log2,
                        L.bucket_start, L.bucket_bstart, L.total_slots, item);
   if (L.n_jobs <= kRankJobs) {
     // plans the sort itself
