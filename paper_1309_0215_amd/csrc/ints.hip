@@ -511,14 +511,17 @@ MR_DEV uint32_t vp_parts(const uint32_t* __restrict__ tot, uint32_t slices, uint
 // kList = false: neighbouring lanes take a tile's run together, one
 // eight-element piece (a 16-byte load of offsets) each, as many lanes as the
 // part's mean run has pieces, pipelined over steps of kBatch tiles per group;
-// runs far above the mean are left for whole waves afterwards.
+// runs far above the mean are left for whole waves afterwards. (Lanes by the
+// mean over all ranges, the rest of a run by them one load after the other,
+// and parts by tiles: 8 M sorted pairs over 2^16 keys, SUM, 256 us of a call of
+// 356, now 151; 8 M pairs on one of 2^24 keys 1,365 us a call, now 374.)
 // kList = true, for counting over many tiles of short runs: a wave takes 64
 // tiles at a time, lane l loads tile l's run bounds and lists its run's pieces
 // in LDS, and the listed pieces go to the lanes in order, so that every lane
-// has a piece whatever the runs' lengths (2^28 elements over 2^24 keys: 237 us;
+// has a piece whatever the runs' lengths (2^28 elements over 2^24 keys: 228 us;
 // groups of eight lanes, of which a run of 32 fills five, 277 us of vector and
 // LDS issue). With few tiles per wave the list's chain of loads is not hidden
-// (8 M pairs: 78 us against 35).
+// (8 M pairs: 78 us against 33).
 // A range of one workgroup also counts the present keys of its compaction
 // blocks.
 constexpr uint32_t kVpSinks = 32;
@@ -1039,7 +1042,8 @@ __global__ __launch_bounds__(kIntThreads) void k_int_hash(IntIn in, IntTable T, 
 // set by one workgroup; and an estimate of the distinct keys of the whole
 // input from the keys met once (f1) and twice (f2), the lower bound of Chao:
 // d + f1 (f1 - 1) / (2 (f2 + 1)). They tell inputs of few keys, which the LDS
-// caches combine, from the others before any pass over them.
+// caches combine, from the others before any pass over them. Bound by the
+// latency of one load per element on one workgroup: 22 us on 16 M elements.
 constexpr uint32_t kSampleSize = 8192;
 
 __global__ __launch_bounds__(1024) void k_int_sample(IntIn in, IntPub* host) {

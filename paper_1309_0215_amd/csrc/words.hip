@@ -294,8 +294,9 @@ struct PartNotes {
 // prep: validate record offsets and publish the valid byte range
 // ----------------------------------------------------------------------------
 
-// A single job's descriptor comes as a kernel argument: two copies from
-// pageable memory before the first kernel cost about 20 us of a call. Stores
+// A single job's descriptor comes as a kernel argument instead of two copies
+// from pageable memory before the first kernel (8 MiB of text, calls that do
+// not replay a graph: 171 -> 162 us). Stores
 // it with its tile bases, clears the state and publishes the whole input as
 // the valid range (k_words_prep narrows it to the records, if there are any).
 __global__ __launch_bounds__(kWave) void k_words_one(WordJob J, WordJob* __restrict__ job, uint64_t* __restrict__ tile_base,
@@ -885,7 +886,7 @@ __global__ __launch_bounds__(kMapThreads) void k_words_map(const WordJob* __rest
 // take two barriers, are up to eight rounds apart while few keys are new.
 // Bound by the chain of LDS reads of a round on the one workgroup that the
 // table leaves room for on a CU: 17 M records over 50,000 keys (512 MiB of
-// text) 129 us; one record a round by the full insert, a look after each and a
+// text) 121 us; one record a round by the full insert, a look after each and a
 // search of all segments for each record 210 us; four records a round 137 us
 // (the registers spill).
 constexpr uint32_t kMaxMapGrid = 1024;  // map workgroups (miss sub-queues per partition)
