@@ -1430,7 +1430,7 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
       MR_HIP(int_enqueue_global_array(L, job->stream));
     }
     if (job->cfg.timing) MR_HIP(hipEventRecord(job->ev3, job->stream));
-    MR_HIP(int_enqueue_dense_out(L, true, dc.vparts ? &dc.vp : nullptr, reinterpret_cast<uint32_t*>(sc + dc.o_tot), job->stream));
+    MR_HIP(int_enqueue_dense_out(L, true, dc.vparts, job->stream));
   }
   // The hash container without a table size of its own: inputs of few keys
   // stay in the LDS caches and a small table; the others are radix sorted. A

@@ -348,6 +348,7 @@ __global__ __launch_bounds__(256) void k_global_array(IntIn in, uint32_t R, uint
 constexpr uint32_t kVpPer = 16;                // elements per thread of the tile kernel
 constexpr uint32_t kVpMaxParts = 2048;         // ranges
 constexpr uint32_t kCompTile = 2048;  // keys per block of the ordered compaction of dense arrays (256 threads x 8)
+constexpr uint32_t kUncounted = ~0u;  // a block whose present keys are still to be counted
 
 // Threads of the tile kernel: 16,384-element tiles for counting, 8,192 where
 // the staged values take twice the keys' LDS.
@@ -485,11 +486,13 @@ __global__ __launch_bounds__(kVpTotThreads) void k_vp_totals(const uint32_t* __r
   }
 }
 
-// Workgroups of range p: one per `split` of its elements; and whether they are
-// spread evenly over the slices of the tiles (a single slice of fewer than 128
-// tiles does not tell: finding the shares there cost 10 us and gained nothing).
-MR_DEV uint32_t vp_parts(const uint32_t* __restrict__ tot, uint32_t slices, uint32_t P, uint32_t p, uint32_t split,
-                         uint32_t* elems = nullptr, bool* even = nullptr) {
+// Workgroups of range p of 2^kb keys: one, up to `split` of its elements or four
+// times its keys (a merged range touches all of its keys again), else one per
+// `split`; and whether the elements are spread evenly over the slices of the
+// tiles (a single slice of fewer than 256 tiles does not tell: finding the
+// shares there cost 10 us and gained nothing).
+MR_DEV uint32_t vp_parts(const uint32_t* __restrict__ tot, uint32_t slices, uint32_t P, uint32_t p, uint32_t kb,
+                         uint32_t split, uint32_t& elems, bool& even) {
   uint32_t c = 0, most = 0;
 #pragma unroll 4
   for (uint32_t y = 0; y < slices; ++y) {
@@ -497,9 +500,9 @@ MR_DEV uint32_t vp_parts(const uint32_t* __restrict__ tot, uint32_t slices, uint
     c += x;
     most = x > most ? x : most;
   }
-  if (elems) *elems = c;
-  if (even) *even = (uint64_t)most * slices <= c + (uint64_t)c / 2;
-  return c <= split ? 1u : (c - 1) / split + 1;  // (c may be close to 2^32)
+  elems = c;
+  even = (uint64_t)most * slices <= c + (uint64_t)c / 2;
+  return c <= split || c <= 4u << kb ? 1u : (c - 1) / split + 1;  // (c may be close to 2^32)
 }
 
 // One workgroup per part of a range (found from the parts' scan). LDS: values
@@ -523,7 +526,7 @@ MR_DEV uint32_t vp_parts(const uint32_t* __restrict__ tot, uint32_t slices, uint
 // LDS issue). With few tiles per wave the list's chain of loads is not hidden
 // (8 M pairs: 78 us against 33).
 // A range of one workgroup also counts the present keys of its compaction
-// blocks.
+// blocks; those of the others are left to k_dense_count.
 constexpr uint32_t kVpSinks = 32;
 constexpr uint32_t kVpList = 384;  // pieces listed per wave
 constexpr uint32_t vp_max_kb(uint32_t op) { return op == 0 ? 15 : 14; }
@@ -551,7 +554,7 @@ __global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uin
 #pragma unroll
   for (uint32_t q = 0; q < kPer; ++q) {
     const uint32_t r = threadIdx.x * per + q;
-    parts[q] = q < per && r < P ? vp_parts(tot, slices, P, r, split, &elems[q], &even[q]) : 0u;
+    parts[q] = q < per && r < P ? vp_parts(tot, slices, P, r, kb, split, elems[q], even[q]) : 0u;
     sum += parts[q];
   }
   const uint32_t incl = wave_incl_scan(sum);
@@ -707,6 +710,7 @@ __global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uin
         }
       }
     }
+    __syncthreads();
   } else {
     constexpr uint32_t kBatch = OP == 0 ? 4 : 2;
     // lanes per run: the pieces of the part's mean run
@@ -800,9 +804,9 @@ __global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uin
           }
         }
       }
+      __syncthreads();
     }
   }
-  __syncthreads();
   const uint64_t key0 = (uint64_t)p << kb;
   const uint32_t nk = R - key0 < K ? (uint32_t)(R - key0) : K;
   if (np == 1) {
@@ -820,6 +824,8 @@ __global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uin
     }
     return;
   }
+  if (part == 0)
+    for (uint32_t q = threadIdx.x; q * kCompTile < nk; q += kThreads) blk[key0 / kCompTile + q] = kUncounted;
   for (uint32_t i = threadIdx.x; i < nk; i += kThreads) {  // (the dense arrays are zero before)
     const uint32_t c = OP == 0 ? val32[i] : here[i];
     if (!c) continue;
@@ -833,11 +839,10 @@ __global__ __launch_bounds__(vp_fill_threads(OP)) void k_vp_fill(uint64_t R, uin
 // ----------------------------------------------------------------------------
 // ordered compaction of dense arrays: keys with count > 0, ascending
 // ----------------------------------------------------------------------------
-// (tot != NULL: the blocks of ranges of one workgroup are counted already)
+// (counted: by the partitions' fill, all but the blocks it left at kUncounted)
 __global__ __launch_bounds__(256) void k_dense_count(const uint32_t* __restrict__ dcnt, uint32_t R, uint32_t* __restrict__ blk,
-                                                     const uint32_t* __restrict__ tot, uint32_t slices, uint32_t P, uint32_t kb,
-                                                     uint32_t split) {
-  if (tot && vp_parts(tot, slices, P, (uint32_t)((uint64_t)blockIdx.x * kCompTile >> kb), split) == 1) return;
+                                                     bool counted) {
+  if (counted && blk[blockIdx.x] != kUncounted) return;
   __shared__ uint32_t s;
   if (threadIdx.x == 0) s = 0;
   __syncthreads();
@@ -1443,7 +1448,7 @@ VpPlan vp_plan(uint64_t n, uint64_t R, uint32_t op, uint32_t n_cu) {
   p.grid = (uint32_t)(p.P + n / p.split);
   const uint64_t pieces = n / ((uint64_t)p.P * p.n_tiles + 1) / 8 + 1;  // 16-byte pieces of a run
   p.list = op == 0 && p.n_tiles >= 8192 && pieces <= 5;
-  p.slices = std::max(1u, std::min(kVpMaxSlices, p.n_tiles / 64));
+  p.slices = std::max(1u, std::min(kVpMaxSlices, p.n_tiles / 128));
   p.usable = p.P <= kVpMaxParts && n >= kVpMin && n < (1ull << 32) && (op == 0 || R < kVpSparse * n);
   return p;
 }
@@ -1485,15 +1490,10 @@ hipError_t int_enqueue_global_array_vp(const IntLaunch& L, const VpPlan& p, uint
 }
 
 // Compaction of the dense arrays into the outputs; clears them when asked.
-// vp (optional): the partitions that filled them, with their totals.
-hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, const VpPlan* vp, const uint32_t* tot, hipStream_t s) {
+// by_parts: partitions filled them.
+hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, bool by_parts, hipStream_t s) {
   const uint32_t nb = (uint32_t)((L.R + kCompTile - 1) / kCompTile);
-  if (vp) {
-    hipLaunchKernelGGL(k_dense_count, dim3(nb ? nb : 1), dim3(256), 0, s, L.dcnt, L.R, L.blk, tot, vp->slices, vp->P, vp->kb,
-                       vp->split);
-  } else {
-    hipLaunchKernelGGL(k_dense_count, dim3(nb ? nb : 1), dim3(256), 0, s, L.dcnt, L.R, L.blk, nullptr, 0u, 0u, 0u, 0u);
-  }
+  hipLaunchKernelGGL(k_dense_count, dim3(nb ? nb : 1), dim3(256), 0, s, L.dcnt, L.R, L.blk, by_parts);
   if (nb <= kScanOneMax) hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneWaves * kWave), 0, s, L.blk, nb, L.n_out, L.end);
   else hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, L.blk, nb, L.n_out, L.end);
   switch (L.op) {

@@ -249,7 +249,7 @@ struct VpPlan {
 VpPlan vp_plan(uint64_t n, uint64_t R, uint32_t op, uint32_t n_cu);
 hipError_t int_enqueue_global_array_vp(const IntLaunch& L, const VpPlan& p, uint32_t* runs, uint16_t* pk, uint32_t* pv,
                                        uint32_t* tot, hipStream_t s);
-hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, const VpPlan* vp, const uint32_t* tot, hipStream_t s);
+hipError_t int_enqueue_dense_out(const IntLaunch& L, bool clear, bool by_parts, hipStream_t s);
 hipError_t int_enqueue_hash_map(const IntLaunch& L, hipStream_t s);
 hipError_t int_enqueue_sample(const IntLaunch& L, IntPub* host, hipStream_t s);  // -> host->sampled, estimate (n at least 8192)
 uint32_t int_small_out_max();  // keys int_enqueue_small_out handles
