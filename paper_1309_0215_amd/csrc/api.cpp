@@ -1179,8 +1179,10 @@ struct DenseCarve {  // LDS or global array over n elements and range R
   VpPlan vp;
 };
 // with_vparts: whether the partitions may be used (without them a global
-// array is filled by atomics, which needs no scratch per element).
-DenseCarve dense_carve(mr_strategy strat, uint64_t n, uint64_t R, uint32_t op, uint32_t n_cu, bool with_vparts) {
+// array is filled by atomics, which needs no scratch per element), and in how
+// many slices of the tiles at most their elements are counted.
+DenseCarve dense_carve(mr_strategy strat, uint64_t n, uint64_t R, uint32_t op, uint32_t n_cu, bool with_vparts,
+                       uint32_t slices = ~0u) {
   DenseCarve d;
   Carve c;
   const uint32_t G = lds_grid(n, n_cu);
@@ -1196,6 +1198,7 @@ DenseCarve dense_carve(mr_strategy strat, uint64_t n, uint64_t R, uint32_t op, u
   }
   if (strat == MR_STRAT_GLOBAL_ARRAY && with_vparts) {
     d.vp = vp_plan(n, R, op, n_cu);
+    d.vp.slices = std::min(d.vp.slices, slices);
     d.vparts = d.vp.usable;
     if (d.vparts) {
       d.o_ph = c.take(4 * d.vp.runs);
@@ -1415,6 +1418,7 @@ mr_status run_u32(mr_job* job, mr_map_kind kind, mr_reduce_op op, const void* d_
     L.dcnt = static_cast<uint32_t*>(job->int_dense);
     L.dval = static_cast<uint8_t*>(job->int_dense) + ((4 * job->int_dense_R + 7) & ~7ull);
     DenseCarve dc = dense_carve(strat, n, key_range, o, (uint32_t)job->n_cu, true);
+    if (dc.vparts && !scratch_fits(job, dc.bytes)) dc = dense_carve(strat, n, key_range, o, (uint32_t)job->n_cu, true, 1);
     if (dc.vparts && !scratch_fits(job, dc.bytes)) dc = dense_carve(strat, n, key_range, o, (uint32_t)job->n_cu, false);
     const uint64_t o_blk = dc.o_blk, o_ph = dc.o_ph, o_pk = dc.o_pk;
     st = scratch(dc.bytes);

@@ -497,3 +497,20 @@ def test_sort_of_large_inputs_at_tile_and_chunk_edges(torch, n, kinds):
             k, v = _reduced(torch, keys, vals, op)
             assert torch.equal(r.keys.long() & 0xFFFFFFFF, k)
             assert torch.equal(r.values.long() if op == "sum" else r.values.long() & 0xFFFFFFFF, v)
+
+
+def test_global_array_in_workspaces_around_its_need(torch):
+    """The partitions with all their slices, with one slice where those do not
+    fit, and atomics where nothing more fits."""
+    from paper_1309_0215_amd import Job, _lib as L, workspace_bytes
+    n, R = 2_200_000, 1 << 16
+    keys, vals = gen.u32_keys(81, n, R, 0.6, with_values=True)
+    keys.sort()
+    need = workspace_bytes(L.MAP_U32_KV, 8 * n, R, strategy=STRATS["global_array"])
+    for less in (0, 256, 1 << 20):
+        ws = torch.empty(need - less, dtype=torch.uint8, device="cuda:0")
+        j = Job(device=0, strategy=STRATS["global_array"], workspace=ws)
+        for _ in range(2):
+            r = _run(torch, j, keys, vals, "sum", R)
+            assert r.stats["device_allocs"] == 0
+            _check(r, keys, vals, "sum")
