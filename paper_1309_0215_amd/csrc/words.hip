@@ -1177,7 +1177,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob
                                                                    uint32_t n_direct, uint32_t gather_log2,
                                                                    const uint32_t* __restrict__ staged,
                                                                    const unsigned long long* __restrict__ staged_bytes,
-                                                                   uint64_t total_slots, uint32_t item) {
+                                                                   uint64_t n_groups, uint32_t item) {
   __shared__ uint32_t s_cnt, s_pos;
   __shared__ unsigned long long s_base, s_bytes;
   __shared__ uint32_t s_at[kMaxWordParts];
@@ -1237,7 +1237,6 @@ __global__ __launch_bounds__(kCompactThreads) void k_words_compact(const WordJob
       }
     }
   }
-  const uint64_t n_groups = (total_slots + item - 1) / item / kGroup;  // (kGroup 1, or a divisor of the items of one job)
   for (uint64_t t = blockIdx.x; t < n_groups; t += gridDim.x) {
     const uint64_t t0 = t * item;
     uint32_t lo = 0, hi = n_jobs;
@@ -2298,14 +2297,15 @@ hipError_t words_enqueue_reduce(const WordsLaunch& L, hipStream_t s) {
   // atomic per item of 1024, 91 in groups of four; 512 MiB of text, whose table
   // holds few keys: 13 and 15 us)
   const uint32_t group = n_direct == 1 && L.total_slots >= 512ull * item ? kCompactGroup : 1u;
-  const uint64_t tiles = std::max<uint64_t>((L.total_slots + item - 1) / item / group, (uint64_t)n_direct << gather_log2);
+  const uint64_t n_groups = (L.total_slots + item - 1) / item / group;  // (groups of four divide the items of one table)
+  const uint64_t tiles = std::max<uint64_t>(n_groups, (uint64_t)n_direct << gather_log2);
   const dim3 cgrid((uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(tiles, 4096)));
   if (group == 1)
     hipLaunchKernelGGL(k_words_compact<1>, cgrid, dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, n_direct, gather_log2,
-                       L.bucket_start, L.bucket_bstart, L.total_slots, item);
+                       L.bucket_start, L.bucket_bstart, n_groups, item);
   else
     hipLaunchKernelGGL(k_words_compact<kCompactGroup>, cgrid, dim3(kCompactThreads), 0, s, L.jobs, L.n_jobs, n_direct, gather_log2,
-                       L.bucket_start, L.bucket_bstart, L.total_slots, item);
+                       L.bucket_start, L.bucket_bstart, n_groups, item);
   if (L.n_jobs <= kRankJobs) {
     // plans the sort itself
     hipLaunchKernelGGL(k_sort_ranks, dim3(L.sort_grid), dim3(kSortThreads), 0, s, L.jobs, L.n_jobs, L.totals,
